@@ -25,7 +25,7 @@
 //            small pass writes first (keys contiguous per d, so the loop transposes
 //            nothing); V is fp16 as it is.  Two MFMAs per tile (V Ph + V Pl).
 // K and V^T tiles are loaded from global memory straight into LDS, once per workgroup, and
-// shared by its four wavefronts (double-buffered; layouts free of bank conflicts for the
+// shared by its four wavefronts (rings of four tiles; layouts free of bank conflicts for the
 // 16-byte operand reads).
 #include "fd_chunk.h"
 
@@ -44,7 +44,6 @@ constexpr int kQB = 2;            // 16-query blocks per wavefront (1: 401, 2: 4
 constexpr int kWaveQ = 16 * kQB;  // queries per wavefront
 constexpr int kQTile = 4 * kWaveQ; // query rows per workgroup
 constexpr int kStep = 32;        // keys per wavefront step
-constexpr int kVAhead = 1;    // V^T operand tiles read from LDS ahead of the MFMAs that use them
 
 // V^T of one KV head is stored tile by tile, in the order the attention kernel consumes it:
 // [32-key step][8-key chunk g][d][8 keys], so the 8 KiB a step needs are contiguous (whole
@@ -91,151 +90,271 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const PrefillProblem p
     }
 }
 
-// 16 bytes per lane from global memory into LDS without passing through registers: lane l's
-// bytes land at lds_base + 16 l (lds_base is the same for the whole wavefront).
-__device__ __forceinline__ void load_to_lds(const void *global, void *lds_base)
-{
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)global,
-                                     (__attribute__((address_space(3))) void *)lds_base, 16, 0, 0);
-}
-
 // ---- the attention kernel ----
 // A workgroup owns 128 queries of one head: wavefront w the 32 queries i0 + 32w .. +31 (two
 // blocks of 16).  The K and V^T tiles of a 32-key step are loaded once per workgroup into LDS
-// (double-buffered, one barrier per step) and read from there by all four wavefronts as MFMA A
-// operands; Q^T stays in registers as the B operand.  Every output row belongs to one wavefront:
-// nothing is reduced across wavefronts, and with the unified phi nothing is ever rescaled.
+// and read from there by all four wavefronts as MFMA A operands; Q^T stays in registers as the B
+// operand.  Every output row belongs to one wavefront: nothing is reduced across wavefronts, and
+// with the unified phi nothing is ever rescaled.
 // A 16-byte LDS access of a wavefront is served 16 lanes per cycle, and the 16 are not
 // consecutive lanes: lanes 0-3, 12-15, 20-27 share a cycle, lanes 4-11, 16-19, 28-31 the next
 // (measured with a two-lane probe; likewise for the upper half).  In terms of lane = 16g + n a
 // cycle holds every n once, taken from two different g.  A layout is conflict-free when the
 // 16-byte unit (address / 16 mod 16) of lane (n, g) is a function of n alone and a permutation
 // of it (the V^T layout below), or n ^ g (the K layout).
-constexpr int kKStride = 256;    // bytes per K row in LDS (16 chunks of 16 bytes, XOR-swizzled)
+constexpr int kTileBytes = kStep * kHeadDim * 2;                // 8 KiB: one 32-key tile of K or V^T
+constexpr int kRing = 4;                                        // tiles of each in LDS (see tile_unified)
 struct PrefillLds {
-    alignas(16) unsigned char k[2][kStep * kKStride];          // 2 x 8 KiB
-    alignas(16) unsigned char v[2][4 * kHeadDim * 16];         // 2 x 8 KiB: [8-key chunk g][d][16 bytes], unit = d % 16
+    alignas(16) unsigned char k[kRing][kTileBytes];             // [key][16 chunks of 16 bytes, XOR-swizzled]
+    alignas(16) unsigned char v[kRing][kTileBytes];             // [8-key chunk g][d][16 bytes], unit = d % 16
     int bad[4], redo[4];
 };
-// V^T: the 16 bytes of keys 8g .. 8g + 7 of row d
-__device__ __forceinline__ int v_slot(int d, int g) { return (g * kHeadDim + d) << 4; }
 
-// K row r, 16-byte chunk c -> byte offset.  Lane (n, g) reads row r(n) in {0..3, 8..11, 16..19,
-// 24..27} (+4 for the second key block), chunk 4 kb + g: XOR with (r & 3) | ((r >> 3) & 3) << 2
-// (= n for those rows) puts it in unit (4 kb + g) ^ n; a row's 16 chunks stay a permutation of
-// themselves, so the row-wise writes are conflict-free too.
-__device__ __forceinline__ int k_slot(int r, int c)
+// K row r, 16-byte chunk c sits in chunk c ^ k_key(r) of the row.  Lane (n, g) reads row r(n) in {0..3, 8..11,
+// 16..19, 24..27} (+4 for the second key block), chunk 4 kb + g: k_key(r) = n for those rows, which puts it in unit
+// (4 kb + g) ^ n; a row's 16 chunks stay a permutation of themselves, so the row-wise writes are conflict-free too.
+__device__ __forceinline__ int k_key(int r) { return (r & 3) | (((r >> 3) & 3) << 2); }
+
+// What both schemes share: a wavefront's place in the tile, its operands in registers, the tile fetch.
+struct TileWave {
+    int lane, wave, n, g;
+    int w0;                      // first query of this wavefront
+    int nsteps, mine;            // key steps of the workgroup, of this wavefront (0: it has no query)
+    const unsigned char *kbase, *vbase;
+    int keys;                    // the prompt's length: K rows that hold a key
+    int k_voff0, k_voff1;        // this thread's two chunks of a K tile, from the tile's start
+    int k_rd[4], v_rd;           // this lane's operand reads, from the start of the LDS tile
+    f16x8 qB[kQB][4];            // Q^T as the B operand: lane (n, g) holds d = 32 kb + 8g .. +7 of query w0 + 16 qb + n
+
+    __device__ __forceinline__ TileWave(const PrefillProblem &p, int b, int hq, int i0, int S)
+    {
+        const int tid = threadIdx.x;
+        lane = tid & 63;
+        wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        n = lane & 15;
+        g = lane >> 4;
+        w0 = i0 + kWaveQ * wave;
+        nsteps = (min(i0 + kQTile, S) - 1) / kStep + 1;
+        const int last_q = min(w0 + kWaveQ, S) - 1;                  // < w0 when the wavefront has no query
+        mine = last_q >= w0 ? last_q / kStep + 1 : 0;
+        const size_t kv_head = (size_t)b * p.Hkv + hq / p.G;
+        kbase = reinterpret_cast<const unsigned char *>(p.k + kv_head * p.Smax * kHeadDim);
+        vbase = reinterpret_cast<const unsigned char *>(p.vt + kv_head * kHeadDim * p.Spad);
+        keys = S;
+        const int r = tid >> 4, c = (tid & 15) ^ k_key(r);
+        k_voff0 = r * 256 + c * 16;
+        k_voff1 = (r + 16) * 256 + (c ^ 8) * 16;                     // k_key(r + 16) = k_key(r) ^ 8
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) k_rd[kb] = (8 * (n >> 2) + (n & 3)) * 256 + (((4 * kb + g) ^ n) << 4);
+        v_rd = (g * kHeadDim + n) << 4;
+        // rows past the prompt may hold anything: zeros in their place
+        const uint16_t *qbase = p.q + (((size_t)b * p.Hq + hq) * p.Smax) * kHeadDim;
+#pragma unroll
+        for (int qb = 0; qb < kQB; ++qb) {
+            const int row = w0 + 16 * qb + n;
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) {
+                u32x4 t = {0u, 0u, 0u, 0u};
+                if (row < S) t = *reinterpret_cast<const u32x4 *>(qbase + (size_t)row * kHeadDim + 32 * kb + 8 * g);
+                qB[qb][kb] = __builtin_bit_cast(f16x8, t);
+            }
+        }
+    }
+    // Tile fetch, global memory straight into LDS (no staging registers): a wavefront's load instruction fills 1 KiB
+    // of LDS, lane l the 16 bytes at 16 l from the wavefront's base.  Thread t moves chunks t and t + 256 of a tile.
+    // Buffer loads through a window of kRing tiles: what lies past the last key of the prompt (or past the last tile)
+    // arrives as zeros and touches no memory, so the loop can run its fetches ahead without a condition, and
+    // inside a window a fetch costs three scalar instructions.
+    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t window(const unsigned char *base, int rows, int t0)
+    {
+        const int left = __builtin_amdgcn_readfirstlane(max(min(rows - t0 * kStep, kRing * kStep), 0));      // (uniform: keep it scalar)
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(base + (size_t)t0 * kTileBytes), 0, left * (kHeadDim * 2), 0x00027000);
+    }
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t k_window(int t0) const { return window(kbase, keys, t0); }
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t v_window(int t0) const { return window(vbase, nsteps * kStep, t0); }
+    __device__ __forceinline__ void fetch(__amdgpu_buffer_rsrc_t rs, int u, int voff0, int voff1, unsigned char *lds_tile) const
+    {
+        auto *dst = (__attribute__((address_space(3))) void *)(lds_tile + wave * 1024);
+        auto *dst1 = (__attribute__((address_space(3))) void *)(lds_tile + wave * 1024 + 4096);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, voff0, u * kTileBytes, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst1, 16, voff1, u * kTileBytes, 0, 0);
+    }
+    // tile u of a window, into place `slot` of the ring
+    __device__ __forceinline__ void fetch_k(PrefillLds &lds, __amdgpu_buffer_rsrc_t rs, int u, int slot) const
+    {
+        fetch(rs, u, k_voff0, k_voff1, lds.k[slot]);
+    }
+    __device__ __forceinline__ void fetch_v(PrefillLds &lds, __amdgpu_buffer_rsrc_t rs, int u, int slot) const
+    {
+        fetch(rs, u, (int)threadIdx.x * 16, (int)threadIdx.x * 16 + 4096, lds.v[slot]);
+    }
+    __device__ __forceinline__ void fetch_k(PrefillLds &lds, int t) const { fetch_k(lds, k_window(t), 0, t & (kRing - 1)); }
+    __device__ __forceinline__ void fetch_v(PrefillLds &lds, int t) const { fetch_v(lds, v_window(t), 0, t & (kRing - 1)); }
+    __device__ __forceinline__ u32x4 read_k(const PrefillLds &lds, int slot, int kb, int t) const
+    {
+        // row m = n of key block t is key 8 (n >> 2) + 4t + (n & 3) of the step, so that the two score
+        // tiles leave lane (n, g) holding keys 8g .. 8g + 7 of query n
+        return *reinterpret_cast<const u32x4 *>(&lds.k[0][0] + slot * kTileBytes + k_rd[kb] + 1024 * t);
+    }
+    __device__ __forceinline__ u32x4 read_v(const PrefillLds &lds, int slot, int dt) const
+    {
+        return *reinterpret_cast<const u32x4 *>(&lds.v[0][0] + slot * kTileBytes + v_rd + 256 * dt);
+    }
+    // scores of one step
+    __device__ __forceinline__ void scores(const PrefillLds &lds, int s, f32x4 (&sc)[kQB][2]) const
+    {
+#pragma unroll
+        for (int qb = 0; qb < kQB; ++qb)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) sc[qb][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        u32x4 ka[2][4];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) ka[t][kb] = read_k(lds, s & (kRing - 1), kb, t);
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int qb = 0; qb < kQB; ++qb)
+                    sc[qb][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, ka[t][kb]), qB[qb][kb], sc[qb][t], 0, 0, 0);
+    }
+};
+
+// The weights of a step as B operands of the second product: fp16 hi and lo parts of keys 8g .. 8g + 7.
+struct Weights {
+    u32x4 hi[kQB], lo[kQB];
+};
+
+// O^T += V^T P^T with P = Ph + Pl, one step
+__device__ __forceinline__ void add_pv(const TileWave &tw, const PrefillLds &lds, int s, const Weights &w, f32x4 (&acc)[8][kQB])
 {
-    return r * kKStride + ((c ^ ((r & 3) | (((r >> 3) & 3) << 2))) << 4);
+    u32x4 a_v[2];
+    const int slot = s & (kRing - 1);
+    a_v[0] = tw.read_v(lds, slot, 0);
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) {
+        if (dt + 1 < 8) a_v[(dt + 1) & 1] = tw.read_v(lds, slot, dt + 1);
+        const f16x8 v8 = __builtin_bit_cast(f16x8, a_v[dt & 1]);
+#pragma unroll
+        for (int qb = 0; qb < kQB; ++qb)
+            acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v8, __builtin_bit_cast(f16x8, w.hi[qb]), acc[dt][qb], 0, 0, 0);
+#pragma unroll
+        for (int qb = 0; qb < kQB; ++qb)
+            acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v8, __builtin_bit_cast(f16x8, w.lo[qb]), acc[dt][qb], 0, 0, 0);
+    }
 }
 
-// One 128-query tile.  ONLINE == false: unified scaling factor (Eq. 4); returns true when the tile
-// has to be redone with the synchronized scheme -- its guard fired (recorded in tile_flags) or a
-// weight left the range of the fp16 operands (not recorded: the result is the same either way).
-// ONLINE == true: the synchronized scheme (running maximum per query, Eq. 2); always stores.
-template <bool ONLINE>
-__device__ __forceinline__ bool tile_all(const PrefillProblem &p, PrefillLds &lds, int b, int hq, int i0, int S)
+// hi = the weights cut to fp16 (11 bits), lo = what that leaves (exact in fp32), rounded to fp16.  neg1 is -1.0 in a
+// register the compiler cannot see through: it keeps e - (float)hi a single mixed-precision fused multiply-add.
+__device__ __forceinline__ void split_pair(float e0, float e1, float neg1, unsigned &hi, unsigned &lo)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n = lane & 15, g = lane >> 4;
-    const int hkv = hq / p.G;
-    const size_t kv_head = (size_t)b * p.Hkv + hkv;
-    const uint16_t *qbase = p.q + (((size_t)b * p.Hq + hq) * p.Smax) * kHeadDim;
-    const uint16_t *kbase = p.k + kv_head * p.Smax * kHeadDim;
-    const uint16_t *vt = p.vt + kv_head * kHeadDim * p.Spad;
+    const f16x2 h = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(e0, e1));
+    const _Float16 h0 = h.x, h1 = h.y;
+    f16x2 l;
+    l.x = (_Float16)__builtin_fmaf((float)h0, neg1, e0);
+    l.y = (_Float16)__builtin_fmaf((float)h1, neg1, e1);
+    hi = __builtin_bit_cast(unsigned, h);
+    lo = __builtin_bit_cast(unsigned, l);
+}
+
+// Output rows of a wavefront: acc / den, zeros for rows past the prompt.
+__device__ __forceinline__ void store_rows(const PrefillProblem &p, const TileWave &tw, int b, int hq, int S, const f32x4 (&acc)[8][kQB], const float (&den)[kQB])
+{
+#pragma unroll
+    for (int qb = 0; qb < kQB; ++qb) {
+        const int row = tw.w0 + 16 * qb + tw.n;
+        if (row >= p.Smax) continue;
+        const bool live = row < S;
+        const float inv = live ? 1.f / den[qb] : 0.f;
+        uint16_t *o = p.out + (((size_t)b * p.Hq + hq) * p.Smax + row) * kHeadDim;
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) {
+            uint2 h = make_uint2(0u, 0u);
+            if (live) {
+                h.x = (unsigned)to_half_bits(acc[dt][qb][0] * inv) | ((unsigned)to_half_bits(acc[dt][qb][1] * inv) << 16);
+                h.y = (unsigned)to_half_bits(acc[dt][qb][2] * inv) | ((unsigned)to_half_bits(acc[dt][qb][3] * inv) << 16);
+            }
+            *reinterpret_cast<uint2 *>(o + 16 * dt + 4 * tw.g) = h;
+        }
+    }
+}
+
+template <int N> __device__ __forceinline__ void wait_fetches()        // at most N of this wavefront's loads outstanding
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void workgroup_barrier()                   // of the LDS tiles: no wait for loads in flight
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// One 128-query tile, unified scaling factor (Eq. 4).  Returns true when the tile has to be redone with the
+// synchronized scheme -- its guard fired (recorded in tile_flags) or a weight left the range of the fp16 operands (not
+// recorded: the result is the same either way).
+//
+// What bounds it: the matrix pipe and the issue port of a SIMD, and at that rate the clock (a run of 8192 tokens holds
+// 1.7 - 1.75 GHz).  A step of a wavefront is 48 matrix instructions of 16 pipe cycles (768) and 88 vector instructions;
+// the vector instructions of one wavefront do not run under the matrix instructions of the other wavefront of its SIMD,
+// but within a wavefront up to two independent ones do per matrix instruction (a probe of 48 + 96 takes 810 cycles, with
+// 16 exponentials 955).  So the three parts of a step are taken from three different steps, which do not depend on
+// each other, and woven together by hand: iteration s runs
+//     P.V of step s  |  weights of step s + 1  |  scores of step s + 2
+// The two wavefronts of a SIMD then take a step per 923 cycles between them, against 1560 for scores, weights and P.V
+// of one step after the other.  Whole call, that form / this, same workgroup order: 4 ragged prompts of up to 1024 tokens
+// 84.7 / 79.2 us, 2 x 64/8 heads x 4001 676.8 / 623.1, 1 x 32 heads x 8192 780.8 / 753.5.
+template <class F> __device__ __forceinline__ void pinned(F f)       // what f issues stays between its neighbours
+{
+    f();
+    __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds &lds, int b, int hq, int i0, int S)
+{
+    const TileWave tw(p, b, hq, i0, S);
+    const int tid = threadIdx.x, lane = tw.lane, wave = tw.wave, n = tw.n, g = tw.g, mine = tw.mine;
     const float c1 = p.scale * kLog2e, c0 = -p.phi * kLog2e;      // log2 of e^{s x - phi} = c1 x + c0
     const float lo2 = p.lo * kLog2e, hi2 = p.hi * kLog2e;
-    const int w0 = i0 + kWaveQ * wave;                       // first query of this wavefront
-    // -1.0 in a register the compiler cannot see through: keeps e - (float)hi a single mixed-precision
-    // fused multiply-add (fp16 operand read in place) instead of a conversion and a subtraction
     float neg1;
     asm("v_mov_b32 %0, -1.0" : "=v"(neg1));
 
-    // Q^T as the B operand: lane (n, g) holds d = 32 kb + 8g .. +7 of query w0 + 16 qb + n
-    f16x8 qB[kQB][4];
-#pragma unroll
-    for (int qb = 0; qb < kQB; ++qb) {
-        const int row = min(w0 + 16 * qb + n, p.Smax - 1);
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-            qB[qb][kb] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4 *>(qbase + (size_t)row * kHeadDim + 32 * kb + 8 * g));
-    }
     f32x4 acc[8][kQB];
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt)
 #pragma unroll
         for (int qb = 0; qb < kQB; ++qb) acc[dt][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float den[kQB], mrun[kQB];
+    // running extremes of log2 of the SCALED weights (guard, fp16 range), and the queries' scale exponents
+    // k_q, folded into the additive constant of the logit
+    float den[kQB], zlo[kQB], zhi[kQB], kq[kQB], c0q[kQB];
 #pragma unroll
-    for (int qb = 0; qb < kQB; ++qb) { den[qb] = 0.f; mrun[qb] = -INFINITY; }
-    // unified scheme: running extremes of log2 of the SCALED weights (guard, fp16 range) and the
-    // queries' scale exponents k_q, folded into the additive constant of the logit
-    float zlo[kQB], zhi[kQB], kq[kQB], c0q[kQB];
-#pragma unroll
-    for (int qb = 0; qb < kQB; ++qb) { zlo[qb] = INFINITY; zhi[qb] = -INFINITY; kq[qb] = 0.f; c0q[qb] = c0; }
+    for (int qb = 0; qb < kQB; ++qb) { den[qb] = 0.f; zlo[qb] = INFINITY; zhi[qb] = -INFINITY; kq[qb] = 0.f; c0q[qb] = c0; }
 
-    // key steps: the workgroup walks 0 .. nsteps - 1 (keys some query of the tile sees); this
-    // wavefront computes while a key of the step is visible to one of its queries
-    const int last_q = min(i0 + kQTile, S) - 1;
-    const int nsteps = last_q / kStep + 1;
-    const int my_last_q = min(w0 + kWaveQ, S) - 1;           // < w0 when the wavefront has no query
-    const int my_steps = my_last_q >= w0 ? my_last_q / kStep + 1 : 0;
+    // Tiles in LDS: rings of four.  Entering iteration s, K tile s + 2 and V tiles s and s + 1 have landed for
+    // every wavefront; iteration s fetches K tile s + 4 and V tile s + 3, whose places were last read in iteration
+    // s - 1 at the latest, and waits at its end for what iteration s - 1 fetched: a load has two iterations to land.
+    tw.fetch_k(lds, 0); tw.fetch_k(lds, 1);
+    tw.fetch_v(lds, 0); tw.fetch_k(lds, 2);
+    tw.fetch_v(lds, 1);
+    tw.fetch_k(lds, 3); tw.fetch_v(lds, 2);
+    auto fetch_ahead = [&](int s) { tw.fetch_k(lds, s + 4); tw.fetch_v(lds, s + 3); };
+    auto next_iteration = [&]() { wait_fetches<4>(); workgroup_barrier(); };
 
-    // Cooperative tile fetch, global memory straight into LDS (no staging registers): a wavefront's
-    // load instruction fills 1 KiB of LDS, lane l the 16 bytes at l * 16 from the wavefront's base,
-    // each lane from a global address of its own.  Thread t moves chunks t and t + 256 of each of
-    // the K and V^T tiles.  The V^T tile in memory is the image of the LDS tile; for K the lane
-    // whose LDS slot is (row r, physical chunk c') fetches logical chunk c' ^ key(r).
-    auto fetch = [&](int s, int buf) {
+    // weights of one step from its scores, not woven into anything: the first and the last step of a wavefront.
+    // last: the step that holds the wavefront's own keys (causal mask).
+    auto weights = [&](bool first, bool last, int s, const f32x4 (&sc)[kQB][2], Weights &w) {
         const int k0 = s * kStep;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int id = tid + 256 * i;
-            const int base = (256 * i + 64 * wave) << 4;         // the wavefront's 1 KiB of each tile
-            const int r = id >> 4, c = (id & 15) ^ ((r & 3) | (((r >> 3) & 3) << 2));
-            const uint16_t *gk = kbase + (size_t)min(k0 + r, p.Smax - 1) * kHeadDim + 8 * c;
-            const size_t at = (size_t)s * (kStep * kHeadDim) + 8 * id;
-            load_to_lds(gk, &lds.k[buf][base]);
-            load_to_lds(vt + at, &lds.v[buf][base]);
-        }
-    };
-    // the loads of this wavefront have landed in LDS
-    auto fetched = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
-    // scores -> weights (fp16 hi / lo B operands) for one query block; log2 domain
-    auto weights = [&](auto masked, bool first, int qb, const f32x4 (&sc)[2], f16x8 &pB, f16x8 &pBl, int k0) {
-        constexpr bool MASKED = decltype(masked)::value;
-        const int qrow = w0 + 16 * qb + n;
-        float z[8];
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) z[4 * t + r] = __builtin_fmaf(sc[t][r], c1, c0q[qb]);
-        bool ok[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) ok[j] = true;
-        if constexpr (MASKED) {
-            const int kmax = qrow < S ? qrow : -1;                       // last key this query sees
+        for (int qb = 0; qb < kQB; ++qb) {
+            const int qrow = tw.w0 + 16 * qb + n;
+            float z[8];
+            bool ok[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                ok[j] = k0 + 8 * g + j <= kmax;                          // j = 4t + r: key k0 + 8g + j
-                z[j] = ok[j] ? z[j] : -INFINITY;                         // weight 0
+                ok[j] = !last | (k0 + 8 * g + j <= qrow);                // j = 4t + r: key k0 + 8g + j
+                z[j] = ok[j] ? __builtin_fmaf(sc[qb][j >> 2][j & 3], c1, c0q[qb]) : -INFINITY;
             }
-        }
-        float shift = 0.f;
-        if constexpr (ONLINE) {
-            float m = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), fmaxf(fmaxf(z[4], z[5]), fmaxf(z[6], z[7])));
-            m = fmaxf(m, __shfl_xor(m, 16));
-            m = fmaxf(m, __shfl_xor(m, 32));
-            const float mnew = fmaxf(mrun[qb], m);
-            if (mnew > mrun[qb]) {                                   // rescale what was summed so far
-                const float alpha = mrun[qb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mrun[qb] - mnew);
-#pragma unroll
-                for (int dt = 0; dt < 8; ++dt) acc[dt][qb] *= alpha;
-                den[qb] *= alpha;
-                mrun[qb] = mnew;
-            }
-            shift = mnew == -INFINITY ? 0.f : mnew;
-        } else {
             if (first) {
                 // The query's scale: its largest weight of this first step becomes 2^kFirstStepLog2.
                 // The four lane groups of a query hold different keys: they agree on the maximum first.
@@ -248,145 +367,260 @@ __device__ __forceinline__ bool tile_all(const PrefillProblem &p, PrefillLds &ld
 #pragma unroll
                 for (int j = 0; j < 8; ++j) z[j] += k;
             }
-            // Guard: running extremes over all keys of the query, compared with the bounds (shifted by
-            // k_q) once, after the last step (three-input min / max: four instructions each per step).
-            float hi_run = zhi[qb], lo_run = zlo[qb];
 #pragma unroll
             for (int j = 0; j < 8; j += 2) {
-                hi_run = fmaxf(fmaxf(z[j], z[j + 1]), hi_run);
-                lo_run = fminf(fminf(ok[j] ? z[j] : INFINITY, ok[j + 1] ? z[j + 1] : INFINITY), lo_run);
+                zhi[qb] = fmaxf(fmaxf(z[j], z[j + 1]), zhi[qb]);
+                zlo[qb] = fminf(fminf(ok[j] ? z[j] : INFINITY, ok[j + 1] ? z[j + 1] : INFINITY), zlo[qb]);
+                const float e0 = __builtin_amdgcn_exp2f(z[j]), e1 = __builtin_amdgcn_exp2f(z[j + 1]);
+                den[qb] += e0;
+                den[qb] += e1;
+                unsigned h, l;
+                split_pair(e0, e1, neg1, h, l);
+                w.hi[qb][j >> 1] = h;
+                w.lo[qb][j >> 1] = l;
             }
-            zhi[qb] = hi_run;
-            zlo[qb] = lo_run;
-        }
-        unsigned hi[4], lo[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float e0 = __builtin_amdgcn_exp2f(z[2 * j] - shift), e1 = __builtin_amdgcn_exp2f(z[2 * j + 1] - shift);
-            den[qb] += e0 + e1;
-            // hi = the weight cut to fp16 (11 bits), lo = what that leaves (exact in fp32) cut to fp16
-            const f16x2 h = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(e0, e1));
-            const _Float16 h0 = h.x, h1 = h.y;
-            const float l0 = __builtin_fmaf((float)h0, neg1, e0), l1 = __builtin_fmaf((float)h1, neg1, e1);
-            hi[j] = __builtin_bit_cast(unsigned, h);
-            lo[j] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(l0, l1));
-        }
-        pB = __builtin_bit_cast(f16x8, u32x4{hi[0], hi[1], hi[2], hi[3]});
-        pBl = __builtin_bit_cast(f16x8, u32x4{lo[0], lo[1], lo[2], lo[3]});
-    };
-    // one step of this wavefront on the tiles in LDS buffer `buf`
-    auto compute = [&](auto masked, int s, int buf) {
-        const int k0 = s * kStep;
-        // scores: row m = n of key block t is key k0 + 8 (n >> 2) + 4t + (n & 3), so that the two
-        // score tiles leave lane (n, g) holding keys k0 + 8g .. 8g + 7 of query n
-        f32x4 sc[kQB][2];
-#pragma unroll
-        for (int qb = 0; qb < kQB; ++qb)
-#pragma unroll
-            for (int t = 0; t < 2; ++t) sc[qb][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // all eight K operands of the step first (their LDS latency overlaps), then the MFMAs
-        u32x4 ka[2][4];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int r = 8 * (n >> 2) + 4 * t + (n & 3);
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb) ka[t][kb] = *reinterpret_cast<const u32x4 *>(&lds.k[buf][k_slot(r, 4 * kb + g)]);
-        }
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int qb = 0; qb < kQB; ++qb)
-                    sc[qb][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, ka[t][kb]), qB[qb][kb], sc[qb][t], 0, 0, 0);
-        // O^T += V^T P^T with P = Ph + Pl: V Ph + V Pl.  The A operand of tile dt + 1 is read from LDS
-        // while the MFMAs of tile dt run; that of tile 0 before the weights are computed.
-        u32x4 a_v[kVAhead + 1];
-        auto read_v = [&](int dt, int slot) { a_v[slot] = *reinterpret_cast<const u32x4 *>(&lds.v[buf][v_slot(16 * dt + n, g)]); };
-#pragma unroll
-        for (int dt = 0; dt < kVAhead; ++dt) read_v(dt, dt);
-        f16x8 pB[kQB], pBl[kQB];
-#pragma unroll
-        for (int qb = 0; qb < kQB; ++qb) weights(masked, s == 0, qb, sc[qb], pB[qb], pBl[qb], k0);
-#pragma unroll
-        for (int dt = 0; dt < 8; ++dt) {
-            if (dt + kVAhead < 8) read_v(dt + kVAhead, (dt + kVAhead) % (kVAhead + 1));
-            const f16x8 v8 = __builtin_bit_cast(f16x8, a_v[dt % (kVAhead + 1)]);
-#pragma unroll
-            for (int qb = 0; qb < kQB; ++qb) acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v8, pB[qb], acc[dt][qb], 0, 0, 0);
-#pragma unroll
-            for (int qb = 0; qb < kQB; ++qb) acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v8, pBl[qb], acc[dt][qb], 0, 0, 0);
-            // keep the order: the next tile's LDS read, then this tile's four MFMAs
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 2 * kQB, 0);
         }
     };
 
-    fetch(0, 0);
-    fetched();
-    __syncthreads();
-#pragma unroll 1
-    for (int s = 0; s < nsteps; ++s) {
-        const int buf = s & 1;
-        // the other buffer was last read in step s - 1, which every wavefront has left
-        if (s + 1 < nsteps) fetch(s + 1, buf ^ 1);       // uniform over the workgroup
-        const bool full = s < my_steps && s * kStep + kStep - 1 <= w0 && w0 + kWaveQ <= S;
-        if (s < my_steps) {                              // uniform over the wavefront
-            // steps entirely below this wavefront's first query, all 32 of whose queries exist, need no mask
-            if (full) compute(std::false_type{}, s, buf);
-            else compute(std::true_type{}, s, buf);
+    // Iteration s in full.  av: the first two V operands of step s, read ahead (and left holding those of s + 1).
+    // The 48 matrix instructions in order, P.V (32) before scores (16); behind each up to two or three vector
+    // instructions of the weights -- pair i of 8 in slots 6i .. 6i + 5, its last two in the next pair's -- and the LDS
+    // read of an operand 8 or 9 slots ahead of its use.
+    // slot: s modulo the ring; rk, rv: windows that hold K tile s + 4 and V tile s + 3 as their tile u.
+    auto iteration = [&](int slot, __amdgpu_buffer_rsrc_t rk, __amdgpu_buffer_rsrc_t rv, int u, const f32x4 (&sc)[kQB][2], f32x4 (&scn)[kQB][2],
+                         const Weights &w, Weights &wn, u32x4 (&av)[3]) {
+        tw.fetch_k(lds, rk, u, slot);
+        tw.fetch_v(lds, rv, u, (slot + 3) & (kRing - 1));
+        u32x4 ka[6];
+        float z0 = 0.f, z1 = 0.f, e0 = 0.f, e1 = 0.f, f0 = 0.f, f1 = 0.f;      // the pair in work; f: its predecessor's weights
+        _Float16 h0 = 0, h1 = 0;                                                 // ... and their hi parts
+        unsigned hp = 0;
+        f16x2 lp = {0, 0};
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < 48; ++m) {
+            // matrix instruction m
+            if (m < 32) {
+                const int dt = m >> 2, qb = m & 1;
+                const u32x4 pw = (m & 2) ? w.lo[qb] : w.hi[qb];
+                acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, av[dt % 3]), __builtin_bit_cast(f16x8, pw), acc[dt][qb], 0, 0, 0);
+            } else {
+                const int op = (m - 32) >> 1, kb = op >> 1, t = op & 1, qb = m & 1;
+                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                scn[qb][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, ka[op % 6]), tw.qB[qb][kb], kb == 0 ? zero : scn[qb][t], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // operand reads
+            if (m < 24 && (m & 3) == 0) av[((m >> 2) + 2) % 3] = tw.read_v(lds, slot, (m >> 2) + 2);
+            if (m >= 23 && m < 38 && ((m - 23) & 1) == 0) {
+                const int op = (m - 23) >> 1;
+                ka[op % 6] = tw.read_k(lds, (slot + 2) & (kRing - 1), op >> 1, op & 1);
+            }
+            if (m == 40) av[0] = tw.read_v(lds, (slot + 1) & (kRing - 1), 0);
+            if (m == 42) av[1] = tw.read_v(lds, (slot + 1) & (kRing - 1), 1);
+            // weights: pair pr = (query block, keys 2j, 2j + 1)
+            const int pr = m / 6, qb = pr >> 2, j = pr & 3;
+            const int pp = pr - 1, pqb = pp >> 2, pj = pp & 3;               // the pair before
+            switch (m % 6) {
+                case 0:
+                    z0 = __builtin_fmaf(sc[qb][j >> 1][2 * (j & 1)], c1, c0q[qb]);
+                    z1 = __builtin_fmaf(sc[qb][j >> 1][2 * (j & 1) + 1], c1, c0q[qb]);
+                    break;
+                case 1:
+                    e0 = __builtin_amdgcn_exp2f(z0);
+                    zhi[qb] = fmaxf(fmaxf(z0, z1), zhi[qb]);
+                    break;
+                case 2:
+                    e1 = __builtin_amdgcn_exp2f(z1);
+                    zlo[qb] = fminf(fminf(z0, z1), zlo[qb]);
+                    break;
+                case 3:
+                    den[qb] += e0;
+                    if (pp >= 0) lp.x = (_Float16)__builtin_fmaf((float)h0, neg1, f0);
+                    break;
+                case 4:
+                    den[qb] += e1;
+                    if (pp >= 0) {
+                        lp.y = (_Float16)__builtin_fmaf((float)h1, neg1, f1);
+                        wn.lo[pqb][pj] = __builtin_bit_cast(unsigned, lp);
+                    }
+                    break;
+                default: {
+                    const f16x2 h = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(e0, e1));
+                    h0 = h.x; h1 = h.y;
+                    hp = __builtin_bit_cast(unsigned, h);
+                    wn.hi[qb][j] = hp;
+                    f0 = e0; f1 = e1;
+                    if (pr == 7) {
+                        lp.x = (_Float16)__builtin_fmaf((float)h0, neg1, f0);
+                        lp.y = (_Float16)__builtin_fmaf((float)h1, neg1, f1);
+                        wn.lo[qb][j] = __builtin_bit_cast(unsigned, lp);
+                    }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        fetched();
-        __syncthreads();
+        next_iteration();
+    };
+
+    f32x4 scA[kQB][2], scB[kQB][2];
+    Weights wA, wB;
+    u32x4 av[3];
+    wait_fetches<10>();                                       // K tiles 0 and 1
+    workgroup_barrier();
+    if (mine > 0) {
+        tw.scores(lds, 0, scB);
+        weights(true, mine == 1, 0, scB, wA);
+        if (mine > 1) tw.scores(lds, 1, scA);
     }
+    wait_fetches<4>();                                        // V tiles 0 and 1, K tile 2
+    workgroup_barrier();
+    int s = 0;
+    if (mine > 2) {
+        av[0] = tw.read_v(lds, 0, 0);
+        av[1] = tw.read_v(lds, 0, 1);
+        // four at a time: places in the ring and registers are then fixed (nothing is computed, nothing is moved)
+#pragma unroll 1
+        for (; s + kRing + 2 <= mine; s += kRing) {
+            const __amdgpu_buffer_rsrc_t rk = tw.k_window(s + 4), rv = tw.v_window(s + 3);
+            iteration(0, rk, rv, 0, scA, scB, wA, wB, av);
+            iteration(1, rk, rv, 1, scB, scA, wB, wA, av);
+            iteration(2, rk, rv, 2, scA, scB, wA, wB, av);
+            iteration(3, rk, rv, 3, scB, scA, wB, wA, av);
+        }
+#pragma unroll 1
+        for (; s + 3 <= mine; ++s) {
+            iteration(s & (kRing - 1), tw.k_window(s + 4), tw.v_window(s + 3), 0, scA, scB, wA, wB, av);
+#pragma unroll
+            for (int qb = 0; qb < kQB; ++qb) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) scA[qb][t] = scB[qb][t];
+                wA.hi[qb] = wB.hi[qb];
+                wA.lo[qb] = wB.lo[qb];
+            }
+        }
+    }
+    // The last two steps of the wavefront, then the fetches and barriers of the steps that only later wavefronts have.
+    if (mine > 1) {                                           // s == mine - 2
+        fetch_ahead(s);
+        add_pv(tw, lds, s, wA, acc);
+        weights(false, true, s + 1, scA, wA);
+        next_iteration();
+        ++s;
+    }
+    if (mine > 0) {                                           // s == mine - 1
+        fetch_ahead(s);
+        add_pv(tw, lds, s, wA, acc);
+        next_iteration();
+        ++s;
+    }
+    for (; s < tw.nsteps; ++s) {
+        fetch_ahead(s);
+        next_iteration();
+    }
+    wait_fetches<0>();                                        // nothing may land in LDS after this tile
+
     // the four lane groups of a query hold disjoint keys: total per query
 #pragma unroll
     for (int qb = 0; qb < kQB; ++qb) {
         den[qb] += __shfl_xor(den[qb], 16);
         den[qb] += __shfl_xor(den[qb], 32);
     }
-    if constexpr (!ONLINE) {
-        // strict guard on x - phi (the extremes carry the query's scale exponent); a NaN logit, which
-        // minimum and maximum skip, shows as a NaN denominator.  Apart from the guard: a weight at or
-        // beyond 2^kOverflowLog2 does not fit the fp16 operands.
-        bool bad = false, range = false;
+    // strict guard on x - phi (the extremes carry the query's scale exponent); a NaN logit, which
+    // minimum and maximum skip, shows as a NaN denominator.  Apart from the guard: a weight at or
+    // beyond 2^kOverflowLog2 does not fit the fp16 operands.
+    bool bad = false, range = false;
 #pragma unroll
-        for (int qb = 0; qb < kQB; ++qb) {
-            bad |= (zhi[qb] >= hi2 + kq[qb]) | (zlo[qb] <= lo2 + kq[qb]) | (den[qb] != den[qb]);
-            range |= zhi[qb] >= kOverflowLog2;
+    for (int qb = 0; qb < kQB; ++qb) {
+        const bool live = tw.w0 + 16 * qb + n < S;
+        bad |= live & ((zhi[qb] >= hi2 + kq[qb]) | (zlo[qb] <= lo2 + kq[qb]) | (den[qb] != den[qb]));
+        range |= live & (zhi[qb] >= kOverflowLog2);
+    }
+    const unsigned long long any_bad = __ballot(bad), any_range = __ballot(range);
+    if (lane == 0) { lds.bad[wave] = any_bad != 0ull; lds.redo[wave] = (any_bad | any_range) != 0ull; }
+    __syncthreads();
+    // one flag byte per 64 queries
+    constexpr int kFlagTiles = kQTile / 64, kWavesPerFlag = 4 / kFlagTiles;
+    if (tid < kFlagTiles) {
+        const int t64 = i0 / 64 + tid;
+        int f = 0;
+#pragma unroll
+        for (int w = 0; w < kWavesPerFlag; ++w) f |= lds.bad[tid * kWavesPerFlag + w];
+        if (t64 < p.tiles) p.tile_flags[((size_t)b * p.Hq + hq) * p.tiles + t64] = f != 0;
+    }
+    if ((lds.redo[0] | lds.redo[1] | lds.redo[2] | lds.redo[3]) != 0) return true;   // uniform: the tile is redone, nothing stored
+    store_rows(p, tw, b, hq, S, acc, den);
+    return false;
+}
+
+// The same tile by the synchronized scheme (running maximum per query, Eq. 2); rare, so plain: one step after the
+// other, one barrier per step, the next step's tiles in flight meanwhile.
+__device__ __forceinline__ void tile_sync(const PrefillProblem &p, PrefillLds &lds, int b, int hq, int i0, int S)
+{
+    const TileWave tw(p, b, hq, i0, S);
+    const float c1 = p.scale * kLog2e, c0 = -p.phi * kLog2e;
+    float neg1;
+    asm("v_mov_b32 %0, -1.0" : "=v"(neg1));
+    f32x4 acc[8][kQB];
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+        for (int qb = 0; qb < kQB; ++qb) acc[dt][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float den[kQB], mrun[kQB];
+#pragma unroll
+    for (int qb = 0; qb < kQB; ++qb) { den[qb] = 0.f; mrun[qb] = -INFINITY; }
+    tw.fetch_k(lds, 0);
+    tw.fetch_v(lds, 0);
+    wait_fetches<0>();
+    __syncthreads();
+#pragma unroll 1
+    for (int s = 0; s < tw.nsteps; ++s) {
+        tw.fetch_k(lds, s + 1);                                // their places were last read in step s - 3
+        tw.fetch_v(lds, s + 1);
+        if (s < tw.mine) {                                    // uniform over the wavefront
+            f32x4 sc[kQB][2];
+            tw.scores(lds, s, sc);
+            Weights w;
+#pragma unroll
+            for (int qb = 0; qb < kQB; ++qb) {
+                const int qrow = tw.w0 + 16 * qb + tw.n;
+                float z[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    z[j] = s * kStep + 8 * tw.g + j <= qrow ? __builtin_fmaf(sc[qb][j >> 2][j & 3], c1, c0) : -INFINITY;
+                float m = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), fmaxf(fmaxf(z[4], z[5]), fmaxf(z[6], z[7])));
+                m = fmaxf(m, __shfl_xor(m, 16));
+                m = fmaxf(m, __shfl_xor(m, 32));
+                const float mnew = fmaxf(mrun[qb], m);
+                if (mnew > mrun[qb]) {                        // rescale what was summed so far
+                    const float alpha = mrun[qb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mrun[qb] - mnew);
+#pragma unroll
+                    for (int dt = 0; dt < 8; ++dt) acc[dt][qb] *= alpha;
+                    den[qb] *= alpha;
+                    mrun[qb] = mnew;
+                }
+                const float shift = mnew == -INFINITY ? 0.f : mnew;
+#pragma unroll
+                for (int j = 0; j < 8; j += 2) {
+                    const float e0 = __builtin_amdgcn_exp2f(z[j] - shift), e1 = __builtin_amdgcn_exp2f(z[j + 1] - shift);
+                    den[qb] += e0 + e1;
+                    unsigned h, l;
+                    split_pair(e0, e1, neg1, h, l);
+                    w.hi[qb][j >> 1] = h;
+                    w.lo[qb][j >> 1] = l;
+                }
+            }
+            add_pv(tw, lds, s, w, acc);
         }
-        const unsigned long long any_bad = __ballot(bad), any_range = __ballot(range);
-        if (lane == 0) { lds.bad[wave] = any_bad != 0ull; lds.redo[wave] = (any_bad | any_range) != 0ull; }
+        wait_fetches<0>();
         __syncthreads();
-        // one flag byte per 64 queries
-        constexpr int kFlagTiles = kQTile / 64, kWavesPerFlag = 4 / kFlagTiles;
-        if (tid < kFlagTiles) {
-            const int t64 = i0 / 64 + tid;
-            int f = 0;
-#pragma unroll
-            for (int w = 0; w < kWavesPerFlag; ++w) f |= lds.bad[tid * kWavesPerFlag + w];
-            if (t64 < p.tiles) p.tile_flags[((size_t)b * p.Hq + hq) * p.tiles + t64] = f != 0;
-        }
-        if ((lds.redo[0] | lds.redo[1] | lds.redo[2] | lds.redo[3]) != 0) return true;   // uniform: the tile is redone, nothing stored
     }
 #pragma unroll
     for (int qb = 0; qb < kQB; ++qb) {
-        const int row = w0 + 16 * qb + n;
-        if (row >= p.Smax) continue;
-        const bool live = row < S;
-        const float inv = live ? 1.f / den[qb] : 0.f;
-        uint16_t *o = p.out + (((size_t)b * p.Hq + hq) * p.Smax + row) * kHeadDim;
-#pragma unroll
-        for (int dt = 0; dt < 8; ++dt) {
-            uint2 h = make_uint2(0u, 0u);
-            if (live) {
-                h.x = (unsigned)to_half_bits(acc[dt][qb][0] * inv) | ((unsigned)to_half_bits(acc[dt][qb][1] * inv) << 16);
-                h.y = (unsigned)to_half_bits(acc[dt][qb][2] * inv) | ((unsigned)to_half_bits(acc[dt][qb][3] * inv) << 16);
-            }
-            *reinterpret_cast<uint2 *>(o + 16 * dt + 4 * g) = h;
-        }
+        den[qb] += __shfl_xor(den[qb], 16);
+        den[qb] += __shfl_xor(den[qb], 32);
     }
-    return false;
+    store_rows(p, tw, b, hq, S, acc, den);
 }
 
 __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillProblem p)
@@ -418,9 +652,9 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillProblem p)
             p.tile_flags[((size_t)b * p.Hq + hq) * p.tiles + i0 / 64 + threadIdx.x] = 0;
         return;
     }
-    if (tile_all<false>(p, lds, b, hq, i0, S)) {         // Section 3 "Recomputation", for this tile
+    if (tile_unified(p, lds, b, hq, i0, S)) {            // Section 3 "Recomputation", for this tile
         __syncthreads();
-        tile_all<true>(p, lds, b, hq, i0, S);
+        tile_sync(p, lds, b, hq, i0, S);
     }
 }
 
