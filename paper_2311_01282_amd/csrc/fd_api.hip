@@ -705,7 +705,7 @@ fd_status fd_calibrate(const uint64_t *hist, int32_t n_bins, float x_min, float 
 }
 
 namespace {
-struct PrefillLayout { size_t vt, flags, total; int spad, tiles; };
+struct PrefillLayout { size_t flags, total; int tiles; };
 fd_status plan_prefill(const fd_shape *shape, PrefillLayout *P)
 {
     if (!shape) return FD_ERR_NULL;
@@ -714,13 +714,12 @@ fd_status plan_prefill(const fd_shape *shape, PrefillLayout *P)
     Layout L;
     fd_status st = plan(&sh, &L);
     if (st != FD_OK) return st;
-    P->spad = (sh.max_seq + 63) / 64 * 64;
-    P->tiles = P->spad / 64;
-    const size_t vt = (size_t)sh.batch * sh.n_kv_heads * fd::kHeadDim * P->spad * sizeof(uint16_t);
-    size_t off = 0;
-    P->vt = off;     off = align_up(off + vt);
-    P->flags = off;  off = align_up(off + (size_t)sh.batch * sh.n_q_heads * P->tiles);
-    P->total = off;
+    P->tiles = (sh.max_seq + 63) / 64;
+    // The size of the workspace is part of the interface: room for a copy of V, which the kernel no longer needs,
+    // stays in front of the flags.
+    const size_t v_copy = (size_t)sh.batch * sh.n_kv_heads * fd::kHeadDim * P->tiles * 64 * sizeof(uint16_t);
+    P->flags = align_up(v_copy);
+    P->total = align_up(P->flags + (size_t)sh.batch * sh.n_q_heads * P->tiles);
     return FD_OK;
 }
 }  // namespace
@@ -753,10 +752,9 @@ fd_status fd_prefill_attn(const fd_shape *shape, const void *q, const void *k_ca
     p.v = static_cast<const uint16_t *>(v_cache);
     p.seq_lens = seq_lens;
     p.out = static_cast<uint16_t *>(out);
-    p.vt = reinterpret_cast<uint16_t *>(base + P.vt);
     p.tile_flags = reinterpret_cast<uint8_t *>(base + P.flags);
     p.B = shape->batch; p.Hq = shape->n_q_heads; p.Hkv = shape->n_kv_heads; p.G = p.Hq / p.Hkv;
-    p.Smax = shape->max_seq; p.Spad = P.spad; p.tiles = P.tiles;
+    p.Smax = shape->max_seq; p.tiles = P.tiles;
     p.scale = shape->scale; p.phi = phi; p.lo = bounds.lo; p.hi = bounds.hi;
     FD_TRY(fd::launch_prefill(p, static_cast<hipStream_t>(stream)));
     return FD_OK;

@@ -132,9 +132,8 @@ struct PrefillProblem {
     const uint16_t *q, *k, *v;   // q [B, Hq, Smax, D]; k, v [B, Hkv, Smax, D]
     const int32_t *seq_lens;
     uint16_t *out;               // [B, Hq, Smax, D]
-    uint16_t *vt;                // workspace: V transposed per KV head, tiled [Spad / 32][4][D][8 keys], fp16
     uint8_t *tile_flags;         // workspace: [B, Hq, tiles]
-    int B, Hq, Hkv, G, Smax, Spad, tiles;   // Spad = Smax rounded up to 64; tiles = Spad / 64
+    int B, Hq, Hkv, G, Smax, tiles;         // tiles = Smax / 64, rounded up
     float scale, phi, lo, hi;
 };
 hipError_t launch_prefill(const PrefillProblem &p, hipStream_t s);

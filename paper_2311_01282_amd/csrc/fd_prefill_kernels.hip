@@ -21,10 +21,10 @@
 //            logits exceed its first step's maximum by more than 2^11.9 would overflow fp16: its
 //            tile is redone with the synchronized scheme, like a tile whose guard fired (but
 //            without raising the guard's flag).
-//   output   O^T[d][query] = V^T . P^T       A = V^T from a transposed copy of V that a
-//            small pass writes first (keys contiguous per d, so the loop transposes
-//            nothing); V is fp16 as it is.  Two MFMAs per tile (V Ph + V Pl).
-// K and V^T tiles are loaded from global memory straight into LDS, once per workgroup, and
+//   output   O^T[d][query] = V^T . P^T       A = V^T, taken out of the V tile in LDS by the
+//            transposing LDS read (ds_read_b64_tr_b16: four keys of one d per lane); V is
+//            fp16 as it is.  Two MFMAs per tile (V Ph + V Pl).
+// K and V tiles are loaded from global memory straight into LDS, once per workgroup, and
 // shared by its four wavefronts (rings of four tiles; layouts free of bank conflicts for the
 // 16-byte operand reads).
 #include "fd_chunk.h"
@@ -34,6 +34,7 @@ namespace fd {
 namespace {
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -45,54 +46,9 @@ constexpr int kWaveQ = 16 * kQB;  // queries per wavefront
 constexpr int kQTile = 4 * kWaveQ; // query rows per workgroup
 constexpr int kStep = 32;        // keys per wavefront step
 
-// V^T of one KV head is stored tile by tile, in the order the attention kernel consumes it:
-// [32-key step][8-key chunk g][d][8 keys], so the 8 KiB a step needs are contiguous (whole
-// cache lines, and the image of the LDS tile).  Element offset of keys key .. key + 7 (key a
-// multiple of 8) of row d within the head:
-__device__ __forceinline__ size_t vt_offset(int key, int d)
-{
-    return (size_t)(key >> 5) * (32 * kHeadDim) + (size_t)((((key >> 3) & 3) * kHeadDim + d) << 3);
-}
-
-// ---- pass 0: V [B,Hkv,Smax,D] fp16 -> tiled V^T (Spad keys) fp16, zero beyond the prompt ----
-__global__ __launch_bounds__(256) void transpose_v_kernel(const PrefillProblem p)
-{
-    __shared__ uint16_t tile[64][kHeadDim + 2];
-    const int gi = blockIdx.y;                          // (sequence, KV head)
-    const int b = gi / p.Hkv;
-    const int k0 = blockIdx.x * 64;
-    int S = p.seq_lens[b];
-    S = S < 0 ? 0 : (S > p.Smax ? p.Smax : S);
-    const int tid = threadIdx.x;
-    // 64 keys x 128 d: thread reads 8 d of one key (16 bytes), 4 times
-    for (int i = tid; i < 64 * 16; i += 256) {
-        const int key = i >> 4, c = i & 15;
-        u32x4 w = {0u, 0u, 0u, 0u};
-        if (k0 + key < S) w = *reinterpret_cast<const u32x4 *>(p.v + ((size_t)gi * p.Smax + k0 + key) * kHeadDim + 8 * c);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t x = w[j];
-            tile[key][8 * c + 2 * j] = (uint16_t)(x & 0xffffu);
-            tile[key][8 * c + 2 * j + 1] = (uint16_t)(x >> 16);
-        }
-    }
-    __syncthreads();
-    // thread writes 8 keys of one d (16 bytes), 4 times; consecutive threads take consecutive d,
-    // which are consecutive 16-byte pieces of the tiled layout
-    for (int i = tid; i < kHeadDim * 8; i += 256) {
-        const int d = i & (kHeadDim - 1), kc = i >> 7;
-        uint32_t o[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            o[j] = (uint32_t)tile[8 * kc + 2 * j][d] | ((uint32_t)tile[8 * kc + 2 * j + 1][d] << 16);
-        const size_t at = (size_t)gi * kHeadDim * p.Spad + vt_offset(k0 + 8 * kc, d);
-        *reinterpret_cast<u32x4 *>(p.vt + at) = u32x4{o[0], o[1], o[2], o[3]};
-    }
-}
-
 // ---- the attention kernel ----
 // A workgroup owns 128 queries of one head: wavefront w the 32 queries i0 + 32w .. +31 (two
-// blocks of 16).  The K and V^T tiles of a 32-key step are loaded once per workgroup into LDS
+// blocks of 16).  The K and V tiles of a 32-key step are loaded once per workgroup into LDS
 // and read from there by all four wavefronts as MFMA A operands; Q^T stays in registers as the B
 // operand.  Every output row belongs to one wavefront: nothing is reduced across wavefronts, and
 // with the unified phi nothing is ever rescaled.
@@ -100,15 +56,27 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const PrefillProblem p
 // consecutive lanes: lanes 0-3, 12-15, 20-27 share a cycle, lanes 4-11, 16-19, 28-31 the next
 // (measured with a two-lane probe; likewise for the upper half).  In terms of lane = 16g + n a
 // cycle holds every n once, taken from two different g.  A layout is conflict-free when the
-// 16-byte unit (address / 16 mod 16) of lane (n, g) is a function of n alone and a permutation
-// of it (the V^T layout below), or n ^ g (the K layout).
-constexpr int kTileBytes = kStep * kHeadDim * 2;                // 8 KiB: one 32-key tile of K or V^T
+// 16-byte unit (address / 16 mod 16) of lane (n, g) is a permutation of n, as n ^ g (the K layout).
+constexpr int kTileBytes = kStep * kHeadDim * 2;                // 8 KiB: one 32-key tile of K or V
+constexpr int kVTileBytes = kTileBytes + 384;                   // ... of V as it lies in LDS (see v_block)
 constexpr int kRing = 4;                                        // tiles of each in LDS (see tile_unified)
 struct PrefillLds {
     alignas(16) unsigned char k[kRing][kTileBytes];             // [key][16 chunks of 16 bytes, XOR-swizzled]
-    alignas(16) unsigned char v[kRing][kTileBytes];             // [8-key chunk g][d][16 bytes], unit = d % 16
+    alignas(16) unsigned char v[kRing][kVTileBytes];            // [key][8 chunks of 32 bytes], swizzled and shifted
     int bad[4], redo[4];
 };
+
+// V keeps its own layout (a key's 256 bytes in a row); ds_read_b64_tr_b16 turns it round: of 16 lanes, lane 4j + i reads
+// 8 bytes, piece i of the 32 bytes (16 d) of key j, and lane n receives d = n of the four keys.  Lane (n, g) of the A
+// operand of tile dt needs keys 8g .. 8g + 7 of d = 16 dt + n: two such reads, keys 8g + (0..3) and 8g + (4..7).  Eight
+// keys are read at a time, 8g + 4h + (0..3) of two neighbouring g, 32 bytes of each: they have to lie in different
+// 32-byte units modulo 8.  So the unit of a row is XORed with key % 4 within its half of the row, and the
+// blocks of four keys of each g are shifted by half a row (128 bytes) against those of g - 1: blocks stay 1 KiB in a row,
+// as the tile fetch writes them, and the unit of tile dt is an XOR with dt % 4 plus an immediate 128 (dt / 4).
+// (Before, a launch of its own wrote a transposed copy of V: 8 - 26 us and 4 bytes of traffic per element.  Whole call, that form /
+// this: 4 ragged prompts of up to 1024 tokens 68.6 / 56.3 us, 1 x 32 heads x 8192 695.7 / 690.6, 2 x 64/8 heads x 4001, where
+// eight heads share the copy, 578.9 / 588.0: a tile of V takes 16 of these reads where it took 8 of 16 bytes.)
+__device__ __forceinline__ int v_block(int blk) { return blk * 1024 + (blk >> 1) * 128; }   // keys 4 blk .. 4 blk + 3
 
 // K row r, 16-byte chunk c sits in chunk c ^ k_key(r) of the row.  Lane (n, g) reads row r(n) in {0..3, 8..11,
 // 16..19, 24..27} (+4 for the second key block), chunk 4 kb + g: k_key(r) = n for those rows, which puts it in unit
@@ -123,7 +91,8 @@ struct TileWave {
     const unsigned char *kbase, *vbase;
     int keys;                    // the prompt's length: K rows that hold a key
     int k_voff0, k_voff1;        // this thread's two chunks of a K tile, from the tile's start
-    int k_rd[4], v_rd;           // this lane's operand reads, from the start of the LDS tile
+    int v_voff0;                 // ... and its first of a V tile (the second is 4 KiB further)
+    int k_rd[4], v_rd[4];        // this lane's operand reads, from the start of the LDS tile
     f16x8 qB[kQB][4];            // Q^T as the B operand: lane (n, g) holds d = 32 kb + 8g .. +7 of query w0 + 16 qb + n
 
     __device__ __forceinline__ TileWave(const PrefillProblem &p, int b, int hq, int i0, int S)
@@ -139,14 +108,16 @@ struct TileWave {
         mine = last_q >= w0 ? last_q / kStep + 1 : 0;
         const size_t kv_head = (size_t)b * p.Hkv + hq / p.G;
         kbase = reinterpret_cast<const unsigned char *>(p.k + kv_head * p.Smax * kHeadDim);
-        vbase = reinterpret_cast<const unsigned char *>(p.vt + kv_head * kHeadDim * p.Spad);
+        vbase = reinterpret_cast<const unsigned char *>(p.v + kv_head * p.Smax * kHeadDim);
         keys = S;
         const int r = tid >> 4, c = (tid & 15) ^ k_key(r);
         k_voff0 = r * 256 + c * 16;
         k_voff1 = (r + 16) * 256 + (c ^ 8) * 16;                     // k_key(r + 16) = k_key(r) ^ 8
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb) k_rd[kb] = (8 * (n >> 2) + (n & 3)) * 256 + (((4 * kb + g) ^ n) << 4);
-        v_rd = (g * kHeadDim + n) << 4;
+        v_voff0 = r * 256 + (((tid & 15) ^ ((r & 3) << 1)) << 4);    // 32-byte unit ^ key % 4, in 16-byte chunks
+#pragma unroll
+        for (int x = 0; x < 4; ++x) v_rd[x] = v_block(2 * g) + (n >> 2) * 256 + ((x ^ (n >> 2)) << 5) + (n & 3) * 8;
         // rows past the prompt may hold anything: zeros in their place
         const uint16_t *qbase = p.q + (((size_t)b * p.Hq + hq) * p.Smax) * kHeadDim;
 #pragma unroll
@@ -165,28 +136,39 @@ struct TileWave {
     // Buffer loads through a window of kRing tiles: what lies past the last key of the prompt (or past the last tile)
     // arrives as zeros and touches no memory, so the loop can run its fetches ahead without a condition, and
     // inside a window a fetch costs three scalar instructions.
-    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t window(const unsigned char *base, int rows, int t0)
+    __device__ __forceinline__ u32x4 window(const unsigned char *base, int t0) const
     {
-        const int left = __builtin_amdgcn_readfirstlane(max(min(rows - t0 * kStep, kRing * kStep), 0));      // (uniform: keep it scalar)
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(base + (size_t)t0 * kTileBytes), 0, left * (kHeadDim * 2), 0x00027000);
+        const unsigned left = __builtin_amdgcn_readfirstlane(max(min(keys - t0 * kStep, kRing * kStep), 0));      // (uniform: keep it scalar)
+        const unsigned long long at = reinterpret_cast<unsigned long long>(base) + (unsigned long long)t0 * kTileBytes;
+        return u32x4{(unsigned)at, (unsigned)(at >> 32) & 0xffffu, left * (kHeadDim * 2), 0x00027000u};          // raw buffer, stride 0
     }
-    __device__ __forceinline__ __amdgpu_buffer_rsrc_t k_window(int t0) const { return window(kbase, keys, t0); }
-    __device__ __forceinline__ __amdgpu_buffer_rsrc_t v_window(int t0) const { return window(vbase, nsteps * kStep, t0); }
-    __device__ __forceinline__ void fetch(__amdgpu_buffer_rsrc_t rs, int u, int voff0, int voff1, unsigned char *lds_tile) const
+    __device__ __forceinline__ u32x4 k_window(int t0) const { return window(kbase, t0); }
+    __device__ __forceinline__ u32x4 v_window(int t0) const { return window(vbase, t0); }
+    // In assembly, because the compiler waits for the loads it knows to write LDS before every transposing LDS read
+    // (a step then takes 1120 cycles instead of 920); no register is written, and the waits are wait_fetches.  KNOWN: the
+    // builtin, for the prologue, whose loads the compiler has to tell from those of Q^T; it waits for them before the loop.
+    template <bool KNOWN> static __device__ __forceinline__ void load(u32x4 rs, int voff, int soff, unsigned char *lds_1k)
     {
-        auto *dst = (__attribute__((address_space(3))) void *)(lds_tile + wave * 1024);
-        auto *dst1 = (__attribute__((address_space(3))) void *)(lds_tile + wave * 1024 + 4096);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, voff0, u * kTileBytes, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst1, 16, voff1, u * kTileBytes, 0, 0);
+        auto *to = (__attribute__((address_space(3))) unsigned char *)lds_1k;
+        if constexpr (KNOWN) {
+            const unsigned long long base = rs.x | ((unsigned long long)rs.y << 32);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(base), 0, (int)rs.z, (int)rs.w),
+                                                     (__attribute__((address_space(3))) void *)to, 16, voff, soff, 0, 0);
+        } else {
+            const unsigned at = (unsigned)reinterpret_cast<uintptr_t>(to);
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(at), "v"(voff), "s"(rs), "s"(soff) : "memory");
+        }
     }
     // tile u of a window, into place `slot` of the ring
-    __device__ __forceinline__ void fetch_k(PrefillLds &lds, __amdgpu_buffer_rsrc_t rs, int u, int slot) const
+    template <bool KNOWN = false> __device__ __forceinline__ void fetch_k(PrefillLds &lds, u32x4 rs, int u, int slot) const
     {
-        fetch(rs, u, k_voff0, k_voff1, lds.k[slot]);
+        load<KNOWN>(rs, k_voff0, u * kTileBytes, lds.k[slot] + wave * 1024);
+        load<KNOWN>(rs, k_voff1, u * kTileBytes, lds.k[slot] + wave * 1024 + 4096);
     }
-    __device__ __forceinline__ void fetch_v(PrefillLds &lds, __amdgpu_buffer_rsrc_t rs, int u, int slot) const
+    template <bool KNOWN = false> __device__ __forceinline__ void fetch_v(PrefillLds &lds, u32x4 rs, int u, int slot) const
     {
-        fetch(rs, u, (int)threadIdx.x * 16, (int)threadIdx.x * 16 + 4096, lds.v[slot]);
+        load<KNOWN>(rs, v_voff0, u * kTileBytes, lds.v[slot] + v_block(wave));
+        load<KNOWN>(rs, v_voff0, u * kTileBytes + 4096, lds.v[slot] + v_block(wave + 4));
     }
     __device__ __forceinline__ void fetch_k(PrefillLds &lds, int t) const { fetch_k(lds, k_window(t), 0, t & (kRing - 1)); }
     __device__ __forceinline__ void fetch_v(PrefillLds &lds, int t) const { fetch_v(lds, v_window(t), 0, t & (kRing - 1)); }
@@ -196,9 +178,14 @@ struct TileWave {
         // tiles leave lane (n, g) holding keys 8g .. 8g + 7 of query n
         return *reinterpret_cast<const u32x4 *>(&lds.k[0][0] + slot * kTileBytes + k_rd[kb] + 1024 * t);
     }
-    __device__ __forceinline__ u32x4 read_v(const PrefillLds &lds, int slot, int dt) const
+    // V^T operand of tile dt: keys 8g .. 8g + 7 of d = 16 dt + n
+    __device__ __forceinline__ f16x8 read_v(PrefillLds &lds, int slot, int dt) const
     {
-        return *reinterpret_cast<const u32x4 *>(&lds.v[0][0] + slot * kTileBytes + v_rd + 256 * dt);
+        typedef __attribute__((address_space(3))) s16x4 *lds_s16x4;
+        unsigned char *at = &lds.v[0][0] + slot * kVTileBytes + v_rd[dt & 3] + 128 * (dt >> 2);
+        const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)at);
+        const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(at + 1024));
+        return __builtin_bit_cast(f16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
     }
     // scores of one step
     __device__ __forceinline__ void scores(const PrefillLds &lds, int s, f32x4 (&sc)[kQB][2]) const
@@ -228,15 +215,15 @@ struct Weights {
 };
 
 // O^T += V^T P^T with P = Ph + Pl, one step
-__device__ __forceinline__ void add_pv(const TileWave &tw, const PrefillLds &lds, int s, const Weights &w, f32x4 (&acc)[8][kQB])
+__device__ __forceinline__ void add_pv(const TileWave &tw, PrefillLds &lds, int s, const Weights &w, f32x4 (&acc)[8][kQB])
 {
-    u32x4 a_v[2];
+    f16x8 a_v[2];
     const int slot = s & (kRing - 1);
     a_v[0] = tw.read_v(lds, slot, 0);
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) {
         if (dt + 1 < 8) a_v[(dt + 1) & 1] = tw.read_v(lds, slot, dt + 1);
-        const f16x8 v8 = __builtin_bit_cast(f16x8, a_v[dt & 1]);
+        const f16x8 v8 = a_v[dt & 1];
 #pragma unroll
         for (int qb = 0; qb < kQB; ++qb)
             acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v8, __builtin_bit_cast(f16x8, w.hi[qb]), acc[dt][qb], 0, 0, 0);
@@ -334,10 +321,11 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
     // Tiles in LDS: rings of four.  Entering iteration s, K tile s + 2 and V tiles s and s + 1 have landed for
     // every wavefront; iteration s fetches K tile s + 4 and V tile s + 3, whose places were last read in iteration
     // s - 1 at the latest, and waits at its end for what iteration s - 1 fetched: a load has two iterations to land.
-    tw.fetch_k(lds, 0); tw.fetch_k(lds, 1);
-    tw.fetch_v(lds, 0); tw.fetch_k(lds, 2);
-    tw.fetch_v(lds, 1);
-    tw.fetch_k(lds, 3); tw.fetch_v(lds, 2);
+    const u32x4 k0 = tw.k_window(0), v0 = tw.v_window(0);
+    tw.fetch_k<true>(lds, k0, 0, 0); tw.fetch_k<true>(lds, k0, 1, 1);
+    tw.fetch_v<true>(lds, v0, 0, 0); tw.fetch_k<true>(lds, k0, 2, 2);
+    tw.fetch_v<true>(lds, v0, 1, 1);
+    tw.fetch_k<true>(lds, k0, 3, 3); tw.fetch_v<true>(lds, v0, 2, 2);
     auto fetch_ahead = [&](int s) { tw.fetch_k(lds, s + 4); tw.fetch_v(lds, s + 3); };
     auto next_iteration = [&]() { wait_fetches<4>(); workgroup_barrier(); };
 
@@ -387,8 +375,8 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
     // instructions of the weights -- pair i of 8 in slots 6i .. 6i + 5, its last two in the next pair's -- and the LDS
     // read of an operand 8 or 9 slots ahead of its use.
     // slot: s modulo the ring; rk, rv: windows that hold K tile s + 4 and V tile s + 3 as their tile u.
-    auto iteration = [&](int slot, __amdgpu_buffer_rsrc_t rk, __amdgpu_buffer_rsrc_t rv, int u, const f32x4 (&sc)[kQB][2], f32x4 (&scn)[kQB][2],
-                         const Weights &w, Weights &wn, u32x4 (&av)[3]) {
+    auto iteration = [&](int slot, u32x4 rk, u32x4 rv, int u, const f32x4 (&sc)[kQB][2], f32x4 (&scn)[kQB][2],
+                         const Weights &w, Weights &wn, f16x8 (&av)[3]) {
         tw.fetch_k(lds, rk, u, slot);
         tw.fetch_v(lds, rv, u, (slot + 3) & (kRing - 1));
         u32x4 ka[6];
@@ -403,7 +391,7 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
             if (m < 32) {
                 const int dt = m >> 2, qb = m & 1;
                 const u32x4 pw = (m & 2) ? w.lo[qb] : w.hi[qb];
-                acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, av[dt % 3]), __builtin_bit_cast(f16x8, pw), acc[dt][qb], 0, 0, 0);
+                acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[dt % 3], __builtin_bit_cast(f16x8, pw), acc[dt][qb], 0, 0, 0);
             } else {
                 const int op = (m - 32) >> 1, kb = op >> 1, t = op & 1, qb = m & 1;
                 const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -465,7 +453,7 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
 
     f32x4 scA[kQB][2], scB[kQB][2];
     Weights wA, wB;
-    u32x4 av[3];
+    f16x8 av[3];
     wait_fetches<10>();                                       // K tiles 0 and 1
     workgroup_barrier();
     if (mine > 0) {
@@ -473,6 +461,11 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
         weights(true, mine == 1, 0, scB, wA);
         if (mine > 1) tw.scores(lds, 1, scA);
     }
+    // (Q^T has arrived on every path: the loop below needs no wait for it)
+#pragma unroll
+    for (int qb = 0; qb < kQB; ++qb)
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) asm volatile("" ::"v"(tw.qB[qb][kb]));
     wait_fetches<4>();                                        // V tiles 0 and 1, K tile 2
     workgroup_barrier();
     int s = 0;
@@ -482,7 +475,7 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
         // four at a time: places in the ring and registers are then fixed (nothing is computed, nothing is moved)
 #pragma unroll 1
         for (; s + kRing + 2 <= mine; s += kRing) {
-            const __amdgpu_buffer_rsrc_t rk = tw.k_window(s + 4), rv = tw.v_window(s + 3);
+            const u32x4 rk = tw.k_window(s + 4), rv = tw.v_window(s + 3);
             iteration(0, rk, rv, 0, scA, scB, wA, wB, av);
             iteration(1, rk, rv, 1, scB, scA, wB, wA, av);
             iteration(2, rk, rv, 2, scA, scB, wA, wB, av);
@@ -667,8 +660,6 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillProblem p)
 hipError_t launch_prefill(const PrefillProblem &p, hipStream_t s)
 {
     if (p.B == 0) return hipSuccess;
-    hipError_t e = launch(transpose_v_kernel, dim3(p.Spad / 64, p.B * p.Hkv), dim3(256), s, p);
-    if (e != hipSuccess) return e;
     const int qtiles = (p.Smax + kQTile - 1) / kQTile;
     return launch(prefill_kernel, dim3((unsigned)((long long)p.B * p.Hq * qtiles)), dim3(256), s, p);
 }
