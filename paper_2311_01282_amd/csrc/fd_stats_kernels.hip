@@ -3,8 +3,10 @@
 // valid scaled logit x = s <q, k_j>, plus their minimum and maximum.  Reads K (256 B
 // per key and KV head, once per block of query heads that share it), nothing else of size.
 //
-// A fixed grid of workgroups strides over (head block, 256-key tile) items; the lane layout
-// and the dot product are those of the chunk kernels (fd_chunk.h).  Counts go to an
+// A wavefront's unit of work is a run of keys of one KV head; one workgroup of 16 wavefronts (4 where there are few
+// runs) per compute unit strides over the runs.  Query heads that share a KV head go through the matrix cores, 16 heads at a time, so that every key
+// is read once per 16 of them; ungrouped heads take the vector ALU with the lane layout and the dot product of
+// the chunk kernels (fd_chunk.h).  Counts go to an
 // LDS histogram first and reach the device histogram as 64-bit integer atomic adds
 // when the workgroup is done: integer sums, so the result does not depend on order.
 #include "fd_chunk.h"
@@ -12,8 +14,7 @@
 namespace fd {
 namespace {
 
-constexpr int kStatsTile = 256;      // keys per item
-constexpr int kStatsThreads = 256;
+constexpr int kStatsWaves = 16, kStatsFew = 4;    // wavefronts per workgroup: many runs, few runs
 
 // float minimum / maximum through integer atomics (the IEEE order of same-sign floats is
 // the order of their bit patterns, reversed for negatives).  NaN never reaches here.
@@ -28,78 +29,104 @@ __device__ __forceinline__ void atomic_min_float(float *addr, float v)
     else atomicMax(reinterpret_cast<unsigned *>(addr), __builtin_bit_cast(unsigned, v));
 }
 
-// GT = query heads handled per K tile: 1 for ungrouped heads; 4 when heads share a KV
-// head, so that the tile is fetched once per four of them (the other fetches of a larger
-// group hit in L2).  An item is (sequence, KV head, block of GT heads, 256-key tile).
-template <int GT>
-__global__ __launch_bounds__(kStatsThreads) void logit_histogram_kernel(
-    const Problem p, const float x_min, const float inv_width, const int n_bins,
+// The slot of a logit in the histogram, NaN with the logits above the window.
+__device__ __forceinline__ int slot_of(float x, float x_min, float inv_width, int n_bins)
+{
+    if (x != x) return n_bins + 1;
+    const float t = floorf((x - x_min) * inv_width);
+    return t < 0.f ? 0 : (t >= (float)n_bins ? n_bins + 1 : (int)t + 1);
+}
+
+// GROUPED: score tile, K staging in LDS and lane layout of the grouped decode kernel (16 keys x 16 heads by four
+// 16x16x32 MFMAs; lane (n, g) ends up with the logits of head n, keys 4r + g).
+// Bound: HBM reads of K, and at the end the adds of all workgroups to the same n_bins + 2 addresses, which serialize
+// (with 1024 smaller workgroups for grouped heads, four dot products per key on the vector ALU and K fetched once per four
+// heads, the 203 MB of 32 ragged sequences x 64/8 heads x 4096 keys took 89.2 us, now 47.0 with the calls around it; with 512 for
+// ungrouped heads, 1 x 32 heads x 8192 keys 22.9, now 17.3).
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+template <bool GROUPED>
+__global__ __launch_bounds__(kStatsWaves * 64) void logit_histogram_kernel(
+    const Problem p, const float x_min, const float inv_width, const int n_bins, const int run,
     unsigned long long *__restrict__ hist, float *__restrict__ min_max)
 {
-    static_assert(GT <= 16, "one lane of a key's 16 per head");
-    extern __shared__ unsigned lds_hist[];              // n_bins + 2 counters, then 8 floats
+    // (GROUPED: 4 KiB of K staging per wavefront), counters, 2 floats per wavefront
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    const int waves = blockDim.x >> 6;
+    unsigned *lds_hist = reinterpret_cast<unsigned *>(lds_raw + (GROUPED ? waves * 4096 : 0));
     float *lds_mm = reinterpret_cast<float *>(lds_hist + n_bins + 2);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int seg = lane & 15, sub = lane >> 4;
-    for (int i = tid; i < n_bins + 2; i += kStatsThreads) lds_hist[i] = 0u;
+    const int n = lane & 15, g = lane >> 4;
+    u32x4 *kst = reinterpret_cast<u32x4 *>(lds_raw) + wave * 256;
+    for (int i = tid; i < n_bins + 2; i += blockDim.x) lds_hist[i] = 0u;
     __syncthreads();
 
-    constexpr int UP = 4;                                // groups of 4 keys per wavefront and stage
-    constexpr int NBLK = kStatsTile / (16 * UP);         // stages per tile
-    const int tiles = (p.Smax + kStatsTile - 1) / kStatsTile;
-    const int hblocks = (p.G + GT - 1) / GT;
-    const long long items = (long long)p.B * p.Hkv * hblocks * tiles;
+    const int runs = (p.Smax + run - 1) / run;
+    const int hblocks = (p.G + 15) / 16;
+    const long long items = (long long)p.B * p.Hkv * hblocks * runs;
     float lo = INFINITY, hi = -INFINITY;
-    for (long long it = blockIdx.x; it < items; it += gridDim.x) {
-        const int t = (int)(it % tiles);
-        const long long r = it / tiles;
+    // consecutive items to consecutive workgroups: the runs of a KV head spread over the chip
+    for (long long it = (long long)wave * gridDim.x + blockIdx.x; it < items; it += (long long)waves * gridDim.x) {
+        const int t = (int)(it % runs);
+        const long long r = it / runs;
         const int hb = (int)(r % hblocks);
         const int gi = (int)(r / hblocks);               // (sequence, KV head)
         const int b = gi / p.Hkv, hkv = gi - b * p.Hkv;
-        const int nvalid = min(kStatsTile, valid_len(p, b) - t * kStatsTile);
-        if (nvalid <= 0) continue;                       // uniform over the workgroup
+        const int nvalid = min(run, valid_len(p, b) - t * run);
+        if (nvalid <= 0) continue;
         const int last = nvalid - 1;
-        const int h0 = hb * GT, nh = min(GT, p.G - h0);  // heads h0 .. h0 + nh - 1 of the group
-        const int row0 = b * p.Hq + hkv * p.G + h0;
-        u32x4 qv[GT];
+        const int nh = min(16, p.G - 16 * hb);           // heads of this block
+        const int row0 = b * p.Hq + hkv * p.G + 16 * hb;
+        // GROUPED: Q as the B operand, heads past the last are zero rows; else this lane's 16-byte segment of q
+        u32x4 qv[GROUPED ? 4 : 1];
+        if constexpr (GROUPED) {
 #pragma unroll
-        for (int g = 0; g < GT; ++g)
-            qv[g] = reinterpret_cast<const u32x4 *>(p.q + (size_t)(row0 + min(g, nh - 1)) * kHeadDim)[seg];
-        const u32x4 *kp = reinterpret_cast<const u32x4 *>(
-                              p.k + (((size_t)b * p.Hkv + hkv) * p.Smax + (size_t)t * kStatsTile) * kHeadDim) + seg;
-        auto key_of = [&](int g) { return (g * 4 + wave) * 4 + sub; };
-        auto issue = [&](int blk, u32x4 (&kk)[UP]) {
+            for (int kb = 0; kb < 4; ++kb) {
+                qv[kb] = u32x4{0u, 0u, 0u, 0u};
+                if (n < nh) qv[kb] = *reinterpret_cast<const u32x4 *>(p.q + (size_t)(row0 + n) * kHeadDim + 32 * kb + 8 * g);
+            }
+        } else {
+            qv[0] = reinterpret_cast<const u32x4 *>(p.q + (size_t)row0 * kHeadDim)[n];
+        }
+        const u32x4 *kp = reinterpret_cast<const u32x4 *>(p.k + ((size_t)gi * p.Smax + (size_t)t * run) * kHeadDim) + n;
+        auto issue = [&](int blk, u32x4 (&kk)[4]) {
 #pragma unroll
-            for (int u = 0; u < UP; ++u) kk[u] = load_stream(kp + (size_t)min(key_of(blk * UP + u), last) * 16);
+            for (int i = 0; i < 4; ++i) kk[i] = load_stream(kp + (size_t)min(16 * blk + 4 * i + g, last) * 16);
         };
-        auto count = [&](int blk, const u32x4 (&kk)[UP]) {
+        auto add = [&](float x) {
+            lo = fminf(lo, x);                           // (the minimum with a NaN is the other operand)
+            hi = fmaxf(hi, x);
+            atomicAdd(&lds_hist[slot_of(x, x_min, inv_width, n_bins)], 1u);
+        };
+        auto count = [&](int blk, const u32x4 (&kk)[4]) {
+            if constexpr (GROUPED) {
 #pragma unroll
-            for (int u = 0; u < UP; ++u) {
-                const bool valid = key_of(blk * UP + u) <= last;
-                // every lane of the key's 16 ends up with all GT logits; lane `seg` bins head `seg`
-                float x = row16_sum(dot8(qv[0], kk[u])) * p.scale;
+                for (int i = 0; i < 4; ++i) kst[(4 * i + g) * 16 + (n ^ (i | (g << 2)))] = kk[i];
+                const int pk = 4 * (n & 3) + (n >> 2);
+                f32x4 sc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int g = 1; g < GT; ++g) {
-                    const float xg = row16_sum(dot8(qv[g], kk[u])) * p.scale;
-                    x = seg == g ? xg : x;
+                for (int kb = 0; kb < 4; ++kb)
+                    sc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, kst[pk * 16 + ((4 * kb + g) ^ n)]),
+                                                                __builtin_bit_cast(f16x8, qv[kb]), sc, 0, 0, 0);
+                if (n < nh) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (16 * blk + 4 * i + g <= last) add(sc[i] * p.scale);
                 }
-                if (seg < nh && valid) {
-                    int slot;
-                    if (x != x) {
-                        slot = n_bins + 1;
-                    } else {
-                        const float tq = floorf((x - x_min) * inv_width);
-                        slot = tq < 0.f ? 0 : (tq >= (float)n_bins ? n_bins + 1 : (int)tq + 1);
-                        lo = fminf(lo, x);
-                        hi = fmaxf(hi, x);
-                    }
-                    atomicAdd(&lds_hist[slot], 1u);
+            } else {
+                // every lane of a key's 16 ends up with its logit; lane i of them bins key 4i + g
+                float x = 0.f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float xi = row16_sum(dot8(qv[0], kk[i])) * p.scale;
+                    x = n == i ? xi : x;
                 }
+                if (n < 4 && 16 * blk + 4 * n + g <= last) add(x);
             }
         };
-        // two stages in flight; loads past the last valid key re-read it and are not counted
-        const int nblk = min(NBLK, (nvalid + 16 * UP - 1) / (16 * UP));
-        u32x4 kA[UP], kB[UP];
+        // two blocks in flight; loads past the last valid key re-read it and are not counted
+        const int nblk = (nvalid + 15) / 16;
+        u32x4 kA[4], kB[4];
         issue(0, kA);
         int blk = 0;
 #pragma unroll 1
@@ -117,21 +144,20 @@ __global__ __launch_bounds__(kStatsThreads) void logit_histogram_kernel(
             count(blk, kA);
         }
     }
-    // workgroup minimum / maximum: wavefront reduction, then four values through LDS
+    // the workgroup's counts and extremes to memory
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         lo = fminf(lo, __shfl_xor(lo, o));
         hi = fmaxf(hi, __shfl_xor(hi, o));
     }
-    if (lane == 0) { lds_mm[wave] = lo; lds_mm[4 + wave] = hi; }
+    if (lane == 0) { lds_mm[2 * wave] = lo; lds_mm[2 * wave + 1] = hi; }
     __syncthreads();
-    for (int i = tid; i < n_bins + 2; i += kStatsThreads) {
-        const unsigned n = lds_hist[i];
-        if (n) atomicAdd(&hist[i], (unsigned long long)n);
+    for (int i = tid; i < n_bins + 2; i += blockDim.x) {
+        const unsigned c = lds_hist[i];
+        if (c) atomicAdd(&hist[i], (unsigned long long)c);
     }
     if (tid == 0 && min_max) {
-        lo = fminf(fminf(lds_mm[0], lds_mm[1]), fminf(lds_mm[2], lds_mm[3]));
-        hi = fmaxf(fmaxf(lds_mm[4], lds_mm[5]), fmaxf(lds_mm[6], lds_mm[7]));
+        for (int w = 0; w < waves; ++w) { lo = fminf(lo, lds_mm[2 * w]); hi = fmaxf(hi, lds_mm[2 * w + 1]); }
         if (lo <= hi) {                                  // at least one logit that is not NaN was seen
             atomic_min_float(&min_max[0], lo);
             atomic_max_float(&min_max[1], hi);
@@ -144,21 +170,23 @@ __global__ __launch_bounds__(kStatsThreads) void logit_histogram_kernel(
 hipError_t launch_logit_histogram(const Problem &p, float x_min, float bin_width, int n_bins,
                                   unsigned long long *hist, float *min_max, hipStream_t s)
 {
-    const int gt = p.G > 1 ? 4 : 1;
-    const long long items = (long long)p.B * p.Hkv * ((p.G + gt - 1) / gt) * ((p.Smax + kStatsTile - 1) / kStatsTile);
-    if (items == 0) return hipSuccess;
-    // Few workgroups: every one of them ends with up to n_bins + 2 atomic adds on the same
-    // addresses, and those serialize (2048 workgroups cost 25 % more time than 512 on a
-    // 1 GiB cache).  The grouped variant does four dot products per key and needs more
-    // wavefronts to cover them.
-    const long long cap = p.G > 1 ? 1024 : 512;
-    const unsigned grid = (unsigned)(items < cap ? items : cap);
-    const size_t lds = (size_t)(n_bins + 2) * sizeof(unsigned) + 8 * sizeof(float);
+    if (p.rows == 0) return hipSuccess;
+    // Runs of 64 .. 256 keys: the longest that give every wavefront two.
+    const long long units = (long long)p.B * p.Hkv * ((p.G + 15) / 16);
+    int run = 256;
+    while (run > 64 && units * ((p.Smax + run - 1) / run) < 2ll * kStatsWaves * kComputeUnits) run /= 2;
+    const long long items = units * ((p.Smax + run - 1) / run);
+    // Up to four runs per compute unit: small workgroups, and no more of them than have work (512 runs, 1 x 32 heads x 1024
+    // keys: 10.3 us on 256 workgroups of 16 wavefronts, 7.5 on 128 of 4; 1304 runs, 1 x 28/4 x 20816: 12.4 / 14.7).
+    const int waves = items <= (long long)kStatsFew * kComputeUnits ? kStatsFew : kStatsWaves;
+    const long long wanted = (items + waves - 1) / waves;
+    const unsigned grid = (unsigned)(wanted < kComputeUnits ? wanted : kComputeUnits);
     const float inv_width = 1.0f / bin_width;
-    void *args[] = {(void *)&p, (void *)&x_min, (void *)&inv_width, (void *)&n_bins, (void *)&hist, (void *)&min_max};
-    const void *fn = p.G > 1 ? reinterpret_cast<const void *>(&logit_histogram_kernel<4>)
-                             : reinterpret_cast<const void *>(&logit_histogram_kernel<1>);
-    return hipLaunchKernel(fn, dim3(grid), dim3(kStatsThreads), args, lds, s);
+    const size_t lds = (p.G > 1 ? waves * 4096 : 0) + (size_t)(n_bins + 2) * sizeof(unsigned) + waves * 2 * sizeof(float);
+    void *args[] = {(void *)&p, (void *)&x_min, (void *)&inv_width, (void *)&n_bins, (void *)&run, (void *)&hist, (void *)&min_max};
+    const void *fn = p.G > 1 ? reinterpret_cast<const void *>(&logit_histogram_kernel<true>)
+                             : reinterpret_cast<const void *>(&logit_histogram_kernel<false>);
+    return hipLaunchKernel(fn, dim3(grid), dim3(waves * 64), args, lds, s);
 }
 
 }  // namespace fd
