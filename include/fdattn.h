@@ -148,7 +148,7 @@ fd_status fd_workspace_init(const fd_shape *shape, fd_workspace ws, void *stream
  *      partial results, each rescaled from its own reference (phi, or the chunk
  *      maximum) to the row maximum of those references.  For grids of more than
  *      1024 workgroups, or of more than 256 workgroups over 320 MiB or more of cache
- *      (fd_decode_attn_gqa: more than 256 workgroups, or more than 8 chunks per row)
+ *      (fd_decode_attn_gqa: more than 256 workgroups, or more than 16 chunks per row)
  *      step 3 runs as a second, tiny
  *      launch instead (one workgroup per row, no counters): large grids are
  *      throughput-bound and the election's two memory round trips per workgroup

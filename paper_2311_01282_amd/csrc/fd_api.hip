@@ -173,14 +173,15 @@ inline int elect_per_row(const fd::Problem &p)
     return elect_in_kernel(workgroups, 1024, workgroups <= 256 || cache_bytes < (320ll << 20));
 }
 
-// The grouped kernel: its elected workgroup finishes the G rows of its head group by itself,
-// walking each row's chunks in order, which is the cheaper way up to 8 chunks per row and 256
+// The grouped kernel: its elected workgroup finishes the G rows of its head group by itself, up to 16 chunks of
+// each in one memory round trip, which is the cheaper way up to 16 chunks per row and 256
 // workgroups; beyond either the second launch (one workgroup per row, 8 chunk slices in
-// parallel) wins: whole call, one launch / two, 64 query on 8 KV heads -- 25.7 / 26.4 us at 4
-// chunks per row, 17.4 / 17.2 at 8, 18.9 / 17.7 at 16, 18.0 / 15.3 at 24, 30.3 / 27.2 at 32.
+// parallel) wins or ties: whole call, one launch / two, 64 query on 8 KV heads -- 18.4 / 18.6 us at 16 (2 x 9001 keys),
+// 14.3 / 13.1 at 32 (8192 keys), 16.4 / 15.2 at 32 (12000 keys); 32 on 8 heads -- 16.6 / 17.3 at 16 (2 x 8192 keys), 26.3 /
+// 26.6 at 32 (32768 keys).
 inline int elect_grouped(const fd::Problem &p)
 {
-    return elect_in_kernel((long long)p.B * p.Hkv * p.nc, 256, p.nc <= 8);
+    return elect_in_kernel((long long)p.B * p.Hkv * p.nc, 256, p.nc <= 16);
 }
 
 #define FD_TRY(expr) do { if ((expr) != hipSuccess) return FD_ERR_HIP; } while (0)

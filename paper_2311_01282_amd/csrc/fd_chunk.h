@@ -652,15 +652,20 @@ __device__ __forceinline__ void row_epilogue(const Problem &p, int row, int n_lo
 }
 
 // The row epilogue for the G <= 16 rows of one head group at once, by 256 threads or more:
-// thread (h, t) = (tid / 32, tid % 32) owns elements 4t..4t+3 of row row0 + h and walks
-// that row's nb partial results in chunk order with a running maximum of the
+// thread (h, t) = (tid / 32, tid % 32) owns elements 4t..4t+3 of row row0 + h and adds
+// that row's nb partial results in chunk order, each scaled from its own reference to the maximum of the
 // references (Eq. 2; every factor is exactly 1 for an unflagged row, which makes it
-// the plain sum of Eq. 4).  No thread needs another's data: one memory round trip
-// per 4 chunks, two batches in flight, no LDS and no barrier.  Loads pass the caches
+// the plain sum of Eq. 4).  No LDS and no barrier.  A row of up to 16 chunks takes one memory round trip: thread t
+// fetches the slot record of chunk t, and all numerators are on their way before the first record is looked at; the
+// factors then go round the row's 32 lanes by lane exchange.  (Walking records and numerators together, four
+// chunks at a time, was one round trip per eight chunks and two loads per chunk and thread: whole call, that form / this,
+// 4 x 32/8 heads x 4096 keys 16.4 / 15.8 us, 1 x 32 heads x 1024 keys 7.5 / 7.25.)  Loads pass the caches
 // (the partial results come from other workgroups of the same launch).
 // COHERENT = false and a per-row chunk count serve a launch of its own over arbitrary rows.
+// n_load: slots that hold defined values whatever the row's length (a launch of its own: all nc of them), so that the
+// loads need not wait for the length; 0: the nb slots themselves.
 template <bool COHERENT = true, typename NbFn>
-__device__ __forceinline__ void rows_epilogue(const Problem &p, int row0, int G, NbFn nb_of)
+__device__ __forceinline__ void rows_epilogue(const Problem &p, int row0, int G, int n_load, NbFn nb_of)
 {
     const int tid = threadIdx.x, t4 = tid & 31;
     auto ld16 = [](const void *ptr) {
@@ -674,74 +679,75 @@ __device__ __forceinline__ void rows_epilogue(const Problem &p, int row0, int G,
     };
     for (int h = tid >> 5; h < G; h += (int)(blockDim.x >> 5)) {
         const int row = row0 + h;
-        const int nb = nb_of(row);
-        if (nb <= 0) {                          // (only a launch of its own gets here: empty sequence)
-            *reinterpret_cast<uint2 *>(p.out + (size_t)row * kHeadDim + 4 * t4) = make_uint2(0u, 0u);
-            if (t4 == 0) p.ws.row_flags[row] = 0;
-            continue;
-        }
+        int nb = n_load ? 0 : nb_of(row);
+        const int loads = n_load ? n_load : nb;
         const size_t r0 = (size_t)row * p.nc;
         const float *num = p.ws.num + r0 * kHeadDim + 4 * t4;
         const SlotMeta *meta = p.ws.meta + r0;
-        const int cap = nb - 1;                 // nb >= 1: the caller holds one of the row's chunks
+        const int cap = max(loads - 1, 0);
         float m = -INFINITY, l = 0.f;
         float s[4] = {0.f, 0.f, 0.f, 0.f};
         int f = 0;
-        auto issue = [&](int c0, u32x4 (&nv)[4], u32x4 (&mv)[4]) {
+        // chunks c0 .. c0 + 31 of the row, N numerators in flight at a time
+        auto block = [&](int c0, auto n, bool first) {
+            constexpr int N = decltype(n)::value;
+            u32x4 nA[N];
+            auto issue = [&](int c, u32x4 (&nv)[N]) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int c = min(c0 + i, cap);
-                nv[i] = ld16(num + (size_t)c * kHeadDim);
-                mv[i] = ld16(meta + c);
-            }
-        };
-        auto process = [&](int c0, const u32x4 (&nv)[4], const u32x4 (&mv)[4]) {
-            float r[4], bm = -INFINITY;
+                for (int i = 0; i < N; ++i) nv[i] = ld16(num + (size_t)min(c + i, cap) * kHeadDim);
+            };
+            const u32x4 mv = ld16(meta + min(c0 + t4, cap));
+            issue(c0, nA);
+            if (first && n_load) nb = nb_of(row);            // a load of its own, in flight with the others
+            const bool in_row = c0 + t4 < nb;
+            const float ref = in_row ? as_f32(mv[1]) : -INFINITY;
+            f |= in_row ? (int)mv[2] : 0;
+            float bm = ref;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const bool in_row = c0 + i < nb;
-                r[i] = in_row ? as_f32(mv[i][1]) : -INFINITY;
-                bm = fmaxf(bm, r[i]);
-                f |= in_row ? (int)mv[i][2] : 0;
-            }
-            if (bm > m) {
-                const float a = __builtin_amdgcn_exp2f((m - bm) * kLog2e);   // 0 on the first batch
+            for (int o = 16; o > 0; o >>= 1) bm = fmaxf(bm, __shfl_xor(bm, o));
+            if (bm > m) {                                    // rescale what was summed so far (never for unflagged rows)
+                const float a = __builtin_amdgcn_exp2f((m - bm) * kLog2e);   // 0 on the first block
 #pragma unroll
                 for (int e = 0; e < 4; ++e) s[e] *= a;
                 l *= a;
                 m = bm;
             }
+            // exactly 1 when ref == m; 0 for slots outside the row (their sums are finite)
+            const float a = ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ref - m) * kLog2e);
+            const float ad = a * (in_row ? as_f32(mv[0]) : 0.f);
+            auto add = [&](int c, const u32x4 (&nv)[N]) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float a = r[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((r[i] - m) * kLog2e);
+                for (int i = 0; i < N; ++i) {
+                    const float ac = __shfl(a, c - c0 + i, 32);
+                    l += __shfl(ad, c - c0 + i, 32);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) s[e] = __builtin_fmaf(a, as_f32(nv[i][e]), s[e]);
-                l = __builtin_fmaf(a, as_f32(mv[i][0]), l);
+                    for (int e = 0; e < 4; ++e) s[e] = __builtin_fmaf(ac, as_f32(nv[i][e]), s[e]);
+                }
+            };
+            add(c0, nA);
+            if (N == 16 && loads - c0 > N) {
+                issue(c0 + N, nA);
+                add(c0 + N, nA);
             }
         };
-        u32x4 nA[4], mA[4], nB[4], mB[4];
-        issue(0, nA, mA);
-        if (nb <= 4) {
-            process(0, nA, mA);
-        } else {
-            for (int c0 = 0; c0 < nb; c0 += 8) {
-                issue(c0 + 4, nB, mB);
-                process(c0, nA, mA);
-                issue(c0 + 8, nA, mA);
-                if (c0 + 4 < nb) process(c0 + 4, nB, mB);
-            }
-        }
+        if (loads <= 4) block(0, std::integral_constant<int, 4>{}, true);
+        else if (loads <= 8) block(0, std::integral_constant<int, 8>{}, true);
+        else
+            for (int c0 = 0; c0 < loads; c0 += 32) block(c0, std::integral_constant<int, 16>{}, c0 == 0);
         FD_PHASE(6);
-        uint2 o;
-        o.x = (unsigned)to_half_bits(s[0] / l) | ((unsigned)to_half_bits(s[1] / l) << 16);
-        o.y = (unsigned)to_half_bits(s[2] / l) | ((unsigned)to_half_bits(s[3] / l) << 16);
+        const unsigned any = (unsigned)(__ballot(f != 0) >> (tid & 32));   // of this row's 32 lanes
+        uint2 o = make_uint2(0u, 0u);                        // an empty sequence: zeros, no flag
+        if (nb > 0) {
+            o.x = (unsigned)to_half_bits(s[0] / l) | ((unsigned)to_half_bits(s[1] / l) << 16);
+            o.y = (unsigned)to_half_bits(s[2] / l) | ((unsigned)to_half_bits(s[3] / l) << 16);
+        }
         *reinterpret_cast<uint2 *>(p.out + (size_t)row * kHeadDim + 4 * t4) = o;
-        if (t4 == 0) p.ws.row_flags[row] = f ? 1 : 0;
+        if (t4 == 0) p.ws.row_flags[row] = any ? 1 : 0;
     }
 }
 __device__ __forceinline__ void group_epilogue(const Problem &p, int row0, int G, int nb)
 {
-    rows_epilogue<true>(p, row0, G, [nb](int) { return nb; });
+    rows_epilogue<true>(p, row0, G, 0, [nb](int) { return nb; });
 }
 
 // Elects the workgroup that completes a row: a radix-8 tree of arrival counters

@@ -29,7 +29,8 @@ __global__ __launch_bounds__(256) void row_epilogue_kernel(const Problem p)
 __global__ __launch_bounds__(256) void rows8_epilogue_kernel(const Problem p)
 {
     const int row0 = blockIdx.x * 8;
-    rows_epilogue<false>(p, row0, min(8, p.rows - row0), [&](int row) { return (valid_len(p, row / p.Hq) + p.C - 1) / p.C; });
+    // every slot of a row holds defined values, so the loads need not wait for the length
+    rows_epilogue<false>(p, row0, min(8, p.rows - row0), p.nc, [&](int row) { return (valid_len(p, row / p.Hq) + p.C - 1) / p.C; });
 }
 
 // Chunk flags -> row flags, ascending list of flagged rows, their count.

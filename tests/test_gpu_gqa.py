@@ -183,3 +183,21 @@ def test_gqa_weights_beyond_the_fp16_operand_range_stay_exact_and_unflagged(orac
         cf, rf, n, rows = dc.flags()
         assert not cf.any() and not rf.any() and n == 0
     assert np.abs(got - dc.run("fd_decode_attn")).max() <= 1e-3
+
+
+@pytest.mark.parametrize("nc", [1, 2, 4, 5, 8, 9, 15, 16, 17, 32, 33])
+def test_row_finish_over_chunk_counts(oracle, H, nc):
+    """The finish of a row at the edges of its batches of partial results (4, 8, 16, 32) and on both sides of the
+    one-launch rule (16 chunks), one row in another sequence shorter by a chunk, one chunk recomputed: references of
+    the partial results differ."""
+    S = 64 * nc - 5
+    case = synth.make_case(B=2, Hq=6, Hkv=2, D=128, Smax=S, seed=7100 + nc, seq_lens=[S, max(1, S - 64)], poison_padding=True)
+    planted = synth.plant_keys(case, 1, 36.0, seed=7200 + nc, allow_shared_kv=True)
+    want = oracle.attn_exact(case["q"], case["k"], case["v"], case["seq_lens"], case["scale"])
+    (b, h, _), = planted
+    for entry in ("fd_decode_attn_gqa", "fd_decode_attn"):
+        dc = H.DeviceCase(case, chunk=64)
+        for _ in range(2):                      # the second call starts from the counters the first one left
+            H.assert_close(dc.run(entry), want, "%s, %d chunks" % (entry, nc))
+        _, row_flags, n, rows = dc.flags()
+        assert row_flags[b, h] == 1 and n == int(row_flags.sum()) and b * case["Hq"] + h in rows.tolist()
