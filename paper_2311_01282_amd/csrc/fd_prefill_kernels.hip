@@ -27,6 +27,8 @@
 // K and V tiles are loaded from global memory straight into LDS, once per workgroup, and
 // shared by its four wavefronts (rings of four tiles; layouts free of bank conflicts for the
 // 16-byte operand reads).
+#include <utility>
+
 #include "fd_chunk.h"
 
 namespace fd {
@@ -170,6 +172,14 @@ struct TileWave {
         load<KNOWN>(rs, v_voff0, u * kTileBytes, lds.v[slot] + v_block(wave));
         load<KNOWN>(rs, v_voff0, u * kTileBytes + 4096, lds.v[slot] + v_block(wave + 4));
     }
+    // one of the four loads of a thread: K tile u of window rk into place k_slot, V tile u of window rv into place v_slot
+    __device__ __forceinline__ void fetch_piece(PrefillLds &lds, int piece, u32x4 rk, u32x4 rv, int u, int k_slot, int v_slot) const
+    {
+        if (piece == 0) load<false>(rk, k_voff0, u * kTileBytes, lds.k[k_slot] + wave * 1024);
+        if (piece == 1) load<false>(rk, k_voff1, u * kTileBytes, lds.k[k_slot] + wave * 1024 + 4096);
+        if (piece == 2) load<false>(rv, v_voff0, u * kTileBytes, lds.v[v_slot] + v_block(wave));
+        if (piece == 3) load<false>(rv, v_voff0, u * kTileBytes + 4096, lds.v[v_slot] + v_block(wave + 4));
+    }
     __device__ __forceinline__ void fetch_k(PrefillLds &lds, int t) const { fetch_k(lds, k_window(t), 0, t & (kRing - 1)); }
     __device__ __forceinline__ void fetch_v(PrefillLds &lds, int t) const { fetch_v(lds, v_window(t), 0, t & (kRing - 1)); }
     __device__ __forceinline__ u32x4 read_k(const PrefillLds &lds, int slot, int kb, int t) const
@@ -268,6 +278,7 @@ __device__ __forceinline__ void store_rows(const PrefillProblem &p, const TileWa
     }
 }
 
+__device__ __forceinline__ void wait_reads() { __builtin_amdgcn_s_waitcnt(0xc07f); }   // lgkmcnt(0): LDS reads have arrived
 template <int N> __device__ __forceinline__ void wait_fetches()        // at most N of this wavefront's loads outstanding
 {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
@@ -293,10 +304,9 @@ __device__ __forceinline__ void workgroup_barrier()                   // of the 
 // The two wavefronts of a SIMD then take a step per 923 cycles between them, against 1560 for scores, weights and P.V
 // of one step after the other.  Whole call, that form / this, same workgroup order: 4 ragged prompts of up to 1024 tokens
 // 84.7 / 79.2 us, 2 x 64/8 heads x 4001 676.8 / 623.1, 1 x 32 heads x 8192 780.8 / 753.5.
-template <class F> __device__ __forceinline__ void pinned(F f)       // what f issues stays between its neighbours
+template <class F, int... I> __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F f)
 {
-    f();
-    __builtin_amdgcn_sched_barrier(0);
+    (f(std::integral_constant<int, I>{}), ...);
 }
 __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds &lds, int b, int hq, int i0, int S)
 {
@@ -370,45 +380,44 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
         }
     };
 
-    // Iteration s in full.  av: the first two V operands of step s, read ahead (and left holding those of s + 1).
+    // Iteration s in full.  av: the V operands of step s, the first four read ahead (and left holding those of s + 1).
     // The 48 matrix instructions in order, P.V (32) before scores (16); behind each up to two or three vector
-    // instructions of the weights -- pair i of 8 in slots 6i .. 6i + 5, its last two in the next pair's -- and the LDS
-    // read of an operand 8 or 9 slots ahead of its use.
+    // instructions of the weights -- pair i of 8 in slots 6i .. 6i + 5, its last two in the next pair's -- and
+    // at most one of the 24 LDS reads or four tile fetches.  The reads of 16 slots are waited for at once, before the 16 that use
+    // them (a wait per operand, 17 an iteration, cost 90 of 1560 cycles, the wavefront that leads its SIMD counted), and the fetches
+    // are spread because the four wavefronts are in step: 16 loads at a time queue for the address unit (another 80).
+    // 1 x 32 heads x 8192 tokens: 673 us with neither, 653 with the first, 648 with both.
     // slot: s modulo the ring; rk, rv: windows that hold K tile s + 4 and V tile s + 3 as their tile u.
     auto iteration = [&](int slot, u32x4 rk, u32x4 rv, int u, const f32x4 (&sc)[kQB][2], f32x4 (&scn)[kQB][2],
-                         const Weights &w, Weights &wn, f16x8 (&av)[3]) {
-        tw.fetch_k(lds, rk, u, slot);
-        tw.fetch_v(lds, rv, u, (slot + 3) & (kRing - 1));
-        u32x4 ka[6];
+                         const Weights &w, Weights &wn, f16x8 (&av)[8]) {
+        u32x4 ka[8];
         float z0 = 0.f, z1 = 0.f, e0 = 0.f, e1 = 0.f, f0 = 0.f, f1 = 0.f;      // the pair in work; f: its predecessor's weights
         _Float16 h0 = 0, h1 = 0;                                                 // ... and their hi parts
         unsigned hp = 0;
         f16x2 lp = {0, 0};
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int m = 0; m < 48; ++m) {
+        unrolled(std::make_integer_sequence<int, 48>{}, [&](auto slot_index) {
+            constexpr int m = decltype(slot_index)::value;
             // matrix instruction m
-            if (m < 32) {
-                const int dt = m >> 2, qb = m & 1;
+            if constexpr (m < 32) {
+                constexpr int dt = m >> 2, qb = m & 1;
                 const u32x4 pw = (m & 2) ? w.lo[qb] : w.hi[qb];
-                acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[dt % 3], __builtin_bit_cast(f16x8, pw), acc[dt][qb], 0, 0, 0);
+                acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[dt], __builtin_bit_cast(f16x8, pw), acc[dt][qb], 0, 0, 0);
             } else {
-                const int op = (m - 32) >> 1, kb = op >> 1, t = op & 1, qb = m & 1;
+                constexpr int op = (m - 32) >> 1, kb = op >> 1, t = op & 1, qb = m & 1;
                 const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-                scn[qb][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, ka[op % 6]), tw.qB[qb][kb], kb == 0 ? zero : scn[qb][t], 0, 0, 0);
+                scn[qb][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, ka[op]), tw.qB[qb][kb], kb == 0 ? zero : scn[qb][t], 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
-            // operand reads
-            if (m < 24 && (m & 3) == 0) av[((m >> 2) + 2) % 3] = tw.read_v(lds, slot, (m >> 2) + 2);
-            if (m >= 23 && m < 38 && ((m - 23) & 1) == 0) {
-                const int op = (m - 23) >> 1;
-                ka[op % 6] = tw.read_k(lds, (slot + 2) & (kRing - 1), op >> 1, op & 1);
-            }
-            if (m == 40) av[0] = tw.read_v(lds, (slot + 1) & (kRing - 1), 0);
-            if (m == 42) av[1] = tw.read_v(lds, (slot + 1) & (kRing - 1), 1);
+            // operand reads and tile fetches
+            if constexpr (m < 8 && m % 2 == 1) av[4 + m / 2] = tw.read_v(lds, slot, 4 + m / 2);
+            if constexpr (m >= 17 && m < 25) ka[m - 17] = tw.read_k(lds, (slot + 2) & (kRing - 1), (m - 17) >> 1, (m - 17) & 1);
+            if constexpr (m >= 33 && m < 41 && m % 2 == 1) av[(m - 33) / 2] = tw.read_v(lds, (slot + 1) & (kRing - 1), (m - 33) / 2);
+            if constexpr (m >= 6 && (m - 6) % 11 == 0) tw.fetch_piece(lds, (m - 6) / 11, rk, rv, u, slot, (slot + 3) & (kRing - 1));
+            if constexpr (m % 16 == 15) wait_reads();
             // weights: pair pr = (query block, keys 2j, 2j + 1)
-            const int pr = m / 6, qb = pr >> 2, j = pr & 3;
-            const int pp = pr - 1, pqb = pp >> 2, pj = pp & 3;               // the pair before
+            constexpr int pr = m / 6, qb = pr >> 2, j = pr & 3;
+            constexpr int pp = pr - 1, pqb = pp >> 2, pj = pp & 3;               // the pair before
             switch (m % 6) {
                 case 0:
                     z0 = __builtin_fmaf(sc[qb][j >> 1][2 * (j & 1)], c1, c0q[qb]);
@@ -424,11 +433,11 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
                     break;
                 case 3:
                     den[qb] += e0;
-                    if (pp >= 0) lp.x = (_Float16)__builtin_fmaf((float)h0, neg1, f0);
+                    if constexpr (pp >= 0) lp.x = (_Float16)__builtin_fmaf((float)h0, neg1, f0);
                     break;
                 case 4:
                     den[qb] += e1;
-                    if (pp >= 0) {
+                    if constexpr (pp >= 0) {
                         lp.y = (_Float16)__builtin_fmaf((float)h1, neg1, f1);
                         wn.lo[pqb][pj] = __builtin_bit_cast(unsigned, lp);
                     }
@@ -439,7 +448,7 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
                     hp = __builtin_bit_cast(unsigned, h);
                     wn.hi[qb][j] = hp;
                     f0 = e0; f1 = e1;
-                    if (pr == 7) {
+                    if constexpr (pr == 7) {
                         lp.x = (_Float16)__builtin_fmaf((float)h0, neg1, f0);
                         lp.y = (_Float16)__builtin_fmaf((float)h1, neg1, f1);
                         wn.lo[qb][j] = __builtin_bit_cast(unsigned, lp);
@@ -447,13 +456,13 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
-        }
+        });
         next_iteration();
     };
 
     f32x4 scA[kQB][2], scB[kQB][2];
     Weights wA, wB;
-    f16x8 av[3];
+    f16x8 av[8];
     wait_fetches<10>();                                       // K tiles 0 and 1
     workgroup_barrier();
     if (mine > 0) {
@@ -470,8 +479,9 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
     workgroup_barrier();
     int s = 0;
     if (mine > 2) {
-        av[0] = tw.read_v(lds, 0, 0);
-        av[1] = tw.read_v(lds, 0, 1);
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) av[dt] = tw.read_v(lds, 0, dt);
+        wait_reads();
         // four at a time: places in the ring and registers are then fixed (nothing is computed, nothing is moved)
 #pragma unroll 1
         for (; s + kRing + 2 <= mine; s += kRing) {
