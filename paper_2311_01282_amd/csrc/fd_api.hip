@@ -176,8 +176,8 @@ inline int elect_per_row(const fd::Problem &p)
 // The grouped kernel: its elected workgroup finishes the G rows of its head group by itself, up to 16 chunks of
 // each in one memory round trip, which is the cheaper way up to 16 chunks per row and 256
 // workgroups; beyond either the second launch (one workgroup per row, 8 chunk slices in
-// parallel) wins or ties: whole call, one launch / two, 64 query on 8 KV heads -- 18.4 / 18.6 us at 16 (2 x 9001 keys),
-// 14.3 / 13.1 at 32 (8192 keys), 16.4 / 15.2 at 32 (12000 keys); 32 on 8 heads -- 16.6 / 17.3 at 16 (2 x 8192 keys), 26.3 /
+// parallel) wins or ties: whole call, one launch / two, 64 query on 8 KV heads -- 18.1 / 18.5 us at 16 (2 x 9001 keys),
+// 14.3 / 13.1 at 32 (8192 keys), 16.4 / 15.2 at 32 (12000 keys); 32 on 8 heads -- 16.3 / 17.4 at 16 (2 x 8192 keys), 26.3 /
 // 26.6 at 32 (32768 keys).
 inline int elect_grouped(const fd::Problem &p)
 {

@@ -15,6 +15,7 @@
 #pragma once
 
 #include <type_traits>
+#include <utility>
 
 #include "fd_internal.h"
 
@@ -88,6 +89,21 @@ __device__ __forceinline__ float row16_sum(float x)
     x += dpp_swap<0x141>(x);  // row_half_mirror      : other quad of the 8
     x += dpp_swap<0x140>(x);  // row_mirror           : other half of the 16
     return x;
+}
+
+// Maximum over the 16 lanes of a DPP row; every lane ends with it.
+__device__ __forceinline__ float row16_max(float x)
+{
+    x = fmaxf(x, dpp_swap<0xB1>(x));
+    x = fmaxf(x, dpp_swap<0x4E>(x));
+    x = fmaxf(x, dpp_swap<0x141>(x));
+    return fmaxf(x, dpp_swap<0x140>(x));
+}
+// The value of lane I of the DPP row in all its lanes (row_newbcast).
+template <int I> __device__ __forceinline__ float row16_lane(float x) { return dpp_swap<0x150 + I>(x); }
+template <class F, int... I> __device__ __forceinline__ void each16(std::integer_sequence<int, I...>, F f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
 }
 
 // Device-coherent accesses for results that another workgroup of the SAME launch
@@ -655,16 +671,18 @@ __device__ __forceinline__ void row_epilogue(const Problem &p, int row, int n_lo
 // thread (h, t) = (tid / 32, tid % 32) owns elements 4t..4t+3 of row row0 + h and adds
 // that row's nb partial results in chunk order, each scaled from its own reference to the maximum of the
 // references (Eq. 2; every factor is exactly 1 for an unflagged row, which makes it
-// the plain sum of Eq. 4).  No LDS and no barrier.  A row of up to 16 chunks takes one memory round trip: thread t
-// fetches the slot record of chunk t, and all numerators are on their way before the first record is looked at; the
-// factors then go round the row's 32 lanes by lane exchange.  (Walking records and numerators together, four
+// the plain sum of Eq. 4).  No LDS and no barrier.  A row of up to 16 chunks takes one memory round trip: threads t and 16 + t
+// fetch the slot record of chunk t, and all numerators are on their way before the first record is looked at; maximum
+// and factors then go round each group of 16 lanes by DPP row operations (through LDS exchanges, five dependent ones for the maximum,
+// 0.3 us more).  (Walking records and numerators together, four
 // chunks at a time, was one round trip per eight chunks and two loads per chunk and thread: whole call, that form / this,
-// 4 x 32/8 heads x 4096 keys 16.4 / 15.8 us, 1 x 32 heads x 1024 keys 7.5 / 7.25.)  Loads pass the caches
+// 4 x 32/8 heads x 4096 keys 16.2 / 15.4 us, 1 x 32 heads x 1024 keys 7.5 / 7.0.)  Loads pass the caches
 // (the partial results come from other workgroups of the same launch).
 // COHERENT = false and a per-row chunk count serve a launch of its own over arbitrary rows.
 // n_load: slots that hold defined values whatever the row's length (a launch of its own: all nc of them), so that the
 // loads need not wait for the length; 0: the nb slots themselves.
-template <bool COHERENT = true, typename NbFn>
+// FLAGS: whether the row flags are written (the synchronized scheme has none).
+template <bool COHERENT = true, bool FLAGS = true, typename NbFn>
 __device__ __forceinline__ void rows_epilogue(const Problem &p, int row0, int G, int n_load, NbFn nb_of)
 {
     const int tid = threadIdx.x, t4 = tid & 31;
@@ -688,23 +706,19 @@ __device__ __forceinline__ void rows_epilogue(const Problem &p, int row0, int G,
         float m = -INFINITY, l = 0.f;
         float s[4] = {0.f, 0.f, 0.f, 0.f};
         int f = 0;
-        // chunks c0 .. c0 + 31 of the row, N numerators in flight at a time
-        auto block = [&](int c0, auto n, bool first) {
+        // chunks c0 .. c0 + N - 1 of the row (N <= 16): their numerators in flight together, lane j of the row's two groups
+        // of 16 holds the record of chunk c0 + j
+        auto block = [&](int c0, auto n) {
             constexpr int N = decltype(n)::value;
-            u32x4 nA[N];
-            auto issue = [&](int c, u32x4 (&nv)[N]) {
+            const u32x4 mv = ld16(meta + min(c0 + (t4 & 15), cap));
+            u32x4 nv[N];
 #pragma unroll
-                for (int i = 0; i < N; ++i) nv[i] = ld16(num + (size_t)min(c + i, cap) * kHeadDim);
-            };
-            const u32x4 mv = ld16(meta + min(c0 + t4, cap));
-            issue(c0, nA);
-            if (first && n_load) nb = nb_of(row);            // a load of its own, in flight with the others
-            const bool in_row = c0 + t4 < nb;
+            for (int i = 0; i < N; ++i) nv[i] = ld16(num + (size_t)min(c0 + i, cap) * kHeadDim);
+            if (c0 == 0 && n_load) nb = nb_of(row);          // a load of its own, in flight with the others
+            const bool in_row = (t4 & 15) < min(N, nb - c0);
             const float ref = in_row ? as_f32(mv[1]) : -INFINITY;
             f |= in_row ? (int)mv[2] : 0;
-            float bm = ref;
-#pragma unroll
-            for (int o = 16; o > 0; o >>= 1) bm = fmaxf(bm, __shfl_xor(bm, o));
+            const float bm = row16_max(ref);
             if (bm > m) {                                    // rescale what was summed so far (never for unflagged rows)
                 const float a = __builtin_amdgcn_exp2f((m - bm) * kLog2e);   // 0 on the first block
 #pragma unroll
@@ -715,25 +729,18 @@ __device__ __forceinline__ void rows_epilogue(const Problem &p, int row0, int G,
             // exactly 1 when ref == m; 0 for slots outside the row (their sums are finite)
             const float a = ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ref - m) * kLog2e);
             const float ad = a * (in_row ? as_f32(mv[0]) : 0.f);
-            auto add = [&](int c, const u32x4 (&nv)[N]) {
+            each16(std::make_integer_sequence<int, N>{}, [&](auto lane_of) {
+                constexpr int i = decltype(lane_of)::value;
+                const float ac = row16_lane<i>(a);
+                l += row16_lane<i>(ad);
 #pragma unroll
-                for (int i = 0; i < N; ++i) {
-                    const float ac = __shfl(a, c - c0 + i, 32);
-                    l += __shfl(ad, c - c0 + i, 32);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) s[e] = __builtin_fmaf(ac, as_f32(nv[i][e]), s[e]);
-                }
-            };
-            add(c0, nA);
-            if (N == 16 && loads - c0 > N) {
-                issue(c0 + N, nA);
-                add(c0 + N, nA);
-            }
+                for (int e = 0; e < 4; ++e) s[e] = __builtin_fmaf(ac, as_f32(nv[i][e]), s[e]);
+            });
         };
-        if (loads <= 4) block(0, std::integral_constant<int, 4>{}, true);
-        else if (loads <= 8) block(0, std::integral_constant<int, 8>{}, true);
+        if (loads <= 4) block(0, std::integral_constant<int, 4>{});
+        else if (loads <= 8) block(0, std::integral_constant<int, 8>{});
         else
-            for (int c0 = 0; c0 < loads; c0 += 32) block(c0, std::integral_constant<int, 16>{}, c0 == 0);
+            for (int c0 = 0; c0 < loads; c0 += 16) block(c0, std::integral_constant<int, 16>{});
         FD_PHASE(6);
         const unsigned any = (unsigned)(__ballot(f != 0) >> (tid & 32));   // of this row's 32 lanes
         uint2 o = make_uint2(0u, 0u);                        // an empty sequence: zeros, no flag
@@ -742,7 +749,7 @@ __device__ __forceinline__ void rows_epilogue(const Problem &p, int row0, int G,
             o.y = (unsigned)to_half_bits(s[2] / l) | ((unsigned)to_half_bits(s[3] / l) << 16);
         }
         *reinterpret_cast<uint2 *>(p.out + (size_t)row * kHeadDim + 4 * t4) = o;
-        if (t4 == 0) p.ws.row_flags[row] = any ? 1 : 0;
+        if (FLAGS && t4 == 0) p.ws.row_flags[row] = any ? 1 : 0;
     }
 }
 __device__ __forceinline__ void group_epilogue(const Problem &p, int row0, int G, int nb)
