@@ -626,6 +626,13 @@ __device__ __forceinline__ void tile_sync(const PrefillProblem &p, PrefillLds &l
     store_rows(p, tw, b, hq, S, acc, den);
 }
 
+// Which tile of the order below workgroup i of `grid` runs: a permutation that keeps i % 8.
+__device__ __forceinline__ int tile_order(int i, int grid)
+{
+    if (i < kComputeUnits || grid > 2 * kComputeUnits || grid % 8 != 0) return i;
+    return kComputeUnits + grid - 8 - (i & ~7) + (i & 7);
+}
+
 __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillProblem p)
 {
     __shared__ PrefillLds lds;
@@ -638,10 +645,15 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillProblem p)
     // 8192 753.5 / 695.7.)
     const int heads = p.B * p.Hq, kv_heads = p.B * p.Hkv;
     const int qtiles = (p.Smax + kQTile - 1) / kQTile;
-    const int rank = blockIdx.x / heads;                         // 0: the last tile of every head
-    const int u = blockIdx.x - rank * heads;
+    // A launch of one to two tiles per compute unit: a compute unit holds workgroups i and i + 256 from the start, so the second
+    // half runs light tiles first and the heaviest shares its compute unit with the lightest (the XCD stays the same).  Whole call,
+    // without / with: 1 x 32 heads x 2048 tokens 60.7 / 55.5 us, 1 x 16 x 4096 107.0 / 96.8, 2 x 32 x 1024 37.7 / 35.4,
+    // 1 x 32 x 1100 28.8 / 28.7.
+    const int item = tile_order(blockIdx.x, gridDim.x);
+    const int rank = item / heads;                               // 0: the last tile of every head
+    const int u = item - rank * heads;
     int head = u;
-    if (kv_heads % 8 == 0) {                                      // u % 8 == blockIdx.x % 8
+    if (kv_heads % 8 == 0) {                                      // u % 8 == item % 8 == blockIdx.x % 8
         const int m = u >> 3;
         head = ((u & 7) + 8 * (m / p.G)) * p.G + m % p.G;
     }

@@ -262,3 +262,24 @@ def test_short_prompts_sweep(H):
         want, flag, margin = pf.prefill_rows(q, k, v, sl, scale, rows, phi=synth.PHI, lo=LO, hi=HI, nthreads=8)
         got, tf = run_gpu(q, k, v, sl, scale)
         close(H, got.reshape(-1, 128), want, "short prompts, seed %d %s" % (seed, (B, Hq, Hkv, Smax, lens)))
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Smax,lens", [
+    (1, 40, 8, 897, [890]),                # 320 tiles: the second half of the launch in reverse, groups of 5
+    (2, 28, 4, 1000, [1000, 333]),         # 448 tiles, KV heads that do not divide by 8: tiles go round-robin
+    (1, 33, 33, 1030, None),               # 297 tiles: a count that 8 does not divide keeps its order
+    (3, 2, 1, 161, [161, 96, 33]),         # ring and loop edges: 1 .. 6 key steps
+    (1, 3, 1, 383, [353]),                 # 12 steps: the loop of four, its remainder, a wavefront without queries
+])
+def test_tile_order_and_loop_edges(H, B, Hq, Hkv, Smax, lens):
+    """Every tile of the launch is run once whatever its order; rows around every tile and step edge."""
+    q, k, v, sl = draw(B, Hq, Hkv, Smax, lens, seed=5000 + Smax)
+    scale = synth.default_scale(128)
+    got, flags = run_gpu(q, k, v, sl, scale)
+    edges = sorted({i for e in range(0, Smax, 32) for i in (e, e + 31) if i < Smax} | {int(n) - 1 for n in sl})
+    rows = np.array([(b, h, i) for b in range(B) for h in range(Hq) for i in edges[(h + b) % 3::3] if i < sl[b]], dtype=np.int32)
+    want, flag, margin = pf.prefill_rows(q, k, v, sl, scale, rows, phi=synth.PHI, lo=LO, hi=HI, nthreads=8)
+    close(H, got[rows[:, 0], rows[:, 1], rows[:, 2]], want, "prefill %s" % ((B, Hq, Hkv, Smax),))
+    assert not flag.any() and not flags.any()
+    for b in range(B):
+        assert not got[b, :, sl[b]:].any()
