@@ -294,16 +294,17 @@ __device__ __forceinline__ void workgroup_barrier()                   // of the 
 // synchronized scheme -- its guard fired (recorded in tile_flags) or a weight left the range of the fp16 operands (not
 // recorded: the result is the same either way).
 //
-// What bounds it: the matrix pipe and the issue port of a SIMD, and at that rate the clock (a run of 8192 tokens holds
-// 1.7 - 1.75 GHz).  A step of a wavefront is 48 matrix instructions of 16 pipe cycles (768) and 88 vector instructions;
-// the vector instructions of one wavefront do not run under the matrix instructions of the other wavefront of its SIMD,
-// but within a wavefront up to two independent ones do per matrix instruction (a probe of 48 + 96 takes 810 cycles, with
-// 16 exponentials 955).  So the three parts of a step are taken from three different steps, which do not depend on
-// each other, and woven together by hand: iteration s runs
+// What bounds it: the matrix pipe and the issue port of a SIMD, and at that rate power (a run of 8192 tokens holds
+// 1.65 GHz; one wavefront per SIMD 2.1).  A step of a wavefront is 48 matrix instructions of 16 pipe cycles (768) and 88
+// vector instructions; the vector instructions of one wavefront do not run under the matrix instructions of the other
+// wavefront of its SIMD, but within a wavefront up to two independent ones do per matrix instruction (a probe of 48 + 96 takes
+// 810 cycles, with 16 exponentials 955).  So the three parts of a step are taken from three different steps, which do not
+// depend on each other, and woven together by hand: iteration s runs
 //     P.V of step s  |  weights of step s + 1  |  scores of step s + 2
-// The two wavefronts of a SIMD then take a step per 923 cycles between them, against 1560 for scores, weights and P.V
-// of one step after the other.  Whole call, that form / this, same workgroup order: 4 ragged prompts of up to 1024 tokens
-// 84.7 / 79.2 us, 2 x 64/8 heads x 4001 676.8 / 623.1, 1 x 32 heads x 8192 780.8 / 753.5.
+// The two wavefronts of a SIMD then take a step per 864 cycles between them, against 1560 for scores, weights and P.V
+// of one step after the other.  1 x 32 heads x 8192 tokens: 853 TFLOP/s of useful work (710 before the weaving and
+// what followed it), 1.28 PFLOP/s issued.  32x32x16 matrix instructions in the same loop: 839 cycles where this one then took
+// 947, but the clock fell from 1.77 to 1.48 GHz (726 us against 685).
 template <class F, int... I> __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F f)
 {
     (f(std::integral_constant<int, I>{}), ...);
