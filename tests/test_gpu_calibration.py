@@ -78,21 +78,22 @@ def test_histogram_accumulates_and_keeps_outliers_apart():
     check_histogram(got, 3 * want, 3 * near)
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,Smax,lens", [
-    (1, 2, 1, 65, None),                   # one key past a run of 64
-    (1, 34, 2, 130, [129]),                # groups of 17: two blocks of heads
-    (2, 32, 2, 1040, [1040, 17]),          # groups of 16: a full block
-    (3, 10, 2, 79, [79, 16, 15]),          # a block of 16 keys, one short of it
-    (9, 16, 8, 1500, None),                # 1728 runs: more than four per compute unit, large workgroups
-    (2, 5, 5, 130, [130, 0]),              # ungrouped, an empty sequence
+@pytest.mark.parametrize("B,Hq,Hkv,Smax,lens,n_bins", [
+    (1, 2, 1, 65, None, 128),               # one key past a run of 64
+    (1, 34, 2, 130, [129], 128),            # groups of 17: two blocks of heads
+    (2, 32, 2, 1040, [1040, 17], 128),      # groups of 16: a full block
+    (3, 10, 2, 79, [79, 16, 15], 128),      # a block of 16 keys, one short of it
+    (9, 16, 8, 1500, None, 128),            # 1728 runs: more than four per compute unit, large workgroups
+    (9, 16, 8, 1500, None, 4096),           # ... and the most counters beside their staging: 80 KiB of LDS
+    (2, 5, 5, 130, [130, 0], 128),          # ungrouped, an empty sequence
 ])
-def test_histogram_runs_and_head_blocks(B, Hq, Hkv, Smax, lens):
+def test_histogram_runs_and_head_blocks(B, Hq, Hkv, Smax, lens, n_bins):
     case = synth.make_case(B=B, Hq=Hq, Hkv=Hkv, D=128, Smax=Smax, seed=811 + Smax, seq_lens=lens, poison_padding=True)
     if B == 3:
         case["k"][0, 1, 70, 5] = np.float16(np.nan)            # its logits go to the last slot, nothing else does
-    want, lo, hi, near = cal.logit_histogram(case["q"], case["k"], case["seq_lens"], case["scale"], -4.0, 0.0625, 128,
+    want, lo, hi, near = cal.logit_histogram(case["q"], case["k"], case["seq_lens"], case["scale"], -4.0, 8.0 / n_bins, n_bins,
                                              nthreads=8, edge_eps=EDGE_EPS)
-    got, mm = gpu_histogram(case, -4.0, 0.0625, 128)
+    got, mm = gpu_histogram(case, -4.0, 8.0 / n_bins, n_bins)
     check_histogram(got, want, near)
     if B != 3:
         assert mm[0] == pytest.approx(lo, abs=1e-4) and mm[1] == pytest.approx(hi, abs=1e-4)
