@@ -283,9 +283,12 @@ template <int N> __device__ __forceinline__ void wait_fetches()        // at mos
 {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
-__device__ __forceinline__ void workgroup_barrier()                   // of the LDS tiles: no wait for loads in flight
+// Of the LDS tiles: past it a place that this wavefront has read may be filled again, so its LDS reads have to have returned (the
+// compiler would let the last ones, and the matrix instructions that use them, drift past a bare barrier); loads in flight are not waited for.
+__device__ __forceinline__ void workgroup_barrier()
 {
     asm volatile("" ::: "memory");
+    wait_reads();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 }
@@ -331,7 +334,8 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
 
     // Tiles in LDS: rings of four.  Entering iteration s, K tile s + 2 and V tiles s and s + 1 have landed for
     // every wavefront; iteration s fetches K tile s + 4 and V tile s + 3, whose places were last read in iteration
-    // s - 1 at the latest, and waits at its end for what iteration s - 1 fetched: a load has two iterations to land.
+    // s - 1 at the latest (those reads have returned: workgroup_barrier), and waits at its end for what iteration s - 1 fetched: a
+    // load has two iterations to land.
     const u32x4 k0 = tw.k_window(0), v0 = tw.v_window(0);
     tw.fetch_k<true>(lds, k0, 0, 0); tw.fetch_k<true>(lds, k0, 1, 1);
     tw.fetch_v<true>(lds, v0, 0, 0); tw.fetch_k<true>(lds, k0, 2, 2);
@@ -415,7 +419,7 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
             if constexpr (m >= 17 && m < 25) ka[m - 17] = tw.read_k(lds, (slot + 2) & (kRing - 1), (m - 17) >> 1, (m - 17) & 1);
             if constexpr (m >= 33 && m < 41 && m % 2 == 1) av[(m - 33) / 2] = tw.read_v(lds, (slot + 1) & (kRing - 1), (m - 33) / 2);
             if constexpr (m >= 6 && (m - 6) % 11 == 0) tw.fetch_piece(lds, (m - 6) / 11, rk, rv, u, slot, (slot + 3) & (kRing - 1));
-            if constexpr (m % 16 == 15) wait_reads();
+            if constexpr (m % 16 == 15 && m < 47) wait_reads();                // (the last 16 slots' reads: at the barrier)
             // weights: pair pr = (query block, keys 2j, 2j + 1)
             constexpr int pr = m / 6, qb = pr >> 2, j = pr & 3;
             constexpr int pp = pr - 1, pqb = pp >> 2, pj = pp & 3;               // the pair before

@@ -1,0 +1,92 @@
+"""The prompt kernel's LDS tiles are filled by loads the compiler does not know of and handed over by bare barriers, so the
+waits around them are the source's own.  These tests compile the kernel for gfx950 and follow them through the assembly."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2311_01282_amd import build
+
+pytestmark = pytest.mark.skipif(not os.path.exists("/opt/rocm/bin/hipcc"), reason="needs hipcc")
+
+
+class Code:
+    """Basic blocks of one kernel: lists of (instruction, whether it stands in inline assembly), and their successors."""
+
+    def __init__(self, text, name):
+        lines = text[re.search(r"^\S*%s\S*:" % name, text, re.M).start():].split("\n")
+        self.blocks, self.next, labels = [[]], [], {}
+        inline = False
+        for line in lines[1:]:
+            if line.startswith(".Lfunc_end"):
+                break
+            label = re.match(r"(\.LBB\w+):", line)
+            if label:
+                if self.blocks[-1]:
+                    self.blocks.append([])
+                labels[label.group(1)] = len(self.blocks) - 1
+                continue
+            if "#ASMSTART" in line or "#ASMEND" in line:
+                inline = "#ASMSTART" in line
+                continue
+            ins = line.split(";")[0].strip()
+            if not ins or ins.startswith("."):
+                continue
+            self.blocks[-1].append((ins, inline))
+            if ins.startswith(("s_cbranch", "s_branch", "s_endpgm")):
+                self.blocks.append([])
+        for i, block in enumerate(self.blocks):
+            last = block[-1][0] if block else ""
+            after = [] if last.startswith(("s_branch", "s_endpgm")) or i + 1 == len(self.blocks) else [i + 1]
+            if last.startswith(("s_branch", "s_cbranch")):
+                after.append(labels[last.split()[-1]])
+            self.next.append(after)
+
+
+def lds_reads_at_barriers(code):
+    """For every s_barrier the number of this wavefront's LDS reads that can still be in flight there: the largest over
+    all paths (LDS operations return in order; lgkmcnt(N) leaves N at most)."""
+    entry = [-1] * len(code.blocks)              # -1: not reached
+    entry[0] = 0
+    found, todo = {}, [0]
+    while todo:
+        i = todo.pop()
+        n = entry[i]
+        for at, (ins, _) in enumerate(code.blocks[i]):
+            if ins.startswith("ds_") and not ins.startswith("ds_write"):
+                n = min(n + 1, 16)               # (the counter ends at 15)
+            wait = re.search(r"lgkmcnt\((\d+)\)", ins)
+            if wait:
+                n = min(n, int(wait.group(1)))
+            if ins.startswith("s_barrier"):
+                found[i, at] = max(n, found.get((i, at), 0))
+        for j in code.next[i]:
+            if n > entry[j]:
+                entry[j] = n
+                todo.append(j)
+    return found
+
+
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("prefill") / "prefill.s")
+    subprocess.check_call([build.hipcc()] + build.FLAGS + ["-S", "--cuda-device-only", "-o", out,
+                           os.path.join(build.CSRC, "fd_prefill_kernels.hip")], stderr=subprocess.DEVNULL)
+    with open(out) as f:
+        return f.read()
+
+
+def test_the_walk_finds_a_read_across_a_barrier():
+    text = "k:\n ds_read_b128 v[0:3], v4\n ds_read_b128 v[4:7], v4\n s_cbranch_scc1 .LBB0_2\n s_waitcnt lgkmcnt(%d)\n" \
+           ".LBB0_2:\n %s s_barrier\n s_endpgm\n.Lfunc_end0:\n"
+    assert list(lds_reads_at_barriers(Code(text % (1, ""), "k")).values()) == [2]        # over the branch
+    assert list(lds_reads_at_barriers(Code(text % (1, "s_waitcnt vmcnt(0) lgkmcnt(1)\n"), "k")).values()) == [1]
+    assert list(lds_reads_at_barriers(Code(text % (1, "s_waitcnt lgkmcnt(0)\n"), "k")).values()) == [0]
+
+
+def test_no_lds_read_is_in_flight_at_a_barrier(assembly):
+    """A tile's place in the ring is filled again after the barrier that ends the step: its reads have to have returned."""
+    found = lds_reads_at_barriers(Code(assembly, "prefill_kernel"))
+    assert len(found) >= 8
+    assert not any(found.values()), found
