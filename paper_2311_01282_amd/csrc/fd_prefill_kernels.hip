@@ -147,7 +147,8 @@ struct TileWave {
     __device__ __forceinline__ u32x4 k_window(int t0) const { return window(kbase, t0); }
     __device__ __forceinline__ u32x4 v_window(int t0) const { return window(vbase, t0); }
     // In assembly, because the compiler waits for the loads it knows to write LDS before every transposing LDS read
-    // (a step then takes 1120 cycles instead of 920); no register is written, and the waits are wait_fetches.  KNOWN: the
+    // (a step then takes 1120 cycles instead of 920); no register is written -- the LDS address goes into m0 as an operand, so that
+    // the compiler knows what m0 holds -- and the waits are wait_fetches.  KNOWN: the
     // builtin, for the prologue, whose loads the compiler has to tell from those of Q^T; it waits for them before the loop.
     template <bool KNOWN> static __device__ __forceinline__ void load(u32x4 rs, int voff, int soff, unsigned char *lds_1k)
     {
@@ -158,7 +159,7 @@ struct TileWave {
                                                      (__attribute__((address_space(3))) void *)to, 16, voff, soff, 0, 0);
         } else {
             const unsigned at = (unsigned)reinterpret_cast<uintptr_t>(to);
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(at), "v"(voff), "s"(rs), "s"(soff) : "memory");
+            asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"{m0}"(at), "v"(voff), "s"(rs), "s"(soff) : "memory");
         }
     }
     // tile u of a window, into place `slot` of the ring

@@ -90,3 +90,17 @@ def test_no_lds_read_is_in_flight_at_a_barrier(assembly):
     found = lds_reads_at_barriers(Code(assembly, "prefill_kernel"))
     assert len(found) >= 8
     assert not any(found.values()), found
+
+
+def test_no_inline_assembly_writes_m0(assembly):
+    """m0 holds the LDS address of a tile fetch.  The compiler uses it for the fetches it knows and is not told of a write
+    inside a statement, so it has to set m0 itself, for every fetch."""
+    code = Code(assembly, "prefill_kernel")
+    fetches = 0
+    for block in code.blocks:
+        for ins, inline in block:
+            if not inline:
+                continue
+            assert not re.match(r"[sv]_\w+ m0\b", ins), ins
+            fetches += ins.startswith("buffer_load") and ins.endswith(" lds")
+    assert fetches >= 16
