@@ -68,6 +68,29 @@ def lds_reads_at_barriers(code):
     return found
 
 
+def waits_over_tile_fetches(code):
+    """The compiler's own waits for vector loads that a tile fetch in inline assembly can be in flight at: such a wait is
+    for an older load, but loads return in order and the compiler counts only those it knows, so it waits for the tile too."""
+    entry = [None] * len(code.blocks)            # False: no such fetch in flight
+    entry[0] = False
+    found, todo = set(), [0]
+    while todo:
+        i = todo.pop()
+        flying = entry[i]
+        for at, (ins, inline) in enumerate(code.blocks[i]):
+            if inline and ins.startswith("buffer_load") and ins.endswith(" lds"):
+                flying = True
+            if "vmcnt(" in ins:
+                if flying and not inline:
+                    found.add((i, at, ins))
+                flying = flying and "vmcnt(0)" not in ins
+        for j in code.next[i]:
+            if entry[j] is None or flying and not entry[j]:
+                entry[j] = flying
+                todo.append(j)
+    return found
+
+
 @pytest.fixture(scope="module")
 def assembly(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("prefill") / "prefill.s")
@@ -104,3 +127,11 @@ def test_no_inline_assembly_writes_m0(assembly):
             assert not re.match(r"[sv]_\w+ m0\b", ins), ins
             fetches += ins.startswith("buffer_load") and ins.endswith(" lds")
     assert fetches >= 16
+
+
+def test_tile_fetches_are_waited_for_by_the_source_alone(assembly):
+    """A tile is fetched two steps ahead: nothing but the wait at the end of the next step may wait for it."""
+    text = "k:\n;#ASMSTART\n buffer_load_dwordx4 v1, s[0:3], s4 offen lds\n;#ASMEND\n%s s_waitcnt vmcnt(3)\n s_endpgm\n.Lfunc_end0:\n"
+    assert len(waits_over_tile_fetches(Code(text % "", "k"))) == 1
+    assert not waits_over_tile_fetches(Code(text % ";#ASMSTART\n s_waitcnt vmcnt(0)\n;#ASMEND\n", "k"))
+    assert not waits_over_tile_fetches(Code(assembly, "prefill_kernel"))
