@@ -679,7 +679,7 @@ __device__ __forceinline__ void row_epilogue(const Problem &p, int row, int n_lo
 // 4 x 32/8 heads x 4096 keys 16.2 / 15.4 us, 1 x 32 heads x 1024 keys 7.5 / 7.0.)  Loads pass the caches
 // (the partial results come from other workgroups of the same launch).
 // COHERENT = false and a per-row chunk count serve a launch of its own over arbitrary rows.
-// n_load: slots that hold defined values whatever the row's length (a launch of its own: all nc of them), so that the
+// n_load: slots that hold defined values whatever the row's length (a launch of its own: all nc of them), so that the first
 // loads need not wait for the length; 0: the nb slots themselves.
 // FLAGS: whether the row flags are written (the synchronized scheme has none).
 template <bool COHERENT = true, bool FLAGS = true, typename NbFn>
@@ -740,7 +740,8 @@ __device__ __forceinline__ void rows_epilogue(const Problem &p, int row0, int G,
         if (loads <= 4) block(0, std::integral_constant<int, 4>{});
         else if (loads <= 8) block(0, std::integral_constant<int, 8>{});
         else
-            for (int c0 = 0; c0 < loads; c0 += 16) block(c0, std::integral_constant<int, 16>{});
+            // (nb is known behind the first block: a row that holds little of a long cache leaves there)
+            for (int c0 = 0; c0 == 0 || c0 < nb; c0 += 16) block(c0, std::integral_constant<int, 16>{});
         FD_PHASE(6);
         const unsigned any = (unsigned)(__ballot(f != 0) >> (tid & 32));   // of this row's 32 lanes
         uint2 o = make_uint2(0u, 0u);                        // an empty sequence: zeros, no flag

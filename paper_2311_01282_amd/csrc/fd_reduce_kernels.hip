@@ -73,7 +73,7 @@ __global__ __launch_bounds__(1024) void flag_reduce_kernel(const Problem p)
 // Eq. 2 over all rows: m = max_c m_c, result = sum_c e^{m_c - m} (f.V)_c / sum_c e^{m_c - m} l_c; two rows per workgroup,
 // any number of chunks.  (128 threads per row that fetched the lengths, then the maxima, then the sums four chunks at a
 // time: whole call, that form / this, 1 x 32 rows of 8192 keys in 64 chunks 31.4 / 27.4 us, in 8 chunks 24.9 / 24.6, 4 x 32 rows of 4
-// chunks 42.3 / 42.4.)
+// chunks 42.3 / 42.4; 1 x 32 rows of 2000 keys in a cache of 512 chunks 26.2 / 26.2, 45.1 if every chunk is walked.)
 __global__ __launch_bounds__(64) void combine_sync_kernel(const Problem p)
 {
     const int row0 = blockIdx.x * 2;
