@@ -478,7 +478,7 @@ def main():
         t_stats = timer(stats, repeats=3)["median"]
         extras["logit_histogram"] = {"us": us(t_stats), "k_bytes": kv_bytes // 2,
                                      "k_gbs": round(kv_bytes / 2 / t_stats / 1e9, 1),
-                                     "note": "K read once per query head; with grouped heads the repeats hit in L2"}
+                                     "note": "K read once per 16 query heads that share a KV head (here: once)"}
         # the same rotation of calls recorded once by a stream capture and replayed as a graph
         # (what a serving loop would do; the calls are capturable: launches only, no allocation)
         try:

@@ -434,7 +434,7 @@ fd_status fd_calibrate(const uint64_t *hist, int32_t n_bins, float x_min, float 
  *            i >= n_b of out are set to zero, keys >= n_b are never used.
  * shape->chunk is ignored.  `ws`: device scratch of fd_prefill_workspace_bytes(shape)
  * bytes, 256-byte aligned, arbitrary previous contents (it receives one flag byte
- * per (row head, 64-query tile); the rest is not used); no initialisation call
+ * per (row head, 64-query tile); the rest, whose size is kept as callers know it, is not used); no initialisation call
  * is needed.  Arithmetic: fp16 products with fp32 accumulation for the scores; fp32
  * exponentials and denominators; the weights enter the second product as fp16 hi + lo
  * pairs (22 significant bits) under a scale 2^k of the query's own, fixed after the

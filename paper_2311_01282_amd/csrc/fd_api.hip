@@ -175,10 +175,14 @@ inline int elect_per_row(const fd::Problem &p)
 
 // The grouped kernel: its elected workgroup finishes the G rows of its head group by itself, up to 16 chunks of
 // each in one memory round trip, which is the cheaper way up to 16 chunks per row and 256
-// workgroups; beyond either the second launch (one workgroup per row, 8 chunk slices in
+// workgroups; at 32 chunks the second launch (one workgroup per row, 8 chunk slices in
 // parallel) wins or ties: whole call, one launch / two, 64 query on 8 KV heads -- 18.1 / 18.5 us at 16 (2 x 9001 keys),
 // 14.3 / 13.1 at 32 (8192 keys), 16.4 / 15.2 at 32 (12000 keys); 32 on 8 heads -- 16.3 / 17.4 at 16 (2 x 8192 keys), 26.3 /
-// 26.6 at 32 (32768 keys).
+// 26.6 at 32 (32768 keys).  Over 257 to 1024 workgroups neither side wins: B x 64/8 heads, full caches read from memory -- 9 x 4096
+// keys in 4 chunks 34.8 / 35.3, 12 x 4096 in 4 38.4 / 38.4, 16 x 4096 in 4 45.2 / 46.0, 8 x 8192 in 8 46.4 / 46.1, 3 x 12000 in 12
+// 35.4 / 35.4, 4 x 8192 in 16 28.3 / 27.8, 24 x 4096 in 2 68.2 / 66.6, 32 x 8192 in 4 (1024 workgroups) 163.9 / 165.0; ragged
+// 12 x 512 .. 4096 in 4 30.3 / 30.7, 16 x 1000 .. 8192 in 4 63.4 / 62.0; a cache that is mostly empty pays for the second launch
+// (8 x 8192 holding about 1000: 16.5 / 18.1).
 inline int elect_grouped(const fd::Problem &p)
 {
     return elect_in_kernel((long long)p.B * p.Hkv * p.nc, 256, p.nc <= 16);
@@ -716,8 +720,8 @@ fd_status plan_prefill(const fd_shape *shape, PrefillLayout *P)
     fd_status st = plan(&sh, &L);
     if (st != FD_OK) return st;
     P->tiles = (sh.max_seq + 63) / 64;
-    // The size of the workspace is part of the interface: room for a copy of V, which the kernel no longer needs,
-    // stays in front of the flags.
+    // The size is a result that callers may have kept, and the bound below which fd_prefill_attn refuses a workspace: neither
+    // changes because the kernel no longer writes the copy of V that the room in front of the flags was for.
     const size_t v_copy = (size_t)sh.batch * sh.n_kv_heads * fd::kHeadDim * P->tiles * 64 * sizeof(uint16_t);
     P->flags = align_up(v_copy);
     P->total = align_up(P->flags + (size_t)sh.batch * sh.n_q_heads * P->tiles);

@@ -43,7 +43,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr float kFirstStepLog2 = 4.f;     // a query's largest weight of its first key step becomes 2^4 ...
 constexpr float kOverflowLog2 = 15.9f;    // ... and no later weight may reach 2^16 (fp16 ends at 65504)
 
-constexpr int kQB = 2;            // 16-query blocks per wavefront (1: 401, 2: 471-500 TFLOP/s at 8K)
+// 16-query blocks per wavefront.  Before the loop was woven, 8192 tokens: 401 TFLOP/s with 1, 471-500 with 2, 426 with 4 (one
+// wavefront per SIMD); the woven loop exists for 2 only.
+constexpr int kQB = 2;
 constexpr int kWaveQ = 16 * kQB;  // queries per wavefront
 constexpr int kQTile = 4 * kWaveQ; // query rows per workgroup
 constexpr int kStep = 32;        // keys per wavefront step

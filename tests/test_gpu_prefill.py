@@ -198,7 +198,7 @@ def test_lower_bound_flags_too(H):
 
 
 def test_prefill_can_be_captured_and_replayed(H):
-    # two launches on the caller's stream and nothing else: a stream capture of the call replays,
+    # one launch on the caller's stream and nothing else: a stream capture of the call replays,
     # also when a tile is flagged and recomputed inside the kernel
     B, Hq, Hkv, Smax = 1, 4, 2, 512
     q, k, v, sl = draw(B, Hq, Hkv, Smax, [500], seed=7500)
