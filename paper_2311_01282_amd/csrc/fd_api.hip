@@ -154,23 +154,21 @@ fd_status set_guard(fd::Problem *p, float phi, fd_bounds b)
 // Whether the chunk kernel should finish the rows itself (one launch) or leave that
 // to a second, tiny launch.  Electing a finisher costs every workgroup two memory
 // round trips at its end (results performed, arrival counter); a second launch costs
-// about 3 us once.  Small grids are latency-bound, so they fuse; large grids keep
-// their workgroups streaming and pay the launch.
-inline int elect_in_kernel(long long workgroups, long long limit = 1024, bool and_also = true)
-{
-    return workgroups <= limit && and_also;
-}
-
-// The per-row kernel: one launch up to 1024 workgroups, unless the launch is long -- more than one
-// round of the chip over 320 MiB or more of cache -- where the second launch wins (whole call, one
-// launch / two, same box: 2 x 32 rows x 16384 keys 90.0 / 84.7 us, 4 x 32 x 8192 85.4 / 83.6, 1 x 32 x
-// 32768 91.3 / 83.7, 1 x 32 x 24000 68.9 / 65.0; at 256 MiB they tie: 44.7 / 44.5, 46.2 / 45.7, 46.3 /
-// 44.8) at the price of a cache that is mostly empty (1 x 32 x 32768 holding 8192 keys: 26.8 / 31.4 us).
+// about 4 us once.
+//
+// The per-row kernel: one wavefront of a workgroup makes those round trips, the others have left.  In a workgroup of four
+// wavefronts (chunks of up to 256 keys) the next workgroup starts meanwhile and one launch wins at any size; in one of
+// eight it does not, and beyond 1024 workgroups the second launch wins.  Whole call, two launches / one, same box:
+// chunks of 128 keys 32 x 32 rows x 512 keys 47.8 / 46.1 us, 20 x 32 x 1000 59.5 / 57.0, 24 x 40 x 100 .. 700 40.2 / 37.2; of 256 keys
+// 16 x 16 x 300 .. 2000 31.8 / 29.8, 12 x 40 x 700 .. 1500 52.4 / 50.5, 32 x 32 x 1500 126.6 / 126.3, 16 x 16 x 4096 87.2 / 87.5;
+// of 512 and more, up to 1024 workgroups 4 x 32 x 8192 84.4 / 83.9, 1 x 32 x 32768 83.9 / 82.9 (holding 8192 keys 45.9 /
+// 43.4), 1 x 16 x 60000 82.2 / 79.5, beyond 6 x 32 x 8192 (1536) 123.9 / 124.8, 8 x 32 x 4096 (2048) 84.5 / 88.9, 16 x 32 x
+// 512 .. 4096 (4096) 105.4 / 106.9.  A row of more than 128 chunks is left to the second launch, which adds eight of them at a time
+// where the elected wavefront needs a round trip per 32.
 inline int elect_per_row(const fd::Problem &p)
 {
     const long long workgroups = (long long)p.rows * p.nc;
-    const long long cache_bytes = (long long)p.B * p.Hkv * p.Smax * fd::kHeadDim * 2 * 2;
-    return elect_in_kernel(workgroups, 1024, workgroups <= 256 || cache_bytes < (320ll << 20));
+    return p.nc <= 128 && (p.C <= 256 || workgroups <= 1024);
 }
 
 // The grouped kernel: its elected workgroup finishes the G rows of its head group by itself, up to 16 chunks of
@@ -185,7 +183,7 @@ inline int elect_per_row(const fd::Problem &p)
 // (8 x 8192 holding about 1000: 16.5 / 18.1).
 inline int elect_grouped(const fd::Problem &p)
 {
-    return elect_in_kernel((long long)p.B * p.Hkv * p.nc, 256, p.nc <= 16);
+    return (long long)p.B * p.Hkv * p.nc <= 256 && p.nc <= 16;
 }
 
 #define FD_TRY(expr) do { if ((expr) != hipSuccess) return FD_ERR_HIP; } while (0)

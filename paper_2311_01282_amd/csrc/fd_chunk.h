@@ -138,6 +138,12 @@ __device__ __forceinline__ void store_coherent4(float *ptr, float a, float b, fl
     store_coherent(&w[1], (unsigned long long)__builtin_bit_cast(unsigned, c) | ((unsigned long long)__builtin_bit_cast(unsigned, d) << 32));
 }
 
+__device__ __forceinline__ void store_coherent2(float *ptr, float a, float b)
+{
+    store_coherent(reinterpret_cast<unsigned long long *>(ptr),
+                   (unsigned long long)__builtin_bit_cast(unsigned, a) | ((unsigned long long)__builtin_bit_cast(unsigned, b) << 32));
+}
+
 // Wait until this thread's earlier stores are performed (vector memory counter at
 // zero); with write-through stores this is the release half of the hand-over.
 __device__ __forceinline__ void wait_stores_performed()
@@ -150,16 +156,31 @@ __device__ __forceinline__ uint16_t to_half_bits(float x)
     return __builtin_bit_cast(uint16_t, (_Float16)x);   // round to nearest even
 }
 
+// The value of the other half of the wavefront / of the neighbouring row of 16 added in, two registers at a time:
+// halves_sum(a, b): lanes 0-31 get a summed over the halves, lanes 32-63 b; rows_sum(a, b): the even rows of 16 get a
+// summed over the pair of rows, the odd ones b.  (Vector elements are taken by value first, see as_h2.)
+__device__ __forceinline__ float halves_sum(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+    const unsigned x = r[0], y = r[1];
+    return as_f32(x) + as_f32(y);
+}
+__device__ __forceinline__ float rows_sum(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+    const unsigned x = r[0], y = r[1];
+    return as_f32(x) + as_f32(y);
+}
+
 // LDS of one workgroup of NW wavefronts.  XN = number of logits kept for the
 // synchronized scheme.
 template <int NW, int XN>
 struct ChunkLds {
-    float acc[NW * 4][kHeadDim];   // [wave*4 + key-in-group][element]; reused by the row epilogue
+    alignas(16) float acc[NW][kHeadDim];   // [wave][pairs of elements, see chunk_body]
+    alignas(16) float den[NW];
+    alignas(16) int   flag[NW];
     float x[XN];
-    float den[NW * 4];
     float mx[NW];
-    int   flag[NW];
-    int   last;
 };
 
 // One (row, chunk) on the VALU path, by a workgroup of NW wavefronts.
@@ -494,42 +515,56 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
     }
 
     if constexpr (!SYNC) FD_PHASE(2);
-    // Workgroup reduction: NW*4 partial vectors (NW wavefronts x 4 keys per group).
-    // LDS row layout: elements 8s..8s+3 at 4s, elements 8s+4..8s+7 at 64 + 4((s + 4) & 15). Both the
-    // 16-byte writes here and the 4-byte reads below then touch every bank once per pass.
-    float *arow = lds.acc[wave * 4 + sub];
-    *reinterpret_cast<float4 *>(&arow[4 * seg]) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    *reinterpret_cast<float4 *>(&arow[64 + 4 * ((seg + 4) & 15)]) = make_float4(acc[4], acc[5], acc[6], acc[7]);
-    if (seg == 0) lds.den[wave * 4 + sub] = den;
+    // Workgroup reduction.  Within a wavefront the four keys of a group are added in registers, exchanging halves and rows of
+    // two registers at a time, so that lane (sub, seg) ends up with elements 8 seg + 2 sub and the next: 12 instructions.
+    // Then wavefront 0 adds the others' sums and writes the slot by itself, and what follows (the arrival, the row's
+    // finish) needs no barrier; the other wavefronts are done and make room.  (Before, all NW * 4 vectors went through LDS and two
+    // wavefronts added them, with a barrier before and after the arrival.)
+    float u[2];
+    {
+        float t[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[i] = halves_sum(acc[i], acc[i + 4]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) u[i] = rows_sum(t[i], t[i + 2]);
+        den = halves_sum(den, den);
+        den = rows_sum(den, den);
+    }
+    // The pair of lane (sub, seg), number 4 seg + sub of its vector, sits in place 4 seg + (sub ^ 2 (seg / 8)): no bank
+    // conflict here, and none where lane l reads pair l back, so that the slot is written in whole lines (pairs stored as the
+    // lanes hold them, 32 bytes apart, cost launches of full caches 1 %).
+    *reinterpret_cast<float2 *>(&lds.acc[wave][8 * seg + 2 * (sub ^ ((seg >> 2) & 2))]) = make_float2(u[0], u[1]);
+    if (lane == 0) lds.den[wave] = den;
     __syncthreads();
     bool flagged = false;
     if constexpr (!SYNC) {
 #pragma unroll
         for (int w = 0; w < NW; ++w) flagged |= lds.flag[w] != 0;
     }
-    if (tid < kHeadDim) {
-        const int es = tid >> 3;                   // element tid sits in 16-byte segment es
-        const int pos = (tid & 4) ? 64 + 4 * ((es + 4) & 15) + (tid & 3) : 4 * es + (tid & 3);
-        float s = 0.f;
+    if (wave == 0) {
+        const int place = 2 * (lane ^ ((lane >> 4) & 2));
+        u[0] = u[1] = den = 0.f;
 #pragma unroll
-        for (int i = 0; i < NW * 4; ++i) s += lds.acc[i][pos];
-        store_coherent(&p.ws.num[slot * kHeadDim + tid], s);
-    } else if (tid == kHeadDim) {
-        float s = 0.f;
-#pragma unroll
-        for (int i = 0; i < NW * 4; ++i) s += lds.den[i];
-        store_coherent(&p.ws.den[slot], s);
-        store_coherent(&p.ws.mloc[slot], mc);
-        // the flag the row epilogue ORs into the row flag: the guard's; a recomputed chunk carries what its caller
-        // says (1 when the guard sent it here, 0 when it is redone for another reason)
-        store_meta(p, slot, s, mc, SYNC ? sync_flag : (int)flagged);
-        if (!SYNC) p.ws.chunk_flags[slot] = flagged ? 1 : 0;
+        for (int w = 0; w < NW; ++w) {             // wavefront order
+            const float2 o = *reinterpret_cast<const float2 *>(&lds.acc[w][place]);
+            u[0] += o.x;
+            u[1] += o.y;
+            den += lds.den[w];
+        }
+        store_coherent2(&p.ws.num[slot * kHeadDim + 2 * lane], u[0], u[1]);
+        if (lane == 0) {
+            store_coherent(&p.ws.den[slot], den);
+            store_coherent(&p.ws.mloc[slot], mc);
+            // the flag the row epilogue ORs into the row flag: the guard's; a recomputed chunk carries what its caller
+            // says (1 when the guard sent it here, 0 when it is redone for another reason)
+            store_meta(p, slot, den, mc, SYNC ? sync_flag : (int)flagged);
+            if (!SYNC) p.ws.chunk_flags[slot] = flagged ? 1 : 0;
+        }
     }
     return flagged;
 }
 
-// Row epilogue, run by the one workgroup that owns the row's output (its first 256
-// threads do the arithmetic): the synchronized update of Eq. 2 over the row's
+// Row epilogue of a workgroup of 256 threads, in a launch of its own: the synchronized update of Eq. 2 over the row's
 // partial results, each scaled by its own reference r_c -- phi for chunks summed
 // with the unified factor, the chunk maximum for recomputed ones:
 //     m = max_c r_c,   out = sum_c e^{r_c-m} num_c / sum_c e^{r_c-m} den_c,
@@ -543,44 +578,31 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
 // Slots [0, n_load) are loaded (all of them hold defined values: chunks without a
 // valid key carry zeros), slots [0, nb) enter the result; passing n_load = nc lets
 // the loads start before the sequence length is known.
-// COHERENT: the partial results come from other workgroups of the same launch and
-// are read past the caches; false is for a launch of its own.
 // `scratch` is >= 8 * 128 + 16 floats of LDS.
-template <int NW, bool COHERENT, typename NbFn>
+template <typename NbFn>
 __device__ __forceinline__ void row_epilogue(const Problem &p, int row, int n_load, NbFn nb_fn, float *scratch)
 {
-    auto ld16 = [](const void *ptr) {
-        if constexpr (COHERENT) {
-            const unsigned long long *w = static_cast<const unsigned long long *>(ptr);
-            const unsigned long long a = load_coherent(&w[0]), b = load_coherent(&w[1]);
-            return u32x4{(unsigned)a, (unsigned)(a >> 32), (unsigned)b, (unsigned)(b >> 32)};
-        } else {
-            return *static_cast<const u32x4 *>(ptr);
-        }
-    };
     const int tid = threadIdx.x;
-    const int slice = (tid >> 5) & 7, t4 = tid & 31;
-    const bool worker = NW * 64 <= 256 || tid < 256;
+    const int slice = tid >> 5, t4 = tid & 31;
     const size_t r0 = (size_t)row * p.nc;
     const float *num = p.ws.num + r0 * kHeadDim + 4 * t4;
     const SlotMeta *meta = p.ws.meta + r0;
 
-    // Within a batch the loads are unconditional and clamped to the last loaded slot (a load
+    // Within a batch of 32 chunks the loads are unconditional and clamped to the last loaded slot (a load
     // inside a divergent branch would force a full wait where the branch rejoins); slots
-    // outside the row are masked in the arithmetic.  The batch is sized to the row -- 1, 2 or
-    // 4 chunks per thread -- and rows of more than 32 chunks keep two batches in flight.
+    // outside the row are masked in the arithmetic.  Two batches are in flight.
     float m = -INFINITY, l = 0.f;
     float s[4] = {0.f, 0.f, 0.f, 0.f};
     int f = 0;
     int nb = 0;
-    if (worker) {
+    {
         const int cap = max(n_load - 1, 0);
         auto issue = [&](int c0, auto &nv, auto &mv, auto n) {
 #pragma unroll
             for (int i = 0; i < decltype(n)::value; ++i) {
                 const int c = min(c0 + 8 * i + slice, cap);
-                nv[i] = ld16(num + (size_t)c * kHeadDim);
-                mv[i] = ld16(meta + c);
+                nv[i] = *reinterpret_cast<const u32x4 *>(num + (size_t)c * kHeadDim);
+                mv[i] = *reinterpret_cast<const u32x4 *>(meta + c);
             }
         };
         auto process = [&](int c0, const auto &nv, const auto &mv, auto n) {
@@ -609,41 +631,22 @@ __device__ __forceinline__ void row_epilogue(const Problem &p, int row, int n_lo
                 l = __builtin_fmaf(a, as_f32(mv[i][0]), l);
             }
         };
-        auto single = [&](auto n) {             // the whole row in one batch of N chunks per thread
-            u32x4 nv[decltype(n)::value], mv[decltype(n)::value];
-            issue(0, nv, mv, n);
-            nb = nb_fn();                       // may be a load of its own, in flight with the batch
-            process(0, nv, mv, n);
-        };
-        if (n_load <= 8) {
-            single(std::integral_constant<int, 1>{});
-        } else if (n_load <= 16) {
-            single(std::integral_constant<int, 2>{});
-        } else if (n_load <= 32) {
-            single(std::integral_constant<int, 4>{});
-        } else {
-            constexpr std::integral_constant<int, 4> n{};
-            u32x4 nA[4], mA[4], nB[4], mB[4];
-            issue(0, nA, mA, n);
-            nb = nb_fn();
-            for (int c0 = 0; c0 < n_load; c0 += 64) {
-                issue(c0 + 32, nB, mB, n);
-                process(c0, nA, mA, n);
-                issue(c0 + 64, nA, mA, n);
-                if (c0 + 32 < n_load) process(c0 + 32, nB, mB, n);
-            }
+        constexpr std::integral_constant<int, 4> n{};
+        u32x4 nA[4], mA[4], nB[4], mB[4];
+        issue(0, nA, mA, n);
+        nb = nb_fn();                           // may be a load of its own, in flight with the batch
+        for (int c0 = 0; c0 == 0 || c0 < nb; c0 += 64) {      // (no further than the row's last chunk)
+            issue(c0 + 32, nB, mB, n);
+            process(c0, nA, mA, n);
+            issue(c0 + 64, nA, mA, n);
+            if (c0 + 32 < nb) process(c0 + 32, nB, mB, n);
         }
-    } else {
-        nb = nb_fn();
     }
     // merge the 8 slices (slice order), divide, round to fp16
     float *S = scratch, *L = scratch + 8 * kHeadDim, *M = L + 8;
-    if (worker) {
-        *reinterpret_cast<float4 *>(&S[slice * kHeadDim + 4 * t4]) = make_float4(s[0], s[1], s[2], s[3]);
-        if (t4 == 0) { L[slice] = l; M[slice] = m; }
-    }
+    *reinterpret_cast<float4 *>(&S[slice * kHeadDim + 4 * t4]) = make_float4(s[0], s[1], s[2], s[3]);
+    if (t4 == 0) { L[slice] = l; M[slice] = m; }
     const int rf = __syncthreads_or(f);
-    FD_PHASE(6);
     if (tid < 32) {
         float mm = M[0];
 #pragma unroll
@@ -762,25 +765,115 @@ __device__ __forceinline__ void group_epilogue(const Problem &p, int row0, int G
 // over the row's nb chunks.  Same-address device-scope atomics complete one after
 // another (about 0.13 us each on MI355X), so a flat counter costs nb of them on the
 // critical path when the workgroups of a row finish together; the tree costs at
-// most 8 per level plus one memory round trip per level.  Called by one thread after the workgroup's results are performed.
-// Returns true for exactly one caller per row, after every other chunk arrived.
+// most 8 per level plus one memory round trip per level.  Called by one whole wavefront after the workgroup's results are
+// performed; lane 0 counts.  Returns true, uniformly, to exactly one caller per row, after every other chunk arrived.
 // Counters are zero before and after (the last arrival at a node resets it).
 __device__ __forceinline__ bool arrive_and_elect(const Problem &p, int row, int c, int nb)
 {
     constexpr int LR = 3, R = 1 << LR;
+    const bool one = (threadIdx.x & 63) == 0;
     int32_t *node = p.ws.ticket + (size_t)row * p.nc;
     int idx = c, n = nb;
     while (n > 1) {
         const int parent = idx >> LR;
         const int children = min(R, n - (parent << LR));
-        const int t = __hip_atomic_fetch_add(&node[parent], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (t != children - 1) return false;
-        store_coherent(&node[parent], 0);
+        int t = 0;
+        if (one) t = __hip_atomic_fetch_add(&node[parent], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__builtin_amdgcn_readfirstlane(t) != children - 1) return false;
+        if (one) store_coherent(&node[parent], 0);
         n = (n + R - 1) >> LR;
         node += n;
         idx = parent;
     }
     return true;
+}
+
+// The row's finish by one wavefront: the rule of row_epilogue, lane l owning elements 2l and 2l + 1.  Up to 32 chunks
+// take one memory round trip: lane j fetches the slot record of chunk j, and the numerators of all chunks are on their way before the
+// first record is looked at.  Where all references agree -- every row without a recomputed chunk -- every factor is 1 and the chunks
+// are simply added (Eq. 4); otherwise each lane has its chunk's factor, which goes round as a scalar.  Fixed order, same
+// bits on every run.  Bound by latency: a round trip past the caches and some eighty instructions in a chain.
+// COHERENT: the partial results come from other workgroups of the same launch and are read past the caches; false is for a
+// launch of its own.
+// n_load: slots that hold defined values whatever the row's length (a launch of its own: all nc of them), so that the first
+// loads need not wait for the length; nb_of gives the row's chunks and may be a load of its own, in flight with them.
+// FLAGS: whether the row flags are written (the synchronized scheme has none).
+template <bool COHERENT, bool FLAGS, typename NbFn>
+__device__ __forceinline__ void finish_row(const Problem &p, int row, int n_load, NbFn nb_of)
+{
+    auto ld8 = [](const void *ptr) {
+        if constexpr (COHERENT) return load_coherent(static_cast<const unsigned long long *>(ptr));
+        else return *static_cast<const unsigned long long *>(ptr);
+    };
+    const int lane = threadIdx.x & 63;
+    const size_t r0 = (size_t)row * p.nc;
+    const float *num = p.ws.num + r0 * kHeadDim + 2 * lane;
+    const SlotMeta *meta = p.ws.meta + r0;
+    float m = -INFINITY, l = 0.f, s[2] = {0.f, 0.f};
+    bool any = false;
+    int nb = 0;
+    auto block = [&](int c0, auto count) {
+        constexpr int N = decltype(count)::value;
+        const unsigned long long *w = reinterpret_cast<const unsigned long long *>(meta + min(c0 + (lane & (N - 1)), n_load - 1));
+        const unsigned long long w0 = ld8(&w[0]), w1 = ld8(&w[1]);
+        unsigned long long nv[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) nv[i] = ld8(num + (size_t)min(c0 + i, n_load - 1) * kHeadDim);
+        if (c0 == 0) nb = nb_of();
+        const int left = nb - c0;                            // uniform
+        const bool mine = lane < min(N, left);
+        const float den = mine ? as_f32((unsigned)w0) : 0.f;
+        const float ref = as_f32((unsigned)(w0 >> 32));
+        any |= __ballot(mine & ((int)w1 != 0)) != 0ull;
+        const float ref0 = as_f32(__builtin_amdgcn_readfirstlane((unsigned)(w0 >> 32)));
+        if ((c0 == 0 || m == ref0) && __ballot(mine & (ref != ref0)) == 0ull) {
+            m = ref0;
+            float d = row16_sum(den);                        // lanes past the row's chunks carry zeros
+            if constexpr (N > 16) d = rows_sum(d, d);
+            l += as_f32(__builtin_amdgcn_readfirstlane(__builtin_bit_cast(unsigned, d)));
+            float t[2][2] = {{s[0], s[1]}, {0.f, 0.f}};      // even and odd chunks: two chains
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const unsigned keep = i < left ? ~0u : 0u;   // (no branch per chunk)
+                t[i & 1][0] += as_f32((unsigned)nv[i] & keep);
+                t[i & 1][1] += as_f32((unsigned)(nv[i] >> 32) & keep);
+            }
+            s[0] = t[0][0] + t[1][0];
+            s[1] = t[0][1] + t[1][1];
+            return;
+        }
+        float bm = mine ? ref : -INFINITY;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) bm = fmaxf(bm, __shfl_xor(bm, o));
+        if (bm > m) {                                        // rescale what was summed so far
+            const float a = __builtin_amdgcn_exp2f((m - bm) * kLog2e);   // 0 on the first block
+            s[0] *= a;
+            s[1] *= a;
+            l *= a;
+            m = bm;
+        }
+        // exactly 1 when ref == m
+        const float a = ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ref - m) * kLog2e);
+        const float ad = a * den;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if (i < left) {
+                const float ac = as_f32(__builtin_amdgcn_readlane(__builtin_bit_cast(unsigned, a), i));
+                l += as_f32(__builtin_amdgcn_readlane(__builtin_bit_cast(unsigned, ad), i));
+                s[0] = __builtin_fmaf(ac, as_f32((unsigned)nv[i]), s[0]);
+                s[1] = __builtin_fmaf(ac, as_f32((unsigned)(nv[i] >> 32)), s[1]);
+            }
+    };
+    if (n_load <= 4) block(0, std::integral_constant<int, 4>{});
+    else if (n_load <= 8) block(0, std::integral_constant<int, 8>{});
+    else if (n_load <= 16) block(0, std::integral_constant<int, 16>{});
+    else
+        for (int c0 = 0; c0 == 0 || c0 < nb; c0 += 32) block(c0, std::integral_constant<int, 32>{});
+    FD_PHASE(6);
+    unsigned o = 0u;                                         // an empty sequence: zeros, no flag
+    if (nb > 0) o = (unsigned)to_half_bits(s[0] / l) | ((unsigned)to_half_bits(s[1] / l) << 16);
+    *reinterpret_cast<unsigned *>(p.out + (size_t)row * kHeadDim + 2 * lane) = o;
+    if (FLAGS && lane == 0) p.ws.row_flags[row] = any ? 1 : 0;
 }
 
 }  // namespace fd

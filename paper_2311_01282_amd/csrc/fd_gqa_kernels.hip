@@ -398,7 +398,10 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
     // Publish, arrive, and let the last arrival of the group finish its G rows.
     wait_stores_performed();
     __syncthreads();
-    if (tid == 0) lds.last = arrive_and_elect(p, row0, c, nb);
+    if (wave == 0) {
+        const bool last = arrive_and_elect(p, row0, c, nb);
+        if (lane == 0) lds.last = last;
+    }
     __syncthreads();
     if (!lds.last) return;
     group_epilogue(p, row0, G, nb);

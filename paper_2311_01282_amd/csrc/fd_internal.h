@@ -67,7 +67,7 @@ struct Problem {
     // Which XCD (workgroup index modulo 8) serves which row of a block of 8 rows (or head groups):
     //   0: row r on XCD r % 8, all its chunks on that one XCD;
     //   1: chunk c of row r on XCD (r + c) % 8 -- every XCD reads from every row.
-    // Set at launch: 1 for the launches that leave the row epilogue to a second launch (see
+    // Set at launch: 1 for the long launches and those that leave the row epilogue to a second one (see
     // row_slot below); the probe build can force 1 everywhere (tests of the hand-over).
     int scatter;
 };
@@ -78,7 +78,7 @@ struct Problem {
 // strides (4096 keys = 1 MiB: a batch of 16 x 32 rows) the memory system then serves it from a part
 // of its channels only: 74 % of the HBM peak against 85 % with the rows spread (batch 16 x 4096
 // keys, 1024-key chunks; 4 x 16384: 81 -> 85 %; 1 x 65536: 79 -> 83 %; shapes that were fast stay
-// fast).  Launches that hand over between workgroups keep a row on one XCD (measured: no
+// fast).  Short launches that hand over between workgroups keep a row on one XCD (measured: no
 // difference there, and the counters of a row then live in one L2).
 __device__ __forceinline__ int row_slot(const Problem &p, int slot, int c)
 {

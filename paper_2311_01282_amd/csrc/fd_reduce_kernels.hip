@@ -21,16 +21,23 @@ __global__ __launch_bounds__(256) void row_epilogue_kernel(const Problem p)
     asm volatile("" ::"s"(p.ws.num), "s"(p.ws.meta), "s"(p.ws.row_flags), "s"(p.seq_lens), "s"(p.out), "s"(p.nc),
                  "s"(p.Hq), "s"(p.C), "s"(p.Smax));
     // every slot of the row holds defined values, so the loads need not wait for the length
-    row_epilogue<4, false>(p, row, p.nc, [&] { return (valid_len(p, row / p.Hq) + p.C - 1) / p.C; }, scratch);
+    row_epilogue(p, row, p.nc, [&] { return (valid_len(p, row / p.Hq) + p.C - 1) / p.C; }, scratch);
 }
 
-// The same for rows of at most 8 chunks: 8 rows per workgroup, 32 threads per row walking
-// the row's chunks in registers (no LDS, no barrier, an eighth of the workgroups).
-__global__ __launch_bounds__(256) void rows8_epilogue_kernel(const Problem p)
+// The same for rows of at most 32 chunks: a workgroup of one wavefront per row, no LDS, no barrier; with FLAGS = false also the
+// merge of the synchronized scheme (Eq. 2).  Whole call, 32 threads per row and eight or two rows to a workgroup / this: 12 x 32/8 heads x
+// 300 .. 6000 keys in 5 chunks 38.8 / 38.4 us, 16 x 64/8 x 4096 in 4 46.1 / 45.7, 1 x 64/8 x 32768 in 32 (eight slices through LDS)
+// 26.8 / 25.9; fd_decode_attn_sync 1 x 32 x 1024 in 8 8.76 / 8.60, 4 x 32 x 4096 in 4 43.7 / 43.4.  Four rows to a workgroup draw
+// their sums through one compute unit: 0.2 us more at 8 chunks per row, 1 us at 64.  At 64 chunks per row the forms with more
+// threads per row win (27.5 / 27.75) or tie.
+template <bool FLAGS>
+__global__ __launch_bounds__(64) void finish_rows_kernel(const Problem p)
 {
-    const int row0 = blockIdx.x * 8;
+    const int row = blockIdx.x;
+    asm volatile("" ::"s"(p.ws.num), "s"(p.ws.meta), "s"(p.ws.row_flags), "s"(p.seq_lens), "s"(p.out), "s"(p.nc),
+                 "s"(p.Hq), "s"(p.C), "s"(p.Smax));
     // every slot of a row holds defined values, so the loads need not wait for the length
-    rows_epilogue<false>(p, row0, min(8, p.rows - row0), p.nc, [&](int row) { return (valid_len(p, row / p.Hq) + p.C - 1) / p.C; });
+    finish_row<false, FLAGS>(p, row, p.nc, [&] { return (valid_len(p, row / p.Hq) + p.C - 1) / p.C; });
 }
 
 // Chunk flags -> row flags, ascending list of flagged rows, their count.
@@ -70,10 +77,8 @@ __global__ __launch_bounds__(1024) void flag_reduce_kernel(const Problem p)
     if (tid == 0) *p.ws.count = base_s;
 }
 
-// Eq. 2 over all rows: m = max_c m_c, result = sum_c e^{m_c - m} (f.V)_c / sum_c e^{m_c - m} l_c; two rows per workgroup,
-// any number of chunks.  (128 threads per row that fetched the lengths, then the maxima, then the sums four chunks at a
-// time: whole call, that form / this, 1 x 32 rows of 8192 keys in 64 chunks 31.4 / 27.4 us, in 8 chunks 24.9 / 24.6, 4 x 32 rows of 4
-// chunks 42.3 / 42.4; 1 x 32 rows of 2000 keys in a cache of 512 chunks 26.2 / 26.2, 45.1 if every chunk is walked.)
+// The same over rows of more than 32 chunks: two rows per workgroup, 32 threads each, a round trip per 16 chunks, no further than
+// the row's last (1 x 32 rows of 2000 keys in a cache of 512 chunks 26.2 us, 45.1 if every chunk is walked).
 __global__ __launch_bounds__(64) void combine_sync_kernel(const Problem p)
 {
     const int row0 = blockIdx.x * 2;
@@ -138,7 +143,7 @@ hipError_t launch_clear_tickets(int32_t *ticket, size_t n, hipStream_t s)
 hipError_t launch_row_epilogue(const Problem &p, hipStream_t s)
 {
     if (p.rows == 0) return hipSuccess;
-    if (p.nc <= 8) return launch(rows8_epilogue_kernel, dim3((p.rows + 7) / 8), dim3(256), s, p);
+    if (p.nc <= 32) return launch(finish_rows_kernel<true>, dim3(p.rows), dim3(64), s, p);
     return launch(row_epilogue_kernel, dim3(p.rows), dim3(256), s, p);
 }
 
@@ -156,6 +161,7 @@ hipError_t launch_chain_finish(const Problem &p, hipStream_t s)
 hipError_t launch_combine_sync(const Problem &p, hipStream_t s)
 {
     if (p.rows == 0) return hipSuccess;
+    if (p.nc <= 32) return launch(finish_rows_kernel<false>, dim3(p.rows), dim3(64), s, p);
     return launch(combine_sync_kernel, dim3((p.rows + 1) / 2), dim3(64), s, p);
 }
 

@@ -80,19 +80,15 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void decode_fused_kernel(const Pr
     }
 
     if (!ELECT) return;                        // a row-epilogue launch follows
-    // Publish this chunk's results (written through by chunk_body), then arrive; the
-    // last arrival owns the row and reads the others' results past the caches.
+    // Publish this chunk's results (written through by wavefront 0), then arrive; the last arrival owns the row and reads
+    // the others' results past the caches.
+    if (tid >= 64) return;
     wait_stores_performed();
-    __syncthreads();
     FD_PHASE(4);
-    if (tid == 0) lds.last = arrive_and_elect(p, row, c, nb);
-    __syncthreads();
+    const bool last = arrive_and_elect(p, row, c, nb);
     FD_PHASE(5);
-    if (!lds.last) return;
-    // up to 16 chunks: 32 threads add them in registers, one round trip, no LDS, no barrier (1 x 32 rows of 16 chunks of 512
-    // keys: 24.8 us, 25.4 by the slices below)
-    if (nb <= 16) group_epilogue(p, row, 1, nb);
-    else row_epilogue<NW, true>(p, row, nb, [nb] { return nb; }, &lds.acc[0][0]);
+    if (!last) return;
+    finish_row<true, true>(p, row, nb, [nb] { return nb; });
 #ifdef FD_PHASE_PROBE
     wait_stores_performed();
     FD_PHASE(7);
@@ -223,7 +219,10 @@ template <int C> struct FusedLauncher {
         const unsigned grid = (unsigned)(8ll * ((p0.rows + 7) / 8) * p0.nc);
         if (grid == 0) return hipSuccess;
         Problem p = p0;
-        p.scatter |= !p.elect;                     // no hand-over inside the launch: every XCD reads from every row
+        // Every XCD reads from every row where the launch is long: more than 1024 workgroups, or more than one round of the
+        // chip over 320 MiB of cache (see row_slot); the results cross between XCDs as well as within one.
+        const long long cache_bytes = (long long)p.B * p.Hkv * p.Smax * kHeadDim * 4;
+        p.scatter |= !p.elect || grid > 1024u || (grid > (unsigned)kComputeUnits && cache_bytes >= (320ll << 20));
         if (p.block_table)
             return p.elect ? launch(decode_fused_kernel<C, true, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p)
                            : launch(decode_fused_kernel<C, false, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p);
