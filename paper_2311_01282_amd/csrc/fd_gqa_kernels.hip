@@ -51,10 +51,10 @@ struct GqaLds {
     // [wave][head][d] (NW x 8 KiB), then (rarely) the per-row recomputation's workspace:
     // never live together.
     alignas(16) float tile[NW * 16 * kHeadDim];
-    float den[NW][64];
-    float e_new[16];                 // weight of an appended key per head (0 when there is none)
-    int   f_new[16];                 // ... and whether it left the bounds
-    unsigned long long bad[NW], over[NW];
+    alignas(16) float den[16][NW];   // per head: the wavefronts' denominators ...
+    alignas(16) float inv[16][NW];   // ... and what takes their scales out of their tiles again
+    alignas(16) unsigned mask[NW];   // heads out of bounds, and << 16 heads with a weight beyond the fp16 operand
+    float e_new[16];                 // weight of an appended key per head (written where there is one)
     int last;
 };
 
@@ -263,23 +263,13 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         } else {
             reduce(blk_of(i), i == 0, kA, vA);
         }
-        // Take the scales out again (exact: integer powers of two).  den belongs to head n; acc[e][r]
-        // to head 4g + r, whose exponent sits in the lanes with n = 4g + r.
-        den *= __builtin_amdgcn_exp2f(-kq);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float inv = __builtin_amdgcn_exp2f(-__shfl(kq, 4 * g + r));
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e][r] *= inv;
-        }
     }
 
     // ---- the appended key, if this chunk takes it: one more term of Eq. 4 per head ----
     // Lane group (wave, g) of the first four wavefronts handles head 4 wave + g on the vector ALU: weight e^{x - phi}
     // and guard from the step's own K row.  The weights go to LDS and enter the sums at
     // the reduction below, multiplied with the step's V row.
-    float e_new = 0.f;
-    int f_new = 0;
+    unsigned new_mask = 0;                     // heads whose appended key left the bounds
     const size_t row_new = at.absolute(owner ? S_res - start : 0);   // where the appended row goes (all lanes look the page up)
     if (owner) {
         const int hh = 4 * wave + g;
@@ -287,10 +277,10 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         const u32x4 kn = reinterpret_cast<const u32x4 *>(p.k_new + at_new)[n];
         const u32x4 qh = reinterpret_cast<const u32x4 *>(p.q + (size_t)(row0 + min(hh, G - 1)) * kHeadDim)[n];
         const float d = row16_sum(dot8(qh, kn)) * scale + nphi;
-        if (hh < G) {                          // (never for a wavefront past the fourth: hh >= 16)
-            f_new = !((d > lo) & (d < hi));
-            e_new = __builtin_amdgcn_exp2f(d * kLog2e);
-        }
+        // (hh < G never holds for a wavefront past the fourth: hh >= 16)
+        if (n == 0 && hh < 16) lds.e_new[hh] = hh < G ? __builtin_amdgcn_exp2f(d * kLog2e) : 0.f;
+        const unsigned long long out = __ballot((n == 0) & (hh < G) & !((d > lo) & (d < hi)));
+        new_mask = (unsigned)((out | (out >> 15) | (out >> 30) | (out >> 45)) & 0xfull) << (4 * wave);
         if (wave == 0 && g == 0) {             // 16 lanes put the rows into the cache
             reinterpret_cast<u32x4 *>(p.k_store)[row_new + n] = kn;
             reinterpret_cast<u32x4 *>(p.v_store)[row_new + n] = reinterpret_cast<const u32x4 *>(p.v_new + at_new)[n];
@@ -298,8 +288,18 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
     }
 
     // ---- workgroup reduction and publication of the G rows' partial results ----
-    const unsigned long long bad_mask = __ballot(bad);
-    const unsigned long long over_mask = __ballot(head_on & (zmax >= kOverflowLog2));   // a weight beyond the fp16 operand
+    // What a wavefront knows about its heads is brought together before it goes to LDS, so that little is left to do
+    // behind the barrier: this part is a chain of instructions of lone wavefronts, 1.1 us when every thread read 16
+    // denominators, 16 flags and four scales for itself, 0.85 now (2 x 64/8 heads x 9001 keys: whole call with the finish's loads
+    // below 17.9 / 17.5 us; 1 x 12/2 x 700: 7.6 / 7.1).
+    const auto heads_of = [](unsigned long long lanes) {       // lane (n, g) -> head n
+        return (unsigned)((lanes | (lanes >> 16) | (lanes >> 32) | (lanes >> 48)) & 0xffffull);
+    };
+    const unsigned mask = heads_of(__ballot(bad)) | new_mask | heads_of(__ballot(head_on & (zmax >= kOverflowLog2))) << 16;
+    // the scales are taken out where the tiles are added (exact: integer powers of two)
+    const float inv = __builtin_amdgcn_exp2f(-kq);
+    den = halves_sum(den, den);
+    den = rows_sum(den, den) * inv;
     __syncthreads();                           // every wavefront is done with its K staging
     // acc[e][r] is (head 4g + r, d = 8n + e) of this wavefront's partial tile.
 #pragma unroll
@@ -313,38 +313,36 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
             dst[16] = make_float4(acc[4][r], acc[5][r], acc[6][r], acc[7][r]);
         }
     }
-    lds.den[wave][lane] = den;
-    if (lane == 0) { lds.bad[wave] = bad_mask; lds.over[wave] = over_mask; }
-    if (n == 0 && wave < 4) { lds.e_new[4 * wave + g] = e_new; lds.f_new[4 * wave + g] = f_new; }
+    if (g == 0) { lds.den[n][wave] = den; lds.inv[n][wave] = inv; }
+    if (lane == 0) lds.mask[wave] = mask;
     __syncthreads();
-    unsigned long long any = 0, any_over = 0;
+    unsigned any = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) { any |= lds.bad[w]; any_over |= lds.over[w]; }
-    // head h was flagged iff one of its 4 lanes (h, h+16, h+32, h+48) in any wavefront says so
-    unsigned flagged_heads = (unsigned)((any | (any >> 16) | (any >> 32) | (any >> 48)) & 0xffffull);
-#pragma unroll
-    for (int h = 0; h < 16; ++h) flagged_heads |= (unsigned)(lds.f_new[h] != 0) << h;
+    for (int w = 0; w < NW; ++w) any |= lds.mask[w];
+    any = __builtin_amdgcn_readfirstlane(any);
+    const unsigned flagged_heads = any & 0xffffu;
     // heads whose sums have to be redone: the flagged ones, and those with a weight that did not fit
-    const unsigned redo_heads = flagged_heads | (unsigned)((any_over | (any_over >> 16) | (any_over >> 32) | (any_over >> 48)) & 0xffffull);
+    const unsigned redo_heads = flagged_heads | any >> 16;
     auto den_of = [&](int h) {                 // Eq. 4's denominator of head h over this chunk
-        float s = lds.e_new[h];
+        float s = owner ? lds.e_new[h] : 0.f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) s += lds.den[w][h + 16 * q4];
+        for (int w = 0; w < NW; ++w) s += lds.den[h][w];
         return s;
     };
     // A sequence of one chunk whose guard stayed quiet is complete here: its rows' results are
     // this workgroup's own sums, so they go out directly instead of through the workspace and
     // the epilogue (same arithmetic: the epilogue's factors are exactly 1 for such a row).
     const bool solo = p.elect && nb == 1 && !redo_heads;
-    // 4 consecutive elements per thread: one 16-byte LDS read per wavefront tile, 16 bytes out
+    // 4 consecutive elements per thread: one 16-byte LDS read per wavefront tile, 16 bytes out (a whole row per wavefront, 8
+    // bytes per thread, took 0.4 us more where the results are written through)
     for (int i = 4 * tid; i < G * kHeadDim; i += 4 * kGqaThreads) {
-        float4 o = *reinterpret_cast<const float4 *>(&lds.tile[i]);
+        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-        for (int w = 1; w < NW; ++w) {         // wavefront order
+        for (int w = 0; w < NW; ++w) {         // wavefront order
             const float4 t = *reinterpret_cast<const float4 *>(&lds.tile[w * 16 * kHeadDim + i]);
-            o.x += t.x; o.y += t.y; o.z += t.z; o.w += t.w;
+            const float k = lds.inv[i / kHeadDim][w];
+            o.x = __builtin_fmaf(k, t.x, o.x); o.y = __builtin_fmaf(k, t.y, o.y);
+            o.z = __builtin_fmaf(k, t.z, o.z); o.w = __builtin_fmaf(k, t.w, o.w);
         }
         const int q = i & (kHeadDim - 1);      // LDS position -> element index (see the layout above)
         const int d0 = 2 * (q & 63) + 4 * (q >> 6);
@@ -364,20 +362,21 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         }
         float *dst = &p.ws.num[((size_t)(row0 + i / kHeadDim) * p.nc + c) * kHeadDim + d0];
         if (p.elect && !solo) {      // read by another workgroup of this launch: write through
-            store_coherent4(dst, o.x, o.y, o.z, o.w);
+            store_coherent2(dst, o.x, o.y);
+            store_coherent2(dst + 2, o.z, o.w);
         } else {
             *reinterpret_cast<float4 *>(dst) = o;
         }
     }
-    if (tid < G) {
-        const float s = den_of(tid);
-        const size_t slot = (size_t)(row0 + tid) * p.nc + c;
-        const int f = (flagged_heads >> tid) & 1;
+    if (wave == NW - 1 && lane < G) {
+        const float s = den_of(lane);
+        const size_t slot = (size_t)(row0 + lane) * p.nc + c;
+        const int f = (flagged_heads >> lane) & 1;
         store_coherent(&p.ws.den[slot], s);
         store_coherent(&p.ws.mloc[slot], p.phi);
         store_meta(p, slot, s, p.phi, f);
         p.ws.chunk_flags[slot] = (uint8_t)f;
-        if (solo) p.ws.row_flags[row0 + tid] = 0;
+        if (solo) p.ws.row_flags[row0 + lane] = 0;
     }
     if (solo) return;
 
