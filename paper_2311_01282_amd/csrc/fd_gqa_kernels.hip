@@ -64,7 +64,76 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 constexpr float kFirstBlockLog2 = 4.f;    // a head's largest weight of the wavefront's first block lies in [2^3, 2^4] ...
 constexpr float kOverflowLog2 = 15.9f;    // ... and no later weight may reach 2^16 (fp16 ends at 65504)
 
-template <int C, bool PAGED = false, int NW = 4>
+// Inclusive sum over the lanes of a wavefront.
+__device__ __forceinline__ int lanes_scan(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8: within rows of 16
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // lane 15 to row 1, lane 47 to row 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // lane 31 to rows 2 and 3
+    return x;
+}
+
+// Order by length (launches of more than one workgroup per compute unit, at most 64 sequences; see GqaLauncher): the chunks
+// that are full first, then the sequences' last, partial chunks from the longest to the shortest, then the chunks without keys; each for
+// all KV heads.  Every workgroup of up to three rounds of the chip starts with the launch and a compute unit holds workgroups i, i + 256, ...,
+// so what it has to stream is decided here: the first 256 go in reverse, and the shortest of them share their compute
+// units with the longest of the rest.  `res`: resident keys of sequence `lane` (p.B <= 64).
+// Returns false for a workgroup beyond the last chunk; else sequence, chunk and KV head.
+__device__ __forceinline__ bool chunk_by_length(const Problem &p, int res, int &b, int &c, int &hkv)
+{
+    const int lane = threadIdx.x & 63;
+    int full = 0, rest = 0, empty = 0;
+    if (lane < p.B) {
+        const int len = effective_len(p, res);
+        full = (int)((float)len * __builtin_amdgcn_rcpf((float)p.C));      // the quotient, or one off
+        full -= full * p.C > len;
+        full += len - full * p.C >= p.C;
+        rest = len - full * p.C;
+        empty = p.nc - full - (rest > 0);
+    }
+    const int scan = lanes_scan(full);
+    const unsigned long long parts = __ballot(rest > 0);
+    const int n_full = __builtin_amdgcn_readlane(scan, 63), n_part = __popcll(parts);
+    const int live = (n_full + n_part) * p.Hkv;
+    int i = blockIdx.x;
+    if (live > kComputeUnits && i < kComputeUnits) i = kComputeUnits - 1 - i;
+    int q = (int)(((float)i + 0.5f) * __builtin_amdgcn_rcpf((float)p.Hkv));   // i / Hkv: exact, i < 2^20
+    const int h = i - q * p.Hkv;
+    if (q < n_full) {
+        b = __popcll(__ballot(scan <= q));
+        c = q - (__builtin_amdgcn_readlane(scan, b) - __builtin_amdgcn_readlane(full, b));
+    } else if (q < n_full + n_part) {
+        // the q-th longest, lengths taken in 64 steps of a chunk: the step it is in, six halvings; in that step by sequence
+        q -= n_full;
+        const int step = rest > 0 ? (int)((float)rest * (64.f * __builtin_amdgcn_rcpf((float)p.C))) : -1;
+        int at = 0;
+#pragma unroll
+        for (int bit = 32; bit > 0; bit >>= 1) at += __popcll(__ballot(step >= at + bit)) > q ? bit : 0;
+        q -= __popcll(__ballot(step > at));
+        const unsigned long long same = __ballot(step == at);
+        const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(same >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)same, 0u));
+        b = __ffsll((unsigned long long)__ballot((step == at) & (before == q))) - 1;
+        c = __builtin_amdgcn_readlane(full, b);
+    } else {
+        q -= n_full + n_part;
+        const int escan = lanes_scan(empty);
+        b = __popcll(__ballot(escan <= q));
+        if (b >= p.B) return false;
+        c = p.nc - (__builtin_amdgcn_readlane(escan, b) - q);
+    }
+    hkv = h + min(c & 7, p.Hkv - 1);           // turned by the chunk: an XCD does not stay with one head
+    hkv -= hkv >= p.Hkv ? p.Hkv : 0;
+    return true;
+}
+
+// kEarly: the first loads go out before the sequence length has arrived (launches of at most one workgroup per compute unit,
+// contiguous cache; see decode_fused_kernel); kByLength: chunk_by_length.
+enum Start { kPlain, kEarly, kByLength };
+
+template <int C, bool PAGED, Start START, int NW = 4>
 __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_kernel(const Problem p)
 {
     static_assert(NW == 4 || NW == 8, "the appended key's lane assignment covers 16 heads with 4 wavefronts");
@@ -73,31 +142,72 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
     constexpr int UP = C / (4 * NW) < 8 ? C / (4 * NW) : 8;    // stage depth of the per-row recomputation
     __shared__ GqaLds<NW> lds;
     constexpr int NBLK = C / 16;               // 16-key blocks in the chunk
+    static_assert(!(PAGED && START == kEarly), "the page table has to arrive before the first load");
+    constexpr bool EARLY = START == kEarly, BY_LENGTH = START == kByLength;
+    fetch_arguments_now(p);
+    asm volatile("" ::"s"(p.B), "s"(p.C), "s"(p.scatter), "s"(p.chunk_major));
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, g = lane >> 4;    // n: head (scores) / 16-byte segment (loads); g: lane group
     const int G = p.G;
 
-    // All chunks of a KV-head group go to the same XCD (see decode_fused_kernel).
-    const int groups = p.B * p.Hkv;
-    // chunk-major in a launch of up to 1024 workgroups, so that chunks past the end of the
-    // sequences come last; row-major beyond (see decode_fused_kernel)
-    const int groups8 = (groups + 7) >> 3;
-    const int j = blockIdx.x >> 3;
-    const int c = p.chunk_major ? j / groups8 : j % p.nc;
-    const int gi = row_slot(p, blockIdx.x & 7, c) + 8 * (p.chunk_major ? j - c * groups8 : j / p.nc);
-    if (gi >= groups) return;
-    const int b = gi / p.Hkv;
+    int b, c, gi;                              // sequence, chunk, (sequence, KV head)
+    const int groups = p.B * p.Hkv, groups8 = (groups + 7) >> 3;
+    int res = 0;
+    bool by_length = BY_LENGTH;
+    if constexpr (BY_LENGTH) {
+        if (lane < p.B) res = clamp_len(p, p.seq_lens[lane]);
+        // equal lengths have nothing to sort, unless the rows do not divide among the XCDs
+        by_length = __ballot((lane < p.B) & (res != __builtin_amdgcn_readfirstlane(res))) != 0ull || groups8 * 8 != groups;
+    }
+    if (by_length) {
+        int hkv;
+        if (!chunk_by_length(p, res, b, c, hkv)) return;
+        gi = b * p.Hkv + hkv;
+    } else {
+        // All chunks of a KV-head group go to the same XCD (see decode_fused_kernel); chunk-major in a launch of up
+        // to 1024 workgroups, so that chunks past the end of the sequences come last; row-major beyond.
+        const int j = blockIdx.x >> 3;
+        const bool cm = p.chunk_major != 0;
+        c = cm ? j / groups8 : j % p.nc;
+        gi = row_slot(p, blockIdx.x & 7, c) + 8 * (cm ? j - c * groups8 : j / p.nc);
+        if (gi >= groups) return;
+        b = gi / p.Hkv;
+    }
     const int row0 = b * p.Hq + (gi - b * p.Hkv) * G;       // first query row of the group
-    const int S_res = clamp_len(p, p.seq_lens[b]);          // keys resident in the cache
-    const int S = effective_len(p, S_res);                  // plus the appended one, if any
+    int raw = 0;
+    if constexpr (EARLY) raw = seq_len_issue(p, b);
     const int len = p.C;                                    // keys per chunk (<= C, the kernel's capacity)
-    const int nb = (S + len - 1) / len;
     const int start = c * len;
+
+    // Q as the B operand: lane (n, g) holds d = 32kb + 8g .. +7 of head n; heads >= G are zero rows.
+    u32x4 qr[4];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+        qr[kb] = *reinterpret_cast<const u32x4 *>(p.q + (size_t)(row0 + min(n, G - 1)) * kHeadDim + 32 * kb + 8 * g);
+
+    const KvRows<PAGED> at(p, b, gi - b * p.Hkv, start, lane);   // rows of the chunk's keys (contiguous or paged)
+    const u32x4 *kp = reinterpret_cast<const u32x4 *>(p.k) + at.base + n;
+    const u32x4 *vp = reinterpret_cast<const u32x4 *>(p.v) + at.base + n;
+    u32x4 kA[4], vA[4];
+    if constexpr (EARLY) {                     // this wavefront's first block, clamped to the chunk's extent in the buffer
+        const int cap = min(len, p.Smax - start) - 1;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) kA[r] = load_stream(kp + at(min(16 * wave + 4 * r + g, cap)));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) vA[r] = load_stream(vp + at(min(16 * wave + 4 * r + g, cap)));
+        asm volatile("" ::: "memory");         // the loads go out before the length is awaited, whatever it decides
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
+    // keys resident in the cache
+    const int S_res = EARLY ? seq_len_finish(p, raw) : BY_LENGTH ? __builtin_amdgcn_readlane(res, b) : clamp_len(p, p.seq_lens[b]);
+    const int S = effective_len(p, S_res);                  // plus the appended one, if any
+    const int nb = (S + len - 1) / len;
     const int nvalid = min(len, S - start);
     const int nres = min(len, S_res - start);
     const bool owner = (S != S_res) & (S_res >= start) & (S_res < start + len);   // this chunk takes the appended key
 
-    if (nvalid <= 0) {                         // padding chunk: zero partials, no flag
+    if (!EARLY && nvalid <= 0) {               // padding chunk: zero partials, no flag (EARLY: by the ordinary path)
         for (int i = tid; i < G * kHeadDim; i += kGqaThreads)
             p.ws.num[((size_t)(row0 + i / kHeadDim) * p.nc + c) * kHeadDim + (i & (kHeadDim - 1))] = 0.f;
         if (tid < G) {
@@ -111,18 +221,9 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         return;
     }
 
-    // Q as the B operand: lane (n, g) holds d = 32kb + 8g .. +7 of head n; heads >= G are zero rows.
     f16x8 qb[4];
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-        u32x4 t = {0u, 0u, 0u, 0u};
-        if (n < G) t = *reinterpret_cast<const u32x4 *>(p.q + (size_t)(row0 + n) * kHeadDim + 32 * kb + 8 * g);
-        qb[kb] = __builtin_bit_cast(f16x8, t);
-    }
-
-    const KvRows<PAGED> at(p, b, gi - b * p.Hkv, start, lane);   // rows of the chunk's keys (contiguous or paged)
-    const u32x4 *kp = reinterpret_cast<const u32x4 *>(p.k) + at.base + n;
-    const u32x4 *vp = reinterpret_cast<const u32x4 *>(p.v) + at.base + n;
+    for (int kb = 0; kb < 4; ++kb) qb[kb] = __builtin_bit_cast(f16x8, n < G ? qr[kb] : u32x4{0u, 0u, 0u, 0u});
     const int last = nres - 1;                 // last resident key; the appended one joins at the reduction
     const float nphi = -p.phi, lo = p.lo, hi = p.hi, scale = p.scale;
     u32x4 *kst = reinterpret_cast<u32x4 *>(lds.tile) + wave * 256;     // this wavefront's 16 x 16 slots
@@ -241,10 +342,17 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         // apart and advance in step are served badly by the memory system for some shapes; 1 x 64/8
         // heads x 262144 keys: 188 us against 161 for the same bytes as 4 x 65536).  Whichever block
         // comes first fixes the scale of the fp16 weights.
-        const int rot = (p.nc > 32 && nmine > 1) ? (int)((unsigned)(c * 3 + gi) % (unsigned)nmine) : 0;
+        const int rot = (!EARLY && p.nc > 32 && nmine > 1) ? (int)((unsigned)(c * 3 + gi) % (unsigned)nmine) : 0;
         auto blk_of = [&](int i) { const int t = i + rot; return wave + NW * (t >= nmine ? t - nmine : t); };
-        u32x4 kA[4], vA[4], kB[4], vB[4];
-        issue(blk_of(0), kA, vA);
+        u32x4 kB[4], vB[4];
+        if constexpr (EARLY) {                 // (no launch of this kind has 32 chunks per row: rot = 0)
+            if (16 * wave + 15 > last)         // what lies past the last key may be anything: no NaN into the products
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (16 * wave + 4 * r + g > last) vA[r] = u32x4{0u, 0u, 0u, 0u};
+        } else {
+            issue(blk_of(0), kA, vA);
+        }
         int i = 0;
 #pragma unroll 1
         for (; i + 2 < nmine; i += 2) {
@@ -332,7 +440,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
     // A sequence of one chunk whose guard stayed quiet is complete here: its rows' results are
     // this workgroup's own sums, so they go out directly instead of through the workspace and
     // the epilogue (same arithmetic: the epilogue's factors are exactly 1 for such a row).
-    const bool solo = p.elect && nb == 1 && !redo_heads;
+    const bool solo = p.elect && nb == 1 && nvalid > 0 && !redo_heads;
     // 4 consecutive elements per thread: one 16-byte LDS read per wavefront tile, 16 bytes out (a whole row per wavefront, 8
     // bytes per thread, took 0.4 us more where the results are written through)
     for (int i = 4 * tid; i < G * kHeadDim; i += 4 * kGqaThreads) {
@@ -379,6 +487,13 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         if (solo) p.ws.row_flags[row0 + lane] = 0;
     }
     if (solo) return;
+    if (EARLY && nvalid <= 0) {                // padding chunk; of an empty sequence, nobody else owns the rows
+        if (nb == 0 && c == 0 && p.elect) {
+            for (int i = tid; i < G * kHeadDim; i += kGqaThreads) p.out[(size_t)row0 * kHeadDim + i] = 0;
+            if (tid < G) p.ws.row_flags[row0 + tid] = 0;
+        }
+        return;
+    }
 
     // Section 3 "Recomputation": a (head, chunk) whose guard fired is redone with the
     // synchronized scheme on the per-row path (rare; re-reads this chunk only).  So is one whose
@@ -418,8 +533,22 @@ template <int C> struct GqaLauncher {
         // 4 wavefronts per workgroup.  (8 were measured for launches of at most one workgroup per
         // compute unit: within 2 % either way at 256 workgroups, 12 % faster only for a lone
         // 4096-key chunk, which fd_pick_chunk never chooses.)
-        if (p.block_table) return launch(decode_fused_gqa_kernel<C, true, 4>, dim3(grid), dim3(256), s, p);
-        return launch(decode_fused_gqa_kernel<C, false, 4>, dim3(grid), dim3(256), s, p);
+        // By length where a compute unit holds more than one workgroup and the lengths of the batch fit a wavefront: what has to be
+        // streamed is spread evenly, and over all XCDs also where the head groups do not divide by 8.  Whole call, general order / this:
+        // 12 x 32/8 heads x 300 .. 6000 keys 37.6 / 34.2 us, 32 x 64/8 x 512 .. 4096 in 1024-key chunks 64.4 / 59.8, 64 x 64/8 x 300 ..
+        // 8192 203 / 182, 5 x 28/4 x 3000 .. 20000 40.4 / 26.4, 1 x 28/4 x 20000 16.4 / 14.8, 1 x 12/2 x 30000 18.4 / 15.0; equal lengths
+        // pay for looking at them: 12 x 64/8 x 4096 36.5 / 36.7, 32 x 64/8 x 16384 320.7 / 321.2.  Beyond 4096 workgroups a
+        // workgroup is short beside the 0.3 us that finding its chunk takes (32 x 64/8 x 1500 .. 3000 in 128-key chunks, 6144
+        // workgroups, 63.0 / 64.2), and they even out by themselves.
+        // Early loads in the launches of one workgroup per compute unit: 2 x 64/8 x 9001 17.1 / 16.8 us, 4 x 32/8 x 4096 14.85 /
+        // 14.6, 1 x 28/4 x 700 7.4 / 7.15.
+        const dim3 g(grid), t(256);
+        if (grid > (unsigned)kComputeUnits && grid <= 4096u && p.B <= 64)
+            return p.block_table ? launch(decode_fused_gqa_kernel<C, true, kByLength>, g, t, s, p)
+                                 : launch(decode_fused_gqa_kernel<C, false, kByLength>, g, t, s, p);
+        if (p.block_table) return launch(decode_fused_gqa_kernel<C, true, kPlain>, g, t, s, p);
+        return grid <= (unsigned)kComputeUnits ? launch(decode_fused_gqa_kernel<C, false, kEarly>, g, t, s, p)
+                                               : launch(decode_fused_gqa_kernel<C, false, kPlain>, g, t, s, p);
     }
 };
 

@@ -1,0 +1,57 @@
+"""The grouped kernel's order by sequence length (launches of more than 256 workgroups, up to 64 sequences): a
+permutation of (sequence, chunk, KV head) that every workgroup works out for itself.  Head counts that do and do not divide among
+the XCDs, batches at both ends of the range and one beyond it, equal lengths, empty and full sequences, lengths that
+leave chunks full, nearly full or with one key, one and many chunks; the epilogue as a second launch throughout.  A chunk that is
+done twice or not at all shows in the output, in the chunk flags or in its partial sum; everything is compared with the fp64 oracle."""
+import numpy as np
+import pytest
+
+from paper_2311_01282_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def H():
+    import fd_harness
+    return fd_harness
+
+
+def lengths(kind, B, Smax, chunk, seed):
+    rng = np.random.default_rng(seed)
+    if kind == "equal":
+        return [Smax] * B
+    if kind == "edges":                    # around multiples of the chunk, with empty and full sequences among them
+        near = [0, Smax, 1, chunk, chunk + 1, max(chunk - 1, 1), min(2 * chunk, Smax), Smax - 1]
+        return [near[(i * 5 + i // 8) % 8] for i in range(B)]
+    return [int(x) for x in rng.integers(0, Smax + 1, B)]
+
+
+@pytest.mark.parametrize("kind", ["edges", "random", "equal"])
+@pytest.mark.parametrize("B,Hq,Hkv,Smax,chunk", [
+    (2, 4, 2, 4160, 64),          # 4 head groups on 8 XCDs, 65 chunks each: 520 workgroups
+    (1, 14, 2, 2240, 64),         # one sequence, 2 head groups, 35 chunks
+    (5, 28, 4, 700, 64),          # 20 head groups
+    (33, 16, 8, 192, 64),         # 264 head groups of three chunks
+    (64, 10, 5, 128, 128),        # 320 head groups of a single chunk: the most sequences
+    (63, 6, 3, 256, 128),         # 189 head groups, odd head count
+    (65, 16, 8, 80, 80),          # a sequence too many: the general order
+    (9, 16, 1, 3600, 208),        # one KV head; a chunk of 208 keys
+    (7, 4, 1, 5000, 112),         # 45 chunks
+])
+def test_every_chunk_once(oracle, H, B, Hq, Hkv, Smax, chunk, kind):
+    lens = lengths(kind, B, Smax, chunk, 9000 + B + Smax)
+    case = synth.make_case(B=B, Hq=Hq, Hkv=Hkv, D=128, Smax=Smax, seed=9100 + B + chunk, seq_lens=lens, poison_padding=True)
+    nc = -(-Smax // chunk)
+    assert 8 * ((B * Hkv + 7) // 8) * nc > 256
+    want = oracle.attn_exact(case["q"], case["k"], case["v"], case["seq_lens"], case["scale"], nthreads=8)
+    ocf, orf, margin = oracle.flags(case["q"], case["k"], case["seq_lens"], case["scale"], synth.PHI, *synth.BOUNDS, chunk, nthreads=8)
+    assert margin.min() > 1e-2
+    dc = H.DeviceCase(case, chunk=chunk)
+    got = dc.run("fd_decode_attn_gqa")
+    H.assert_close(got, want, "by length")
+    cf, rf, n, _ = dc.flags()
+    assert np.array_equal(cf, ocf) and np.array_equal(rf, orf) and n == int(orf.sum())
+    _, den = dc.partials()
+    with_keys = np.arange(nc)[None, None, :] * chunk < np.asarray(lens)[:, None, None]
+    assert np.array_equal(den > 0, np.broadcast_to(with_keys, den.shape))
