@@ -176,14 +176,15 @@ inline int elect_per_row(const fd::Problem &p)
 // workgroups; at 32 chunks the second launch (one workgroup per row, 8 chunk slices in
 // parallel) wins or ties: whole call, one launch / two, 64 query on 8 KV heads -- 18.1 / 18.5 us at 16 (2 x 9001 keys),
 // 14.3 / 13.1 at 32 (8192 keys), 16.4 / 15.2 at 32 (12000 keys); 32 on 8 heads -- 16.3 / 17.4 at 16 (2 x 8192 keys), 26.3 /
-// 26.6 at 32 (32768 keys).  Over 257 to 1024 workgroups neither side wins: B x 64/8 heads, full caches read from memory -- 9 x 4096
-// keys in 4 chunks 34.8 / 35.3, 12 x 4096 in 4 38.4 / 38.4, 16 x 4096 in 4 45.2 / 46.0, 8 x 8192 in 8 46.4 / 46.1, 3 x 12000 in 12
-// 35.4 / 35.4, 4 x 8192 in 16 28.3 / 27.8, 24 x 4096 in 2 68.2 / 66.6, 32 x 8192 in 4 (1024 workgroups) 163.9 / 165.0; ragged
-// 12 x 512 .. 4096 in 4 30.3 / 30.7, 16 x 1000 .. 8192 in 4 63.4 / 62.0; a cache that is mostly empty pays for the second launch
-// (8 x 8192 holding about 1000: 16.5 / 18.1).
+// 26.6 at 32 (32768 keys).  Launches of up to three workgroups per compute unit, which all start with the launch, finish
+// rows of up to 8 chunks as well: two launches / one, 12 x 32/8 heads x 300 .. 6000 keys in 5 chunks 34.1 / 33.5 us (paged 35.8 / 35.4), 17 x 64/8 x 400
+// .. 2500 in 7 27.2 / 26.6, 24 x 64/8 x 500 .. 2000 in 4 30.8 / 30.5, 32 x 64/8 x 500 .. 1990 in 2, one with keys, 36.9 / 34.4, 9 x 32/8 x 4096
+// in 7 28.45 / 28.2, 12 x 64/8 x 4096 in 5 a tie; 3 x 64/8 x 12000 in 12 34.5 / 35.0, and at 1024 workgroups 32 x 64/8 x 4096 in 4
+// 86.9 / 88.0, 64 x 64/8 x 300 .. 8192 in 2 183.4 / 185.2, 16 x 64/8 x 8192 in 8 89.0 / 88.5.
 inline int elect_grouped(const fd::Problem &p)
 {
-    return (long long)p.B * p.Hkv * p.nc <= 256 && p.nc <= 16;
+    const long long workgroups = (long long)p.B * p.Hkv * p.nc;
+    return (workgroups <= fd::kComputeUnits && p.nc <= 16) || (workgroups <= 3 * fd::kComputeUnits && p.nc <= 8);
 }
 
 #define FD_TRY(expr) do { if ((expr) != hipSuccess) return FD_ERR_HIP; } while (0)

@@ -1,7 +1,7 @@
 """The grouped kernel's order by sequence length (launches of more than 256 workgroups, up to 64 sequences): a
 permutation of (sequence, chunk, KV head) that every workgroup works out for itself.  Head counts that do and do not divide among
 the XCDs, batches at both ends of the range and one beyond it, equal lengths, empty and full sequences, lengths that
-leave chunks full, nearly full or with one key, one and many chunks; the epilogue as a second launch throughout.  A chunk that is
+leave chunks full, nearly full or with one key, one and many chunks; rows finished inside the launch and by a second one.  A chunk that is
 done twice or not at all shows in the output, in the chunk flags or in its partial sum; everything is compared with the fp64 oracle."""
 import numpy as np
 import pytest
@@ -38,6 +38,9 @@ def lengths(kind, B, Smax, chunk, seed):
     (65, 16, 8, 80, 80),          # a sequence too many: the general order
     (9, 16, 1, 3600, 208),        # one KV head; a chunk of 208 keys
     (7, 4, 1, 5000, 112),         # 45 chunks
+    (12, 16, 8, 512, 64),         # 768 workgroups of 8 chunks: the largest launch that finishes its rows ...
+    (13, 16, 8, 512, 64),         # ... and one beyond it
+    (16, 4, 2, 576, 64),          # 9 chunks
 ])
 def test_every_chunk_once(oracle, H, B, Hq, Hkv, Smax, chunk, kind):
     lens = lengths(kind, B, Smax, chunk, 9000 + B + Smax)
@@ -48,10 +51,11 @@ def test_every_chunk_once(oracle, H, B, Hq, Hkv, Smax, chunk, kind):
     ocf, orf, margin = oracle.flags(case["q"], case["k"], case["seq_lens"], case["scale"], synth.PHI, *synth.BOUNDS, chunk, nthreads=8)
     assert margin.min() > 1e-2
     dc = H.DeviceCase(case, chunk=chunk)
-    got = dc.run("fd_decode_attn_gqa")
-    H.assert_close(got, want, "by length")
-    cf, rf, n, _ = dc.flags()
-    assert np.array_equal(cf, ocf) and np.array_equal(rf, orf) and n == int(orf.sum())
+    for rep in range(2):                   # (arrival counters back at zero)
+        got = dc.run("fd_decode_attn_gqa")
+        H.assert_close(got, want, "by length, pass %d" % rep)
+        cf, rf, n, _ = dc.flags()
+        assert np.array_equal(cf, ocf) and np.array_equal(rf, orf) and n == int(orf.sum())
     _, den = dc.partials()
     with_keys = np.arange(nc)[None, None, :] * chunk < np.asarray(lens)[:, None, None]
     assert np.array_equal(den > 0, np.broadcast_to(with_keys, den.shape))
