@@ -27,6 +27,7 @@
 // K and V tiles are loaded from global memory straight into LDS, once per workgroup, and
 // shared by its four wavefronts (rings of four tiles; layouts free of bank conflicts for the
 // 16-byte operand reads).
+#include <type_traits>
 #include <utility>
 
 #include "fd_chunk.h"
@@ -39,6 +40,7 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kFirstStepLog2 = 4.f;     // a query's largest weight of its first key step becomes 2^4 ...
 constexpr float kOverflowLog2 = 15.9f;    // ... and no later weight may reach 2^16 (fp16 ends at 65504)
@@ -230,22 +232,19 @@ struct Weights {
 // O^T += V^T P^T with P = Ph + Pl, one step
 __device__ __forceinline__ void add_pv(const TileWave &tw, PrefillLds &lds, int s, const Weights &w, f32x4 (&acc)[8][kQB])
 {
-    f16x8 a_v[2];
-    const int slot = s & (kRing - 1);
-    a_v[0] = tw.read_v(lds, slot, 0);
+    f16x8 av[8];
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) av[dt] = tw.read_v(lds, s & (kRing - 1), dt);
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) {
-        if (dt + 1 < 8) a_v[(dt + 1) & 1] = tw.read_v(lds, slot, dt + 1);
-        const f16x8 v8 = a_v[dt & 1];
 #pragma unroll
         for (int qb = 0; qb < kQB; ++qb)
-            acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v8, __builtin_bit_cast(f16x8, w.hi[qb]), acc[dt][qb], 0, 0, 0);
+            acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[dt], __builtin_bit_cast(f16x8, w.hi[qb]), acc[dt][qb], 0, 0, 0);
 #pragma unroll
         for (int qb = 0; qb < kQB; ++qb)
-            acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v8, __builtin_bit_cast(f16x8, w.lo[qb]), acc[dt][qb], 0, 0, 0);
+            acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[dt], __builtin_bit_cast(f16x8, w.lo[qb]), acc[dt][qb], 0, 0, 0);
     }
 }
-
 // hi = the weights cut to fp16 (11 bits), lo = what that leaves (exact in fp32), rounded to fp16.  neg1 is -1.0 in a
 // register the compiler cannot see through: it keeps e - (float)hi a single mixed-precision fused multiply-add.
 __device__ __forceinline__ void split_pair(float e0, float e1, float neg1, unsigned &hi, unsigned &lo)
@@ -259,25 +258,63 @@ __device__ __forceinline__ void split_pair(float e0, float e1, float neg1, unsig
     lo = __builtin_bit_cast(unsigned, l);
 }
 
-// Output rows of a wavefront: acc / den, zeros for rows past the prompt.
-__device__ __forceinline__ void store_rows(const PrefillProblem &p, const TileWave &tw, int b, int hq, int S, const f32x4 (&acc)[8][kQB], const float (&den)[kQB])
+// Over the four lane groups of a query (lanes n, n + 16, n + 32, n + 48): its sum and its maximum, in every lane.
+__device__ __forceinline__ float query_sum(float a)
 {
+    a = rows_sum(a, a);
+    return halves_sum(a, a);
+}
+__device__ __forceinline__ float query_max(float a)
+{
+    const unsigned u = __builtin_bit_cast(unsigned, a);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned r0 = r[0], r1 = r[1];
+    const unsigned v = __builtin_bit_cast(unsigned, fmaxf(__builtin_bit_cast(float, r0), __builtin_bit_cast(float, r1)));
+    const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    const unsigned h0 = h[0], h1 = h[1];
+    return fmaxf(__builtin_bit_cast(float, h0), __builtin_bit_cast(float, h1));
+}
+
+// Output rows of a wavefront: acc / den, zeros for rows past the prompt.  The accumulators hold 8 bytes of each of 16 rows
+// per instruction; they go through 8 KiB of LDS of the wavefront's own (16-byte chunk c of row r in chunk c ^ (r % 16)), so that a
+// store instruction writes four whole rows; all of it is under way at once, without a branch.  What bounds a short prompt is
+// what a workgroup does outside its loop: straight from the accumulators, 16 stores of 16 half lines each took a wavefront 3500
+// cycles, this 2000.  The rings have to be out of use.
+__device__ __forceinline__ void store_rows(const PrefillProblem &p, const TileWave &tw, PrefillLds &lds, int b, int hq, int S, const f32x4 (&acc)[8][kQB], const float (&den)[kQB])
+{
+    static_assert(4 * kWaveQ * kHeadDim * 2 <= sizeof(lds.k));
+    unsigned char *rows = &lds.k[0][0] + tw.wave * (kWaveQ * kHeadDim * 2);
+    const int n = tw.n, g = tw.g;
 #pragma unroll
     for (int qb = 0; qb < kQB; ++qb) {
-        const int row = tw.w0 + 16 * qb + tw.n;
-        if (row >= p.Smax) continue;
-        const bool live = row < S;
-        const float inv = live ? 1.f / den[qb] : 0.f;
-        uint16_t *o = p.out + (((size_t)b * p.Hq + hq) * p.Smax + row) * kHeadDim;
+        const float inv = 1.f / den[qb];
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) {
-            uint2 h = make_uint2(0u, 0u);
-            if (live) {
-                h.x = (unsigned)to_half_bits(acc[dt][qb][0] * inv) | ((unsigned)to_half_bits(acc[dt][qb][1] * inv) << 16);
-                h.y = (unsigned)to_half_bits(acc[dt][qb][2] * inv) | ((unsigned)to_half_bits(acc[dt][qb][3] * inv) << 16);
-            }
-            *reinterpret_cast<uint2 *>(o + 16 * dt + 4 * tw.g) = h;
+            f16x2 a, c;
+            a.x = (_Float16)(acc[dt][qb][0] * inv);
+            a.y = (_Float16)(acc[dt][qb][1] * inv);
+            c.x = (_Float16)(acc[dt][qb][2] * inv);
+            c.y = (_Float16)(acc[dt][qb][3] * inv);
+            *reinterpret_cast<u32x2 *>(rows + (16 * qb + n) * 256 + (((2 * dt + (g >> 1)) ^ n) << 4) + (g & 1) * 8) =
+                u32x2{__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, c)};
         }
+    }
+    u32x4 t[kWaveQ / 4];                                       // lane (n, g): chunk n of rows 4 i + g
+#pragma unroll
+    for (int i = 0; i < kWaveQ / 4; ++i) {
+        const int r = 4 * i + g;
+        t[i] = *reinterpret_cast<const u32x4 *>(rows + r * 256 + ((n ^ (r & 15)) << 4));
+    }
+    // through a window that ends at the buffer's last row: what lies past it is not written
+    uint16_t *o = p.out + (((size_t)b * p.Hq + hq) * p.Smax + tw.w0) * kHeadDim;
+    const int left = __builtin_amdgcn_readfirstlane(max(min(p.Smax - tw.w0, kWaveQ), 0)) * (kHeadDim * 2);
+    const auto window = __builtin_amdgcn_make_buffer_rsrc(o, 0, left, 0x00027000);
+#pragma unroll
+    for (int i = 0; i < kWaveQ / 4; ++i) {
+        const int r = 4 * i + g;
+        const bool live = tw.w0 + r < S;
+        const u32x4 x = {live ? t[i][0] : 0u, live ? t[i][1] : 0u, live ? t[i][2] : 0u, live ? t[i][3] : 0u};
+        __builtin_amdgcn_raw_buffer_store_b128(x, window, r * 256 + n * 16, 0, 0);
     }
 }
 
@@ -356,32 +393,29 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
     auto fetch_ahead = [&](int s) { tw.fetch_k(lds, s + 4); tw.fetch_v(lds, s + 3); };
     auto next_iteration = [&]() { wait_fetches<4>(); workgroup_barrier(); };
 
-    // weights of one step from its scores, not woven into anything: the first and the last step of a wavefront.
-    // last: the step that holds the wavefront's own keys (causal mask).
-    auto weights = [&](bool first, bool last, int s, const f32x4 (&sc)[kQB][2], Weights &w) {
-        const int k0 = s * kStep;
+    // The last step of a wavefront holds its own 32 keys (causal mask): key 8g + j of the step, j = 4t + r, is visible to query
+    // 16 qb + n of the wavefront where j - 16 qb <= own.
+    const int own = n - 8 * g;
+    // weights of a wavefront's first step from its scores, not woven into anything; last: it is its last one, too
+    auto first_weights = [&](bool last, const f32x4 (&sc)[kQB][2], Weights &w) {
 #pragma unroll
         for (int qb = 0; qb < kQB; ++qb) {
-            const int qrow = tw.w0 + 16 * qb + n;
             float z[8];
             bool ok[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                ok[j] = !last | (k0 + 8 * g + j <= qrow);                // j = 4t + r: key k0 + 8g + j
+                ok[j] = !last | (j - 16 * qb <= own);
                 z[j] = ok[j] ? __builtin_fmaf(sc[qb][j >> 2][j & 3], c1, c0q[qb]) : -INFINITY;
             }
-            if (first) {
-                // The query's scale: its largest weight of this first step becomes 2^kFirstStepLog2.
-                // The four lane groups of a query hold different keys: they agree on the maximum first.
-                float m = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), fmaxf(fmaxf(z[4], z[5]), fmaxf(z[6], z[7])));
-                m = fmaxf(m, __shfl_xor(m, 16));
-                m = fmaxf(m, __shfl_xor(m, 32));
-                const float k = (m == -INFINITY || m != m) ? 0.f : kFirstStepLog2 - m;      // no visible key, or NaN: leave as is
-                kq[qb] = k;
-                c0q[qb] = c0 + k;
+            // The query's scale: its largest weight of this first step becomes 2^kFirstStepLog2.
+            // The four lane groups of a query hold different keys: they agree on the maximum first.
+            float m = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), fmaxf(fmaxf(z[4], z[5]), fmaxf(z[6], z[7])));
+            m = query_max(m);
+            const float k = (m == -INFINITY || m != m) ? 0.f : kFirstStepLog2 - m;      // no visible key, or NaN: leave as is
+            kq[qb] = k;
+            c0q[qb] = c0 + k;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) z[j] += k;
-            }
+            for (int j = 0; j < 8; ++j) z[j] += k;
 #pragma unroll
             for (int j = 0; j < 8; j += 2) {
                 zhi[qb] = fmaxf(fmaxf(z[j], z[j + 1]), zhi[qb]);
@@ -405,13 +439,20 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
     // are spread because the four wavefronts are in step: 16 loads at a time queue for the address unit (another 80).
     // 1 x 32 heads x 8192 tokens: 673 us with neither, 653 with the first, 648 with both.
     // slot: s modulo the ring; rk, rv: windows that hold K tile s + 4 and V tile s + 3 as their tile u.
-    auto iteration = [&](int slot, u32x4 rk, u32x4 rv, int u, const f32x4 (&sc)[kQB][2], f32x4 (&scn)[kQB][2],
+    // last: step s + 1 is the wavefront's last (its weights are masked, there are no scores of step s + 2).
+    auto iteration = [&](auto last, int slot, u32x4 rk, u32x4 rv, int u, const f32x4 (&sc)[kQB][2], f32x4 (&scn)[kQB][2],
                          const Weights &w, Weights &wn, f16x8 (&av)[8]) {
+        constexpr bool kLast = decltype(last)::value;
+        float y0 = 0.f, y1 = 0.f;                                                // z0, z1 as the minimum takes them
         u32x4 ka[8];
         float z0 = 0.f, z1 = 0.f, e0 = 0.f, e1 = 0.f, f0 = 0.f, f1 = 0.f;      // the pair in work; f: its predecessor's weights
         _Float16 h0 = 0, h1 = 0;                                                 // ... and their hi parts
         unsigned hp = 0;
         f16x2 lp = {0, 0};
+        if constexpr (kLast) {
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt) av[dt] = tw.read_v(lds, slot, dt);
+        }
         __builtin_amdgcn_sched_barrier(0);
         unrolled(std::make_integer_sequence<int, 48>{}, [&](auto slot_index) {
             constexpr int m = decltype(slot_index)::value;
@@ -420,18 +461,18 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
                 constexpr int dt = m >> 2, qb = m & 1;
                 const u32x4 pw = (m & 2) ? w.lo[qb] : w.hi[qb];
                 acc[dt][qb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[dt], __builtin_bit_cast(f16x8, pw), acc[dt][qb], 0, 0, 0);
-            } else {
+            } else if constexpr (!kLast) {
                 constexpr int op = (m - 32) >> 1, kb = op >> 1, t = op & 1, qb = m & 1;
                 const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
                 scn[qb][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, ka[op]), tw.qB[qb][kb], kb == 0 ? zero : scn[qb][t], 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
             // operand reads and tile fetches
-            if constexpr (m < 8 && m % 2 == 1) av[4 + m / 2] = tw.read_v(lds, slot, 4 + m / 2);
-            if constexpr (m >= 17 && m < 25) ka[m - 17] = tw.read_k(lds, (slot + 2) & (kRing - 1), (m - 17) >> 1, (m - 17) & 1);
-            if constexpr (m >= 33 && m < 41 && m % 2 == 1) av[(m - 33) / 2] = tw.read_v(lds, (slot + 1) & (kRing - 1), (m - 33) / 2);
+            if constexpr (!kLast && m < 8 && m % 2 == 1) av[4 + m / 2] = tw.read_v(lds, slot, 4 + m / 2);
+            if constexpr (!kLast && m >= 17 && m < 25) ka[m - 17] = tw.read_k(lds, (slot + 2) & (kRing - 1), (m - 17) >> 1, (m - 17) & 1);
+            if constexpr (!kLast && m >= 33 && m < 41 && m % 2 == 1) av[(m - 33) / 2] = tw.read_v(lds, (slot + 1) & (kRing - 1), (m - 33) / 2);
             if constexpr (m >= 6 && (m - 6) % 11 == 0) tw.fetch_piece(lds, (m - 6) / 11, rk, rv, u, slot, (slot + 3) & (kRing - 1));
-            if constexpr (m % 16 == 15 && m < 47) wait_reads();                // (the last 16 slots' reads: at the barrier)
+            if constexpr (!kLast && m % 16 == 15 && m < 47) wait_reads();                // (the last 16 slots' reads: at the barrier)
             // weights: pair pr = (query block, keys 2j, 2j + 1)
             constexpr int pr = m / 6, qb = pr >> 2, j = pr & 3;
             constexpr int pp = pr - 1, pqb = pp >> 2, pj = pp & 3;               // the pair before
@@ -439,6 +480,12 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
                 case 0:
                     z0 = __builtin_fmaf(sc[qb][j >> 1][2 * (j & 1)], c1, c0q[qb]);
                     z1 = __builtin_fmaf(sc[qb][j >> 1][2 * (j & 1) + 1], c1, c0q[qb]);
+                    y0 = z0; y1 = z1;
+                    if constexpr (kLast) {
+                        const bool ok0 = 2 * j - 16 * qb <= own, ok1 = 2 * j + 1 - 16 * qb <= own;
+                        y0 = ok0 ? z0 : INFINITY; z0 = ok0 ? z0 : -INFINITY;
+                        y1 = ok1 ? z1 : INFINITY; z1 = ok1 ? z1 : -INFINITY;
+                    }
                     break;
                 case 1:
                     e0 = __builtin_amdgcn_exp2f(z0);
@@ -446,7 +493,7 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
                     break;
                 case 2:
                     e1 = __builtin_amdgcn_exp2f(z1);
-                    zlo[qb] = fminf(fminf(z0, z1), zlo[qb]);
+                    zlo[qb] = fminf(fminf(y0, y1), zlo[qb]);
                     break;
                 case 3:
                     den[qb] += e0;
@@ -483,9 +530,10 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
     wait_fetches<10>();                                       // K tiles 0 and 1
     workgroup_barrier();
     if (mine > 0) {
+        // (step 1's scores also where there is no such step: they run under the weights of step 0)
         tw.scores(lds, 0, scB);
-        weights(true, mine == 1, 0, scB, wA);
-        if (mine > 1) tw.scores(lds, 1, scA);
+        tw.scores(lds, 1, scA);
+        first_weights(mine == 1, scB, wA);
     }
     all_landed();                                             // V tiles 0 to 2, K tiles 2 and 3; Q^T on every path
     workgroup_barrier();
@@ -495,17 +543,18 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
         for (int dt = 0; dt < 4; ++dt) av[dt] = tw.read_v(lds, 0, dt);
         wait_reads();
         // four at a time: places in the ring and registers are then fixed (nothing is computed, nothing is moved)
+        constexpr std::false_type inner;
 #pragma unroll 1
         for (; s + kRing + 2 <= mine; s += kRing) {
             const u32x4 rk = tw.k_window(s + 4), rv = tw.v_window(s + 3);
-            iteration(0, rk, rv, 0, scA, scB, wA, wB, av);
-            iteration(1, rk, rv, 1, scB, scA, wB, wA, av);
-            iteration(2, rk, rv, 2, scA, scB, wA, wB, av);
-            iteration(3, rk, rv, 3, scB, scA, wB, wA, av);
+            iteration(inner, 0, rk, rv, 0, scA, scB, wA, wB, av);
+            iteration(inner, 1, rk, rv, 1, scB, scA, wB, wA, av);
+            iteration(inner, 2, rk, rv, 2, scA, scB, wA, wB, av);
+            iteration(inner, 3, rk, rv, 3, scB, scA, wB, wA, av);
         }
 #pragma unroll 1
         for (; s + 3 <= mine; ++s) {
-            iteration(s & (kRing - 1), tw.k_window(s + 4), tw.v_window(s + 3), 0, scA, scB, wA, wB, av);
+            iteration(inner, s & (kRing - 1), tw.k_window(s + 4), tw.v_window(s + 3), 0, scA, scB, wA, wB, av);
 #pragma unroll
             for (int qb = 0; qb < kQB; ++qb) {
 #pragma unroll
@@ -516,11 +565,14 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
         }
     }
     // The last two steps of the wavefront, then the fetches and barriers of the steps that only later wavefronts have.
+    // (The first of the two is woven like the loop's, with its V operands read at the start.  P.V and masked weights one after the other,
+    // V one operand ahead, took 2000 to 2500 cycles, this 1450.  With the stores through LDS and the first two steps' scores
+    // together before the first weights (2400 cycles, now 1660), whole call before / now: 4 ragged prompts of up to 1024 tokens 55.5 /
+    // 52.0 us, 1 x 32 heads x 100 8.9 / 7.6, 1 x 32 x 1024 27.2 / 25.7, 2 x 64/8 x 4001 560 / 550, 1 x 32 x 8192 663 / 658.)
     if (mine > 1) {                                           // s == mine - 2
-        fetch_ahead(s);
-        add_pv(tw, lds, s, wA, acc);
-        weights(false, true, s + 1, scA, wA);
-        next_iteration();
+        iteration(std::true_type{}, s & (kRing - 1), tw.k_window(s + 4), tw.v_window(s + 3), 0, scA, scB, wA, wB, av);
+#pragma unroll
+        for (int qb = 0; qb < kQB; ++qb) { wA.hi[qb] = wB.hi[qb]; wA.lo[qb] = wB.lo[qb]; }
         ++s;
     }
     if (mine > 0) {                                           // s == mine - 1
@@ -538,8 +590,7 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
     // the four lane groups of a query hold disjoint keys: total per query
 #pragma unroll
     for (int qb = 0; qb < kQB; ++qb) {
-        den[qb] += __shfl_xor(den[qb], 16);
-        den[qb] += __shfl_xor(den[qb], 32);
+        den[qb] = query_sum(den[qb]);
     }
     // strict guard on x - phi (the extremes carry the query's scale exponent); a NaN logit, which
     // minimum and maximum skip, shows as a NaN denominator.  Apart from the guard: a weight at or
@@ -564,7 +615,7 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
         if (t64 < p.tiles) p.tile_flags[((size_t)b * p.Hq + hq) * p.tiles + t64] = f != 0;
     }
     if ((lds.redo[0] | lds.redo[1] | lds.redo[2] | lds.redo[3]) != 0) return true;   // uniform: the tile is redone, nothing stored
-    store_rows(p, tw, b, hq, S, acc, den);
+    store_rows(p, tw, lds, b, hq, S, acc, den);
     return false;
 }
 
@@ -604,8 +655,7 @@ __device__ __forceinline__ void tile_sync(const PrefillProblem &p, PrefillLds &l
                 for (int j = 0; j < 8; ++j)
                     z[j] = s * kStep + 8 * tw.g + j <= qrow ? __builtin_fmaf(sc[qb][j >> 2][j & 3], c1, c0) : -INFINITY;
                 float m = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), fmaxf(fmaxf(z[4], z[5]), fmaxf(z[6], z[7])));
-                m = fmaxf(m, __shfl_xor(m, 16));
-                m = fmaxf(m, __shfl_xor(m, 32));
+                m = query_max(m);
                 const float mnew = fmaxf(mrun[qb], m);
                 if (mnew > mrun[qb]) {                        // rescale what was summed so far
                     const float alpha = mrun[qb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mrun[qb] - mnew);
@@ -632,10 +682,9 @@ __device__ __forceinline__ void tile_sync(const PrefillProblem &p, PrefillLds &l
     }
 #pragma unroll
     for (int qb = 0; qb < kQB; ++qb) {
-        den[qb] += __shfl_xor(den[qb], 16);
-        den[qb] += __shfl_xor(den[qb], 32);
+        den[qb] = query_sum(den[qb]);
     }
-    store_rows(p, tw, b, hq, S, acc, den);
+    store_rows(p, tw, lds, b, hq, S, acc, den);
 }
 
 // Which tile of the order below workgroup i of `grid` runs: a permutation that keeps i % 8.
