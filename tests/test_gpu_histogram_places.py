@@ -1,0 +1,27 @@
+"""The histogram kernel starts each (sequence, KV head) at a place of its own: every key is counted once, whether the number of
+runs divides the workgroups or not, with as many items as workgroups hold, fewer and more."""
+import pytest
+
+from oracle import fd_calibration_oracle as cal
+from paper_2311_01282_amd import synth
+from test_gpu_calibration import EDGE_EPS, check_histogram, gpu_histogram
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Smax,lens", [
+    (1, 4, 2, 40, [40]),                                  # one run per head
+    (4, 8, 8, 2048, [2048, 100, 1500, 64]),               # 32 runs of 64 keys on 256 workgroups
+    (3, 6, 3, 1999, [1999, 1, 1030]),                     # 32 runs, the last short; 9 heads
+    (2, 24, 2, 8192, [8192, 5000]),                       # 128 runs
+    (2, 34, 2, 700, [700, 321]),                          # two blocks of heads on one KV head
+    (16, 16, 16, 2500, [2500 - 150 * i for i in range(16)]),   # several rounds of the workgroups
+])
+def test_every_key_is_counted_once(B, Hq, Hkv, Smax, lens):
+    case = synth.make_case(B=B, Hq=Hq, Hkv=Hkv, D=128, Smax=Smax, seq_lens=lens, seed=400 + Smax, poison_padding=True)
+    want, lo, hi, near = cal.logit_histogram(case["q"], case["k"], case["seq_lens"], case["scale"], -6.0, 0.125, 96,
+                                             nthreads=8, edge_eps=EDGE_EPS)
+    got, mm = gpu_histogram(case, -6.0, 0.125, 96)
+    check_histogram(got, want, near)
+    assert got.sum() == sum(lens) * Hq
+    assert mm[0] == pytest.approx(lo, abs=1e-4) and mm[1] == pytest.approx(hi, abs=1e-4)
