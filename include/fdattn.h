@@ -146,13 +146,12 @@ fd_status fd_workspace_init(const fd_shape *shape, fd_workspace ws, void *stream
  *      run in fixed order -- forms the row: unflagged rows by the plain outer
  *      sums of Eq. 4, flagged rows by the synchronized update of Eq. 2 over all
  *      partial results, each rescaled from its own reference (phi, or the chunk
- *      maximum) to the row maximum of those references.  For grids of more than
- *      1024 workgroups, or of more than 256 workgroups over 320 MiB or more of cache
- *      (fd_decode_attn_gqa: more than 256 workgroups, or more than 16 chunks per row)
- *      step 3 runs as a second, tiny
- *      launch instead (one workgroup per row, no counters): large grids are
- *      throughput-bound and the election's two memory round trips per workgroup
- *      cost more than a launch.
+ *      maximum) to the row maximum of those references.  Large
+ *      launches run step 3 as a second, tiny launch instead (no counters) where the
+ *      election's two memory round trips per workgroup cost more than that: chunks of
+ *      more than 256 keys in more than 1024 workgroups, or rows of more than 128 chunks
+ *      (fd_decode_attn_gqa: more than 16 chunks per row, or more than 256 workgroups, 768
+ *      for rows of up to 8 chunks).
  * A flagged row is thus produced by the synchronized scheme, but only the
  * partial vectors that left the bounds are re-read; the others already are
  * valid partial-softmax results relative to phi.  fd_decode_attn_multikernel
