@@ -202,18 +202,16 @@ class Runner:
         self.gqa = gqa
         nc = -(-wl.Smax // chunk)
         wgs = wl.B * (wl.Hkv if gqa else wl.Hq) * nc
-        # the library's own rule: the grouped kernel finishes its rows itself up to 256 workgroups and 16 chunks
-        # per row, the per-row kernel up to 1024 workgroups unless the launch is long (more than 256 workgroups over
-        # 320 MiB or more of cache); beyond, the row epilogue is a launch of its own
+        # the library's own rule (elect_per_row, elect_grouped): which launches finish their rows themselves; the others leave
+        # the row epilogue to a launch of its own
         fused = entry in ("fd_decode_attn", "fd_decode_attn_gqa", "fd_decode_attn_static")
-        cache_bytes = wl.B * wl.Hkv * wl.Smax * wl.D * 2 * 2
-        self.single_launch = fused and ((wgs <= 256 and nc <= 16) if gqa else
-                                        (wgs <= 1024 and (wgs <= 256 or cache_bytes < (320 << 20))))
+        self.single_launch = fused and (((wgs <= 256 and nc <= 16) or (wgs <= 768 and nc <= 8)) if gqa else
+                                        (nc <= 128 and (chunk <= 256 or wgs <= 1024)))
         self.launches = 1 if self.single_launch else (3 if entry == "fd_decode_attn_multikernel" else 2)
         self.grid = (wl.B * wl.Hkv * nc) if gqa else 8 * ((wl.B * wl.Hq + 7) // 8) * nc
 
     def kernel_name(self):
-        """Template arguments as the profiler prints them: <chunk capacity, paged, wavefronts> for the grouped
+        """Template arguments: <chunk capacity, paged, wavefronts> for the grouped (the profiler also prints its start variant)
         kernel, <chunk capacity, in-kernel hand-over, paged, early loads> for the per-row one."""
         cap = 64
         while cap < self.chunk:
