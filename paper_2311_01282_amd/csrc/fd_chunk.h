@@ -144,6 +144,9 @@ __device__ __forceinline__ void wait_stores_performed()
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+// Wait until this wavefront's earlier vector loads have arrived (and nothing else: vmcnt(0) alone).
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+
 __device__ __forceinline__ uint16_t to_half_bits(float x)
 {
     return __builtin_bit_cast(uint16_t, (_Float16)x);   // round to nearest even
@@ -267,7 +270,9 @@ template <bool PAGED> struct KvRows {
 // length is replaced by zeros before use.  Takes the length load off the critical
 // path of a short launch; a padding chunk then reads one block for nothing, so
 // large ragged launches leave it off.
-template <int C, int NW, int UP, bool SYNC, int XN, bool EARLY = false, bool PAGED = false>
+// ONE (unified scheme only): a wavefront asks for a block of keys only when the one before has arrived, instead of
+// keeping two in flight (LoadAhead in fd_row_kernels.hip says where).
+template <int C, int NW, int UP, bool SYNC, int XN, bool EARLY = false, bool PAGED = false, bool ONE = false>
 __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, ChunkLds<NW, XN> &lds, int *len_out = nullptr,
                                            int sync_flag = 1)
 {
@@ -418,8 +423,10 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
             issue(0, kA, vA);
 #pragma unroll 1
             for (; blk + 2 < nblk; blk += 2) {
+                if constexpr (ONE) wait_loads();
                 issue(blk + 1, kB, vB);
                 reduce(blk, kA, vA);
+                if constexpr (ONE) wait_loads();
                 issue(blk + 2, kA, vA);
                 reduce(blk + 1, kB, vB);
             }

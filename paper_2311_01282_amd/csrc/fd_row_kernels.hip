@@ -33,7 +33,8 @@ template <int C> struct Tune {
 //        start behind somebody else's stream anyway, and where the launch covers more than the
 //        sequences hold (max_seq beyond the lengths) many of them are chunks without keys,
 //        which then leave without reading any.
-template <int C, bool ELECT, bool PAGED = false, bool EARLY = false>
+// ONE: one block of keys in flight per wavefront, not two (LoadAhead).
+template <int C, bool ELECT, bool PAGED = false, bool EARLY = false, bool ONE = false>
 __global__ __launch_bounds__(Tune<C>::NW * 64) void decode_fused_kernel(const Problem p)
 {
     static_assert(!EARLY || (ELECT && !PAGED), "early loads: in-kernel hand-over, contiguous cache");
@@ -64,7 +65,7 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void decode_fused_kernel(const Pr
     if (row >= p.rows) return;
     FD_PHASE(0);
     int S;
-    const bool flagged = chunk_body<C, NW, UP, false, C, EARLY, PAGED>(p, row, c, lds, &S);
+    const bool flagged = chunk_body<C, NW, UP, false, C, EARLY, PAGED, ONE>(p, row, c, lds, &S);
     FD_PHASE(3);
     const int nb = (S + p.C - 1) / p.C;        // chunks of this row that hold a valid key
     if (c >= nb) {                             // padding chunk: zero partials were written
@@ -98,8 +99,9 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void decode_fused_kernel(const Pr
 // First launch of the literal chain: Eq. 4 inner sums and the range guard, nothing else (no
 // recomputation, no hand-over).  Same workgroup shape, workgroup order and early loads as the
 // fused kernel: SMALL = a launch of at most 1024 workgroups (kernel arguments fetched in one batch),
-// EARLY = of at most 256 (chunk-major order, first loads before the sequence length has arrived).
-template <int C, bool SMALL, bool EARLY>
+// EARLY = of at most 256 (chunk-major order, first loads before the sequence length has arrived).  ONE: see
+// LoadAhead.
+template <int C, bool SMALL, bool EARLY, bool ONE = false>
 __global__ __launch_bounds__(Tune<C>::NW * 64) void partial_unified_kernel(const Problem p)
 {
     static_assert(!EARLY || SMALL, "early loads belong to the small launches");
@@ -111,7 +113,7 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void partial_unified_kernel(const
     const int c = EARLY ? j / groups8 : j % p.nc;              // the fused kernel's orders
     const int row = row_slot(p, blockIdx.x & 7, c) + 8 * (EARLY ? j - c * groups8 : j / p.nc);
     if (row >= p.rows) return;
-    chunk_body<C, NW, UP, false, 1, EARLY, false>(p, row, c, lds);
+    chunk_body<C, NW, UP, false, 1, EARLY, false, ONE>(p, row, c, lds);
 }
 
 // Second launch of the literal chain, over (row, chunk) items: every item first forms its row's
@@ -213,6 +215,18 @@ hipError_t dispatch_chunk(int C, Args... args)
     }
 }
 
+// Whether a wavefront asks for a block of keys only when the one before has arrived (chunk_body's ONE), instead of keeping two in
+// flight.  Where the chunks are turned (more than 32 per row, see `rot` there) what bounds rows of a power-of-two stride is the memory
+// channels that the workgroups in flight share, and more requests at a time make it worse; rows of other strides do not mind.  Whole
+// call, two blocks / one, chunks of 1024 keys: 16 rows x 65536 keys 98.1 / 92.1 us, 2 x 8 x 20000 .. 65536 91.2 / 84.6, 8 x 131072 102.6 /
+// 94.6, 32 x 131072 396 / 362, 16 x 66560 107.3 / 101.4, 16 x 60000 80.4 / 80.2; of 512 16 x 65536 94.3 / 93.8; of 256 1 x 32 x 16384
+// 49.1 / 49.0.  Chunks of 2048 keys gain nothing (32 x 131072 314.7 / 316.4); rows of up to 32 chunks lose (3 x 32 x 1500 in 5 15.0 / 15.35,
+// 1 x 40 x 60000 in 30 of 2000 keys 198.0 / 202.1).  Shorter chunks have no third block; pages are not a power of two apart.
+template <int C> struct LoadAhead {
+    static constexpr bool kOneBuilt = C >= 256 && C <= 1024;
+    static bool one(const Problem &p) { return kOneBuilt && p.nc > 32; }
+};
+
 template <int C> struct FusedLauncher {
     static hipError_t run(const Problem &p0, hipStream_t s)
     {
@@ -228,6 +242,11 @@ template <int C> struct FusedLauncher {
                            : launch(decode_fused_kernel<C, false, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p);
         if (p.elect && grid <= (unsigned)kComputeUnits)
             return launch(decode_fused_kernel<C, true, false, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p);
+        if constexpr (LoadAhead<C>::kOneBuilt) {
+            if (LoadAhead<C>::one(p))
+                return p.elect ? launch(decode_fused_kernel<C, true, false, false, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p)
+                               : launch(decode_fused_kernel<C, false, false, false, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p);
+        }
         return p.elect ? launch(decode_fused_kernel<C, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p)
                        : launch(decode_fused_kernel<C, false>, dim3(grid), dim3(Tune<C>::NW * 64), s, p);
     }
@@ -242,6 +261,11 @@ template <int C> struct UnifiedLauncher {
         p.scatter |= grid > 1024u;                 // no hand-over in this launch; measured on large grids only
         const dim3 block(Tune<C>::NW * 64);
         if (grid <= (unsigned)kComputeUnits) return launch(partial_unified_kernel<C, true, true>, dim3(grid), block, s, p);
+        if constexpr (LoadAhead<C>::kOneBuilt) {
+            if (LoadAhead<C>::one(p))
+                return grid <= 1024u ? launch(partial_unified_kernel<C, true, false, true>, dim3(grid), block, s, p)
+                                     : launch(partial_unified_kernel<C, false, false, true>, dim3(grid), block, s, p);
+        }
         if (grid <= 1024u) return launch(partial_unified_kernel<C, true, false>, dim3(grid), block, s, p);
         return launch(partial_unified_kernel<C, false, false>, dim3(grid), block, s, p);
     }
