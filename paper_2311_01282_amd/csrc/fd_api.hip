@@ -153,22 +153,34 @@ fd_status set_guard(fd::Problem *p, float phi, fd_bounds b)
 
 // Whether the chunk kernel should finish the rows itself (one launch) or leave that
 // to a second, tiny launch.  Electing a finisher costs every workgroup two memory
-// round trips at its end (results performed, arrival counter); a second launch costs
-// about 4 us once.
+// round trips at its end (results performed, arrival counter), a third one per eight workgroups where a row has more
+// than eight chunks; a second launch costs about 4 us once.
 //
-// The per-row kernel: one wavefront of a workgroup makes those round trips, the others have left.  In a workgroup of four
-// wavefronts (chunks of up to 256 keys) the next workgroup starts meanwhile and one launch wins at any size; in one of
-// eight it does not, and beyond 1024 workgroups the second launch wins.  Whole call, two launches / one, same box:
-// chunks of 128 keys 32 x 32 rows x 512 keys 47.8 / 46.1 us, 20 x 32 x 1000 59.5 / 57.0, 24 x 40 x 100 .. 700 40.2 / 37.2; of 256 keys
-// 16 x 16 x 300 .. 2000 31.8 / 29.8, 12 x 40 x 700 .. 1500 52.4 / 50.5, 32 x 32 x 1500 126.6 / 126.3, 16 x 16 x 4096 87.2 / 87.5;
-// of 512 and more, up to 1024 workgroups 4 x 32 x 8192 84.4 / 83.9, 1 x 32 x 32768 83.9 / 82.9 (holding 8192 keys 45.9 /
-// 43.4), 1 x 16 x 60000 82.2 / 79.5, beyond 6 x 32 x 8192 (1536) 123.9 / 124.8, 8 x 32 x 4096 (2048) 84.5 / 88.9, 16 x 32 x
-// 512 .. 4096 (4096) 105.4 / 106.9.  A row of more than 128 chunks is left to the second launch, which adds eight of them at a time
-// where the elected wavefront needs a round trip per 32.
+// The per-row kernel: one wavefront of a workgroup makes those round trips, the others have left.
+//   Up to 1024 workgroups one launch wins, short of the long launches.  Whole call, two launches / one, same box: 4 x 32 rows x 700 keys 11.8 / 10.2
+// us, 3 x 32 x 1500 16.2 / 14.95, 2 x 40 x 3000 23.65 / 22.3, 8 x 16 x 750 .. 6000 (768 workgroups, 375 MiB) 54.4 / 53.6, 1 x 32 x 32768 in
+// 16 chunks 82.9 / 83.1 (holding 8192 keys 45.9 / 43.4), 3 x 32 x 8192 62.7 / 62.5.  Rows of 33 .. 128 chunks are no exception: the row's
+// wavefront needs a round trip per 32, the second launch adds eight at a time: 1 x 8 x 60000 in 59 42.7 / 40.9, 1 x 8 x 131072 in 64 85.1 / 83.8, 1 x 4
+// x 4096 in 64 8.8 / 8.35.  Beyond 128 chunks they tie (1 row of 256 chunks 16.2 / 16.0 and 31.8 / 34.4) or the second launch wins (469: 26.4 / 29.8).
+// (Fewer than eight rows are another matter: handed over inside they keep to as many XCDs, row_slot, where the second launch's rows go to all
+// eight: 4 x 16384 14.6 / 13.3 us, 4 x 131072 72.8 / 52.0, one launch / two.  That is the placement's cost, not the hand-over's.)
+//   In a long launch -- more than three workgroups per compute unit over 320 MiB or more of cache -- a workgroup of eight wavefronts
+// that waits is not covered by another, and the second launch wins for rows of more than eight chunks: 4 x 8 x 32768 in 32 82.5 / 84.3, 4 x 8 x
+// 6000 .. 30000 in 30 66.4 / 67.3, 1 x 32 x 65536 in 32 159.3 / 162.1, 2 x 32 x 16384 in 16 82.25 / 84.2, 16 x 65536 in 64 88.9 / 92.1; about even 2 x 8 x
+// 60000 in 59 81.3 / 81.9, 6 x 8 x 20000 in 20 79.7 / 78.8, 3 x 16 x 20000 in 20 77.6 / 78.85 and 79.65 / 78.8; of eight 4 x 32 x 8192 84.5 / 84.0.
+//   Beyond 1024 workgroups eight wavefronts always leave it to the second launch: 6 x 32 x 8192 (1536) 123.9 / 124.8, 8 x 32 x 4096 (2048) 84.5 /
+// 88.9, 16 x 32 x 512 .. 4096 (4096) 105.4 / 106.9.  Behind one of four (chunks of up to 256 keys) the next workgroup starts meanwhile, and rows of up to
+// eight chunks are finished in the launch: chunks of 128 keys 32 x 32 x 512 46.0 / 45.9, 20 x 32 x 1000 59.5 / 57.0, 24 x 16 x 90 .. 700 21.4 / 19.9, 32 x 40
+// x 112 .. 900 69.2 / 68.3; of 256 12 x 40 x 187 .. 1500 48.1 / 46.8, 32 x 32 x 2000 167.1 / 167.8 (250 .. 2000 107.5 / 107.7), 32 x 32 x 1500 125.4 / 127.7
+// (187 .. 1500 88.1 / 87.3); not of more: 8 x 16 x 8192 in 32 85.2 / 87.7, 8 x 32 x 4096 in 64 90.2 / 94.4 (512 .. 4096 64.0 / 68.4), 8 x 32 x 2048 in 16 45.6 /
+// 47.0, 32 x 16 x 3000 in 12 123.8 / 126.7.  Chunks of less than 128 keys are too short to cover it in large numbers: of 64 16 x 32 x 300 (2560
+// workgroups) 17.1 / 16.8, 37 .. 300 13.6 / 12.9, but 32 x 32 x 200 (4096) 21.9 / 22.9, 20 x 40 x 62 .. 500 (6400) 26.9 / 27.7.
 inline int elect_per_row(const fd::Problem &p)
 {
     const long long workgroups = (long long)p.rows * p.nc;
-    return p.nc <= 128 && (p.C <= 256 || workgroups <= 1024);
+    if (p.nc > 128) return 0;
+    if (workgroups <= 3 * fd::kComputeUnits || (workgroups <= 1024 && fd::cache_bytes(p) < fd::kLongLaunchBytes)) return 1;
+    return p.nc <= 8 && (workgroups <= (p.C >= 128 ? 1024 : 3072) || (p.C >= 128 && p.C <= 256));
 }
 
 // The grouped kernel: its elected workgroup finishes the G rows of its head group by itself, up to 16 chunks of

@@ -85,6 +85,10 @@ __device__ __forceinline__ int row_slot(const Problem &p, int slot, int c)
     return p.scatter ? (slot - c) & 7 : slot;
 }
 
+// Bytes of K and V, full length; from kLongLaunchBytes on a launch of more than one round of the chip is a long one.
+constexpr long long kLongLaunchBytes = 320ll << 20;
+inline long long cache_bytes(const Problem &p) { return (long long)p.B * p.Hkv * p.Smax * kHeadDim * 2 * 2; }
+
 // Number of keys resident in the cache: the clamped entry of seq_lens.
 __device__ __forceinline__ int clamp_len(const Problem &p, int raw)
 {

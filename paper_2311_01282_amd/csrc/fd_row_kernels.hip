@@ -235,8 +235,7 @@ template <int C> struct FusedLauncher {
         Problem p = p0;
         // Every XCD reads from every row where the launch is long: more than 1024 workgroups, or more than one round of the
         // chip over 320 MiB of cache (see row_slot); the results cross between XCDs as well as within one.
-        const long long cache_bytes = (long long)p.B * p.Hkv * p.Smax * kHeadDim * 4;
-        p.scatter |= !p.elect || grid > 1024u || (grid > (unsigned)kComputeUnits && cache_bytes >= (320ll << 20));
+        p.scatter |= !p.elect || grid > 1024u || (grid > (unsigned)kComputeUnits && cache_bytes(p) >= kLongLaunchBytes);
         if (p.block_table)
             return p.elect ? launch(decode_fused_kernel<C, true, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p)
                            : launch(decode_fused_kernel<C, false, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p);

@@ -1,6 +1,8 @@
 """Test-side plumbing: puts a seeded problem on the GPU and calls libfdattn
 through its ctypes binding.  torch is used for device memory and the stream
 only; no attention arithmetic happens here."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -99,3 +101,23 @@ def assert_close(got, want, what="", rel_floor=REL_FLOOR):
     assert a <= ABS_TOL and r <= REL_TOL, "%s: max-abs %.3e (tol %.0e), max-rel %.3e (tol %.0e)" % (
         what, a, ABS_TOL, r, REL_TOL)
     return a, r
+
+
+def kernels_of(call, device="cuda:0"):
+    """Number of kernels that ``call(stream)`` enqueues, counted in a stream capture (nothing runs): which of its launch forms an entry
+    point takes for a shape."""
+    hip = fdattn._lib                              # (its dependencies' symbols with it: the runtime the library launches through)
+    side = torch.cuda.Stream(torch.device(device))
+    stream, graph, n = ctypes.c_void_p(side.cuda_stream), ctypes.c_void_p(), ctypes.c_size_t()
+    torch.cuda.synchronize(device)
+    assert hip.hipStreamBeginCapture(stream, 2) == 0          # hipStreamCaptureModeRelaxed
+    try:
+        call(side.cuda_stream)
+    finally:
+        status = hip.hipStreamEndCapture(stream, ctypes.byref(graph))
+    assert status == 0 and graph.value
+    try:
+        assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    finally:
+        assert hip.hipGraphDestroy(graph) == 0
+    return n.value
