@@ -670,83 +670,63 @@ __device__ __forceinline__ void row_epilogue(const Problem &p, int row, int n_lo
     if (tid == 0) p.ws.row_flags[row] = rf ? 1 : 0;
 }
 
-// The row epilogue for the G <= 16 rows of one head group at once, by 256 threads or more:
-// thread (h, t) = (tid / 32, tid % 32) owns elements 2t, 2t + 1, 64 + 2t and 65 + 2t of row row0 + h (so that a load takes
+// The row epilogue for the G <= 16 rows of one head group at once, nb <= 16 chunks each (elect_grouped sees to it), by 256
+// threads: thread (h, t) = (tid / 32, tid % 32) owns elements 2t, 2t + 1, 64 + 2t and 65 + 2t of row row0 + h (so that a load takes
 // whole lines: with 4t .. 4t + 3, two loads of half of every line, the 64 KB of eight rows of 16 chunks took 1.8 us, now 1.6; what one
 // compute unit draws past the caches is the bound) and adds
 // that row's nb partial results in chunk order, each scaled from its own reference to the maximum of the
 // references (Eq. 2; every factor is exactly 1 for an unflagged row, which makes it
-// the plain sum of Eq. 4).  No LDS and no barrier.  A row of up to 16 chunks takes one memory round trip: threads t and 16 + t
+// the plain sum of Eq. 4).  No LDS and no barrier, one memory round trip: threads t and 16 + t
 // fetch the slot record of chunk t, and all numerators are on their way before the first record is looked at; maximum
 // and factors then go round each group of 16 lanes by DPP row operations (through LDS exchanges, five dependent ones for the maximum,
 // 0.3 us more).  (Walking records and numerators together, four
 // chunks at a time, was one round trip per eight chunks and two loads per chunk and thread: whole call, that form / this,
 // 4 x 32/8 heads x 4096 keys 16.2 / 15.4 us, 1 x 32 heads x 1024 keys 7.5 / 7.0.)  Loads pass the caches
 // (the partial results come from other workgroups of the same launch).
-// COHERENT = false and a per-row chunk count serve a launch of its own over arbitrary rows.
-// n_load: slots that hold defined values whatever the row's length (a launch of its own: all nc of them), so that the first
-// loads need not wait for the length; 0: the nb slots themselves.
-// FLAGS: whether the row flags are written (the synchronized scheme has none).
-template <bool COHERENT = true, bool FLAGS = true, typename NbFn>
-__device__ __forceinline__ void rows_epilogue(const Problem &p, int row0, int G, int n_load, NbFn nb_of)
+__device__ __forceinline__ void group_epilogue(const Problem &p, int row0, int G, int nb)
 {
     const int tid = threadIdx.x, t4 = tid & 31;
-    auto ld8 = [](const void *ptr) {
-        if constexpr (COHERENT) return load_coherent(static_cast<const unsigned long long *>(ptr));
-        else return *static_cast<const unsigned long long *>(ptr);
-    };
     auto two = [](unsigned long long a, unsigned long long b) {
         return u32x4{(unsigned)a, (unsigned)(a >> 32), (unsigned)b, (unsigned)(b >> 32)};
     };
     for (int h = tid >> 5; h < G; h += (int)(blockDim.x >> 5)) {
         const int row = row0 + h;
-        int nb = n_load ? 0 : nb_of(row);
-        const int loads = n_load ? n_load : nb;
         const size_t r0 = (size_t)row * p.nc;
         const float *num = p.ws.num + r0 * kHeadDim + 2 * t4;
         const SlotMeta *meta = p.ws.meta + r0;
-        const int cap = max(loads - 1, 0);
-        float m = -INFINITY, l = 0.f;
+        float l = 0.f;
         float s[4] = {0.f, 0.f, 0.f, 0.f};
         int f = 0;
-        // chunks c0 .. c0 + N - 1 of the row (N <= 16): their numerators in flight together, lane j of the row's two groups
-        // of 16 holds the record of chunk c0 + j
-        auto block = [&](int c0, auto n) {
+        // a row of up to N <= 16 chunks: its numerators in flight together, lane j of the row's two groups of 16 holds the
+        // record of chunk j
+        auto block = [&](auto n) {
             constexpr int N = decltype(n)::value;
-            const unsigned long long *w = reinterpret_cast<const unsigned long long *>(meta + min(c0 + (t4 & 15), cap));
-            const u32x4 mv = two(ld8(&w[0]), ld8(&w[1]));
+            const unsigned long long *w = reinterpret_cast<const unsigned long long *>(meta + min(t4 & 15, nb - 1));
+            const u32x4 mv = two(load_coherent(&w[0]), load_coherent(&w[1]));
             u32x4 nv[N];
 #pragma unroll
             for (int i = 0; i < N; ++i) {
-                const float *at = num + (size_t)min(c0 + i, cap) * kHeadDim;
-                nv[i] = two(ld8(at), ld8(at + 64));
+                const unsigned long long *at = reinterpret_cast<const unsigned long long *>(num + (size_t)min(i, nb - 1) * kHeadDim);
+                nv[i] = two(load_coherent(at), load_coherent(at + 32));
             }
-            if (c0 == 0 && n_load) nb = nb_of(row);          // a load of its own, in flight with the others
-            const bool in_row = (t4 & 15) < min(N, nb - c0);
+            const bool in_row = (t4 & 15) < nb;
             const float ref = in_row ? as_f32(mv[1]) : -INFINITY;
-            f |= in_row ? (int)mv[2] : 0;
-            // Where all references agree, in both rows of the wavefront -- no recomputed chunk -- every factor is 1.
-            const float ref0 = row16_lane<0>(ref);           // of a chunk of the row: c0 < nb, or nothing is
-            if (__ballot((in_row & (ref != ref0)) | (c0 > 0 && m != ref0)) == 0ull) {
-                m = ref0;
-                l += row16_sum(in_row ? as_f32(mv[0]) : 0.f);
+            f = in_row ? (int)mv[2] : 0;
+            // Where all references agree, in both rows of the wavefront -- no recomputed chunk -- every factor is 1.  (This is in
+            // line, as the larger blocks are: a launch runs this part once, and jumps to code not fetched before cost 0.2 us at 8 chunks.)
+            const float ref0 = row16_lane<0>(ref);
+            if (__builtin_expect(__ballot(in_row & (ref != ref0)) == 0ull, 1)) {
+                l = row16_sum(in_row ? as_f32(mv[0]) : 0.f);
 #pragma unroll
                 for (int i = 0; i < N; ++i) {
-                    const unsigned keep = c0 + i < nb ? ~0u : 0u;
+                    const unsigned keep = i < nb ? ~0u : 0u;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) s[e] += as_f32(nv[i][e] & keep);
                 }
                 return;
             }
-            const float bm = row16_max(ref);
-            if (bm > m) {                                    // rescale what was summed so far (never for unflagged rows)
-                const float a = __builtin_amdgcn_exp2f((m - bm) * kLog2e);   // 0 on the first block
-#pragma unroll
-                for (int e = 0; e < 4; ++e) s[e] *= a;
-                l *= a;
-                m = bm;
-            }
-            // exactly 1 when ref == m; 0 for slots outside the row (their sums are finite)
+            // exactly 1 where the reference is the maximum; 0 for slots outside the row (their sums are finite)
+            const float m = row16_max(ref);
             const float a = ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ref - m) * kLog2e);
             const float ad = a * (in_row ? as_f32(mv[0]) : 0.f);
             each16(std::make_integer_sequence<int, N>{}, [&](auto lane_of) {
@@ -757,27 +737,16 @@ __device__ __forceinline__ void rows_epilogue(const Problem &p, int row0, int G,
                 for (int e = 0; e < 4; ++e) s[e] = __builtin_fmaf(ac, as_f32(nv[i][e]), s[e]);
             });
         };
-        if (loads <= 4) block(0, std::integral_constant<int, 4>{});
-        else if (loads <= 8) block(0, std::integral_constant<int, 8>{});
-        else
-            // (nb is known behind the first block: a row that holds little of a long cache leaves there)
-            for (int c0 = 0; c0 == 0 || c0 < nb; c0 += 16) block(c0, std::integral_constant<int, 16>{});
+        if (nb > 8) block(std::integral_constant<int, 16>{});
+        else if (nb > 4) block(std::integral_constant<int, 8>{});
+        else block(std::integral_constant<int, 4>{});
         FD_PHASE(6);
         const unsigned any = (unsigned)(__ballot(f != 0) >> (tid & 32));   // of this row's 32 lanes
-        unsigned o[2] = {0u, 0u};                            // an empty sequence: zeros, no flag
-        if (nb > 0) {
-            o[0] = (unsigned)to_half_bits(s[0] / l) | ((unsigned)to_half_bits(s[1] / l) << 16);
-            o[1] = (unsigned)to_half_bits(s[2] / l) | ((unsigned)to_half_bits(s[3] / l) << 16);
-        }
         unsigned *out = reinterpret_cast<unsigned *>(p.out + (size_t)row * kHeadDim + 2 * t4);
-        out[0] = o[0];
-        out[32] = o[1];
-        if (FLAGS && t4 == 0) p.ws.row_flags[row] = any ? 1 : 0;
+        out[0] = (unsigned)to_half_bits(s[0] / l) | ((unsigned)to_half_bits(s[1] / l) << 16);
+        out[32] = (unsigned)to_half_bits(s[2] / l) | ((unsigned)to_half_bits(s[3] / l) << 16);
+        if (t4 == 0) p.ws.row_flags[row] = any ? 1 : 0;
     }
-}
-__device__ __forceinline__ void group_epilogue(const Problem &p, int row0, int G, int nb)
-{
-    rows_epilogue<true>(p, row0, G, 0, [nb](int) { return nb; });
 }
 
 // Elects the workgroup that completes a row: a radix-8 tree of arrival counters

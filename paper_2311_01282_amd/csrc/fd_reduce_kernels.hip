@@ -77,12 +77,54 @@ __global__ __launch_bounds__(1024) void flag_reduce_kernel(const Problem p)
     if (tid == 0) *p.ws.count = base_s;
 }
 
-// The same over rows of more than 32 chunks: two rows per workgroup, 32 threads each, a round trip per 16 chunks, no further than
-// the row's last (1 x 32 rows of 2000 keys in a cache of 512 chunks 26.2 us, 45.1 if every chunk is walked).
+// The merge of the synchronized scheme (Eq. 2) over rows of more than 32 chunks: two rows per workgroup, 32 threads each that own four
+// elements; 16 chunks to a memory round trip, lane j of the row's two groups of 16 holding the record of chunk c0 + j, no further than the
+// row's last chunk (1 x 32 rows of 2000 keys in a cache of 512 chunks 26.2 us, 45.1 if every chunk is walked).  Every slot holds defined
+// values, so the first loads need not wait for the length.
 __global__ __launch_bounds__(64) void combine_sync_kernel(const Problem p)
 {
-    const int row0 = blockIdx.x * 2;
-    rows_epilogue<false, false>(p, row0, min(2, p.rows - row0), p.nc, [&](int row) { return (valid_len(p, row / p.Hq) + p.C - 1) / p.C; });
+    const int t4 = threadIdx.x & 31;
+    const int row = blockIdx.x * 2 + (threadIdx.x >> 5);
+    if (row >= p.rows) return;
+    const size_t r0 = (size_t)row * p.nc;
+    const u32x4 *num = reinterpret_cast<const u32x4 *>(p.ws.num + r0 * kHeadDim) + t4;
+    const u32x4 *meta = reinterpret_cast<const u32x4 *>(p.ws.meta + r0);
+    float m = -INFINITY, l = 0.f;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    int nb = 0;
+    for (int c0 = 0; c0 == 0 || c0 < nb; c0 += 16) {
+        const u32x4 mv = meta[min(c0 + (t4 & 15), p.nc - 1)];
+        u32x4 nv[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) nv[i] = num[(size_t)min(c0 + i, p.nc - 1) * (kHeadDim / 4)];
+        if (c0 == 0) nb = (valid_len(p, row / p.Hq) + p.C - 1) / p.C;        // a load of its own, in flight with the others
+        const bool in_row = (t4 & 15) < min(16, nb - c0);
+        const float ref = in_row ? as_f32(mv[1]) : -INFINITY;
+        const float bm = row16_max(ref);
+        if (bm > m) {                                        // rescale what was summed so far
+            const float a = __builtin_amdgcn_exp2f((m - bm) * kLog2e);       // 0 on the first block
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] *= a;
+            l *= a;
+            m = bm;
+        }
+        // exactly 1 when ref == m; 0 for slots outside the row (their sums are finite)
+        const float a = ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ref - m) * kLog2e);
+        const float ad = a * (in_row ? as_f32(mv[0]) : 0.f);
+        each16(std::make_integer_sequence<int, 16>{}, [&](auto lane_of) {
+            constexpr int i = decltype(lane_of)::value;
+            const float ac = row16_lane<i>(a);
+            l += row16_lane<i>(ad);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] = __builtin_fmaf(ac, as_f32(nv[i][e]), s[e]);
+        });
+    }
+    uint2 o = make_uint2(0u, 0u);                            // an empty sequence: zeros
+    if (nb > 0) {
+        o.x = (unsigned)to_half_bits(s[0] / l) | ((unsigned)to_half_bits(s[1] / l) << 16);
+        o.y = (unsigned)to_half_bits(s[2] / l) | ((unsigned)to_half_bits(s[3] / l) << 16);
+    }
+    *reinterpret_cast<uint2 *>(p.out + (size_t)row * kHeadDim + 4 * t4) = o;
 }
 
 // Third launch of the literal chain.  Blocks 0 .. gridDim.x - 2 stride over the rows and finish the
