@@ -63,25 +63,22 @@ __global__ __launch_bounds__(kStatsWaves * 64) void logit_histogram_kernel(
 
     const int runs = (p.Smax + run - 1) / run;
     const int hblocks = (p.G + 15) / 16;
-    const long long items = (long long)p.B * p.Hkv * hblocks * runs;
+    const unsigned items = (unsigned)(p.B * p.Hkv * hblocks) * (unsigned)runs;   // < 2^31: at most rows * ceil(Smax / 64)
+    const unsigned stride = (unsigned)waves * gridDim.x;
     float lo = INFINITY, hi = -INFINITY;
-    // consecutive items to consecutive workgroups: the runs of a KV head spread over the chip.  Each (sequence, KV head) starts at a
-    // place of its own, the next for every round of the workgroups: where the number of runs divides that of the workgroups, all runs
-    // of a workgroup would otherwise lie at the same place of their sequences, and ragged lengths would load the compute units
-    // unevenly (32 sequences of 2048 .. 4096 keys: 3085 on average and 4096 on the fullest; 42.3 us, now 39.0).
-    for (long long it = (long long)wave * gridDim.x + blockIdx.x; it < items; it += (long long)waves * gridDim.x) {
-        long long r;
-        int t;
-        if (items >> 31) {
-            r = it / runs;
-            t = (int)((it + r * runs / gridDim.x) % runs);
-        } else {                                         // (a 64-bit division costs 0.1 us)
-            const unsigned i = (unsigned)it, q = i / (unsigned)runs;
-            r = q;
-            t = (int)((i + q * (unsigned)runs / gridDim.x) % (unsigned)runs);
-        }
-        const int hb = (int)(r % hblocks);
-        const int gi = (int)(r / hblocks);               // (sequence, KV head)
+    // Consecutive items to consecutive workgroups: the runs of a KV head spread over the chip.  Where they are many (runs of more than 64
+    // keys: two per wavefront or more), each (sequence, KV head) starts at a place of its own, the next for every round of the
+    // workgroups: where the number of runs divides that of the workgroups, all runs of a workgroup would otherwise lie at the same place
+    // of their sequences, and ragged lengths would load the compute units unevenly (32 sequences of 2048 .. 4096 keys: 3085 on
+    // average and 4096 on the fullest; 41.2 us, turned 37.2; 32 x 32 heads x 100 .. 1000 keys 34.6 / 29.1).  With hardly a run per wavefront there is
+    // little to even out, and it helps that the workgroups at the sequences' ends have nothing to add to memory: not turned / turned 32 x 64/8
+    // x 100 .. 1000 12.7 / 14.2, 32 x 64/8 x 200 .. 1500 17.1 / 18.0, 6 x 40 x 200 .. 1500 17.0 / 17.8, 16 x 16 x 1500 20.7 / 21.1.
+    const bool turned = run > 64;
+    for (unsigned it = (unsigned)wave * gridDim.x + blockIdx.x; it < items; it += stride) {
+        const unsigned r = it / (unsigned)runs;
+        const int t = (int)((turned ? it + r * (unsigned)runs / gridDim.x : it) % (unsigned)runs);
+        const int hb = (int)(r % (unsigned)hblocks);
+        const int gi = (int)(r / (unsigned)hblocks);     // (sequence, KV head)
         const int b = gi / p.Hkv, hkv = gi - b * p.Hkv;
         const int nvalid = min(run, valid_len(p, b) - t * run);
         if (nvalid <= 0) continue;

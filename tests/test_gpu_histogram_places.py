@@ -1,5 +1,6 @@
-"""The histogram kernel starts each (sequence, KV head) at a place of its own: every key is counted once, whether the number of
-runs divides the workgroups or not, with as many items as workgroups hold, fewer and more."""
+"""The histogram kernel starts each (sequence, KV head) at a place of its own, where the runs are longer than 64 keys, or at its first
+run: every key is counted once, whether the number of runs divides the workgroups or not, with as many items as workgroups hold,
+fewer and more."""
 import pytest
 
 from oracle import fd_calibration_oracle as cal
@@ -16,6 +17,9 @@ pytestmark = pytest.mark.gpu
     (2, 24, 2, 8192, [8192, 5000]),                       # 128 runs
     (2, 34, 2, 700, [700, 321]),                          # two blocks of heads on one KV head
     (16, 16, 16, 2500, [2500 - 150 * i for i in range(16)]),   # several rounds of the workgroups
+    (32, 16, 16, 1000, [1000 - 30 * i for i in range(32)]),    # 512 heads of 16 runs of 64 keys: two rounds, every head at its first run
+    (32, 32, 32, 1000, [1000 - 30 * i for i in range(32)]),    # 1024 heads: 8 runs of 128 keys, each head at a place of its own
+    (3, 64, 8, 20001, [20001, 2500, 64]),                      # more runs than workgroups
 ])
 def test_every_key_is_counted_once(B, Hq, Hkv, Smax, lens):
     case = synth.make_case(B=B, Hq=Hq, Hkv=Hkv, D=128, Smax=Smax, seq_lens=lens, seed=400 + Smax, poison_padding=True)
