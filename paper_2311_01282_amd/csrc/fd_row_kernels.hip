@@ -216,15 +216,23 @@ hipError_t dispatch_chunk(int C, Args... args)
 }
 
 // Whether a wavefront asks for a block of keys only when the one before has arrived (chunk_body's ONE), instead of keeping two in
-// flight.  Where the chunks are turned (more than 32 per row, see `rot` there) what bounds rows of a power-of-two stride is the memory
-// channels that the workgroups in flight share, and more requests at a time make it worse; rows of other strides do not mind.  Whole
-// call, two blocks / one, chunks of 1024 keys: 16 rows x 65536 keys 98.1 / 92.1 us, 2 x 8 x 20000 .. 65536 91.2 / 84.6, 8 x 131072 102.6 /
-// 94.6, 32 x 131072 396 / 362, 16 x 66560 107.3 / 101.4, 16 x 60000 80.4 / 80.2; of 512 16 x 65536 94.3 / 93.8; of 256 1 x 32 x 16384
-// 49.1 / 49.0.  Chunks of 2048 keys gain nothing (32 x 131072 314.7 / 316.4); rows of up to 32 chunks lose (3 x 32 x 1500 in 5 15.0 / 15.35,
-// 1 x 40 x 60000 in 30 of 2000 keys 198.0 / 202.1).  Shorter chunks have no third block; pages are not a power of two apart.
+// flight.  Whole call, two blocks / one.
+//   Where the chunks are turned (more than 32 per row, see `rot` there) what bounds rows of a power-of-two stride is the memory
+// channels that the workgroups in flight share, and more requests at a time make it worse; rows of other strides do not mind.  Chunks of
+// 1024 keys: 16 rows x 65536 keys 98.1 / 92.1 us, 2 x 8 x 20000 .. 65536 91.2 / 84.6, 8 x 131072 102.6 / 94.6, 32 x 131072 396 / 362, 16 x
+// 66560 107.3 / 101.4, 16 x 60000 80.4 / 80.2; of 512 16 x 65536 94.3 / 93.8; of 256 1 x 32 x 16384 49.1 / 49.0.
+//   A launch of more than three workgroups per compute unit that hands nothing over has other workgroups to cover the wait, and
+// wins or ties: 2 x 32 x 29393 in 29 157.6 / 153.5 us (14696 .. 29393 144.1 / 140.0), 4 x 16 x 30000 in 30 163.1 / 160.2, 3 x 32 x 14602
+// 116.0 / 114.3, 4 x 32 x 16000 .. 32768 279.1 / 276.2, 8 x 32 x 8192 162.9 / 163.3, 16 x 32 x 4096 164.0 / 163.8.
+//   Smaller launches of up to 32 chunks per row lose (3 x 32 x 1500 in 5 15.0 / 15.35, 3 x 32 x 4096 33.15 / 33.8), and so do chunks of
+// 2048 keys (1 x 40 x 60000 in 30 198.0 / 202.1, 32 x 131072 314.7 / 316.4).  Shorter chunks than 256 keys have no third block; pages
+// are not a power of two apart.
 template <int C> struct LoadAhead {
     static constexpr bool kOneBuilt = C >= 256 && C <= 1024;
-    static bool one(const Problem &p) { return kOneBuilt && p.nc > 32; }
+    static bool one(const Problem &p)
+    {
+        return kOneBuilt && (p.nc > 32 || (!p.elect && (long long)p.rows * p.nc > 3 * kComputeUnits));
+    }
 };
 
 template <int C> struct FusedLauncher {

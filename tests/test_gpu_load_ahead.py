@@ -1,5 +1,5 @@
-"""Rows of more than 32 chunks of 256 to 1024 keys, whose wavefronts ask for one block of keys at a time (elsewhere for two): lengths
-that leave the last chunk with one key, one to all blocks (of 64 or 128 keys), odd and even counts of them; the last chunk count
+"""Chunks of 256 to 1024 keys whose wavefronts ask for one block of keys at a time, in rows of more than 32 chunks and in launches of more
+than three workgroups per compute unit that leave the rows to a second one (elsewhere they ask for two): lengths that leave the last chunk with one key, one to all blocks (of 64 or 128 keys), odd and even counts of them; the last chunk count
 without the rule and the first with it; recomputed chunks; the fused call, its chunk kernel alone and the chain of launches."""
 import numpy as np
 import pytest
@@ -34,3 +34,20 @@ def test_one_block_at_a_time(oracle, H, chunk, nc, plant):
         H.assert_close(got, want, "%s, %d chunks of %d" % (entry, nc, chunk))
         cf, rf, n, _ = dc.flags()
         assert np.array_equal(cf, ocf) and np.array_equal(rf, orf) and n == int(orf.sum())
+
+
+@pytest.mark.parametrize("B,heads,chunk,nc", [(5, 31, 256, 9), (12, 8, 512, 11), (8, 14, 752, 9), (8, 15, 1024, 9)])
+def test_one_block_at_a_time_in_a_large_launch(oracle, H, B, heads, chunk, nc):
+    tails = [1, 65, 129, 193, 385, 513, 641, 897, chunk]
+    lens = [(nc - 1) * chunk + min(tails[i % len(tails)], chunk) - (chunk * (i // 5)) for i in range(B - 1)] + [0]
+    case = synth.make_case(B=B, Hq=heads, Hkv=heads, D=128, Smax=nc * chunk, seed=8700 + nc * chunk, seq_lens=lens, poison_padding=True)
+    want = oracle.attn_exact(case["q"], case["k"], case["v"], case["seq_lens"], case["scale"], nthreads=8)
+    dc = H.DeviceCase(case, chunk=chunk)
+    for entry in ("fd_decode_attn", "fd_decode_attn_multikernel"):
+        H.assert_close(dc.run(entry), want, "%s, %d x %d rows, %d chunks of %d" % (entry, B, heads, nc, chunk))
+    dc.out.fill_(float("nan"))
+    dc.run_partial()
+    num, den = dc.partials()
+    with np.errstate(invalid="ignore"):
+        got = np.where(den.sum(-1, keepdims=True) > 0, num.astype(np.float64).sum(2) / den.astype(np.float64).sum(-1, keepdims=True), 0.0)
+    H.assert_close(got, want, "the chunk kernel alone")
