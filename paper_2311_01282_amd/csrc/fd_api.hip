@@ -166,8 +166,10 @@ fd_status set_guard(fd::Problem *p, float phi, fd_bounds b)
 // eight: 4 x 16384 14.6 / 13.3 us, 4 x 131072 72.8 / 52.0, one launch / two.  That is the placement's cost, not the hand-over's.)
 //   In a long launch -- more than three workgroups per compute unit over 320 MiB or more of cache -- a workgroup of eight wavefronts
 // that waits is not covered by another, and the second launch wins for rows of more than eight chunks: 4 x 8 x 32768 in 32 82.5 / 84.3, 4 x 8 x
-// 6000 .. 30000 in 30 66.4 / 67.3, 1 x 32 x 65536 in 32 159.3 / 162.1, 2 x 32 x 16384 in 16 82.25 / 84.2, 16 x 65536 in 64 88.9 / 92.1; about even 2 x 8 x
-// 60000 in 59 81.3 / 81.9, 6 x 8 x 20000 in 20 79.7 / 78.8, 3 x 16 x 20000 in 20 77.6 / 78.85 and 79.65 / 78.8; of eight 4 x 32 x 8192 84.5 / 84.0.
+// 6000 .. 30000 in 30 66.4 / 67.3, 1 x 32 x 65536 in 32 159.3 / 162.1, 2 x 32 x 16384 in 16 82.25 / 84.2; about even 6 x 8 x 20000 in 20 79.7 /
+// 78.8, 3 x 16 x 20000 in 20 77.6 / 78.85 and 79.65 / 78.8; of eight 4 x 32 x 8192 84.5 / 84.0.  For rows of more than 32 chunks, which cost the
+// second launch more, that line is at 960 workgroups: 2 x 12 x 8000 .. 40000 in 40 (960) 74.4 / 73.1, 2 x 8 x 10000 .. 60000 in 59 (944) 77.8 / 77.4, 12 x
+// 65536 in 64 (768) 73.9 / 73.2, 16 x 65536 in 64 (1024) 88.9 / 92.1.
 //   Beyond 1024 workgroups eight wavefronts always leave it to the second launch: 6 x 32 x 8192 (1536) 123.9 / 124.8, 8 x 32 x 4096 (2048) 84.5 /
 // 88.9, 16 x 32 x 512 .. 4096 (4096) 105.4 / 106.9.  Behind one of four (chunks of up to 256 keys) the next workgroup starts meanwhile, and rows of up to
 // eight chunks are finished in the launch: chunks of 128 keys 32 x 32 x 512 46.0 / 45.9, 20 x 32 x 1000 59.5 / 57.0, 24 x 16 x 90 .. 700 21.4 / 19.9, 32 x 40
@@ -179,7 +181,7 @@ inline int elect_per_row(const fd::Problem &p)
 {
     const long long workgroups = (long long)p.rows * p.nc;
     if (p.nc > 128) return 0;
-    if (workgroups <= 3 * fd::kComputeUnits || (workgroups <= 1024 && fd::cache_bytes(p) < fd::kLongLaunchBytes)) return 1;
+    if (workgroups <= (p.nc <= 32 ? 768 : 960) || (workgroups <= 1024 && fd::cache_bytes(p) < fd::kLongLaunchBytes)) return 1;
     return p.nc <= 8 && (workgroups <= (p.C >= 128 ? 1024 : 3072) || (p.C >= 128 && p.C <= 256));
 }
 

@@ -28,6 +28,7 @@ def kernels(H, entry, B, Hq, Hkv, Smax, chunk):
     (1, 32, 1024, 128, 1), (1, 4, 64 * 128, 64, 1), (1, 4, 64 * 129, 64, 2),           # 128 chunks and one more
     (1, 32, 24 * 1024, 1024, 1), (1, 32, 25 * 1024, 1024, 2),                          # 320 MiB from 20480 keys; 768 workgroups and 800
     (2, 20, 20 * 512, 512, 1), (1, 64, 12 * 1024, 1024, 1), (1, 64, 13 * 1024, 1024, 2),
+    (2, 12, 40 * 1024, 1024, 1), (1, 29, 33 * 1008, 1008, 1), (1, 30, 33 * 1008, 1008, 2),   # more than 32 chunks: 960, 957, 990
     (4, 32, 8 * 1024, 1024, 1), (4, 28, 9 * 1024, 1024, 2),                            # eight chunks, nine (1008 workgroups)
     (1, 32, 32 * 512, 512, 1), (1, 33, 32 * 512, 512, 2), (8, 33, 4 * 512, 512, 2),    # 1024 workgroups of eight wavefronts, more
     (8, 32, 8 * 256, 256, 1), (8, 32, 9 * 256, 256, 2), (40, 40, 8 * 128, 128, 1),     # of four, beyond 1024
