@@ -79,8 +79,17 @@ __device__ __forceinline__ int lanes_scan(int x)
 // Order by length (launches of more than one workgroup per compute unit, at most 64 sequences; see GqaLauncher): the chunks
 // that are full first, then the sequences' last, partial chunks from the longest to the shortest, then the chunks without keys; each for
 // all KV heads.  Every workgroup of up to three rounds of the chip starts with the launch and a compute unit holds workgroups i, i + 256, ...,
-// so what it has to stream is decided here: the first 256 go in reverse, and the shortest of them share their compute
-// units with the longest of the rest.  `res`: resident keys of sequence `lane` (p.B <= 64).
+// so what it has to stream is decided here.
+//   Up to 256 full chunks: the first 256 go in reverse, and the shortest of them share their compute units with the longest of
+// the rest.
+//   More: some compute units take a full chunk more than others in any order, and as a compute unit draws 38 bytes a nanosecond at most they
+// end late while the rest has nothing left to do (first in reverse, 48 with two chunks beside 160 with one).  But fewer than all saturate
+// the memory: the live chunks are dealt to as many compute units as take the same number each, the others get what has no keys.  General
+// order / first in reverse / this: 8 x 64/8 heads x 2725 .. 21800 keys (352 live chunks, 288 full) 80.0 / 88.1 / 77.1 us, 16 x 12/2 x 6427 .. 51420
+// (334, 302) 101 / 105.7 / 91.6, 19 x 12/2 x 26865 .. 53731 (566, 528) 139.3 / 147.0 / 130.8, 12 x 32/8 x 300 .. 6000 39.4 / 40.1 / 37.3, 7 x 64/8 x
+// 1041 .. 8335 33.8 / 34.2 / 31.1.  Not where the partial chunks make a round of their own (22 x 28/4 x 12577 .. 25155, 512 full and 88:
+// 155.1 / 157.8).
+// `res`: resident keys of sequence `lane` (p.B <= 64).
 // Returns false for a workgroup beyond the last chunk; else sequence, chunk and KV head.
 __device__ __forceinline__ bool chunk_by_length(const Problem &p, int res, int &b, int &c, int &hkv)
 {
@@ -99,7 +108,19 @@ __device__ __forceinline__ bool chunk_by_length(const Problem &p, int res, int &
     const int n_full = __builtin_amdgcn_readlane(scan, 63), n_part = __popcll(parts);
     const int live = (n_full + n_part) * p.Hkv;
     int i = blockIdx.x;
-    if (live > kComputeUnits && i < kComputeUnits) i = kComputeUnits - 1 - i;
+    const int fulls = n_full * p.Hkv;
+    bool dealt = false;
+    if (fulls > kComputeUnits) {
+        const int rounds = (fulls + kComputeUnits - 1) / kComputeUnits;
+        const int used = ((live + rounds - 1) / rounds + 7) & ~7;          // compute units: the same number of each XCD
+        const int last = kComputeUnits * (rounds - 1);                     // first workgroup of the last round
+        dealt = used < kComputeUnits && last + used <= 8 * ((p.B * p.Hkv + 7) >> 3) * p.nc;
+        if (dealt && i < last + kComputeUnits) {                           // (a permutation: the rest of each round takes what is left)
+            const int k = i / kComputeUnits, j = i % kComputeUnits;
+            i = j < used ? k * used + j : used * rounds + k * (kComputeUnits - used) + (j - used);
+        }
+    }
+    if (!dealt && live > kComputeUnits && i < kComputeUnits) i = kComputeUnits - 1 - i;
     int q = (int)(((float)i + 0.5f) * __builtin_amdgcn_rcpf((float)p.Hkv));   // i / Hkv: exact, i < 2^20
     const int h = i - q * p.Hkv;
     if (q < n_full) {

@@ -59,3 +59,45 @@ def test_every_chunk_once(oracle, H, B, Hq, Hkv, Smax, chunk, kind):
     _, den = dc.partials()
     with_keys = np.arange(nc)[None, None, :] * chunk < np.asarray(lens)[:, None, None]
     assert np.array_equal(den > 0, np.broadcast_to(with_keys, den.shape))
+
+
+def dealt(B, Hkv, Smax, chunk, lens):
+    """Rounds and compute units the live chunks are dealt to, or None where they are not (up to 256 full chunks, or more live ones
+    than fit the rounds that the full ones need, or a launch too small for them)."""
+    full = sum(n // chunk for n in lens) * Hkv
+    live = full + sum(n % chunk > 0 for n in lens) * Hkv
+    rounds = -(-full // 256)
+    if rounds < 2:
+        return None
+    used = (-(-live // rounds) + 7) // 8 * 8
+    grid = 8 * ((B * Hkv + 7) // 8) * -(-Smax // chunk)
+    return (rounds, used) if used < 256 and 256 * (rounds - 1) + used <= grid else None
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Smax,chunk,lens,want", [
+    (9, 16, 8, 512, 64, [512, 512, 500, 320, 64, 0, 449, 450, 129], (2, 200)),           # 360 full, 32 partial
+    (11, 16, 8, 512, 64, [512] * 4 + [130] * 6 + [1], (2, 208)),
+    (11, 16, 8, 512, 64, [512] * 4 + [1] * 7, None),                                     # 256 full chunks: in reverse
+    (20, 10, 5, 256, 64, [256] * 13 + [10] * 7, (2, 152)),                               # 260 full of 5 heads, 35 partial
+    (20, 10, 5, 256, 64, [256] * 18 + [129, 64], None),                                  # a launch too small to be dealt
+    (8, 4, 2, 2560, 64, [2560] * 3 + [640, 650, 0, 1, 2559], (2, 184)),
+    (64, 10, 5, 576, 64, [576] * 12 + [0] * 34 + [70] * 18, (3, 240)),                   # three rounds
+    (64, 10, 5, 576, 64, [576] * 12 + [100] * 52, None),                                 # the partial chunks make a round of their own
+    (6, 28, 4, 1152, 64, [1152, 1152, 900, 1153, 1087, 0], (2, 176)),                    # 24 head groups, the last workgroup needed; a length past the cache
+    (3, 16, 8, 800, 64, [800, 799, 768], None),
+])
+def test_more_full_chunks_than_compute_units(oracle, H, B, Hq, Hkv, Smax, chunk, lens, want):
+    inside = [min(n, Smax) for n in lens]
+    assert dealt(B, Hkv, Smax, chunk, inside) == want
+    case = synth.make_case(B=B, Hq=Hq, Hkv=Hkv, D=128, Smax=Smax, seed=9200 + B + Smax, seq_lens=inside, poison_padding=True)
+    # (a row of an empty sequence takes no key: the next seed)
+    planted = next(filter(None, (synth.plant_keys(case, 1, 36.0, seed=s, allow_shared_kv=True) for s in range(9201, 9301))))
+    exact = oracle.attn_exact(case["q"], case["k"], case["v"], case["seq_lens"], case["scale"], nthreads=8)
+    ocf, orf, margin = oracle.flags(case["q"], case["k"], case["seq_lens"], case["scale"], synth.PHI, *synth.BOUNDS, chunk, nthreads=8)
+    assert margin.min() > 1e-2 and len(planted) == 1 and orf.sum() >= 1
+    case["seq_lens"] = np.asarray(lens, dtype=np.int32)
+    dc = H.DeviceCase(case, chunk=chunk)
+    for rep in range(2):
+        H.assert_close(dc.run("fd_decode_attn_gqa"), exact, "dealt %s, pass %d" % (want, rep))
+        cf, rf, n, _ = dc.flags()
+        assert np.array_equal(cf, ocf) and np.array_equal(rf, orf) and n == int(orf.sum())
