@@ -168,8 +168,11 @@ def test_calls_can_be_captured_in_a_graph_and_replayed(oracle, H):
     each replayed five times with eager work in between and compared with the eager result."""
     import torch
     for (B, Hq, Hkv, Smax, chunk, entry) in ((1, 32, 32, 2048, 256, "fd_decode_attn"),        # 256 workgroups: one launch
-                                             (8, 32, 32, 2048, 256, "fd_decode_attn"),        # 2048: two launches
-                                             (4, 64, 8, 1024, 256, "fd_decode_attn_gqa")):
+                                             (8, 32, 32, 2048, 256, "fd_decode_attn"),        # 2048: one
+                                             (8, 32, 32, 2304, 256, "fd_decode_attn"),        # 2304 of nine chunks: two
+                                             (4, 64, 8, 1024, 256, "fd_decode_attn_gqa"),     # 128: one
+                                             (12, 16, 8, 512, 64, "fd_decode_attn_gqa"),      # 768, ordered by length: one
+                                             (13, 16, 8, 512, 64, "fd_decode_attn_gqa")):     # 832: two
         case = synth.make_case(B=B, Hq=Hq, Hkv=Hkv, D=128, Smax=Smax, seed=8800 + B)
         dc = H.DeviceCase(case, chunk=chunk)
         want = oracle.attn_exact(case["q"], case["k"], case["v"], case["seq_lens"], case["scale"], nthreads=8)

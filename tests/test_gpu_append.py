@@ -74,11 +74,17 @@ def check(oracle, H, case, chunk, k_new=None, v_new=None, seed=1, expect_flagged
     (3, 8, 8, 1024, [0, 1, 1023], 128),               # empty sequence: the new key is the only one
     (4, 8, 8, 777, [776, 5, 64, 700], 64),            # odd maximum length, chunk edges
     (2, 32, 32, 2048, [2047, 1000], 1024),            # 8-wavefront workgroups
-    (8, 32, 32, 2048, None, 256),                     # 2048 workgroups: row epilogue as a second launch
+    (8, 32, 32, 2048, None, 256),                     # 2048 workgroups that finish their rows
+    (8, 32, 32, 2304, [2303, 0, 2304, 2048, 2047, 256, 1000, 1791], 256),   # 2304 of nine chunks: row epilogue as a second launch
+    (7, 32, 32, 2560, [2559, 0, 2560, 2048, 511, 512, 1000], 512),          # 1120 of eight wavefronts: a second launch
+    (2, 4, 4, 9000, [8999, 8447], 256),               # 36 chunks per row: one block of keys in flight
     (2, 16, 2, 600, [599, 256], 256),                 # grouped kernel, groups of 8
     (2, 12, 4, 515, [512, 0], 128),                   # groups of 3; new chunk; empty sequence
     (1, 64, 8, 4096, [4000], 1024),                   # grouped, long chunks
-    (16, 64, 8, 1024, None, 256),                     # grouped, 512 workgroups: second launch
+    (16, 64, 8, 1024, None, 256),                     # grouped, 512 workgroups, ordered by length, that finish their rows
+    (13, 16, 8, 512, [511, 0, 512, 64, 63, 320, 100, 449, 447, 1, 256, 500, 511], 64),   # 832: a second launch
+    (11, 16, 8, 512, [511, 512, 511, 511, 64, 130, 0, 63, 130, 130, 1], 64),             # more full chunks than compute units
+    (40, 8, 4, 2048, [2047 - 50 * i for i in range(40)], 64),                            # 5120: too many to be ordered
     (1, 34, 2, 300, [299], 64),                       # groups of 17: per-row kernel with shared KV heads
     (3, 16, 2, 512, [300, 510, 0], 512),              # grouped, one chunk per sequence: no epilogue; new key alone
     (2, 16, 2, 1024, [512, 511], 512),                # grouped: the new key opens a second chunk / completes the only one
@@ -102,6 +108,16 @@ def test_append_of_an_overflowing_key_is_flagged_and_recomputed(oracle, H):
         qv = case["q"][1, 0].astype(np.float64)                 # aim at row (1, 0): KV head 0 of sequence 1
         k_new[1, 0] = (36.0 * qv / np.linalg.norm(qv)).astype(np.float16)
         check(oracle, H, case, chunk, k_new=k_new, seed=5, expect_flagged=1)
+
+    # in launches ordered by length (rows finished inside and by a second launch), where the new key opens a chunk, and in a per-row
+    # launch with a second one
+    for (B, Hq, Hkv, Smax, n, chunk) in ((12, 16, 8, 512, 64, 64), (13, 16, 8, 512, 320, 64), (8, 32, 32, 2304, 1792, 256)):
+        lens = [n if b == 1 else (37 * b * chunk // 8) % Smax for b in range(B)]
+        case = synth.make_case(B=B, Hq=Hq, Hkv=Hkv, D=128, Smax=Smax, seq_lens=lens, seed=93, poison_padding=True)
+        k_new = np.random.default_rng(4).standard_normal((B, Hkv, 128)).astype(np.float16)
+        qv = case["q"][1, 0].astype(np.float64)
+        k_new[1, 0] = (36.0 * qv / np.linalg.norm(qv)).astype(np.float16)
+        check(oracle, H, case, chunk, k_new=k_new, seed=6, expect_flagged=1)
 
 
 def test_append_then_plain_call_agree(oracle, H):

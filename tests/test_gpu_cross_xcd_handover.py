@@ -1,8 +1,10 @@
 """The hand-over between the workgroups of one fused launch must not depend on where the workgroups run.
-The product library deals all chunks of a row to one XCD (one L2); the probe build of the library
-(``libfdattn_phase.so``, -DFD_PHASE_PROBE) can deal them to eight different XCDs instead, so that every
+The library deals all chunks of a row to one XCD (one L2) in short launches and to all eight in long ones (the per-row kernel beyond
+1024 workgroups, or beyond 256 over 320 MiB of cache; the grouped kernel beyond 256); its probe build
+(``libfdattn_phase.so``, -DFD_PHASE_PROBE) can deal them to eight XCDs in every launch, so that every
 partial result and every arrival crosses from one L2 to another.  Same inputs, both placements: the outputs
-must agree bit for bit (fixed summation order) and with the oracle, over hundreds of back-to-back calls."""
+must agree bit for bit (fixed summation order) and with the oracle, over hundreds of back-to-back calls.  The long launches
+that finish their rows are called as often, in the placement they have."""
 import ctypes
 import os
 
@@ -37,9 +39,14 @@ def H():
 
 @pytest.mark.parametrize("B,Hq,Hkv,Smax,chunk,entry", [
     (1, 32, 32, 8192, 1024, "fd_decode_attn"),        # 8 chunks per row: one level of arrival counters, register epilogue
-    (1, 32, 32, 8192, 256, "fd_decode_attn"),         # 32 chunks per row: two levels, sliced epilogue
+    (1, 32, 32, 8192, 256, "fd_decode_attn"),         # 32 chunks per row: two levels
+    (1, 8, 8, 8192, 64, "fd_decode_attn"),            # 128 chunks per row: three levels, four rounds of the finish
     (2, 16, 16, 2048, 64, "fd_decode_attn"),          # 1024 workgroups, several per compute unit
     (4, 64, 8, 4096, 512, "fd_decode_attn_gqa"),      # grouped kernel, 8 chunks per head group
+    (8, 32, 32, 512, 64, "fd_decode_attn"),           # spread by itself: 2048 workgroups of four wavefronts
+    (1, 32, 32, 22528, 1024, "fd_decode_attn"),       # ... 704 over 352 MiB
+    (12, 16, 8, 512, 64, "fd_decode_attn_gqa"),       # ... 768 of the grouped kernel, two chunks of each row or more to an XCD
+    (5, 64, 8, 1024, 128, "fd_decode_attn_gqa"),      # ... 320
 ])
 def test_outputs_do_not_depend_on_placement(oracle, H, probe_lib, B, Hq, Hkv, Smax, chunk, entry):
     cases = [synth.make_case(B=B, Hq=Hq, Hkv=Hkv, D=128, Smax=Smax, seed=9900 + l + Smax + chunk) for l in (0, 1)]

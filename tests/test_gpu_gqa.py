@@ -40,7 +40,9 @@ CASES = [
     (3, 12, 4, 256, [256, 100, 255], 256),  # the same with groups of 3
     (2, 16, 2, 700, [700, 200], 512),       # a sequence of two chunks next to one of a single chunk
     (8, 64, 8, 1024, [1024, 100, 300, 1, 0, 513, 512, 900], 256),   # 256 workgroups, ragged: many chunks past the ends
-    (10, 64, 8, 1024, None, 256),           # 320 workgroups: the row epilogue as a second launch
+    (10, 64, 8, 1024, None, 256),           # 320 workgroups, ordered by length, that finish their rows
+    (13, 64, 8, 1024, None, 128),           # 832 workgroups: the row epilogue as a second launch
+    (40, 8, 4, 2048, None, 64),             # 5120: too many to be ordered
     (2, 16, 2, 3000, [3000, 1111], 1152),   # a chunk length that is no power of two (capacity 2048)
     (1, 8, 2, 600, [555], 80),              # ... of 80 keys (capacity 128)
     (2, 16, 2, 9000, [8999, 4097], 3008),   # ... of 3008 keys (capacity 4096)

@@ -46,6 +46,21 @@ def test_grouped(H, B, Hq, Hkv, Smax, chunk, launches):
     assert kernels(H, "fd_decode_attn_gqa", B, Hq, Hkv, Smax, chunk) == launches
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,Smax,page,chunk,launches", [
+    (8, 32, 32, 2048, 128, 256, 1), (8, 32, 32, 2304, 128, 256, 2), (7, 32, 32, 2560, 64, 512, 2), (12, 16, 8, 512, 16, 64, 1),
+    (13, 16, 8, 512, 16, 64, 2), (9, 12, 4, 1280, 32, 128, 2), (2, 8, 8, 9216, 256, 256, 1), (40, 8, 4, 2048, 64, 64, 2),
+])
+def test_append_and_paged(H, B, Hq, Hkv, Smax, page, chunk, launches):
+    shape = fdattn.make_shape(B, Hq, Hkv, 128, Smax, chunk, synth.default_scale(128))
+    n = fdattn.fd_workspace_bytes(shape)
+    at = torch.zeros(4096, dtype=torch.uint8, device="cuda:0").data_ptr()
+    tail = (synth.PHI, synth.BOUNDS, at, at, n)
+    for call in (lambda s: fdattn.fd_decode_attn_append(shape, at, at, at, at, at, at, *tail, s),
+                 lambda s: fdattn.fd_decode_attn_paged(shape, at, at, at, at, page, 4096, at, *tail, s),
+                 lambda s: fdattn.fd_decode_attn_paged_append(shape, at, at, at, at, at, at, page, 4096, at, *tail, s)):
+        assert H.kernels_of(call) == launches
+
+
 @pytest.mark.parametrize("B,heads,Smax,lens,chunk", [
     (8, 32, 512, [512, 1, 64, 300, 449, 511, 0, 130], 64),             # 2048 workgroups of eight chunks: in the launch
     (8, 49, 512, [512, 1, 64, 300, 449, 511, 0, 130], 64),             # 3136: a second one

@@ -75,7 +75,10 @@ def check(H, case, page, chunk, expect_flagged=0):
     (3, 4, 4, 1024, [1024, 1, 0], 64, 256),            # one token; empty sequence
     (2, 8, 8, 2048, [2047, 700], 256, 256),            # page = chunk
     (2, 8, 8, 2048, [2048, 1300], 1024, 256),          # several chunks share a page
-    (8, 32, 32, 2048, None, 128, 256),                 # 2048 workgroups: row epilogue as a second launch
+    (8, 32, 32, 2048, None, 128, 256),                 # 2048 workgroups that finish their rows
+    (8, 32, 32, 2304, [2304, 1, 0, 2049, 2048, 257, 1000, 2300], 128, 256),    # 2304 of nine chunks: row epilogue as a second launch
+    (8, 33, 33, 1024, [1024, 1, 0, 1023, 512, 513, 255, 700], 64, 256),        # 1056 workgroups, rows that do not divide by 8
+    (7, 32, 32, 2560, [2560, 1, 0, 2049, 2048, 257, 1000], 64, 512),           # 1120 of eight wavefronts: a second launch
     (2, 16, 2, 1024, [1023, 256], 16, 256),            # grouped kernel, groups of 8
     (2, 12, 4, 512, [512, 0], 64, 128),                # groups of 3; empty sequence
     (1, 64, 8, 4096, [4000], 256, 1024),               # grouped, long chunks
@@ -110,13 +113,43 @@ def test_paged_flag_and_recompute(H, Hq, Hkv):
     assert np.array_equal(cf, ocf) and np.array_equal(rf, orf)
 
 
+@pytest.mark.parametrize("B,heads,nc", [(12, 16, 8), (13, 16, 8), (11, 16, 8), (8, 32, 8), (8, 32, 9)])
+def test_paged_recompute_in_large_launches(H, B, heads, nc):
+    """Recomputed chunks of launches ordered by length (rows finished inside, by a second launch; more full chunks than compute
+    units) and of large per-row launches, through the paged loads."""
+    Hkv, chunk = (8, 64) if heads == 16 else (32, 256)
+    Smax = nc * chunk
+    lens = [[Smax, Smax - 1, chunk, 5 * chunk + 1, Smax, 3, 2 * chunk - 1][i % 7] for i in range(B)]
+    case = synth.make_case(B=B, Hq=heads, Hkv=Hkv, D=128, Smax=Smax, seed=8250 + B, seq_lens=lens, poison_padding=True)
+    planted = synth.plant_keys(case, 5, 36.0, seed=8251, allow_shared_kv=True)
+    pc = PagedCase(H, case, 64, chunk)
+    want = po.attn_exact(case["q"], pc.k_pool, pc.v_pool, pc.table, 64, case["seq_lens"], case["scale"], nthreads=8)
+    ocf, orf, margin = po.flags(case["q"], pc.k_pool, pc.table, 64, case["seq_lens"], case["scale"], synth.PHI, LO, HI, chunk, nthreads=8)
+    assert margin.min() > 1e-2 and orf.sum() >= len(planted) == 5
+    for rep in range(2):
+        H.assert_close(pc.run(), want, "paged with recomputation, pass %d" % rep)
+        cf, rf, n, rows = pc.dc.flags()
+        assert np.array_equal(cf, ocf) and np.array_equal(rf, orf)
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,Smax,lens,page,chunk", [
     (4, 4, 4, 512, [300, 256, 511, 512], 64, 256),     # mid-page; first row of a fresh page; last free row; full (dropped)
     (3, 8, 8, 1024, [0, 1, 1023], 16, 128),            # empty sequence: the new key is the only one
     (2, 32, 32, 2048, [2047, 1000], 256, 1024),        # 8-wavefront workgroups
     (2, 16, 2, 1024, [1000, 512], 32, 256),            # grouped kernel; a fresh page that opens a chunk
     (2, 16, 2, 1024, [1000, 512], 32, 1024),           # grouped kernel, one chunk per sequence
-    (8, 32, 32, 2048, None, 128, 256),                 # every sequence full: nothing appended, second launch
+    (8, 32, 32, 2048, None, 128, 256),                 # every sequence full: nothing appended
+    (8, 32, 32, 2304, [2303, 0, 2304, 2048, 2047, 256, 1000, 1791], 128, 256),  # a second launch; new keys that open and close chunks
+    (7, 32, 32, 2560, [2559, 0, 2560, 2048, 511, 512, 1000], 64, 512),          # ... of eight wavefronts
+    # the grouped kernel's order by length (more than 256 workgroups, up to 64 sequences): an empty and a full sequence, new keys that
+    # are a chunk of their own, the last of one, inside one
+    (12, 16, 8, 512, [511, 0, 512, 64, 63, 320, 100, 449, 447, 1, 256, 500], 16, 64),   # 768 workgroups: rows finished in the launch
+    (12, 64, 8, 512, [0, 1, 5, 64, 63, 32, 10, 511, 512, 128, 2, 127], 64, 128),        # 384 of groups of 8, hardly any full chunk
+    (13, 16, 8, 512, [511, 0, 512, 64, 63, 320, 100, 449, 447, 1, 256, 500, 511], 16, 64),   # 832: a second launch
+    (9, 12, 4, 1280, [1279, 0, 1280, 1151, 1152, 640, 127, 128, 1279], 32, 128),        # ten chunks, groups of 3: a second launch
+    (11, 16, 8, 512, [511, 512, 511, 511, 64, 130, 0, 63, 130, 130, 1], 32, 64),        # more full chunks than compute units
+    (40, 8, 4, 2048, [2047 - 50 * i for i in range(40)], 64, 64),                       # 5120 workgroups: too many to be ordered
+    (65, 16, 8, 128, [127 - i % 128 for i in range(65)], 16, 64),                       # a sequence too many
 ])
 def test_paged_append(H, B, Hq, Hkv, Smax, lens, page, chunk):
     case = synth.make_case(B=B, Hq=Hq, Hkv=Hkv, D=128, Smax=Smax, seed=8300 + page + chunk, seq_lens=lens, poison_padding=True)

@@ -96,7 +96,7 @@ def test_c4_overflow_stress(oracle, H):
 @pytest.mark.parametrize("Smax,lens,chunk,mib", [(8192, [8192, 5000], 1024, 256), (8192, [8192, 8100], 512, 256),
                                                  (16384, [16384, 9000], 1024, 512), (12288, [12288, 700], 768, 384)])
 def test_launches_of_257_to_1024_workgroups(oracle, H, Smax, lens, chunk, mib):
-    """Between one and four workgroups per compute unit the per-row call picks its launch form by the
+    """Above three and up to four workgroups per compute unit the per-row call picks its launch form, for rows of 9 to 32 chunks, by the
     size of the cache (row epilogue elected inside the kernel below 320 MiB, a second launch from
     there on): both forms, full and part-filled sequences, two planted out-of-range keys, checked
     on every output element, flag, list entry and count."""
