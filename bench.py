@@ -200,7 +200,7 @@ class Runner:
         fdattn.fd_workspace_init(self.shape, self.ws.data_ptr(), self.ws_bytes, wl.stream)
         gqa = entry == "fd_decode_attn_gqa" or (entry == "fd_decode_attn_static" and wl.grouped)
         self.gqa = gqa
-        nc = -(-wl.Smax // chunk)
+        self.nc = nc = -(-wl.Smax // chunk)
         wgs = wl.B * (wl.Hkv if gqa else wl.Hq) * nc
         # the library's own rule (elect_per_row, elect_grouped): which launches finish their rows themselves; the others leave
         # the row epilogue to a launch of its own
@@ -213,16 +213,20 @@ class Runner:
         self.grid = (wl.B * wl.Hkv * nc) if gqa else 8 * ((wl.B * wl.Hq + 7) // 8) * nc
 
     def kernel_name(self):
-        """Template arguments: <chunk capacity, paged, wavefronts> for the grouped (the profiler also prints its start variant)
-        kernel, <chunk capacity, in-kernel hand-over, paged, early loads> for the per-row one."""
+        """The chunk kernel of this launch, with its template arguments as the profiler prints them (namespaces left out): <chunk
+        capacity, paged, start variant, wavefronts> for the grouped kernel, <chunk capacity, in-kernel hand-over, paged, early
+        loads, one block in flight> for the per-row one."""
+        wl = self.wl
         cap = 64
         while cap < self.chunk:
             cap *= 2
         if self.gqa:
-            return "decode_fused_gqa_kernel<%d, false, 4>" % cap
+            grid = 8 * ((wl.B * wl.Hkv + 7) // 8) * self.nc
+            start = 1 if grid <= 256 else (2 if grid <= 4096 and wl.B <= 64 else 0)
+            return "decode_fused_gqa_kernel<%d, false, (Start)%d, 4>" % (cap, start)
         early = self.single_launch and self.grid <= 256
-        return "decode_fused_kernel<%d, %s, false, %s>" % (cap, "true" if self.single_launch else "false",
-                                                           "true" if early else "false")
+        one = not early and 256 <= cap <= 1024 and (self.nc > 32 or (not self.single_launch and wl.B * wl.Hq * self.nc > 768))
+        return "decode_fused_kernel<%d, %s>" % (cap, ", ".join("true" if x else "false" for x in (self.single_launch, False, early, one)))
 
     def step(self, i):
         wl, fdattn = self.wl, self.wl.fdattn

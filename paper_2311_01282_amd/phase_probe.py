@@ -63,7 +63,7 @@ def main():
     nc = -(-Smax // chunk)
     grid = 8 * ((B * Hq + 7) // 8) * nc
     if grid > 1024:
-        raise SystemExit("the launch has %d workgroups: beyond 1024 the row epilogue is a launch of its own" % grid)
+        raise SystemExit("the launch has %d workgroups: the probe reads launches of up to 1024 that finish their rows" % grid)
     dev = torch.device("cuda:0")
     torch.cuda.set_device(dev)
     layers = max(2, min(64, -(-(1 << 30) // (B * Hkv * Smax * D * 4))))
@@ -111,10 +111,11 @@ def main():
         for ph in range(SLOTS):
             x = rel[finisher, ph] if ph >= 6 else rel[:, ph]
             rows.append((float(x.min()), float(np.median(x)), float(x.max())))
-        # per-workgroup durations between consecutive phases
-        d = [float(np.median(rel[:, ph] - rel[:, ph - 1])) for ph in range(1, 6)]
-        df = [float(np.median(rel[finisher, 6] - rel[finisher, 5])), float(np.median(rel[finisher, 7] - rel[finisher, 6]))]
-        per_round.append((rows, d + df))
+        # per-workgroup durations between consecutive phases (chunks of one or two blocks have no stamp 1)
+        stamped = [ph for ph in range(SLOTS) if t[:, ph].max() >= t0]
+        step = {b: float(np.median((rel[:, b] - rel[:, a])[finisher if b >= 6 else slice(None)]))
+                for a, b in zip(stamped, stamped[1:])}
+        per_round.append((rows, step))
         if args.detail:
             # workgroup index -> (XCD, chunk): blockIdx & 7 is the XCD, blockIdx >> 3 = chunk * groups8 + row group
             groups8 = (B * Hq + 7) // 8
@@ -133,7 +134,9 @@ def main():
         lo = med([pr[0][ph][0] for pr in per_round])
         mid = med([pr[0][ph][1] for pr in per_round])
         hi = med([pr[0][ph][2] for pr in per_round])
-        step = "" if ph == 0 else "%.2f" % med([pr[1][ph - 1] for pr in per_round])
+        if ph and ph not in per_round[0][1]:
+            continue
+        step = "" if ph == 0 else "%.2f" % med([pr[1][ph] for pr in per_round])
         print("| %d %s | %.2f | %.2f | %.2f | %s |" % (ph, PHASES[ph], lo, mid, hi, step))
     if args.detail:
         fmt = lambda a: " ".join("%.2f" % x for x in a)
