@@ -530,8 +530,8 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
         den = halves_sum(den, den);
         den = rows_sum(den, den);
     }
-    // The pair of lane (sub, seg), number 4 seg + sub of its vector, sits in place 4 seg + (sub ^ 2 (seg / 8)): no bank
-    // conflict here, and none where lane l reads pair l back, so that the slot is written in whole lines (pairs stored as the
+    // The pair of lane (sub, seg), number 4 seg + sub of its vector, sits in place 4 seg + (sub ^ 2 (seg / 8)): few bank
+    // conflicts here (4 cycles per wavefront), and none where lane l reads pair l back, so that the slot is written in whole lines (pairs stored as the
     // lanes hold them, 32 bytes apart, cost launches of full caches 1 %).
     *reinterpret_cast<float2 *>(&lds.acc[wave][8 * seg + 2 * (sub ^ ((seg >> 2) & 2))]) = make_float2(u[0], u[1]);
     if (lane == 0) lds.den[wave] = den;

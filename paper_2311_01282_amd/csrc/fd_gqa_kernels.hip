@@ -185,7 +185,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         if (!chunk_by_length(p, res, b, c, hkv)) return;
         gi = b * p.Hkv + hkv;
     } else {
-        // All chunks of a KV-head group go to the same XCD (see decode_fused_kernel); chunk-major in a launch of up
+        // All chunks of a KV-head group go to the same XCD, or in turn to all (row_slot); chunk-major in a launch of up
         // to 1024 workgroups, so that chunks past the end of the sequences come last; row-major beyond.
         const int j = blockIdx.x >> 3;
         const bool cm = p.chunk_major != 0;

@@ -25,7 +25,7 @@ template <int C> struct Tune {
     static constexpr int UP = NG < 4 ? NG : 4;
 };
 
-// ELECT: the launch is small enough for the in-kernel hand-over.
+// ELECT: rows are finished in the launch (elect_per_row in fd_api.hip says which launches do).
 // PAGED: K and V are page pools addressed through the sequence's block table.
 // EARLY: the first loads go out before the sequence length has arrived -- for launches of at
 //        most one workgroup per compute unit, where every workgroup starts with the launch and
@@ -42,10 +42,10 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void decode_fused_kernel(const Pr
     __shared__ ChunkLds<NW, C> lds;
     const int tid = threadIdx.x;
     if constexpr (ELECT) fetch_arguments_now(p);
-    // Workgroups are dealt to the 8 XCDs round-robin by index.  In a launch that hands its rows
+    // Workgroups are dealt to the 8 XCDs round-robin by index.  In a short launch that hands its rows
     // over inside the kernel all chunks of a row go to the same XCD (row % 8), so the row's counters
-    // and partial results stay in one L2 instead of bouncing between eight; a launch that leaves the
-    // epilogue to a second one spreads them (row_slot).  Placement only affects speed: every
+    // and partial results stay in one L2 instead of bouncing between eight; long ones and those that leave the
+    // epilogue to a second launch spread them (FusedLauncher, row_slot).  Placement only affects speed: every
     // hand-over below is device-coherent wherever the workgroups land.
     // Order within that: row-major -- all chunks of rows 0..7, then of rows 8..15, ... -- except in
     // the launches of at most one workgroup per compute unit (EARLY), which go chunk-major and whose

@@ -39,8 +39,10 @@ def test_row_of_nb_chunks(oracle, H, nb, plant):
 
 
 @pytest.mark.parametrize("B,heads,Smax,lens,chunk", [
-    (3, 32, 1024, [1024, 1, 300], 64),            # 1536 workgroups of four wavefronts, finished inside the launch
-    (2, 40, 4000, [4000, 2300], 208),             # 1600, a chunk of 208 keys
+    (8, 32, 512, [512, 1, 300, 449, 2, 511, 64, 130], 64),        # 2048 workgroups of four wavefronts, finished inside the launch
+    (6, 40, 1600, [1600, 1300, 1, 1457, 208, 2], 208),            # 1920, chunks of 208 keys
+    (3, 32, 1024, [1024, 1, 300], 64),            # 1536 of 16 chunks per row: a second launch
+    (2, 40, 4000, [4000, 2300], 208),             # 1600 of 20
     (3, 32, 5800, [5800, 300, 4097], 512),        # 1152 of eight: a second launch
     (2, 32, 8192, [8192, 1000], 512),             # 1024 of eight: inside the launch
 ])
