@@ -86,8 +86,10 @@ __device__ __forceinline__ int lanes_scan(int x)
 // end late while the rest has nothing left to do (first in reverse, 48 with two chunks beside 160 with one).  But fewer than all saturate
 // the memory: the live chunks are dealt to as many compute units as take the same number each, the others get what has no keys.  General
 // order / first in reverse / this: 8 x 64/8 heads x 2725 .. 21800 keys (352 live chunks, 288 full) 80.0 / 88.1 / 77.1 us, 16 x 12/2 x 6427 .. 51420
-// (334, 302) 101 / 105.7 / 91.6, 19 x 12/2 x 26865 .. 53731 (566, 528) 139.3 / 147.0 / 130.8, 12 x 32/8 x 300 .. 6000 39.4 / 40.1 / 37.3, 7 x 64/8 x
-// 1041 .. 8335 33.8 / 34.2 / 31.1.  Not where the partial chunks make a round of their own (22 x 28/4 x 12577 .. 25155, 512 full and 88:
+// (334, 302) 101 / 105.7 / 91.6, 19 x 12/2 x 26865 .. 53731 (566, 528) 139.3 / 143.6 / 126.8, 12 x 32/8 x 300 .. 6000 39.4 / 40.1 / 37.3, 7 x 64/8 x
+// 1041 .. 8335 33.8 / 34.2 / 31.1.  Beyond three rounds workgroups wait for others to end, wherever that is, and nothing is dealt (28 x 16/8 x 87 ..
+// 696, 920 full chunks, in reverse / dealt 15.6 / 16.0); nor are chunks of less than 256 keys, too short to be bound by what a compute unit
+// draws (of 160 22 x 32/8 x 79 .. 632 10.85 / 11.0, of 224 18 x 32/8 x 138 .. 1104 13.3 / 13.5, of 288 9 x 64/8 x 990 .. 1980 15.7 / 15.6); nor where the partial chunks make a round of their own (22 x 28/4 x 12577 .. 25155, 512 full and 88:
 // 155.1 / 157.8).
 // `res`: resident keys of sequence `lane` (p.B <= 64).
 // Returns false for a workgroup beyond the last chunk; else sequence, chunk and KV head.
@@ -110,9 +112,10 @@ __device__ __forceinline__ bool chunk_by_length(const Problem &p, int res, int &
     int i = blockIdx.x;
     const int fulls = n_full * p.Hkv;
     bool dealt = false;
-    if (fulls > kComputeUnits) {
+    if (fulls > kComputeUnits && fulls <= 3 * kComputeUnits && p.C >= 256) {
         const int rounds = (fulls + kComputeUnits - 1) / kComputeUnits;
-        const int used = ((live + rounds - 1) / rounds + 7) & ~7;          // compute units: the same number of each XCD
+        // live / rounds rounded up (exact, as below), to the same number of compute units of each XCD
+        const int used = ((int)(((float)(live + rounds - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)rounds)) + 7) & ~7;
         const int last = kComputeUnits * (rounds - 1);                     // first workgroup of the last round
         dealt = used < kComputeUnits && last + used <= 8 * ((p.B * p.Hkv + 7) >> 3) * p.nc;
         if (dealt && i < last + kComputeUnits) {                           // (a permutation: the rest of each round takes what is left)

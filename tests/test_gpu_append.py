@@ -83,7 +83,7 @@ def check(oracle, H, case, chunk, k_new=None, v_new=None, seed=1, expect_flagged
     (1, 64, 8, 4096, [4000], 1024),                   # grouped, long chunks
     (16, 64, 8, 1024, None, 256),                     # grouped, 512 workgroups, ordered by length, that finish their rows
     (13, 16, 8, 512, [511, 0, 512, 64, 63, 320, 100, 449, 447, 1, 256, 500, 511], 64),   # 832: a second launch
-    (11, 16, 8, 512, [511, 512, 511, 511, 64, 130, 0, 63, 130, 130, 1], 64),             # more full chunks than compute units
+    (11, 16, 8, 2048, [2047, 2048, 2047, 2047, 256, 520, 0, 255, 520, 520, 1], 256),     # more full chunks than compute units
     (40, 8, 4, 2048, [2047 - 50 * i for i in range(40)], 64),                            # 5120: too many to be ordered
     (1, 34, 2, 300, [299], 64),                       # groups of 17: per-row kernel with shared KV heads
     (3, 16, 2, 512, [300, 510, 0], 512),              # grouped, one chunk per sequence: no epilogue; new key alone

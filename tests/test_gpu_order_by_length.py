@@ -62,12 +62,12 @@ def test_every_chunk_once(oracle, H, B, Hq, Hkv, Smax, chunk, kind):
 
 
 def dealt(B, Hkv, Smax, chunk, lens):
-    """Rounds and compute units the live chunks are dealt to, or None where they are not (up to 256 full chunks, or more live ones
-    than fit the rounds that the full ones need, or a launch too small for them)."""
+    """Rounds and compute units the live chunks are dealt to, or None where they are not (chunks of less than 256 keys, up to 256 full
+    ones, more than three rounds of them, more live ones than fit the rounds that the full ones need, or a launch too small for them)."""
     full = sum(n // chunk for n in lens) * Hkv
     live = full + sum(n % chunk > 0 for n in lens) * Hkv
     rounds = -(-full // 256)
-    if rounds < 2:
+    if rounds not in (2, 3) or chunk < 256:
         return None
     used = (-(-live // rounds) + 7) // 8 * 8
     grid = 8 * ((B * Hkv + 7) // 8) * -(-Smax // chunk)
@@ -75,16 +75,18 @@ def dealt(B, Hkv, Smax, chunk, lens):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,Smax,chunk,lens,want", [
-    (9, 16, 8, 512, 64, [512, 512, 500, 320, 64, 0, 449, 450, 129], (2, 200)),           # 360 full, 32 partial
-    (11, 16, 8, 512, 64, [512] * 4 + [130] * 6 + [1], (2, 208)),
-    (11, 16, 8, 512, 64, [512] * 4 + [1] * 7, None),                                     # 256 full chunks: in reverse
-    (20, 10, 5, 256, 64, [256] * 13 + [10] * 7, (2, 152)),                               # 260 full of 5 heads, 35 partial
-    (20, 10, 5, 256, 64, [256] * 18 + [129, 64], None),                                  # a launch too small to be dealt
-    (8, 4, 2, 2560, 64, [2560] * 3 + [640, 650, 0, 1, 2559], (2, 184)),
-    (64, 10, 5, 576, 64, [576] * 12 + [0] * 34 + [70] * 18, (3, 240)),                   # three rounds
-    (64, 10, 5, 576, 64, [576] * 12 + [100] * 52, None),                                 # the partial chunks make a round of their own
-    (6, 28, 4, 1152, 64, [1152, 1152, 900, 1153, 1087, 0], (2, 176)),                    # 24 head groups, the last workgroup needed; a length past the cache
-    (3, 16, 8, 800, 64, [800, 799, 768], None),
+    (9, 16, 8, 2048, 256, [2048, 2048, 2000, 1280, 256, 0, 1796, 1800, 516], (2, 200)),      # 360 full, 32 partial
+    (11, 16, 8, 2048, 256, [2048] * 4 + [520] * 6 + [1], (2, 208)),
+    (11, 16, 8, 2048, 256, [2048] * 4 + [1] * 7, None),                                      # 256 full chunks: in reverse
+    (11, 16, 8, 1664, 208, [1664] * 4 + [420] * 6 + [1], None),                              # chunks of less than 256 keys
+    (20, 10, 5, 1024, 256, [1024] * 13 + [40] * 7, (2, 152)),                                # 260 full of 5 heads, 35 partial
+    (20, 10, 5, 1152, 288, [1152] * 18 + [577, 288], None),                                  # a launch too small to be dealt
+    (8, 4, 2, 10240, 256, [10240] * 3 + [2560, 2600, 0, 1, 10239], (2, 184)),
+    (64, 10, 5, 2304, 256, [2304] * 12 + [0] * 34 + [280] * 18, (3, 240)),                   # three rounds
+    (64, 10, 5, 2304, 256, [2304] * 17 + [0] * 34 + [280] * 13, None),                       # 830 full: a fourth round
+    (64, 10, 5, 2304, 256, [2304] * 12 + [160] * 52, None),                                  # the partial chunks make a round of their own
+    (6, 28, 4, 4608, 256, [4608, 4608, 3600, 4609, 4350, 0], (2, 176)),                      # 24 head groups, the last workgroup needed; a length past the cache
+    (3, 16, 8, 3200, 256, [3200, 3199, 3072], None),
 ])
 def test_more_full_chunks_than_compute_units(oracle, H, B, Hq, Hkv, Smax, chunk, lens, want):
     inside = [min(n, Smax) for n in lens]

@@ -113,11 +113,11 @@ def test_paged_flag_and_recompute(H, Hq, Hkv):
     assert np.array_equal(cf, ocf) and np.array_equal(rf, orf)
 
 
-@pytest.mark.parametrize("B,heads,nc", [(12, 16, 8), (13, 16, 8), (11, 16, 8), (8, 32, 8), (8, 32, 9)])
-def test_paged_recompute_in_large_launches(H, B, heads, nc):
+@pytest.mark.parametrize("B,heads,nc,chunk", [(12, 16, 8, 64), (13, 16, 8, 64), (12, 16, 8, 256), (8, 32, 8, 256), (8, 32, 9, 256)])
+def test_paged_recompute_in_large_launches(H, B, heads, nc, chunk):
     """Recomputed chunks of launches ordered by length (rows finished inside, by a second launch; more full chunks than compute
     units) and of large per-row launches, through the paged loads."""
-    Hkv, chunk = (8, 64) if heads == 16 else (32, 256)
+    Hkv = 8 if heads == 16 else 32
     Smax = nc * chunk
     lens = [[Smax, Smax - 1, chunk, 5 * chunk + 1, Smax, 3, 2 * chunk - 1][i % 7] for i in range(B)]
     case = synth.make_case(B=B, Hq=heads, Hkv=Hkv, D=128, Smax=Smax, seed=8250 + B, seq_lens=lens, poison_padding=True)
@@ -147,7 +147,7 @@ def test_paged_recompute_in_large_launches(H, B, heads, nc):
     (12, 64, 8, 512, [0, 1, 5, 64, 63, 32, 10, 511, 512, 128, 2, 127], 64, 128),        # 384 of groups of 8, hardly any full chunk
     (13, 16, 8, 512, [511, 0, 512, 64, 63, 320, 100, 449, 447, 1, 256, 500, 511], 16, 64),   # 832: a second launch
     (9, 12, 4, 1280, [1279, 0, 1280, 1151, 1152, 640, 127, 128, 1279], 32, 128),        # ten chunks, groups of 3: a second launch
-    (11, 16, 8, 512, [511, 512, 511, 511, 64, 130, 0, 63, 130, 130, 1], 32, 64),        # more full chunks than compute units
+    (11, 16, 8, 2048, [2047, 2048, 2047, 2047, 256, 520, 0, 255, 520, 520, 1], 32, 256),  # more full chunks than compute units
     (40, 8, 4, 2048, [2047 - 50 * i for i in range(40)], 64, 64),                       # 5120 workgroups: too many to be ordered
     (65, 16, 8, 128, [127 - i % 128 for i in range(65)], 16, 64),                       # a sequence too many
 ])
