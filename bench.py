@@ -207,7 +207,7 @@ class Runner:
         fused = entry in ("fd_decode_attn", "fd_decode_attn_gqa", "fd_decode_attn_static")
         long_cache = wl.B * wl.Hkv * wl.Smax * wl.D * 2 * 2 >= 320 << 20
         per_row = nc <= 128 and (wgs <= (768 if nc <= 32 else 960) or (wgs <= 1024 and not long_cache) or
-                                 (nc <= 8 and (wgs <= (1024 if chunk >= 128 else 3072) or 128 <= chunk <= 256)))
+                                 (nc <= 8 and (wgs <= (1024 if chunk >= 128 else 4095) or 128 <= chunk <= 256)))
         self.single_launch = fused and (((wgs <= 256 and nc <= 16) or (wgs <= 768 and nc <= 8)) if gqa else per_row)
         self.launches = 1 if self.single_launch else (3 if entry == "fd_decode_attn_multikernel" else 2)
         self.grid = (wl.B * wl.Hkv * nc) if gqa else 8 * ((wl.B * wl.Hq + 7) // 8) * nc

@@ -151,7 +151,7 @@ fd_status fd_workspace_init(const fd_shape *shape, fd_workspace ws, void *stream
  *      trips per workgroup cost more than that: rows of more than 128 chunks; rows of more than 8
  *      chunks in more than 1024 workgroups, or in more than 768 (960 for more than 32 chunks) over
  *      320 MiB or more of cache; chunks of
- *      more than 256 keys in more than 1024 workgroups, of less than 128 in more than 3072
+ *      more than 256 keys in more than 1024 workgroups, of less than 128 in 4096 and more
  *      (fd_decode_attn_gqa: more than 16 chunks per row, or more than 256 workgroups, 768
  *      for rows of up to 8 chunks).
  * A flagged row is thus produced by the synchronized scheme, but only the

@@ -176,13 +176,14 @@ fd_status set_guard(fd::Problem *p, float phi, fd_bounds b)
 // x 112 .. 900 69.2 / 68.3; of 256 12 x 40 x 187 .. 1500 48.1 / 46.8, 32 x 32 x 2000 167.1 / 167.8 (250 .. 2000 107.5 / 107.7), 32 x 32 x 1500 125.4 / 127.7
 // (187 .. 1500 88.1 / 87.3); not of more: 8 x 16 x 8192 in 32 85.2 / 87.7, 8 x 32 x 4096 in 64 90.2 / 94.4 (512 .. 4096 64.0 / 68.4), 8 x 32 x 2048 in 16 45.6 /
 // 47.0, 32 x 16 x 3000 in 12 123.8 / 126.7.  Chunks of less than 128 keys are too short to cover it in large numbers: of 64 16 x 32 x 300 (2560
-// workgroups) 17.1 / 16.8, 37 .. 300 13.6 / 12.9, but 32 x 32 x 200 (4096) 21.9 / 22.9, 20 x 40 x 62 .. 500 (6400) 26.9 / 27.7.
+// workgroups) 17.1 / 16.8, 37 .. 300 13.6 / 12.9, 28 x 16 x 443 (3136) 20.95 / 20.1, but 32 x 32 x 200 (4096) 21.9 / 22.9, 32 x 40 x 31 .. 250 (5120) 24.1 /
+// 25.5, 20 x 40 x 62 .. 500 (6400) 26.9 / 27.7; from there on equal lengths of several hundred keys would still gain 2 % (24 x 32 x 400, 5376, 29.4 / 28.8).
 inline int elect_per_row(const fd::Problem &p)
 {
     const long long workgroups = (long long)p.rows * p.nc;
     if (p.nc > 128) return 0;
     if (workgroups <= (p.nc <= 32 ? 768 : 960) || (workgroups <= 1024 && fd::cache_bytes(p) < fd::kLongLaunchBytes)) return 1;
-    return p.nc <= 8 && (workgroups <= (p.C >= 128 ? 1024 : 3072) || (p.C >= 128 && p.C <= 256));
+    return p.nc <= 8 && (workgroups <= (p.C >= 128 ? 1024 : 4095) || (p.C >= 128 && p.C <= 256));
 }
 
 // The grouped kernel: its elected workgroup finishes the G rows of its head group by itself, up to 16 chunks of

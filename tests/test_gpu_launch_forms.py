@@ -32,7 +32,7 @@ def kernels(H, entry, B, Hq, Hkv, Smax, chunk):
     (4, 32, 8 * 1024, 1024, 1), (4, 28, 9 * 1024, 1024, 2),                            # eight chunks, nine (1008 workgroups)
     (1, 32, 32 * 512, 512, 1), (1, 33, 32 * 512, 512, 2), (8, 33, 4 * 512, 512, 2),    # 1024 workgroups of eight wavefronts, more
     (8, 32, 8 * 256, 256, 1), (8, 32, 9 * 256, 256, 2), (40, 40, 8 * 128, 128, 1),     # of four, beyond 1024
-    (8, 48, 8 * 64, 64, 1), (8, 49, 8 * 64, 64, 2), (8, 49, 8 * 112, 112, 2),          # 3072 of less than 128 keys
+    (8, 63, 8 * 64, 64, 1), (8, 64, 8 * 64, 64, 2), (8, 64, 8 * 112, 112, 2),          # 4096 of less than 128 keys
 ])
 def test_per_row(H, B, heads, Smax, chunk, launches):
     assert kernels(H, "fd_decode_attn", B, heads, heads, Smax, chunk) == launches
@@ -63,7 +63,7 @@ def test_append_and_paged(H, B, Hq, Hkv, Smax, page, chunk, launches):
 
 @pytest.mark.parametrize("B,heads,Smax,lens,chunk", [
     (8, 32, 512, [512, 1, 64, 300, 449, 511, 0, 130], 64),             # 2048 workgroups of eight chunks: in the launch
-    (8, 49, 512, [512, 1, 64, 300, 449, 511, 0, 130], 64),             # 3136: a second one
+    (8, 64, 512, [512, 1, 64, 300, 449, 511, 0, 130], 64),             # 4096: a second one
     (8, 32, 2048, [2048, 1, 1793, 300, 256, 2000, 0, 1100], 256),      # 2048, eight chunks of 256
     (8, 32, 2304, [2304, 1, 1793, 300, 256, 2000, 0, 2049], 256),      # 2304, nine
     (40, 40, 1024, [1024 - 25 * i for i in range(40)], 128),           # 12800 of 128 keys, eight chunks
