@@ -202,6 +202,16 @@ inline int elect_grouped(const fd::Problem &p)
     return (workgroups <= fd::kComputeUnits && p.nc <= 16) || (workgroups <= 3 * fd::kComputeUnits && p.nc <= 8);
 }
 
+// The synchronized scheme: heads that share a KV head take the grouped kernel's tile, which reads K and V once, not once per head.  Whole call,
+// per-row / grouped kernel: 17 x 12/2 x 4865 .. 9731 keys 134.7 / 25.3 us, 12 x 32/8 x 673 .. 5386 123.5 / 35.1, 2 x 64/8 x 72 .. 580 9.24 /
+// 7.82; of two heads to one 16 x 32/16 x 1500 61.3 / 33.6, 1 x 32/16 x 700 10.2 / 9.8, 1 x 8/4 x 9000 in 144-key chunks 14.7 / 12.7.  Not two heads
+// on a few KV heads in chunks that leave a wavefront one block of 16 keys: 1 x 2/1 x 9000 in 64 12.7 / 13.2, 4 x 2/1 x 4096 in 64 10.1 / 11.1 (in 96
+// 8 x 3000 9.85 / 9.66).
+inline bool sync_grouped(const fd::Problem &p)
+{
+    return p.G >= 2 && p.G <= 16 && (p.G > 2 || p.C >= 96 || (long long)p.B * p.Hkv >= 8);
+}
+
 #define FD_TRY(expr) do { if ((expr) != hipSuccess) return FD_ERR_HIP; } while (0)
 
 // A problem description that carries only the shape and the workspace views.
@@ -609,7 +619,7 @@ fd_status fd_decode_attn_sync(const fd_shape *shape, const void *q, const void *
     if (st != FD_OK) return st;
     if (p.rows == 0) return FD_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    FD_TRY(fd::launch_partial_sync(p, s));
+    FD_TRY(sync_grouped(p) ? fd::launch_partial_sync_gqa(p, s) : fd::launch_partial_sync(p, s));
     FD_TRY(fd::launch_combine_sync(p, s));
     return FD_OK;
 }

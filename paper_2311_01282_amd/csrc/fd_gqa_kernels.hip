@@ -52,7 +52,8 @@ struct GqaLds {
     // never live together.
     alignas(16) float tile[NW * 16 * kHeadDim];
     alignas(16) float den[16][NW];   // per head: the wavefronts' denominators ...
-    alignas(16) float inv[16][NW];   // ... and what takes their scales out of their tiles again
+    alignas(16) float inv[16][NW];   // ... and what takes their scales out of their tiles again (SYNC: the scale exponents ...
+    alignas(16) float top[16][NW];   // ... and the wavefronts' largest logits)
     alignas(16) unsigned mask[NW];   // heads out of bounds, and << 16 heads with a weight beyond the fp16 operand
     float e_new[16];                 // weight of an appended key per head (written where there is one)
     int last;
@@ -63,6 +64,7 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kFirstBlockLog2 = 4.f;    // a head's largest weight of the wavefront's first block lies in [2^3, 2^4] ...
 constexpr float kOverflowLog2 = 15.9f;    // ... and no later weight may reach 2^16 (fp16 ends at 65504)
+constexpr float kNoScale = 3e38f;         // SYNC: scale exponent of a head that has met no finite logit yet; any one sets it
 
 // Inclusive sum over the lanes of a wavefront.
 __device__ __forceinline__ int lanes_scan(int x)
@@ -157,7 +159,13 @@ __device__ __forceinline__ bool chunk_by_length(const Problem &p, int res, int &
 // contiguous cache; see decode_fused_kernel); kByLength: chunk_by_length.
 enum Start { kPlain, kEarly, kByLength };
 
-template <int C, bool PAGED, Start START, int NW = 4>
+// SYNC: the chunk's part of the synchronized partial softmax (Eq. 2; fd_decode_attn_sync) by the same tile: m = max x, l = sum
+// e^{x-m}, f.V = sum e^{x-m} v, no guard, no flag.  The scale 2^k of a (wavefront, head) stands in for the running maximum: it is set by the first block
+// as above, and where a later weight would reach 2^15.9 it is set anew and the sums are brought to it, exactly (a power of two); m itself enters
+// at the workgroup reduction.  Bound by HBM reads like the rest; the check is a compare and a branch per 16 keys.  The per-row form
+// read K and V once per query head, out of the caches where they held them: whole call, that / this, 5 x 28/4 heads x 14729 keys 107.0 / 28.8
+// us, 12 x 12/2 x 7924 79.4 / 20.0, 2 x 64/8 x 1000 10.5 / 8.35.
+template <int C, bool PAGED, Start START, bool SYNC = false, int NW = 4>
 __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_kernel(const Problem p)
 {
     static_assert(NW == 4 || NW == 8, "the appended key's lane assignment covers 16 heads with 4 wavefronts");
@@ -167,6 +175,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
     __shared__ GqaLds<NW> lds;
     constexpr int NBLK = C / 16;               // 16-key blocks in the chunk
     static_assert(!(PAGED && START == kEarly), "the page table has to arrive before the first load");
+    static_assert(!(PAGED && SYNC), "the synchronized entry point takes contiguous caches");
     constexpr bool EARLY = START == kEarly, BY_LENGTH = START == kByLength;
     fetch_arguments_now(p);
     asm volatile("" ::"s"(p.B), "s"(p.C), "s"(p.scatter), "s"(p.chunk_major));
@@ -229,15 +238,16 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
     const int nb = (S + len - 1) / len;
     const int nvalid = min(len, S - start);
     const int nres = min(len, S_res - start);
-    const bool owner = (S != S_res) & (S_res >= start) & (S_res < start + len);   // this chunk takes the appended key
+    const bool owner = !SYNC & (S != S_res) & (S_res >= start) & (S_res < start + len);   // this chunk takes the appended key
 
     if (!EARLY && nvalid <= 0) {               // padding chunk: zero partials, no flag (EARLY: by the ordinary path)
         for (int i = tid; i < G * kHeadDim; i += kGqaThreads)
             p.ws.num[((size_t)(row0 + i / kHeadDim) * p.nc + c) * kHeadDim + (i & (kHeadDim - 1))] = 0.f;
         if (tid < G) {
             const size_t slot = (size_t)(row0 + tid) * p.nc + c;
-            p.ws.den[slot] = 0.f; p.ws.mloc[slot] = p.phi;
-            p.ws.chunk_flags[slot] = 0; store_meta(p, slot, 0.f, p.phi, 0);
+            p.ws.den[slot] = 0.f; p.ws.mloc[slot] = SYNC ? -INFINITY : p.phi;
+            if (!SYNC) p.ws.chunk_flags[slot] = 0;
+            store_meta(p, slot, 0.f, p.phi, 0);
             if (nb == 0 && c == 0 && p.elect) p.ws.row_flags[row0 + tid] = 0;
         }
         if (nb == 0 && c == 0 && p.elect)      // empty sequence: nobody else owns these rows
@@ -258,8 +268,9 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
     float den = 0.f;
     bool bad = false;
     const bool head_on = n < G;
-    float kq = 0.f;                            // scale exponent of (this wavefront, head n), set by the first block
+    float kq = SYNC ? kNoScale : 0.f;          // scale exponent of (this wavefront, head n), set by the first block
     float zmax = -INFINITY;                    // largest log2 of a scaled weight of head n so far
+    float xmax = -INFINITY;                    // SYNC: largest logit of this lane's keys so far
     float neg1;                                // -1.0 the compiler cannot fold: keeps e - (float)hi one mixed-precision FMA
     asm("v_mov_b32 %0, -1.0" : "=v"(neg1));
 
@@ -309,10 +320,30 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             valid[r] = k0 + 4 * r + g <= last;
-            dd[r] = sc[r] * scale + nphi;
-            bad |= valid[r] & head_on & !((dd[r] > lo) & (dd[r] < hi));
+            dd[r] = SYNC ? sc[r] * scale : sc[r] * scale + nphi;
+            if constexpr (!SYNC) bad |= valid[r] & head_on & !((dd[r] > lo) & (dd[r] < hi));
         }
-        if (first) {
+        if constexpr (SYNC) {
+            float top = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) top = fmaxf(top, valid[r] ? dd[r] : -INFINITY);
+            xmax = fmaxf(xmax, top);
+            if (__ballot(__builtin_fmaf(top, kLog2e, kq) >= kOverflowLog2) != 0ull) {       // the first block; rarely another
+                // the four lane groups of a head hold different keys: they agree on the new scale
+                float m = fmaxf(top, __shfl_xor(top, 16));
+                m = fmaxf(m, __shfl_xor(m, 32));
+                const float k = __builtin_fmaf(m, kLog2e, kq) >= kOverflowLog2 ? kFirstBlockLog2 - ceilf(m * kLog2e) : kq;
+                const float by = __builtin_amdgcn_exp2f(k - kq);       // 0 where there was none (the sums are zeros then), 1 where it stays
+                kq = k;
+                den *= by;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float f = __shfl(by, 4 * g + r);             // acc[e][r] is of head 4g + r
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) acc[e][r] *= f;
+                }
+            }
+        } else if (first) {
             // the head's scale: the four lane groups of a head hold different keys and agree on the maximum first
             float m = -INFINITY;
 #pragma unroll
@@ -325,7 +356,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const float z = __builtin_fmaf(dd[r], kLog2e, kq);
-            zmax = fmaxf(zmax, valid[r] ? z : -INFINITY);
+            if constexpr (!SYNC) zmax = fmaxf(zmax, valid[r] ? z : -INFINITY);
             const float e = __builtin_amdgcn_exp2f(z);
             pw[r] = valid[r] ? e : 0.f;
             den += pw[r];
@@ -429,9 +460,15 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
     };
     const unsigned mask = heads_of(__ballot(bad)) | new_mask | heads_of(__ballot(head_on & (zmax >= kOverflowLog2))) << 16;
     // the scales are taken out where the tiles are added (exact: integer powers of two)
-    const float inv = __builtin_amdgcn_exp2f(-kq);
+    const float inv = SYNC ? kq : __builtin_amdgcn_exp2f(-kq);
     den = halves_sum(den, den);
-    den = rows_sum(den, den) * inv;
+    den = rows_sum(den, den);
+    if constexpr (SYNC) {
+        xmax = fmaxf(xmax, __shfl_xor(xmax, 16));
+        xmax = fmaxf(xmax, __shfl_xor(xmax, 32));
+    } else {
+        den *= inv;
+    }
     __syncthreads();                           // every wavefront is done with its K staging
     // acc[e][r] is (head 4g + r, d = 8n + e) of this wavefront's partial tile.
 #pragma unroll
@@ -445,7 +482,11 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
             dst[16] = make_float4(acc[4][r], acc[5][r], acc[6][r], acc[7][r]);
         }
     }
-    if (g == 0) { lds.den[n][wave] = den; lds.inv[n][wave] = inv; }
+    if (g == 0) {
+        lds.den[n][wave] = den;
+        lds.inv[n][wave] = inv;
+        if constexpr (SYNC) lds.top[n][wave] = xmax;
+    }
     if (lane == 0) lds.mask[wave] = mask;
     __syncthreads();
     unsigned any = 0;
@@ -461,6 +502,18 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         for (int w = 0; w < NW; ++w) s += lds.den[h][w];
         return s;
     };
+    // SYNC: head h's maximum over the chunk, and what brings each wavefront's sums from its scale to that reference (0 for a
+    // wavefront without a finite logit)
+    auto sync_scales = [&](int h, float (&by)[NW]) {
+        float m = lds.top[h][0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) m = fmaxf(m, lds.top[h][w]);
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+            by[w] = lds.top[h][w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(-__builtin_fmaf(m, kLog2e, lds.inv[h][w]));
+        return m;
+    };
+    bool unsound = false;                      // SYNC: this thread met a sum that is not a finite number, or an impossible l
     // A sequence of one chunk whose guard stayed quiet is complete here: its rows' results are
     // this workgroup's own sums, so they go out directly instead of through the workspace and
     // the epilogue (same arithmetic: the epilogue's factors are exactly 1 for such a row).
@@ -469,13 +522,17 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
     // bytes per thread, took 0.4 us more where the results are written through)
     for (int i = 4 * tid; i < G * kHeadDim; i += 4 * kGqaThreads) {
         float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+        float by[NW];
+        if constexpr (SYNC) sync_scales(i / kHeadDim, by);
 #pragma unroll
         for (int w = 0; w < NW; ++w) {         // wavefront order
             const float4 t = *reinterpret_cast<const float4 *>(&lds.tile[w * 16 * kHeadDim + i]);
-            const float k = lds.inv[i / kHeadDim][w];
+            const float k = SYNC ? by[w] : lds.inv[i / kHeadDim][w];
             o.x = __builtin_fmaf(k, t.x, o.x); o.y = __builtin_fmaf(k, t.y, o.y);
             o.z = __builtin_fmaf(k, t.z, o.z); o.w = __builtin_fmaf(k, t.w, o.w);
         }
+        if constexpr (SYNC)
+            unsound |= !(fabsf(o.x) + fabsf(o.y) + fabsf(o.z) + fabsf(o.w) < INFINITY);
         const int q = i & (kHeadDim - 1);      // LDS position -> element index (see the layout above)
         const int d0 = 2 * (q & 63) + 4 * (q >> 6);
         if (owner) {                           // + e_new[head] * v_new[d0 .. d0 + 3]
@@ -499,6 +556,29 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         } else {
             *reinterpret_cast<float4 *>(dst) = o;
         }
+    }
+    if constexpr (SYNC) {
+        if (wave == NW - 1 && lane < G) {
+            float by[NW], s = 0.f;
+            const float m = sync_scales(lane, by);
+#pragma unroll
+            for (int w = 0; w < NW; ++w) s = __builtin_fmaf(by[w], lds.den[lane][w], s);
+            unsound |= !(s >= 0.5f);                               // the largest logit alone makes it 1
+            const size_t slot = (size_t)(row0 + lane) * p.nc + c;
+            store_coherent(&p.ws.den[slot], s);
+            store_coherent(&p.ws.mloc[slot], m);
+            store_meta(p, slot, s, m, 1);
+        }
+        // Where a logit or a V element is not a finite number the result is what the per-row path makes of it (hi and lo parts of a
+        // weight would turn an infinite V element into NaN).
+        if (__syncthreads_or(unsound) && nvalid > 0) {
+            wait_stores_performed();           // the stores above must not overtake the rewrite
+            for (int h = 0; h < G; ++h) {
+                __syncthreads();
+                chunk_body<C, NW, UP, true, C>(p, row0 + h, c, *reinterpret_cast<ChunkLds<NW, C> *>(lds.tile));
+            }
+        }
+        return;
     }
     if (wave == NW - 1 && lane < G) {
         const float s = den_of(lane);
@@ -545,7 +625,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
     group_epilogue(p, row0, G, nb);
 }
 
-template <int C> struct GqaLauncher {
+template <int C, bool SYNC> struct GqaLauncher {
     static hipError_t run(const Problem &p0, hipStream_t s)
     {
         const long long groups = (long long)p0.B * p0.Hkv;
@@ -568,29 +648,35 @@ template <int C> struct GqaLauncher {
         // Early loads in the launches of one workgroup per compute unit: 2 x 64/8 x 9001 17.1 / 16.8 us, 4 x 32/8 x 4096 14.85 /
         // 14.6, 1 x 28/4 x 700 7.4 / 7.15.
         const dim3 g(grid), t(256);
-        if (grid > (unsigned)kComputeUnits && grid <= 4096u && p.B <= 64)
-            return p.block_table ? launch(decode_fused_gqa_kernel<C, true, kByLength>, g, t, s, p)
-                                 : launch(decode_fused_gqa_kernel<C, false, kByLength>, g, t, s, p);
-        if (p.block_table) return launch(decode_fused_gqa_kernel<C, true, kPlain>, g, t, s, p);
-        return grid <= (unsigned)kComputeUnits ? launch(decode_fused_gqa_kernel<C, false, kEarly>, g, t, s, p)
-                                               : launch(decode_fused_gqa_kernel<C, false, kPlain>, g, t, s, p);
+        const bool by_length = grid > (unsigned)kComputeUnits && grid <= 4096u && p.B <= 64;
+        if constexpr (!SYNC) {
+            if (p.block_table)
+                return by_length ? launch(decode_fused_gqa_kernel<C, true, kByLength>, g, t, s, p)
+                                 : launch(decode_fused_gqa_kernel<C, true, kPlain>, g, t, s, p);
+        }
+        return by_length                          ? launch(decode_fused_gqa_kernel<C, false, kByLength, SYNC>, g, t, s, p)
+               : grid <= (unsigned)kComputeUnits ? launch(decode_fused_gqa_kernel<C, false, kEarly, SYNC>, g, t, s, p)
+                                                 : launch(decode_fused_gqa_kernel<C, false, kPlain, SYNC>, g, t, s, p);
     }
 };
 
 }  // namespace
 
-hipError_t launch_decode_fused_gqa(const Problem &p, hipStream_t s)
+template <bool SYNC> static hipError_t dispatch_gqa(const Problem &p, hipStream_t s)
 {
     switch (chunk_capacity(p.C)) {
-        case 64:   return GqaLauncher<64>::run(p, s);
-        case 128:  return GqaLauncher<128>::run(p, s);
-        case 256:  return GqaLauncher<256>::run(p, s);
-        case 512:  return GqaLauncher<512>::run(p, s);
-        case 1024: return GqaLauncher<1024>::run(p, s);
-        case 2048: return GqaLauncher<2048>::run(p, s);
-        case 4096: return GqaLauncher<4096>::run(p, s);
+        case 64:   return GqaLauncher<64, SYNC>::run(p, s);
+        case 128:  return GqaLauncher<128, SYNC>::run(p, s);
+        case 256:  return GqaLauncher<256, SYNC>::run(p, s);
+        case 512:  return GqaLauncher<512, SYNC>::run(p, s);
+        case 1024: return GqaLauncher<1024, SYNC>::run(p, s);
+        case 2048: return GqaLauncher<2048, SYNC>::run(p, s);
+        case 4096: return GqaLauncher<4096, SYNC>::run(p, s);
         default:   return hipErrorInvalidValue;
     }
 }
+
+hipError_t launch_decode_fused_gqa(const Problem &p, hipStream_t s) { return dispatch_gqa<false>(p, s); }
+hipError_t launch_partial_sync_gqa(const Problem &p, hipStream_t s) { return dispatch_gqa<true>(p, s); }
 
 }  // namespace fd

@@ -128,6 +128,7 @@ hipError_t launch_clear_tickets(int32_t *ticket, size_t n, hipStream_t s);
 hipError_t launch_row_epilogue(const Problem &p, hipStream_t s);
 // fd_gqa_kernels.hip : one KV head (a group of query heads) per workgroup (MFMA path)
 hipError_t launch_decode_fused_gqa(const Problem &p, hipStream_t s);
+hipError_t launch_partial_sync_gqa(const Problem &p, hipStream_t s);      // contiguous cache, nothing appended
 // fd_stats_kernels.hip : histogram of the scaled logits (uses q, k, seq_lens and the shape only)
 hipError_t launch_logit_histogram(const Problem &p, float x_min, float bin_width, int n_bins,
                                   unsigned long long *hist, float *min_max, hipStream_t s);

@@ -1,0 +1,80 @@
+"""The synchronized scheme where query heads share KV heads (the matrix-core tile of the grouped decode kernel), against the fp64
+oracle: every group size's edges, ragged and empty sequences, the launch's three orders, logits that climb, fall and lie far from zero
+(the tile's scale is set anew, or far below the first one), and values that are not finite numbers, which come out as from heads of their own."""
+import numpy as np
+import pytest
+
+from paper_2311_01282_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def H():
+    import fd_harness
+    return fd_harness
+
+
+def _ramp(case, lo, hi):
+    """Logits that run from lo to hi along each sequence: one element of every key, times one of q."""
+    case["q"][..., 0] = 16.0
+    for b, n in enumerate(np.clip(case["seq_lens"], 0, case["Smax"])):
+        if n:
+            case["k"][b, :, :n, 0] = (np.linspace(lo, hi, n) / (16.0 * case["scale"])).astype(np.float16)
+
+
+def _check(oracle, H, case, chunk, what, ramp):
+    want = oracle.attn_exact(case["q"], case["k"], case["v"], case["seq_lens"], case["scale"], nthreads=8)
+    got = H.DeviceCase(case, chunk=chunk).run("fd_decode_attn_sync")
+    if ramp is None:
+        H.assert_close(got, want, what)
+        return
+    # A logit is an fp32 sum in which one product dominates: up to 24 roundings of its size (128 products in four instructions of 32 or
+    # 16 lanes of eight, the scale, the reference taken off), each 2^-24 of |x|.  A weight carries that as a relative error, the
+    # mean of V twice that times the largest |v|.
+    delta = 24 * 2.0 ** -24 * (max(abs(x) for x in ramp) + 10.0)
+    assert np.isfinite(got).all(), what
+    err = np.abs(got - want).max(initial=0.0)
+    tol = 2.0 ** -11 * np.abs(want).max() + 2.0 * delta * np.nanmax(np.abs(case["v"].astype(np.float64)))
+    assert err <= tol, "%s: max-abs %.3e (tol %.3e)" % (what, err, tol)
+
+
+# (batch, query heads, KV heads, lengths, max_seq, chunk): one launch of up to 256 workgroups; more, in order of length; more than 64
+# sequences, in plain order; two heads sharing one on few workgroups of 64 keys (the per-row kernel) and of 96 (the tile)
+@pytest.mark.parametrize("B,Hq,Hkv,lens,Smax,chunk", [
+    (4, 16, 2, [1, 15, 16, 17], 80, 64),
+    (3, 16, 1, [0, 700, 64], 700, 64),
+    (2, 4, 2, [300, 129], 300, 128),
+    (2, 15, 3, [1024, 1009], 1024, 80),
+    (1, 17, 1, [200], 200, 64),
+    (1, 8, 1, [4096 + 33], 4200, 4096),
+    (5, 10, 5, [3000, 1, 0, 2048, 1999], 3000, 160),
+    (70, 8, 4, list(range(1, 71)), 128, 64),
+    (2, 12, 2, [64 * 40, 64 * 33 + 1], 64 * 40, 64),
+    (1, 2, 1, [900], 900, 64),
+    (1, 2, 1, [900], 900, 96),
+])
+@pytest.mark.parametrize("ramp", [None, (-150.0, 150.0), (150.0, -150.0), (-900.0, -880.0), (700.0, 720.0)])
+def test_grouped_rows(oracle, H, B, Hq, Hkv, lens, Smax, chunk, ramp):
+    case = synth.make_case(B=B, Hq=Hq, Hkv=Hkv, D=128, Smax=Smax, seed=9300 + Hq + Smax, seq_lens=lens, poison_padding=True)
+    if ramp:
+        _ramp(case, *ramp)
+    _check(oracle, H, case, chunk, "%d x %d/%d, %s" % (B, Hq, Hkv, ramp), ramp)
+
+
+@pytest.mark.parametrize("what", ["v_inf", "v_nan", "k_nan", "k_inf", "k_minus_inf"])
+def test_not_finite_as_from_heads_of_their_own(H, what):
+    G, Hkv, Smax = 4, 3, 500
+    case = synth.make_case(B=1, Hq=G * Hkv, Hkv=Hkv, D=128, Smax=Smax, seed=9400, seq_lens=[Smax])
+    if what[0] == "v":
+        case["v"][0, 1, 77, 5] = np.inf if what == "v_inf" else np.nan
+    else:
+        case["q"][..., 9] = np.abs(case["q"][..., 9]) + np.float16(0.25)          # no zero times infinity
+        case["k"][0, 1, 77, 9] = {"k_nan": np.nan, "k_inf": np.inf, "k_minus_inf": -np.inf}[what]
+    got = H.DeviceCase(case, chunk=128).run("fd_decode_attn_sync")
+    own = dict(case, Hkv=G * Hkv, k=np.repeat(case["k"], G, axis=1), v=np.repeat(case["v"], G, axis=1))
+    want = H.DeviceCase(own, chunk=128).run("fd_decode_attn_sync")
+    fin = np.isfinite(want)
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~fin], want[~fin], equal_nan=True)
+    assert np.abs(got[fin] - want[fin]).max() <= H.ABS_TOL
+    assert fin.all() == (what == "k_minus_inf")
