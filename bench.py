@@ -214,8 +214,8 @@ class Runner:
 
     def kernel_name(self):
         """The chunk kernel of this launch, with its template arguments as the profiler prints them (namespaces left out): <chunk
-        capacity, paged, start variant, wavefronts> for the grouped kernel, <chunk capacity, in-kernel hand-over, paged, early
-        loads, one block in flight> for the per-row one."""
+        capacity, paged, start variant, synchronized, wavefronts> for the grouped kernel, <chunk capacity, in-kernel hand-over, paged, early
+        loads, one block in flight, synchronized> for the per-row one."""
         wl = self.wl
         cap = 64
         while cap < self.chunk:
@@ -223,10 +223,10 @@ class Runner:
         if self.gqa:
             grid = 8 * ((wl.B * wl.Hkv + 7) // 8) * self.nc
             start = 1 if grid <= 256 else (2 if grid <= 4096 and wl.B <= 64 else 0)
-            return "decode_fused_gqa_kernel<%d, false, (Start)%d, 4>" % (cap, start)
+            return "decode_fused_gqa_kernel<%d, false, (Start)%d, false, 4>" % (cap, start)
         early = self.single_launch and self.grid <= 256
         one = not early and 256 <= cap <= 1024 and (self.nc > 32 or (not self.single_launch and wl.B * wl.Hq * self.nc > 768))
-        return "decode_fused_kernel<%d, %s>" % (cap, ", ".join("true" if x else "false" for x in (self.single_launch, False, early, one)))
+        return "decode_fused_kernel<%d, %s>" % (cap, ", ".join("true" if x else "false" for x in (self.single_launch, False, early, one, False)))
 
     def step(self, i):
         wl, fdattn = self.wl, self.wl.fdattn

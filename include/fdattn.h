@@ -10,7 +10,8 @@
  * partial softmax of Eq. 2 instead (Section 3, "Recomputation").  How much of a
  * flagged row is re-read differs by entry point: fd_decode_attn_multikernel
  * recomputes every chunk of the row, as the paper's text has it; fd_decode_attn
- * and its variants recompute only the chunks that left the bounds and merge all
+ * goes over to the synchronized scheme where a chunk leaves the bounds and reads
+ * nothing again, its grouped variants recompute the chunks that did; both merge all
  * of the row's partial results by Eq. 2 (see the description of each call).
  *
  * Conventions common to every call
@@ -139,14 +140,17 @@ fd_status fd_workspace_init(const fd_shape *shape, fd_workspace ws, void *stream
  * one kernel launch (two for large grids, see step 3).  Per (row, chunk) workgroup:
  *   1. logits, range guard, sum e^{x-phi} and sum e^{x-phi} v with no maximum
  *      and no rescaling                               (Eq. 4, inner sums);
- *   2. if the guard fired for this chunk, its partial softmax is recomputed at
- *      once with the chunk's own maximum: (m, l, f.V)  (Eq. 2; "Recomputation");
+ *   2. where the guard fires, the keys from there on are summed by the synchronized
+ *      scheme, with a reference of their own, and what was summed before is brought to
+ *      it: (m, l, f.V)  (Eq. 2; "Recomputation").  Bounds below -64 or above 60 admit
+ *      sums that cannot be brought to another reference in fp32: with those the chunk
+ *      is recomputed at once instead;
  *   3. the workgroup that completes a row last -- elected by a small tree of
  *      integer arrival counters per row; the sums themselves use no atomics and
  *      run in fixed order -- forms the row: unflagged rows by the plain outer
  *      sums of Eq. 4, flagged rows by the synchronized update of Eq. 2 over all
- *      partial results, each rescaled from its own reference (phi, or the chunk
- *      maximum) to the row maximum of those references.  Some launches run step 3 as
+ *      partial results, each rescaled from its own reference (phi, or that of
+ *      step 2) to the row maximum of those references.  Some launches run step 3 as
  *      a second, tiny launch instead (no counters), where the election's memory round
  *      trips per workgroup cost more than that: rows of more than 128 chunks; rows of more than 8
  *      chunks in more than 1024 workgroups, or in more than 768 (960 for more than 32 chunks) over
@@ -154,9 +158,9 @@ fd_status fd_workspace_init(const fd_shape *shape, fd_workspace ws, void *stream
  *      more than 256 keys in more than 1024 workgroups, of less than 128 in 4096 and more
  *      (fd_decode_attn_gqa: more than 16 chunks per row, or more than 256 workgroups, 768
  *      for rows of up to 8 chunks).
- * A flagged row is thus produced by the synchronized scheme, but only the
- * partial vectors that left the bounds are re-read; the others already are
- * valid partial-softmax results relative to phi.  fd_decode_attn_multikernel
+ * A flagged row is thus produced by the synchronized scheme, in which the partial
+ * vectors that stayed in the bounds already are valid partial-softmax results
+ * relative to phi.  fd_decode_attn_multikernel
  * recomputes every chunk of a flagged row instead; both give the same result up
  * to fp32 rounding.  Works for any head grouping (each query head is a row).
  * Requires fd_workspace_init.  Fills chunk_flags and row_flags.
@@ -361,8 +365,9 @@ fd_status fd_list_flagged_rows(const fd_shape *shape, const int32_t *seq_lens,
  * Device pointers into `ws` to the per-chunk partial results (D3 of Eq. 4):
  *   num [batch*n_q_heads, ceil(max_seq/chunk), head_dim] fp32 = sum e^{x-phi} v
  *   den [batch*n_q_heads, ceil(max_seq/chunk)]           fp32 = sum e^{x-phi}
- * Chunks without a valid key hold zeros.  Chunks that were recomputed hold the
- * synchronized scheme's (f.V, l) instead.
+ * Chunks without a valid key hold zeros.  Chunks whose guard fired or that were
+ * recomputed hold the synchronized scheme's (f.V, l) instead, by a reference of
+ * their own; after fd_decode_attn_sync all do.
  */
 fd_status fd_get_partials(const fd_shape *shape, fd_workspace ws,
                           const float **num, const float **den);

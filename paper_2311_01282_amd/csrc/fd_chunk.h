@@ -168,27 +168,72 @@ __device__ __forceinline__ float rows_sum(float a, float b)
     return as_f32(x) + as_f32(y);
 }
 
-// LDS of one workgroup of NW wavefronts.  XN = number of logits kept for the
-// synchronized scheme.
-template <int NW, int XN>
+// The maximum over the four rows of 16 of a wavefront, in every lane.
+__device__ __forceinline__ float columns_max(float a)
+{
+    const unsigned u = __builtin_bit_cast(unsigned, a);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned r0 = r[0], r1 = r[1];
+    const unsigned v = __builtin_bit_cast(unsigned, fmaxf(as_f32(r0), as_f32(r1)));
+    const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    const unsigned h0 = h[0], h1 = h[1];
+    return fmaxf(as_f32(h0), as_f32(h1));
+}
+
+// LDS of one workgroup of NW wavefronts.
+template <int NW>
 struct ChunkLds {
     alignas(16) float acc[NW][kHeadDim];   // [wave][pairs of elements, see chunk_body]
     alignas(16) float den[NW];
     alignas(16) int   flag[NW];
-    float x[XN];
-    float mx[NW];
+    alignas(16) float ref[NW];             // what the wavefronts' sums are scaled by ...
+    alignas(16) float top[NW];             // ... and, in the synchronized scheme, their largest logits
 };
+
+// References that move (chunk_body).
+constexpr float kNoRef = -3e38f;           // the largest logit of no logit
+constexpr float kRaise = 40.f;             // a logit this far above the wavefront's reference raises it
+// The bounds within which the weights of in-range logits leave sums that can be brought to another reference: e^-64 and 4096 e^60 max|v|
+// are ordinary fp32 numbers.
+constexpr float kInPlaceLo = -64.f, kInPlaceHi = 60.f;
+
+// A wavefront's four columns of sums added in registers, exchanging halves and rows of
+// two registers at a time, so that lane (sub, seg) ends up with elements 8 seg + 2 sub and the next: 12 instructions.
+__device__ __forceinline__ void wave_sums(const float (&acc)[8], float &den, float (&u)[2])
+{
+    float t[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = halves_sum(acc[i], acc[i + 4]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) u[i] = rows_sum(t[i], t[i + 2]);
+    den = halves_sum(den, den);
+    den = rows_sum(den, den);
+}
+// The pair of lane (sub, seg), number 4 seg + sub of its vector, sits in place 4 seg + (sub ^ 2 (seg / 8)) of a wavefront's vector in LDS: few bank
+// conflicts there (4 cycles per wavefront), and none where lane l reads pair l back, so that the slot is written in whole lines (pairs stored as the
+// lanes hold them, 32 bytes apart, cost launches of full caches 1 %).
+__device__ __forceinline__ float2 *sums_place(float *acc, int lane)
+{
+    const int seg = lane & 15, sub = lane >> 4;
+    return reinterpret_cast<float2 *>(acc + 8 * seg + 2 * (sub ^ ((seg >> 2) & 2)));
+}
+__device__ __forceinline__ const float2 *sums_read(const float *acc, int lane)
+{
+    return reinterpret_cast<const float2 *>(acc + 2 * (lane ^ ((lane >> 4) & 2)));
+}
 
 // One (row, chunk) on the VALU path, by a workgroup of NW wavefronts.
 //   SYNC == false : unified scaling factor phi -- Eq. 4 inner sums and the range
 //                   guard of Section 3 "Recomputation".  Writes num, den,
-//                   chunk_flags and mloc = phi (the reference the sums are scaled by).
-//   SYNC == true  : the chunk's part of the synchronized partial softmax, Eq. 2:
-//                   m = max x, l = sum e^{x-m}, f.V = sum e^{x-m} v.  Writes num,
-//                   den, mloc = m and leaves chunk_flags alone; `sync_flag` is what the
+//                   chunk_flags and mloc = phi (the reference the sums are scaled by).  Where the guard fires the wavefront goes on by the
+//                   synchronized scheme from that block of keys on (see `adapt` below), and the slot's reference is the largest of its
+//                   wavefronts'; with bounds beyond kInPlaceLo, kInPlaceHi the caller has to redo the chunk instead.
+//   SYNC == true  : the chunk's part of the synchronized partial softmax, Eq. 2, in one pass: a wavefront keeps a reference that
+//                   a logit more than kRaise above it raises, and its sums are brought to m = max x at the end: l = sum e^{x-m}, f.V = sum
+//                   e^{x-m} v.  Writes num, den, mloc = m and leaves chunk_flags alone; `sync_flag` is what the
 //                   slot's record tells the row epilogue about the guard.
 // UP = groups of 4 keys per wavefront per pipeline stage.
-// Returns (uniformly over the workgroup) whether the guard fired (false for SYNC).
+// Returns (uniformly over the workgroup) whether the chunk has to be redone with SYNC.
 // Pins the kernel arguments the chunk loop needs into scalar registers at this point,
 // so that their loads leave in one batch at the top of the kernel.  Left alone the
 // compiler fetches each cache line of the argument block where it is first used --
@@ -264,24 +309,25 @@ template <bool PAGED> struct KvRows {
     }
 };
 
-// EARLY (unified scheme only): the first block's loads are issued before the
+// EARLY: the first block's loads are issued before the
 // sequence length has arrived, clamped to the chunk's extent in the padded buffer
 // instead of to the last valid key; what they bring in from beyond the valid
 // length is replaced by zeros before use.  Takes the length load off the critical
 // path of a short launch; a padding chunk then reads one block for nothing, so
 // large ragged launches leave it off.
-// ONE (unified scheme only): a wavefront asks for a block of keys only when the one before has arrived, instead of
+// ONE: a wavefront asks for a block of keys only when the one before has arrived, instead of
 // keeping two in flight (LoadAhead in fd_row_kernels.hip says where).
-template <int C, int NW, int UP, bool SYNC, int XN, bool EARLY = false, bool PAGED = false, bool ONE = false>
-__device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, ChunkLds<NW, XN> &lds, int *len_out = nullptr,
+template <int C, int NW, int UP, bool SYNC, bool EARLY = false, bool PAGED = false, bool ONE = false>
+__device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, ChunkLds<NW> &lds, int *len_out = nullptr,
                                            int sync_flag = 1)
 {
-    static_assert(!(EARLY && SYNC), "early loads belong to the unified scheme");
     static_assert(!(EARLY && PAGED), "the page table has to arrive before the first load");
-    static_assert(!SYNC || XN >= C, "the synchronized scheme keeps the chunk's logits in LDS");
     constexpr int NG = C / (4 * NW);           // groups of 4 keys each wavefront handles
     static_assert(NG >= 1 && NG % UP == 0, "chunk, wavefront count and stage depth must divide");
     constexpr int NBLK = NG / UP;
+    // Keys whose logits are checked together, before any of them is added: a stage, but half of one where its registers would take a
+    // wavefront per SIMD (133 in the long paged kernels).  One or two at a time made no difference elsewhere (23 shapes within 1 %).
+    constexpr int UG = PAGED && C >= 1024 ? 2 : UP;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int seg = lane & 15, sub = lane >> 4;
@@ -343,14 +389,36 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
 
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float den = 0.f;
-    float mc = p.phi;
 
-    if constexpr (!SYNC) {
-        // Software pipeline over blocks of UP groups: the loads of block i+1 are in
-        // flight while block i is reduced.  Keys past the valid length re-read the
-        // last valid key (always in bounds, never padding) and get weight zero.
-        const float nphi = -p.phi, lo = p.lo, hi = p.hi, scale = p.scale;
-        bool bad = false;
+    // Software pipeline over blocks of UP groups: the loads of block i+1 are in
+    // flight while block i is reduced.  Keys past the valid length re-read the
+    // last valid key (always in bounds, never padding) and get weight zero.
+    const float scale = p.scale;
+    float nref = SYNC ? 0.f : -p.phi;          // minus this wavefront's reference
+    float lo = SYNC ? INFINITY : p.lo, hi = SYNC ? kRaise : p.hi;                 // (SYNC: the first block in any case)
+    const bool in_place = SYNC || (p.lo >= kInPlaceLo && p.hi <= kInPlaceHi);     // uniform
+    bool out_of_range = false;                 // a logit of this wavefront was outside (lo, hi)
+    float xmax = kNoRef;                       // SYNC: largest logit of this lane's keys
+    // A logit is out of range: the wavefront's reference becomes the largest of the block, or stays if it is larger, and the sums
+    // are brought to it (Eq. 2); from here on only a logit far above moves it again.  Without sums it takes that largest in any case.
+    // d: this lane's largest, less the reference; returns by how much the reference moves.  (Re-reading the chunk by a second,
+    // synchronized pass cost a short launch the time in which one workgroup streams a chunk by itself: whole call with one flagged row, that / this,
+    // 1 x 32 x 8192 34.1 / 22.4 us, 4 x 16 x 6400 53.2 / 35.5, 1 x 32 x 1024 9.0 / 6.1, 1 x 16 x 9000 .. 60000 96 / 79.7.)
+    auto adapt = [&](float d) {
+        d = columns_max(d);
+        const bool fresh = __ballot(den != 0.f) == 0ull;
+        const float by = d == -INFINITY ? 0.f : fresh ? d : fmaxf(d, 0.f);
+        if (!fresh) {
+            const float f = __builtin_amdgcn_exp2f(-by * kLog2e);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] *= f;
+            den *= f;
+        }
+        nref -= by;
+        if (d != -INFINITY) { lo = -INFINITY; hi = kRaise; }
+        return by;
+    };
+    {
         // Rows of more than 32 chunks: every workgroup starts its chunk at a different block and wraps
         // around (the sums do not care about the order).  The workgroups of such a launch start at
         // addresses a power of two apart and walk them in step, and for some shapes the memory system
@@ -369,15 +437,35 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
         auto reduce = [&](int blk0, const u32x4 (&kk)[UP], const u32x4 (&vv)[UP]) {
             const int blk = phys(blk0);
 #pragma unroll
-            for (int u = 0; u < UP; ++u) {
-                const bool valid = key_of(blk * UP + u) <= last;
-                const float x = row16_sum(dot8(qv, kk[u])) * scale;
-                const float d = x + nphi;                       // x - phi
-                bad |= valid & !((d > lo) & (d < hi));          // equality and NaN flag
-                float e = __builtin_amdgcn_exp2f(d * kLog2e);   // e^{x - phi}
-                e = valid ? e : 0.f;
-                den += e;
-                axpy8(acc, e, vv[u]);
+            for (int u0 = 0; u0 < UP; u0 += UG) {
+                bool valid[UG], bad = false;
+                float d[UG];
+#pragma unroll
+                for (int u = 0; u < UG; ++u) {
+                    valid[u] = key_of(blk * UP + u0 + u) <= last;
+                    const float x = row16_sum(dot8(qv, kk[u0 + u])) * scale;
+                    if constexpr (SYNC) xmax = fmaxf(xmax, valid[u] ? x : kNoRef);
+                    d[u] = x + nref;                                // x - phi
+                    bad |= valid[u] & !((d[u] > lo) & (d[u] < hi)); // equality and NaN flag
+                }
+                if (__builtin_expect(__ballot(bad) != 0ull, 0)) {
+                    out_of_range = true;
+                    if (in_place) {
+                        float top = -INFINITY;
+#pragma unroll
+                        for (int u = 0; u < UG; ++u) top = fmaxf(top, valid[u] ? d[u] : -INFINITY);
+                        const float by = adapt(top);
+#pragma unroll
+                        for (int u = 0; u < UG; ++u) d[u] -= by;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < UG; ++u) {
+                    float e = __builtin_amdgcn_exp2f(d[u] * kLog2e);   // e^{x - phi}
+                    e = valid[u] ? e : 0.f;
+                    den += e;
+                    axpy8(acc, e, vv[u0 + u]);
+                }
             }
         };
         u32x4 kB[UP], vB[UP];
@@ -438,102 +526,42 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
                 reduce(blk, kA, vA);
             }
         }
-        if (owner && wave == 0 && sub == 0) {
+        if (owner && wave == 0) {
             // The appended key: one more term of Eq. 4, taken from the step's own K/V rows by
-            // the 16 lanes of the first key column, which also put the rows into the cache.
+            // the 16 lanes of the first key column, which also put the rows into the cache (a chunk that is redone has
+            // stored them already).
             const u32x4 kn = *knp, vn = *vnp;
-            const float d = row16_sum(dot8(qv, kn)) * scale + nphi;
-            bad |= !((d > lo) & (d < hi));
-            const float e = __builtin_amdgcn_exp2f(d * kLog2e);
-            den += e;
-            axpy8(acc, e, vn);
-            if (hq == hkv * p.G) {                  // one writer per KV head
-                reinterpret_cast<u32x4 *>(p.k_store)[row_new + seg] = kn;
-                reinterpret_cast<u32x4 *>(p.v_store)[row_new + seg] = vn;
+            const float x = row16_sum(dot8(qv, kn)) * scale;
+            if constexpr (SYNC) xmax = fmaxf(xmax, x);
+            float d = x + nref;
+            if (!((d > lo) & (d < hi))) {
+                out_of_range = true;
+                if (in_place) d -= adapt(d);
             }
-        }
-        const unsigned long long any_bad = __ballot(bad);
-        if (lane == 0) lds.flag[wave] = any_bad != 0ull;
-    } else {
-        // Pass 1: logits of the whole chunk into LDS, and their maximum.  An appended key
-        // takes its place at offset jn with the logit of the step's own K row; loads of
-        // non-resident positions are clamped into the chunk and their values replaced.
-        float m = -INFINITY;
-        const float scale = p.scale;
-        const int jnew = owner ? jn : -1;
-        u32x4 vn = {0u, 0u, 0u, 0u};
-        float x_new = -INFINITY;
-        if (owner) {
-            x_new = row16_sum(dot8(qv, *knp)) * scale;
-            vn = *vnp;
-        }
-        const int nblk_all = min(NBLK, (nvalid + UP * NW * 4 - 1) / (UP * NW * 4));
-#pragma unroll 1
-        for (int blk = 0; blk < nblk_all; ++blk) {
-            u32x4 kk[UP];
-#pragma unroll
-            for (int u = 0; u < UP; ++u) kk[u] = load_stream(kp + at(max(min(key_of(blk * UP + u), last), 0)));
-#pragma unroll
-            for (int u = 0; u < UP; ++u) {
-                const int kidx = key_of(blk * UP + u);
-                float x = row16_sum(dot8(qv, kk[u])) * scale;
-                x = kidx <= last ? x : (kidx == jnew ? x_new : -INFINITY);
-                if (seg == 0) lds.x[kidx] = x;
-                m = fmaxf(m, x);
-            }
-        }
-        // chunk maximum: over the 4 keys of the lane's column, then the wavefronts
-        m = fmaxf(m, __shfl_xor(m, 16));
-        m = fmaxf(m, __shfl_xor(m, 32));
-        if (lane == 0) lds.mx[wave] = m;
-        __syncthreads();
-        mc = lds.mx[0];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) mc = fmaxf(mc, lds.mx[w]);
-        // Pass 2: e^{x - m} and the V products.
-#pragma unroll 1
-        for (int blk = 0; blk < nblk_all; ++blk) {
-            u32x4 vv[UP];
-#pragma unroll
-            for (int u = 0; u < UP; ++u) vv[u] = load_stream(vp + at(max(min(key_of(blk * UP + u), last), 0)));
-#pragma unroll
-            for (int u = 0; u < UP; ++u) {
-                const int kidx = key_of(blk * UP + u);
-                const float e = __builtin_amdgcn_exp2f((lds.x[kidx] - mc) * kLog2e);   // 0 for padding
+            if (sub == 0) {
+                const float e = __builtin_amdgcn_exp2f(d * kLog2e);
                 den += e;
-                // the appended V row for its key, and for every key when no resident row was
-                // there to clamp to (weight zero then, but the cache may hold anything)
-                axpy8(acc, e, ((kidx == jnew) | (nres <= 0)) ? vn : vv[u]);
+                axpy8(acc, e, vn);
+                if (!SYNC && hq == hkv * p.G) {     // one writer per KV head
+                    reinterpret_cast<u32x4 *>(p.k_store)[row_new + seg] = kn;
+                    reinterpret_cast<u32x4 *>(p.v_store)[row_new + seg] = vn;
+                }
             }
-        }
-        if (owner && hq == hkv * p.G && wave == 0 && sub == 0 && p.k_store) {
-            // a recomputed chunk of the fused kernels has stored the rows already; the
-            // synchronized entry points come here first
-            reinterpret_cast<u32x4 *>(p.k_store)[row_new + seg] = *knp;
-            reinterpret_cast<u32x4 *>(p.v_store)[row_new + seg] = vn;
         }
     }
+    if constexpr (SYNC) {
+        xmax = columns_max(xmax);
+        if (lane == 0) lds.top[wave] = xmax;
+    }
+    if (lane == 0) { lds.flag[wave] = out_of_range; lds.ref[wave] = -nref; }
 
     if constexpr (!SYNC) FD_PHASE(2);
-    // Workgroup reduction.  Within a wavefront the four keys of a group are added in registers, exchanging halves and rows of
-    // two registers at a time, so that lane (sub, seg) ends up with elements 8 seg + 2 sub and the next: 12 instructions.
-    // Then wavefront 0 adds the others' sums and writes the slot by itself, and what follows (the arrival, the row's
-    // finish) needs no barrier; the other wavefronts are done and make room.  (Before, all NW * 4 vectors went through LDS and two
-    // wavefronts added them, with a barrier before and after the arrival.)
+    // Workgroup reduction.  Within a wavefront in registers; then wavefront 0 adds the others' sums and writes the slot by itself, and
+    // what follows (the arrival, the row's finish) needs no barrier; the other wavefronts are done and make room.  (Before, all NW * 4 vectors
+    // went through LDS and two wavefronts added them, with a barrier before and after the arrival.)
     float u[2];
-    {
-        float t[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) t[i] = halves_sum(acc[i], acc[i + 4]);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) u[i] = rows_sum(t[i], t[i + 2]);
-        den = halves_sum(den, den);
-        den = rows_sum(den, den);
-    }
-    // The pair of lane (sub, seg), number 4 seg + sub of its vector, sits in place 4 seg + (sub ^ 2 (seg / 8)): few bank
-    // conflicts here (4 cycles per wavefront), and none where lane l reads pair l back, so that the slot is written in whole lines (pairs stored as the
-    // lanes hold them, 32 bytes apart, cost launches of full caches 1 %).
-    *reinterpret_cast<float2 *>(&lds.acc[wave][8 * seg + 2 * (sub ^ ((seg >> 2) & 2))]) = make_float2(u[0], u[1]);
+    wave_sums(acc, den, u);
+    *sums_place(lds.acc[wave], lane) = make_float2(u[0], u[1]);
     if (lane == 0) lds.den[wave] = den;
     __syncthreads();
     bool flagged = false;
@@ -542,14 +570,30 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
         for (int w = 0; w < NW; ++w) flagged |= lds.flag[w] != 0;
     }
     if (wave == 0) {
-        const int place = 2 * (lane ^ ((lane >> 4) & 2));
         u[0] = u[1] = den = 0.f;
+        float mc = p.phi;
+        if (SYNC || (flagged & in_place)) {
+            // from each wavefront's reference to the chunk's: the largest of those with sums (SYNC: the largest logit)
+            mc = kNoRef;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {             // wavefront order
-            const float2 o = *reinterpret_cast<const float2 *>(&lds.acc[w][place]);
-            u[0] += o.x;
-            u[1] += o.y;
-            den += lds.den[w];
+            for (int w = 0; w < NW; ++w) mc = fmaxf(mc, SYNC ? lds.top[w] : lds.den[w] != 0.f ? lds.ref[w] : kNoRef);
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const float2 o = *sums_read(lds.acc[w], lane);
+                const float l = lds.den[w], f = l == 0.f ? 0.f : __builtin_amdgcn_exp2f((lds.ref[w] - mc) * kLog2e);
+                u[0] = __builtin_fmaf(f, o.x, u[0]);
+                u[1] = __builtin_fmaf(f, o.y, u[1]);
+                den = __builtin_fmaf(f, l, den);
+            }
+            if (mc == kNoRef) mc = -INFINITY;      // no key, or no logit above -infinity
+        } else {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {         // wavefront order
+                const float2 o = *sums_read(lds.acc[w], lane);
+                u[0] += o.x;
+                u[1] += o.y;
+                den += lds.den[w];
+            }
         }
         store_coherent2(&p.ws.num[slot * kHeadDim + 2 * lane], u[0], u[1]);
         if (lane == 0) {
@@ -561,7 +605,7 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
             if (!SYNC) p.ws.chunk_flags[slot] = flagged ? 1 : 0;
         }
     }
-    return flagged;
+    return flagged & !in_place;
 }
 
 // Row epilogue of a workgroup of 256 threads, in a launch of its own: the synchronized update of Eq. 2 over the row's

@@ -169,9 +169,9 @@ template <int C, bool PAGED, Start START, bool SYNC = false, int NW = 4>
 __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_kernel(const Problem p)
 {
     static_assert(NW == 4 || NW == 8, "the appended key's lane assignment covers 16 heads with 4 wavefronts");
-    static_assert(sizeof(ChunkLds<NW, C>) <= sizeof(GqaLds<NW>::tile), "recompute workspace must fit the tile");
+    static_assert(sizeof(ChunkLds<NW>) <= sizeof(GqaLds<NW>::tile), "recompute workspace must fit the tile");
     constexpr int kGqaThreads = NW * 64;
-    constexpr int UP = C / (4 * NW) < 8 ? C / (4 * NW) : 8;    // stage depth of the per-row recomputation
+    constexpr int UP = C / (4 * NW) < 4 ? C / (4 * NW) : 4;    // stage depth of the per-row recomputation
     __shared__ GqaLds<NW> lds;
     constexpr int NBLK = C / 16;               // 16-key blocks in the chunk
     static_assert(!(PAGED && START == kEarly), "the page table has to arrive before the first load");
@@ -575,7 +575,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
             wait_stores_performed();           // the stores above must not overtake the rewrite
             for (int h = 0; h < G; ++h) {
                 __syncthreads();
-                chunk_body<C, NW, UP, true, C>(p, row0 + h, c, *reinterpret_cast<ChunkLds<NW, C> *>(lds.tile));
+                chunk_body<C, NW, UP, true>(p, row0 + h, c, *reinterpret_cast<ChunkLds<NW> *>(lds.tile));
             }
         }
         return;
@@ -607,8 +607,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         for (int h = 0; h < G; ++h) {
             if (!((redo_heads >> h) & 1)) continue;
             __syncthreads();
-            chunk_body<C, NW, UP, true, C, false, PAGED>(p, row0 + h, c, *reinterpret_cast<ChunkLds<NW, C> *>(lds.tile), nullptr,
-                                                         (int)((flagged_heads >> h) & 1));
+            chunk_body<C, NW, UP, true, false, PAGED>(p, row0 + h, c, *reinterpret_cast<ChunkLds<NW> *>(lds.tile), nullptr,
+                                                      (int)((flagged_heads >> h) & 1));
         }
     }
 

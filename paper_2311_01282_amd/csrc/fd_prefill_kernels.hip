@@ -264,16 +264,7 @@ __device__ __forceinline__ float query_sum(float a)
     a = rows_sum(a, a);
     return halves_sum(a, a);
 }
-__device__ __forceinline__ float query_max(float a)
-{
-    const unsigned u = __builtin_bit_cast(unsigned, a);
-    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    const unsigned r0 = r[0], r1 = r[1];
-    const unsigned v = __builtin_bit_cast(unsigned, fmaxf(__builtin_bit_cast(float, r0), __builtin_bit_cast(float, r1)));
-    const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    const unsigned h0 = h[0], h1 = h[1];
-    return fmaxf(__builtin_bit_cast(float, h0), __builtin_bit_cast(float, h1));
-}
+__device__ __forceinline__ float query_max(float a) { return columns_max(a); }
 
 // Output rows of a wavefront: acc / den, zeros for rows past the prompt.  The accumulators hold 8 bytes of each of 16 rows
 // per instruction; they go through 8 KiB of LDS of the wavefront's own (16-byte chunk c of row r in chunk c ^ (r % 16)), so that a

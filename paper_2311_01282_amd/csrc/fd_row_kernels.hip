@@ -10,7 +10,6 @@
 //   partial_unified_kernel : Eq. 4 inner sums + guard only (first launch of the chain).
 //   chain_combine_kernel   : row flags; Eq. 4 outer sums for clean rows, per-chunk
 //       synchronized recomputation for flagged rows (second launch of the chain).
-//   partial_sync_kernel    : per-chunk part of the synchronized scheme, for all rows.
 #include "fd_chunk.h"
 
 namespace fd {
@@ -25,6 +24,11 @@ template <int C> struct Tune {
     static constexpr int UP = NG < 4 ? NG : 4;
 };
 
+// The synchronized scheme: whether the workgroups simply take one chunk after the other, row by row, instead of the same chunk
+// of eight rows on the eight XCDs (row_slot), then the next.  Where the rows do not divide among the XCDs that order leaves some of them
+// idle, and where the chunks of a row do not divide by 4, one after the other they go round all XCDs, too.
+__device__ __forceinline__ bool plain_order(const Problem &p) { return (p.rows & 7) != 0 || ((p.nc & 3) != 0 && p.nc <= 32); }
+
 // ELECT: rows are finished in the launch (elect_per_row in fd_api.hip says which launches do).
 // PAGED: K and V are page pools addressed through the sequence's block table.
 // EARLY: the first loads go out before the sequence length has arrived -- for launches of at
@@ -34,14 +38,16 @@ template <int C> struct Tune {
 //        sequences hold (max_seq beyond the lengths) many of them are chunks without keys,
 //        which then leave without reading any.
 // ONE: one block of keys in flight per wavefront, not two (LoadAhead).
-template <int C, bool ELECT, bool PAGED = false, bool EARLY = false, bool ONE = false>
+// SYNC: the synchronized partial softmax of every (row, chunk) instead (fd_decode_attn_sync); no election.
+template <int C, bool ELECT, bool PAGED = false, bool EARLY = false, bool ONE = false, bool SYNC = false>
 __global__ __launch_bounds__(Tune<C>::NW * 64) void decode_fused_kernel(const Problem p)
 {
-    static_assert(!EARLY || (ELECT && !PAGED), "early loads: in-kernel hand-over, contiguous cache");
-    constexpr int NW = Tune<C>::NW, UP = Tune<C>::UP;
-    __shared__ ChunkLds<NW, C> lds;
+    static_assert(!EARLY || ((ELECT || SYNC) && !PAGED), "early loads: in-kernel hand-over, contiguous cache");
+    static_assert(!(SYNC && ELECT), "the synchronized scheme has no counters to elect by");
+    constexpr int NW = Tune<C>::NW, UP = SYNC && C == 128 ? 8 : Tune<C>::UP;
+    __shared__ ChunkLds<NW> lds;
     const int tid = threadIdx.x;
-    if constexpr (ELECT) fetch_arguments_now(p);
+    if constexpr (ELECT || SYNC) fetch_arguments_now(p);
     // Workgroups are dealt to the 8 XCDs round-robin by index.  In a short launch that hands its rows
     // over inside the kernel all chunks of a row go to the same XCD (row % 8), so the row's counters
     // and partial results stay in one L2 instead of bouncing between eight; long ones and those that leave the
@@ -60,12 +66,17 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void decode_fused_kernel(const Pr
     const int groups8 = (p.rows + 7) >> 3;
     const int j = blockIdx.x >> 3;
     constexpr bool CM = EARLY;                 // chunk-major in the one-round launches only (see below)
-    const int c = CM ? j / groups8 : j % p.nc;
-    const int row = row_slot(p, blockIdx.x & 7, c) + 8 * (CM ? j - c * groups8 : j / p.nc);
+    const bool plain = SYNC && plain_order(p);
+    const int c = plain ? (int)blockIdx.x % p.nc : CM ? j / groups8 : j % p.nc;
+    const int row = plain ? (int)blockIdx.x / p.nc : row_slot(p, blockIdx.x & 7, c) + 8 * (CM ? j - c * groups8 : j / p.nc);
     if (row >= p.rows) return;
     FD_PHASE(0);
+    if constexpr (SYNC) {
+        chunk_body<C, NW, UP, true, EARLY, PAGED, ONE>(p, row, c, lds);
+        return;
+    }
     int S;
-    const bool flagged = chunk_body<C, NW, UP, false, C, EARLY, PAGED, ONE>(p, row, c, lds, &S);
+    const bool redo = chunk_body<C, NW, UP, false, EARLY, PAGED, ONE>(p, row, c, lds, &S);
     FD_PHASE(3);
     const int nb = (S + p.C - 1) / p.C;        // chunks of this row that hold a valid key
     if (c >= nb) {                             // padding chunk: zero partials were written
@@ -75,9 +86,9 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void decode_fused_kernel(const Pr
         }
         return;
     }
-    if (flagged) {                             // Section 3 "Recomputation", for this partial vector
+    if (redo) {                                // Section 3 "Recomputation", for this partial vector (not done in place)
         __syncthreads();
-        chunk_body<C, NW, UP, true, C, false, PAGED>(p, row, c, lds);
+        chunk_body<C, NW, UP < 2 ? UP : 2, true, false, PAGED>(p, row, c, lds);
     }
 
     if (!ELECT) return;                        // a row-epilogue launch follows
@@ -106,14 +117,14 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void partial_unified_kernel(const
 {
     static_assert(!EARLY || SMALL, "early loads belong to the small launches");
     constexpr int NW = Tune<C>::NW, UP = Tune<C>::UP;
-    __shared__ ChunkLds<NW, 1> lds;
+    __shared__ ChunkLds<NW> lds;
     if constexpr (SMALL) fetch_arguments_now(p);
     const int groups8 = (p.rows + 7) >> 3;
     const int j = blockIdx.x >> 3;
     const int c = EARLY ? j / groups8 : j % p.nc;              // the fused kernel's orders
     const int row = row_slot(p, blockIdx.x & 7, c) + 8 * (EARLY ? j - c * groups8 : j / p.nc);
     if (row >= p.rows) return;
-    chunk_body<C, NW, UP, false, 1, EARLY, false, ONE>(p, row, c, lds);
+    chunk_body<C, NW, UP, false, EARLY, false, ONE>(p, row, c, lds);
 }
 
 // Second launch of the literal chain, over (row, chunk) items: every item first forms its row's
@@ -128,14 +139,14 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void partial_unified_kernel(const
 template <int C> struct ChainTune {
     static constexpr int NW = 8;
     static constexpr int NG = C / (4 * NW);
-    static constexpr int UP = NG < 8 ? NG : 8;
+    static constexpr int UP = NG < 4 ? NG : 4;
 };
 template <int C>
 __global__ __launch_bounds__(ChainTune<C>::NW * 64) void chain_combine_kernel(const Problem p)
 {
     constexpr int NW = ChainTune<C>::NW, UP = ChainTune<C>::UP;
     constexpr int KB = NW * 2;                  // items per batch: one per half wavefront
-    __shared__ ChunkLds<NW, C> lds;
+    __shared__ ChunkLds<NW> lds;
     __shared__ int item_flag[KB];
     const int tid = threadIdx.x, half = tid >> 5, j = tid & 31;
     const long long items = (long long)p.rows * p.nc;
@@ -190,16 +201,6 @@ __global__ __launch_bounds__(ChainTune<C>::NW * 64) void chain_combine_kernel(co
     }
 }
 
-// The synchronized partial softmax of every (row, chunk), one per workgroup (fd_decode_attn_sync).
-template <int C>
-__global__ __launch_bounds__(256) void partial_sync_kernel(const Problem p)
-{
-    constexpr int UP = C / 16 < 8 ? C / 16 : 8;
-    __shared__ ChunkLds<4, C> lds;
-    const int w = blockIdx.x;
-    chunk_body<C, 4, UP, true>(p, w / p.nc, w % p.nc, lds);
-}
-
 template <template <int> class Launcher, typename... Args>
 hipError_t dispatch_chunk(int C, Args... args)
 {
@@ -225,8 +226,9 @@ hipError_t dispatch_chunk(int C, Args... args)
 // wins or ties: 2 x 32 x 29393 in 29 157.6 / 153.5 us (14696 .. 29393 144.1 / 140.0), 4 x 16 x 30000 in 30 163.1 / 160.2, 3 x 32 x 14602
 // 116.0 / 114.3, 4 x 32 x 16000 .. 32768 279.1 / 276.2, 8 x 32 x 8192 162.9 / 163.3, 16 x 32 x 4096 164.0 / 163.8.
 //   Smaller launches of up to 32 chunks per row lose (3 x 32 x 1500 in 5 15.0 / 15.35, 3 x 32 x 4096 33.15 / 33.8), and so do chunks of
-// 2048 keys (1 x 40 x 60000 in 30 198.0 / 202.1, 32 x 131072 314.7 / 316.4).  Shorter chunks than 256 keys have no third block; pages
-// are not a power of two apart.
+// 2048 keys (1 x 40 x 60000 in 30 198.0 / 202.1, 32 x 131072 314.7 / 316.4).  Shorter chunks than 256 keys have no third block.
+//   Paged caches in launches without a hand-over the same: 3 x 32 x 2470 .. 19765 (page 256) 95.7 / 93.6, 8 x 16 x 4000 .. 16000 (64) 108.75 / 108.3,
+// 11 x 16 x 1275 .. 10200 (16) 101.4 / 101.8.
 template <int C> struct LoadAhead {
     static constexpr bool kOneBuilt = C >= 256 && C <= 1024;
     static bool one(const Problem &p)
@@ -244,6 +246,10 @@ template <int C> struct FusedLauncher {
         // Every XCD reads from every row where the launch is long: more than 1024 workgroups, or more than one round of the
         // chip over 320 MiB of cache (see row_slot); the results cross between XCDs as well as within one.
         p.scatter |= !p.elect || grid > 1024u || (grid > (unsigned)kComputeUnits && cache_bytes(p) >= kLongLaunchBytes);
+        if constexpr (LoadAhead<C>::kOneBuilt) {
+            if (p.block_table && !p.elect && LoadAhead<C>::one(p))
+                return launch(decode_fused_kernel<C, false, true, false, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p);
+        }
         if (p.block_table)
             return p.elect ? launch(decode_fused_kernel<C, true, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p)
                            : launch(decode_fused_kernel<C, false, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p);
@@ -289,12 +295,118 @@ template <int C> struct ChainCombineLauncher {
     }
 };
 
+// The synchronized scheme of a (row, chunk) in two passes: the logits into LDS and their maximum; weights and V.  See SyncLauncher.
+template <int C>
+__global__ __launch_bounds__(256) void partial_sync_kernel(const Problem p)
+{
+    constexpr int NW = 4, UP = 8, NBLK = C / (4 * NW * UP);
+    __shared__ ChunkLds<NW> lds;
+    __shared__ float logit[C];
+    fetch_arguments_now(p);
+    const bool plain = plain_order(p) || p.nc > 32;
+    const int j = blockIdx.x >> 3;
+    const int c = plain ? (int)blockIdx.x % p.nc : j % p.nc;
+    const int row = plain ? (int)blockIdx.x / p.nc : row_slot(p, blockIdx.x & 7, c) + 8 * (j / p.nc);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, seg = lane & 15, sub = lane >> 4;
+    const int b = row / p.Hq, hkv = (row - b * p.Hq) / p.G, start = c * p.C;
+    const size_t slot = (size_t)row * p.nc + c;
+    const int last = min(p.C, clamp_len(p, p.seq_lens[b]) - start) - 1;
+    if (last < 0) {                            // empty chunk: zero partials
+        if (tid < kHeadDim) p.ws.num[slot * kHeadDim + tid] = 0.f;
+        if (tid == 0) {
+            p.ws.den[slot] = 0.f;
+            p.ws.mloc[slot] = -INFINITY;
+            store_meta(p, slot, 0.f, p.phi, 0);
+        }
+        return;
+    }
+    const u32x4 qv = reinterpret_cast<const u32x4 *>(p.q + (size_t)row * kHeadDim)[seg];
+    const size_t base = (((size_t)b * p.Hkv + hkv) * p.Smax + start) * 16 + seg;
+    const u32x4 *kp = reinterpret_cast<const u32x4 *>(p.k) + base, *vp = reinterpret_cast<const u32x4 *>(p.v) + base;
+    auto key_of = [&](int g) { return (g * NW + wave) * 4 + sub; };
+    const int nblk = min(NBLK, last / (UP * NW * 4) + 1);
+    float m = -INFINITY;
+#pragma unroll 1
+    for (int blk = 0; blk < nblk; ++blk) {
+        u32x4 kk[UP];
+#pragma unroll
+        for (int u = 0; u < UP; ++u) kk[u] = load_stream(kp + (size_t)min(key_of(blk * UP + u), last) * 16);
+#pragma unroll
+        for (int u = 0; u < UP; ++u) {
+            const int key = key_of(blk * UP + u);
+            float x = row16_sum(dot8(qv, kk[u])) * p.scale;
+            x = key <= last ? x : -INFINITY;
+            if (seg == 0) logit[key] = x;
+            m = fmaxf(m, x);
+        }
+    }
+    m = columns_max(m);
+    if (lane == 0) lds.top[wave] = m;
+    __syncthreads();
+    m = lds.top[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m = fmaxf(m, lds.top[w]);
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float den = 0.f;
+#pragma unroll 1
+    for (int blk = 0; blk < nblk; ++blk) {
+        u32x4 vv[UP];
+#pragma unroll
+        for (int u = 0; u < UP; ++u) vv[u] = load_stream(vp + (size_t)min(key_of(blk * UP + u), last) * 16);
+#pragma unroll
+        for (int u = 0; u < UP; ++u) {
+            const float e = __builtin_amdgcn_exp2f((logit[key_of(blk * UP + u)] - m) * kLog2e);   // 0 for padding
+            den += e;
+            axpy8(acc, e, vv[u]);
+        }
+    }
+    float u[2];
+    wave_sums(acc, den, u);
+    *sums_place(lds.acc[wave], lane) = make_float2(u[0], u[1]);
+    if (lane == 0) lds.den[wave] = den;
+    __syncthreads();
+    if (wave != 0) return;
+    u[0] = u[1] = den = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {             // wavefront order
+        const float2 o = *sums_read(lds.acc[w], lane);
+        u[0] += o.x;
+        u[1] += o.y;
+        den += lds.den[w];
+    }
+    *reinterpret_cast<float2 *>(&p.ws.num[slot * kHeadDim + 2 * lane]) = make_float2(u[0], u[1]);
+    if (lane == 0) {
+        p.ws.den[slot] = den;
+        p.ws.mloc[slot] = m;
+        store_meta(p, slot, den, m, 1);
+    }
+}
+
+// Chunks beyond 512 keys in launches of more than one workgroup per compute unit, and beyond 1024 always, take two passes: with K and V streamed one after
+// the other the chip reads from half as many places at a time.  Shorter chunks, and launches whose workgroups are alone on their compute units,
+// take the loop of the other kernels in one.  Whole call, one pass / two: 4 x 32 x 4096 keys in 1024 43.6 / 42.7 us, 2 x 16 x 65536 166.8 / 160.4,
+// 2 x 32 x 11851 .. 23703 117.4 / 114.5, 1 x 16 x 60000 in 2048 78.0 / 75.6, 1 x 40 x 52622 173 / 176; 3 x 16 x 2252 .. 4504 in 912 18.6 / 22.0, 16 x 32 x
+// 512 .. 4096 in 512 110.8 / 119.1, 23 x 16 x 379 .. 3037 in 256 58.8 / 61.0, 3 x 5 x 3000 in 192 9.4 / 10.8, 8 x 16 x 2000 in 256 25.3 / 24.8.  Both go by
+// plain_order; the two passes took one chunk after the other in every launch before, which cost 16 x 32 x 512 .. 4096 138 us, 32 x 32 x
+// 127 .. 1022 70.8 (now 60).
 template <int C> struct SyncLauncher {
-    static hipError_t run(const Problem &p, hipStream_t s)
+    static hipError_t run(const Problem &p0, hipStream_t s)
     {
-        const long long all = (long long)p.rows * p.nc;
-        if (all == 0) return hipSuccess;
-        return launch(partial_sync_kernel<C>, dim3((unsigned)all), dim3(256), s, p);
+        const unsigned grid = (unsigned)((long long)p0.rows * p0.nc);       // (rows that 8 does not divide: plain_order)
+        if (grid == 0) return hipSuccess;
+        Problem p = p0;
+        p.scatter = 1;
+        const dim3 block(Tune<C>::NW * 64);
+        if constexpr (C <= 1024) {
+            if (grid <= (unsigned)kComputeUnits) return launch(decode_fused_kernel<C, false, false, true, false, true>, dim3(grid), block, s, p);
+        }
+        if constexpr (C >= 1024) return launch(partial_sync_kernel<C>, dim3(grid), dim3(256), s, p);
+        else {
+            if constexpr (LoadAhead<C>::kOneBuilt) {
+                if (LoadAhead<C>::one(p)) return launch(decode_fused_kernel<C, false, false, false, true, true>, dim3(grid), block, s, p);
+            }
+            return launch(decode_fused_kernel<C, false, false, false, false, true>, dim3(grid), block, s, p);
+        }
     }
 };
 

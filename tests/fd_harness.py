@@ -103,6 +103,25 @@ def assert_close(got, want, what="", rel_floor=REL_FLOOR):
     return a, r
 
 
+def ramp(case, lo, hi):
+    """Logits that run from lo to hi along each sequence: one element of every key, times one of q."""
+    case["q"][..., 0] = 16.0
+    for b, n in enumerate(np.clip(case["seq_lens"], 0, case["Smax"])):
+        if n:
+            case["k"][b, :, :n, 0] = (np.linspace(lo, hi, n) / (16.0 * case["scale"])).astype(np.float16)
+
+
+def assert_close_ramp(got, want, case, ends, what=""):
+    """A logit of ``ramp`` is an fp32 sum in which one product dominates: up to 24 roundings of its size (128 products in four
+    instructions of 32 or 16 lanes of eight, the scale, the reference taken off), each 2^-24 of |x|.  A weight carries that as a
+    relative error, the mean of V twice that times the largest |v|; the output is rounded to 2^-11."""
+    delta = 24 * 2.0 ** -24 * (max(abs(x) for x in ends) + 10.0)
+    assert np.isfinite(got).all(), what
+    err = np.abs(got - want).max(initial=0.0)
+    tol = 2.0 ** -11 * np.abs(want).max() + 2.0 * delta * np.nanmax(np.abs(case["v"].astype(np.float64)))
+    assert err <= tol, "%s: max-abs %.3e (tol %.3e)" % (what, err, tol)
+
+
 def kernels_of(call, device="cuda:0"):
     """Number of kernels that ``call(stream)`` enqueues, counted in a stream capture (nothing runs): which of its launch forms an entry
     point takes for a shape."""

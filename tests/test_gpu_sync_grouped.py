@@ -15,28 +15,13 @@ def H():
     return fd_harness
 
 
-def _ramp(case, lo, hi):
-    """Logits that run from lo to hi along each sequence: one element of every key, times one of q."""
-    case["q"][..., 0] = 16.0
-    for b, n in enumerate(np.clip(case["seq_lens"], 0, case["Smax"])):
-        if n:
-            case["k"][b, :, :n, 0] = (np.linspace(lo, hi, n) / (16.0 * case["scale"])).astype(np.float16)
-
-
 def _check(oracle, H, case, chunk, what, ramp):
     want = oracle.attn_exact(case["q"], case["k"], case["v"], case["seq_lens"], case["scale"], nthreads=8)
     got = H.DeviceCase(case, chunk=chunk).run("fd_decode_attn_sync")
     if ramp is None:
         H.assert_close(got, want, what)
         return
-    # A logit is an fp32 sum in which one product dominates: up to 24 roundings of its size (128 products in four instructions of 32 or
-    # 16 lanes of eight, the scale, the reference taken off), each 2^-24 of |x|.  A weight carries that as a relative error, the
-    # mean of V twice that times the largest |v|.
-    delta = 24 * 2.0 ** -24 * (max(abs(x) for x in ramp) + 10.0)
-    assert np.isfinite(got).all(), what
-    err = np.abs(got - want).max(initial=0.0)
-    tol = 2.0 ** -11 * np.abs(want).max() + 2.0 * delta * np.nanmax(np.abs(case["v"].astype(np.float64)))
-    assert err <= tol, "%s: max-abs %.3e (tol %.3e)" % (what, err, tol)
+    H.assert_close_ramp(got, want, case, ramp, what)
 
 
 # (batch, query heads, KV heads, lengths, max_seq, chunk): one launch of up to 256 workgroups; more, in order of length; more than 64
@@ -58,7 +43,7 @@ def _check(oracle, H, case, chunk, what, ramp):
 def test_grouped_rows(oracle, H, B, Hq, Hkv, lens, Smax, chunk, ramp):
     case = synth.make_case(B=B, Hq=Hq, Hkv=Hkv, D=128, Smax=Smax, seed=9300 + Hq + Smax, seq_lens=lens, poison_padding=True)
     if ramp:
-        _ramp(case, *ramp)
+        H.ramp(case, *ramp)
     _check(oracle, H, case, chunk, "%d x %d/%d, %s" % (B, Hq, Hkv, ramp), ramp)
 
 
