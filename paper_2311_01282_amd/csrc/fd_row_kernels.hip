@@ -24,9 +24,13 @@ template <int C> struct Tune {
     static constexpr int UP = NG < 4 ? NG : 4;
 };
 
-// The synchronized scheme: whether the workgroups simply take one chunk after the other, row by row, instead of the same chunk
+// Launches that hand nothing over: whether the workgroups simply take one chunk after the other, row by row, instead of the same chunk
 // of eight rows on the eight XCDs (row_slot), then the next.  Where the rows do not divide among the XCDs that order leaves some of them
-// idle, and where the chunks of a row do not divide by 4, one after the other they go round all XCDs, too.
+// idle; and where the chunks of a row do not divide by 4, one after the other they go round all XCDs, too, and a compute unit's
+// neighbours stream neighbouring chunks: whole call, by eight rows / this, 3 x 32 x 4000 .. 30000 keys in 30 chunks 213 / 200 us, 30 x 16 x 1718 .. 3436 in 14
+// 110.6 / 107.5, 12 x 40 x 187 .. 1500 in 6 41.6 / 41.0, 4 x 16 x 30000 in 30 156.7 / 155.8, 2 x 40 x 12564 .. 25128 in 25 a tie.  Where they do divide by 4, an XCD gets the
+// same few chunks of every row, which in a ragged batch are the full or the empty ones (16 x 32 x 512 .. 4096 in 8 110 / 136, 24 x 16 x 500 .. 4000
+// in 16 84.7 / 93.4, 23 x 16 x 379 .. 3037 in 12 59.0 / 61.8); rows of more than 32 chunks are turned (2 x 16 x 6740 .. 53923 in 53 130.2 / 133.6).
 __device__ __forceinline__ bool plain_order(const Problem &p) { return (p.rows & 7) != 0 || ((p.nc & 3) != 0 && p.nc <= 32); }
 
 // ELECT: rows are finished in the launch (elect_per_row in fd_api.hip says which launches do).
@@ -66,7 +70,7 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void decode_fused_kernel(const Pr
     const int groups8 = (p.rows + 7) >> 3;
     const int j = blockIdx.x >> 3;
     constexpr bool CM = EARLY;                 // chunk-major in the one-round launches only (see below)
-    const bool plain = SYNC && plain_order(p);
+    const bool plain = !ELECT && plain_order(p);
     const int c = plain ? (int)blockIdx.x % p.nc : CM ? j / groups8 : j % p.nc;
     const int row = plain ? (int)blockIdx.x / p.nc : row_slot(p, blockIdx.x & 7, c) + 8 * (CM ? j - c * groups8 : j / p.nc);
     if (row >= p.rows) return;
