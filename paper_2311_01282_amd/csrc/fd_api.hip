@@ -162,8 +162,6 @@ fd_status set_guard(fd::Problem *p, float phi, fd_bounds b)
 // 16 chunks 82.9 / 83.1 (holding 8192 keys 45.9 / 43.4), 3 x 32 x 8192 62.7 / 62.5.  Rows of 33 .. 128 chunks are no exception: the row's
 // wavefront needs a round trip per 32, the second launch adds eight at a time: 1 x 8 x 60000 in 59 42.7 / 40.9, 1 x 8 x 131072 in 64 85.1 / 83.8, 1 x 4
 // x 4096 in 64 8.8 / 8.35.  Beyond 128 chunks they tie (1 row of 256 chunks 16.2 / 16.0 and 31.8 / 34.4) or the second launch wins (469: 26.4 / 29.8).
-// (Fewer than eight rows are another matter: handed over inside they keep to as many XCDs, row_slot, where the second launch's rows go to all
-// eight: 4 x 16384 14.6 / 13.3 us, 4 x 131072 72.8 / 52.0, one launch / two.  That is the placement's cost, not the hand-over's.)
 //   In a long launch -- more than three workgroups per compute unit over 320 MiB or more of cache -- a workgroup of eight wavefronts
 // that waits is not covered by another, and the second launch wins for rows of more than eight chunks: 4 x 8 x 32768 in 32 82.5 / 84.3, 4 x 8 x
 // 6000 .. 30000 in 30 66.4 / 67.3, 1 x 32 x 65536 in 32 159.3 / 162.1, 2 x 32 x 16384 in 16 82.25 / 84.2; about even 6 x 8 x 20000 in 20 79.7 /

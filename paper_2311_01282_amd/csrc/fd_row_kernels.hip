@@ -55,7 +55,7 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void decode_fused_kernel(const Pr
     // Workgroups are dealt to the 8 XCDs round-robin by index.  In a short launch that hands its rows
     // over inside the kernel all chunks of a row go to the same XCD (row % 8), so the row's counters
     // and partial results stay in one L2 instead of bouncing between eight; long ones and those that leave the
-    // epilogue to a second launch spread them (FusedLauncher, row_slot).  Placement only affects speed: every
+    // epilogue to a second launch spread them, as do long rows of which there are fewer than eight (FusedLauncher, row_slot).  Placement only affects speed: every
     // hand-over below is device-coherent wherever the workgroups land.
     // Order within that: row-major -- all chunks of rows 0..7, then of rows 8..15, ... -- except in
     // the launches of at most one workgroup per compute unit (EARLY), which go chunk-major and whose
@@ -248,8 +248,12 @@ template <int C> struct FusedLauncher {
         if (grid == 0) return hipSuccess;
         Problem p = p0;
         // Every XCD reads from every row where the launch is long: more than 1024 workgroups, or more than one round of the
-        // chip over 320 MiB of cache (see row_slot); the results cross between XCDs as well as within one.
-        p.scatter |= !p.elect || grid > 1024u || (grid > (unsigned)kComputeUnits && cache_bytes(p) >= kLongLaunchBytes);
+        // chip over 320 MiB of cache (see row_slot); the results cross between XCDs as well as within one.  So they do in rows of more
+        // than 32 chunks where there are fewer than eight, which would else use as many XCDs as there are rows: whole call, rows on fixed
+        // XCDs / this, 2 rows x 131072 keys 59.4 / 38.1 us, 1 x 131072 32.5 / 21.4, 4 x 131072 73.0 / 50.8, 4 x 16384 14.6 / 12.3, 2 x 2 x 8192 10.1 / 9.0,
+        // 2 x 4096 7.8 / 7.5; not up to 32: 1 x 1000 in 16 5.1 / 5.4, 4 x 700 in 11 5.5 / 5.8, 4 x 2048 in 32 5.95 / 5.98.
+        const bool few = p.rows < 8 && grid > (unsigned)kComputeUnits;
+        p.scatter |= !p.elect || few || grid > 1024u || (grid > (unsigned)kComputeUnits && cache_bytes(p) >= kLongLaunchBytes);
         if constexpr (LoadAhead<C>::kOneBuilt) {
             if (p.block_table && !p.elect && LoadAhead<C>::one(p))
                 return launch(decode_fused_kernel<C, false, true, false, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p);
