@@ -140,6 +140,7 @@ struct PrefillProblem {
     uint8_t *tile_flags;         // workspace: [B, Hq, tiles]
     int B, Hq, Hkv, G, Smax, tiles;         // tiles = Smax / 64, rounded up
     float scale, phi, lo, hi;
+    int group, parts;            // heads whose tiles are dealt out together, and how many such groups; set at launch
 };
 hipError_t launch_prefill(const PrefillProblem &p, hipStream_t s);
 

@@ -709,8 +709,15 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillProblem p)
     // without / with: 1 x 32 heads x 2048 tokens 60.7 / 55.5 us, 1 x 16 x 4096 107.0 / 96.8, 2 x 32 x 1024 37.7 / 35.4,
     // 1 x 32 x 1100 28.8 / 28.7.
     const int item = tile_order(blockIdx.x, gridDim.x);
-    const int rank = item / heads;                               // 0: the last tile of every head
-    const int u = item - rank * heads;
+    int first = 0, left = item, size = heads;                    // the heads whose tiles are dealt out together (see head_group)
+    if (p.group < heads) {
+        const int part = min(item / (p.group * qtiles), p.parts - 1);
+        first = part * p.group;
+        left = item - first * qtiles;
+        size = part == p.parts - 1 ? heads - first : p.group;
+    }
+    const int rank = left / size;                                // 0: the last tile of every head
+    const int u = first + left - rank * size;
     int head = u;
     if (kv_heads % 8 == 0) {                                      // u % 8 == item % 8 == blockIdx.x % 8
         const int m = u >> 3;
@@ -738,10 +745,32 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillProblem p)
 
 }  // namespace
 
-hipError_t launch_prefill(const PrefillProblem &p, hipStream_t s)
+// Heads whose tiles are dealt out together, heaviest first, before those of the next: all of them, except in launches of many heads that share
+// nothing.  There the tiles in flight at a time are one or two of every head, each streams K and V past the L2s for itself, and the
+// launch draws 5 TB/s from the memory behind them.  In groups of half a round of the chip the tiles of a head run together and find its keys in
+// their XCD's L2; the last group, of two rounds and more, evens out what is left.  Whole call, all heads / groups: 8 x 40 heads x 1280 tokens 226.5 /
+// 208.0 us, 7 x 40 x 667 .. 2003 261 / 251, 7 x 32 x 328 .. 984 67.6 / 65.8; groups of a round, without the large last one 216, 269, 73.  Fewer heads lose what the
+// group ends cost: 4 x 32 x 1024 61.0 / 61.2, 8 x 16 x 2808 347.7 / 350.1, 2 x 40 x 4000 426 / 430, 1 x 32 x 8192 648 / 662, 8 x 32/8 x 498 .. 1496 133 / 136, 2 x 64/8 x
+// 4001 583 / 602.
+static void head_group(PrefillProblem &p, int qtiles)
 {
-    if (p.B == 0) return hipSuccess;
+    const int heads = p.B * p.Hq;
+    const long long tiles = (long long)heads * qtiles;
+    p.group = heads;
+    p.parts = 1;
+    if ((long long)p.B * p.Hkv < 192 || tiles < 5 * kComputeUnits) return;
+    p.group = (kComputeUnits / qtiles + 7) / 8 * 8;              // (a multiple of 8: a head's tiles stay on one XCD)
+    if (p.group == 0) p.group = 8;
+    p.parts = (int)((tiles - 4 * kComputeUnits) / ((long long)p.group * qtiles)) + 1;
+    if (p.parts == 1) p.group = heads;
+}
+
+hipError_t launch_prefill(const PrefillProblem &p0, hipStream_t s)
+{
+    if (p0.B == 0) return hipSuccess;
+    PrefillProblem p = p0;
     const int qtiles = (p.Smax + kQTile - 1) / kQTile;
+    head_group(p, qtiles);
     return launch(prefill_kernel, dim3((unsigned)((long long)p.B * p.Hq * qtiles)), dim3(256), s, p);
 }
 
