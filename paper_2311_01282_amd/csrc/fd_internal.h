@@ -141,6 +141,7 @@ struct PrefillProblem {
     int B, Hq, Hkv, G, Smax, tiles;         // tiles = Smax / 64, rounded up
     float scale, phi, lo, hi;
     int group, parts;            // heads whose tiles are dealt out together, and how many such groups; set at launch
+    int shift;                   // queries by which the tiles start in front of the prompt, 0 or 64; set at launch
 };
 hipError_t launch_prefill(const PrefillProblem &p, hipStream_t s);
 

@@ -110,8 +110,8 @@ struct TileWave {
         g = lane >> 4;
         w0 = i0 + kWaveQ * wave;
         nsteps = (min(i0 + kQTile, S) - 1) / kStep + 1;
-        const int last_q = min(w0 + kWaveQ, S) - 1;                  // < w0 when the wavefront has no query
-        mine = last_q >= w0 ? last_q / kStep + 1 : 0;
+        const int last_q = min(w0 + kWaveQ, S) - 1;                  // < w0 when the wavefront has no query (as in front of the prompt)
+        mine = last_q >= w0 && w0 >= 0 ? last_q / kStep + 1 : 0;
         const size_t kv_head = (size_t)b * p.Hkv + hq / p.G;
         kbase = reinterpret_cast<const unsigned char *>(p.k + kv_head * p.Smax * kHeadDim);
         vbase = reinterpret_cast<const unsigned char *>(p.v + kv_head * p.Smax * kHeadDim);
@@ -132,7 +132,7 @@ struct TileWave {
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb) {
                 u32x4 t = {0u, 0u, 0u, 0u};
-                if (row < S) t = *reinterpret_cast<const u32x4 *>(qbase + (size_t)row * kHeadDim + 32 * kb + 8 * g);
+                if ((unsigned)row < (unsigned)S) t = *reinterpret_cast<const u32x4 *>(qbase + (size_t)row * kHeadDim + 32 * kb + 8 * g);
                 qB[qb][kb] = __builtin_bit_cast(f16x8, t);
             }
         }
@@ -297,8 +297,9 @@ __device__ __forceinline__ void store_rows(const PrefillProblem &p, const TileWa
         t[i] = *reinterpret_cast<const u32x4 *>(rows + r * 256 + ((n ^ (r & 15)) << 4));
     }
     // through a window that ends at the buffer's last row: what lies past it is not written
-    uint16_t *o = p.out + (((size_t)b * p.Hq + hq) * p.Smax + tw.w0) * kHeadDim;
-    const int left = __builtin_amdgcn_readfirstlane(max(min(p.Smax - tw.w0, kWaveQ), 0)) * (kHeadDim * 2);
+    const int row0 = max(tw.w0, 0);
+    uint16_t *o = p.out + (((size_t)b * p.Hq + hq) * p.Smax + row0) * kHeadDim;
+    const int left = __builtin_amdgcn_readfirstlane(tw.w0 < 0 ? 0 : max(min(p.Smax - row0, kWaveQ), 0)) * (kHeadDim * 2);
     const auto window = __builtin_amdgcn_make_buffer_rsrc(o, 0, left, 0x00027000);
 #pragma unroll
     for (int i = 0; i < kWaveQ / 4; ++i) {
@@ -610,7 +611,7 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
         int f = 0;
 #pragma unroll
         for (int w = 0; w < kWavesPerFlag; ++w) f |= lds.bad[tid * kWavesPerFlag + w];
-        if (t64 < p.tiles) p.tile_flags[((size_t)b * p.Hq + hq) * p.tiles + t64] = f != 0;
+        if ((unsigned)t64 < (unsigned)p.tiles) p.tile_flags[((size_t)b * p.Hq + hq) * p.tiles + t64] = f != 0;
     }
     if ((lds.redo[0] | lds.redo[1] | lds.redo[2] | lds.redo[3]) != 0) return true;   // uniform: the tile is redone, nothing stored
     store_rows(p, tw, lds, b, hq, S, acc, den);
@@ -725,16 +726,18 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillProblem p)
     }
     const int qt = qtiles - 1 - rank;
     const int b = head / p.Hq, hq = head - b * p.Hq;
-    const int i0 = qt * kQTile;
+    const int i0 = qt * kQTile - p.shift;
     int S = p.seq_lens[b];
-    S = S < 0 ? 0 : (S > p.Smax ? p.Smax : S);
+    // (uniform, as the compiler has to see: else the loop's counters end up in vector registers, 0.4 % of 8192 tokens)
+    S = __builtin_amdgcn_readfirstlane(S < 0 ? 0 : (S > p.Smax ? p.Smax : S));
     if (i0 >= S) {                                       // no prompt token in this tile: zeros, no flag
-        uint16_t *o = p.out + (((size_t)b * p.Hq + hq) * p.Smax + i0) * kHeadDim;
-        const int rows = min(kQTile, p.Smax - i0);
+        const int at = max(i0, 0);
+        uint16_t *o = p.out + (((size_t)b * p.Hq + hq) * p.Smax + at) * kHeadDim;
+        const int rows = min(i0 + kQTile, p.Smax) - at;
         for (int i = threadIdx.x; i < rows * (kHeadDim / 8); i += 256)
             reinterpret_cast<u32x4 *>(o)[i] = u32x4{0u, 0u, 0u, 0u};
-        if (threadIdx.x < kQTile / 64 && i0 / 64 + (int)threadIdx.x < p.tiles)
-            p.tile_flags[((size_t)b * p.Hq + hq) * p.tiles + i0 / 64 + threadIdx.x] = 0;
+        const int t64 = i0 / 64 + (int)threadIdx.x;
+        if (threadIdx.x < kQTile / 64 && (unsigned)t64 < (unsigned)p.tiles) p.tile_flags[((size_t)b * p.Hq + hq) * p.tiles + t64] = 0;
         return;
     }
     if (tile_unified(p, lds, b, hq, i0, S)) {            // Section 3 "Recomputation", for this tile
@@ -771,6 +774,16 @@ hipError_t launch_prefill(const PrefillProblem &p0, hipStream_t s)
     PrefillProblem p = p0;
     const int qtiles = (p.Smax + kQTile - 1) / kQTile;
     head_group(p, qtiles);
+    // Tiles end at a multiple of 128 queries, or of 64 where that leaves the last one of a prompt as long as the buffer at least half
+    // full: it sees all keys, and with its queries as they come one or two wavefronts would walk them by themselves.  The first tile then starts 64 in
+    // front of the prompt and its first two wavefronts have nothing to do; there are as many tiles as without.  Whole call, without / with: 8 x 40
+    // heads x 1284 tokens 233.9 / 218.7 us, 4 x 32 x 1030 67.2 / 64.8, 8 x 64/8 x 400 57.0 / 55.5, 1 x 32 x 4100 175.2 / 173.2.  A launch of up to two
+    // tiles per compute unit ends with its longest tile, which is shorter with fewer of its wavefronts at work: there only for one of them (2 x
+    // 28/4 x 650, 336 tiles, 20.5 / 19.6; 1 x 32 x 1088, 288, two wavefronts, 24.5 / 25.5), and not in one of up to one tile (1 x 32 x 150 7.5 / 7.9, 300 10.2 / 11.2).
+    const long long tiles = (long long)p.B * p.Hq * qtiles;
+    const int over = p.Smax % kQTile;                                          // queries of the last tile as they come
+    const int most = tiles > 2 * kComputeUnits ? 2 * kWaveQ : tiles > kComputeUnits ? kWaveQ : 0;
+    p.shift = over > 0 && over <= most ? 64 : 0;
     return launch(prefill_kernel, dim3((unsigned)((long long)p.B * p.Hq * qtiles)), dim3(256), s, p);
 }
 
