@@ -168,6 +168,18 @@ __device__ __forceinline__ float rows_sum(float a, float b)
     return as_f32(x) + as_f32(y);
 }
 
+// Inclusive sum over the lanes of a wavefront.
+__device__ __forceinline__ int lanes_scan(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8: within rows of 16
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // lane 15 to row 1, lane 47 to row 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // lane 31 to rows 2 and 3
+    return x;
+}
+
 // The maximum over the four rows of 16 of a wavefront, in every lane.
 __device__ __forceinline__ float columns_max(float a)
 {

@@ -66,18 +66,6 @@ constexpr float kFirstBlockLog2 = 4.f;    // a head's largest weight of the wave
 constexpr float kOverflowLog2 = 15.9f;    // ... and no later weight may reach 2^16 (fp16 ends at 65504)
 constexpr float kNoScale = 3e38f;         // SYNC: scale exponent of a head that has met no finite logit yet; any one sets it
 
-// Inclusive sum over the lanes of a wavefront.
-__device__ __forceinline__ int lanes_scan(int x)
-{
-    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8: within rows of 16
-    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // lane 15 to row 1, lane 47 to row 3
-    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // lane 31 to rows 2 and 3
-    return x;
-}
-
 // Order by length (launches of more than one workgroup per compute unit, at most 64 sequences; see GqaLauncher): the chunks
 // that are full first, then the sequences' last, partial chunks from the longest to the shortest, then the chunks without keys; each for
 // all KV heads.  Every workgroup of up to three rounds of the chip starts with the launch and a compute unit holds workgroups i, i + 256, ...,

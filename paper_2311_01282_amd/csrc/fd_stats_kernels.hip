@@ -45,7 +45,7 @@ __device__ __forceinline__ int slot_of(float x, float x_min, float inv_width, in
 // ungrouped heads, 1 x 32 heads x 8192 keys 22.9, now 17.3).
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-template <bool GROUPED>
+template <bool GROUPED, bool LIVE>
 __global__ __launch_bounds__(kStatsWaves * 64) void logit_histogram_kernel(
     const Problem p, const float x_min, const float inv_width, const int n_bins, const int run,
     unsigned long long *__restrict__ hist, float *__restrict__ min_max)
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(kStatsWaves * 64) void logit_histogram_kernel(
     const int waves = blockDim.x >> 6;
     unsigned *lds_hist = reinterpret_cast<unsigned *>(lds_raw + (GROUPED ? waves * 4096 : 0));
     float *lds_mm = reinterpret_cast<float *>(lds_hist + n_bins + 2);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = LIVE ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
     const int n = lane & 15, g = lane >> 4;
     u32x4 *kst = reinterpret_cast<u32x4 *>(lds_raw) + wave * 256;
     for (int i = tid; i < n_bins + 2; i += blockDim.x) lds_hist[i] = 0u;
@@ -63,25 +63,48 @@ __global__ __launch_bounds__(kStatsWaves * 64) void logit_histogram_kernel(
 
     const int runs = (p.Smax + run - 1) / run;
     const int hblocks = (p.G + 15) / 16;
-    const unsigned items = (unsigned)(p.B * p.Hkv * hblocks) * (unsigned)runs;   // < 2^31: at most rows * ceil(Smax / 64)
+    unsigned items = (unsigned)(p.B * p.Hkv * hblocks) * (unsigned)runs;         // < 2^31: at most rows * ceil(Smax / 64)
     const unsigned stride = (unsigned)waves * gridDim.x;
     float lo = INFINITY, hi = -INFINITY;
     // Consecutive items to consecutive workgroups: the runs of a KV head spread over the chip.  Where they are many (runs of more than 64
-    // keys: two per wavefront or more), each (sequence, KV head) starts at a place of its own, the next for every round of the
-    // workgroups: where the number of runs divides that of the workgroups, all runs of a workgroup would otherwise lie at the same place
-    // of their sequences, and ragged lengths would load the compute units unevenly (32 sequences of 2048 .. 4096 keys: 3085 on
-    // average and 4096 on the fullest; 41.2 us, turned 37.2; 32 x 32 heads x 100 .. 1000 keys 34.6 / 29.1).  With hardly a run per wavefront there is
-    // little to even out, and it helps that the workgroups at the sequences' ends have nothing to add to memory: not turned / turned 32 x 64/8
-    // x 100 .. 1000 12.7 / 14.2, 32 x 64/8 x 200 .. 1500 17.1 / 18.0, 6 x 40 x 200 .. 1500 17.0 / 17.8, 16 x 16 x 1500 20.7 / 21.1.
+    // keys: two per wavefront or more) ragged lengths would load the compute units unevenly, all runs of a workgroup lying at the same place of
+    // their sequences where the number of runs divides that of the workgroups.  LIVE (the lengths of the batch fit a wavefront): the items are the runs
+    // that hold keys; every wavefront has all lengths, one a lane, and finds its runs by their prefix sums, (sequence, KV head) after (sequence, KV head).
+    // Otherwise each (sequence, KV head) starts at a place of its own, the next for every round of the workgroups: `turned`.  Whole call, one after
+    // the other / turned / LIVE: 32 x 64/8 heads x 2048 .. 4096 keys 47.5 / 45.0 / 43.3 us; turned / LIVE 5 x 64/8 x 5000 .. 40000 52.0 / 48.1, 24 x 32/8 x 700 ..
+    // 5600 40.2 / 37.7, full lengths 32 x 64/8 x 4096 51.1 / 51.0.  With hardly a run per wavefront there is little to even out, and it helps that the
+    // workgroups at the sequences' ends have nothing to add to memory: one after the other / turned 32 x 64/8 x 100 .. 1000 12.7 / 14.2, 32 x 64/8 x 200 .. 1500
+    // 17.1 / 18.0, 6 x 40 x 200 .. 1500 17.0 / 17.8, 16 x 16 x 1500 20.7 / 21.1; one after the other / LIVE 32 x 64/8 x 100 .. 1000 19.7 / 22.9, 12 x 32/8 x 670 .. 5367 26.4 / 27.6.
     const bool turned = run > 64;
+    int len = 0, own = 0, upto = 0;                      // lane b: keys of sequence b, its runs, those of the sequences up to it for all KV heads
+    if constexpr (LIVE) {
+        if (lane < p.B) len = valid_len(p, lane);
+        own = (len + run - 1) / run;
+        upto = lanes_scan(own * p.Hkv * hblocks);
+        items = (unsigned)__builtin_amdgcn_readlane(upto, 63);
+    }
     for (unsigned it = (unsigned)wave * gridDim.x + blockIdx.x; it < items; it += stride) {
-        const unsigned r = it / (unsigned)runs;
-        const int t = (int)((turned ? it + r * (unsigned)runs / gridDim.x : it) % (unsigned)runs);
-        const int hb = (int)(r % (unsigned)hblocks);
-        const int gi = (int)(r / (unsigned)hblocks);     // (sequence, KV head)
-        const int b = gi / p.Hkv, hkv = gi - b * p.Hkv;
-        const int nvalid = min(run, valid_len(p, b) - t * run);
-        if (nvalid <= 0) continue;
+        int b, t, hb, hkv, gi, nvalid;                   // gi: (sequence, KV head)
+        if constexpr (LIVE) {
+            b = __popcll(__ballot(upto <= (int)it));
+            const unsigned of_b = (unsigned)__builtin_amdgcn_readlane(own, b);
+            const unsigned at = it - (unsigned)__builtin_amdgcn_readlane(upto, b) + of_b * (unsigned)(p.Hkv * hblocks);
+            const unsigned r = at / of_b;
+            t = (int)(at - r * of_b);
+            hkv = (int)(r / (unsigned)hblocks);
+            hb = (int)r - hkv * hblocks;
+            gi = b * p.Hkv + hkv;
+            nvalid = min(run, __builtin_amdgcn_readlane(len, b) - t * run);
+        } else {
+            const unsigned r = it / (unsigned)runs;
+            t = (int)((turned ? it + r * (unsigned)runs / gridDim.x : it) % (unsigned)runs);
+            hb = (int)(r % (unsigned)hblocks);
+            gi = (int)(r / (unsigned)hblocks);
+            b = gi / p.Hkv;
+            hkv = gi - b * p.Hkv;
+            nvalid = min(run, valid_len(p, b) - t * run);
+            if (nvalid <= 0) continue;
+        }
         const int last = nvalid - 1;
         const int nh = min(16, p.G - 16 * hb);           // heads of this block
         const int row0 = b * p.Hq + hkv * p.G + 16 * hb;
@@ -192,8 +215,11 @@ hipError_t launch_logit_histogram(const Problem &p, float x_min, float bin_width
     const float inv_width = 1.0f / bin_width;
     const size_t lds = (p.G > 1 ? waves * 4096 : 0) + (size_t)(n_bins + 2) * sizeof(unsigned) + waves * 2 * sizeof(float);
     void *args[] = {(void *)&p, (void *)&x_min, (void *)&inv_width, (void *)&n_bins, (void *)&run, (void *)&hist, (void *)&min_max};
-    const void *fn = p.G > 1 ? reinterpret_cast<const void *>(&logit_histogram_kernel<true>)
-                             : reinterpret_cast<const void *>(&logit_histogram_kernel<false>);
+    const bool live = run > 64 && p.B <= 64;
+    const void *fn = p.G > 1 ? (live ? reinterpret_cast<const void *>(&logit_histogram_kernel<true, true>)
+                                     : reinterpret_cast<const void *>(&logit_histogram_kernel<true, false>))
+                             : (live ? reinterpret_cast<const void *>(&logit_histogram_kernel<false, true>)
+                                     : reinterpret_cast<const void *>(&logit_histogram_kernel<false, false>));
     return hipLaunchKernel(fn, dim3(grid), dim3(waves * 64), args, lds, s);
 }
 

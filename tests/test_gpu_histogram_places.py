@@ -29,3 +29,24 @@ def test_every_key_is_counted_once(B, Hq, Hkv, Smax, lens):
     check_histogram(got, want, near)
     assert got.sum() == sum(lens) * Hq
     assert mm[0] == pytest.approx(lo, abs=1e-4) and mm[1] == pytest.approx(hi, abs=1e-4)
+
+
+# The runs that hold keys dealt out by the lengths' prefix sums: empty sequences first, last and between, lengths at the edges of a run, a sequence
+# that holds all keys, 64 sequences (the last with this order) and 65, two blocks of heads on one KV head
+@pytest.mark.parametrize("B,Hq,Hkv,Smax,lens", [
+    (6, 24, 24, 9000, [0, 9000, 0, 1, 4097, 0]),
+    (5, 36, 2, 120000, [0, 60000, 128, 127, 129]),
+    (64, 4, 4, 5000, [73 * i for i in range(64)]),
+    (65, 4, 4, 5000, [73 * i for i in range(65)]),
+    (3, 64, 32, 12000, [0, 0, 12000]),
+    (3, 64, 32, 12000, [0, 0, 0]),
+])
+def test_every_key_is_counted_once_among_runs_without_keys(B, Hq, Hkv, Smax, lens):
+    case = synth.make_case(B=B, Hq=Hq, Hkv=Hkv, D=128, Smax=Smax, seq_lens=lens, seed=500 + Smax, poison_padding=True)
+    got, mm = gpu_histogram(case, -6.0, 0.125, 96)
+    assert got.sum() == sum(lens) * Hq
+    if sum(lens):
+        want, lo, hi, near = cal.logit_histogram(case["q"], case["k"], case["seq_lens"], case["scale"], -6.0, 0.125, 96,
+                                                 nthreads=8, edge_eps=EDGE_EPS)
+        check_histogram(got, want, near)
+        assert mm[0] == pytest.approx(lo, abs=1e-4) and mm[1] == pytest.approx(hi, abs=1e-4)
