@@ -433,7 +433,8 @@ fd_status fd_calibrate(const uint64_t *hist, int32_t n_bins, float x_min, float 
  * unified factor phi, partial sums over disjoint key sets added without a
  * maximum exchange, the range guard lo < x - phi < hi on every logit that takes
  * part, and on-the-spot recomputation with the synchronized scheme for a tile of
- * 128 queries in which the guard fired (flags are recorded per 64 queries).
+ * 128 queries (64 in small launches) in which the guard fired (flags are recorded per
+ * 64 queries).
  *   q, out   [batch, n_q_heads, max_seq, head_dim] fp16 (out is written)
  *   k_cache, v_cache [batch, n_kv_heads, max_seq, head_dim] fp16 (the prompt's keys)
  *   seq_lens [batch]: prompt length n_b = clamp(seq_lens[b], 0, max_seq); rows
@@ -446,8 +447,9 @@ fd_status fd_calibrate(const uint64_t *hist, int32_t n_bins, float x_min, float 
  * pairs (22 significant bits) under a scale 2^k of the query's own, fixed after the
  * query's first 32 keys (it cancels in the division and is constant over the keys, so
  * partial sums still just add); V is used as it is.  A query whose later weights exceed
- * that scale's headroom (a logit more than 8.2 above the largest of its first 32) has
- * its 128-query tile redone with the synchronized scheme: same result, NO flag (the
+ * that scale's headroom (a logit more than 8.2 above the largest of its first 32; small
+ * launches sum a query's even and odd runs of 32 keys apart, each under a scale fixed
+ * after its own first 32) has its tile redone with the synchronized scheme: same result, NO flag (the
  * flags report the guard alone).  Guard: as in decode a logit outside the bounds flags,
  * and so does a NaN logit; the comparison is made on log2 e^{x - phi} (plus k) against
  * the bounds times log2 e (plus k), so a logit within fp32 rounding of a bound may fall
@@ -460,7 +462,7 @@ fd_status fd_prefill_attn(const fd_shape *shape, const void *q, const void *k_ca
                           const int32_t *seq_lens, float phi, fd_bounds bounds, void *out,
                           fd_workspace ws, void *stream);
 /* Device pointer into `ws`: tile_flags [batch, n_q_heads, ceil(max_seq / 64)], 1 where
- * the guard fired for a logit of those 64 queries (their 128-query tile was recomputed). */
+ * the guard fired for a logit of those 64 queries (the tile they are in was recomputed). */
 fd_status fd_prefill_get_flags(const fd_shape *shape, fd_workspace ws, const uint8_t **tile_flags);
 
 /* Static, human-readable name of a status code. */

@@ -2,7 +2,7 @@
 // prompt attends to itself and the tokens before it (Eq. 1 under the causal mask), all
 // weights taken against the unified scaling factor phi.  Partial sums over successive key
 // tiles then simply add (Eq. 4): no running maximum, and the output accumulators are never
-// rescaled while the keys stream by.  A 128-query tile whose guard fires is redone on the
+// rescaled while the keys stream by.  A tile of queries whose guard fires is redone on the
 // spot with the synchronized scheme (running maximum per query, Eq. 2).
 //
 // Matrix-core mapping (16x16x32 MFMA; lane = (n, g) = (lane % 16, lane / 16)):
@@ -53,7 +53,7 @@ constexpr int kQTile = 4 * kWaveQ; // query rows per workgroup
 constexpr int kStep = 32;        // keys per wavefront step
 
 // ---- the attention kernel ----
-// A workgroup owns 128 queries of one head: wavefront w the 32 queries i0 + 32w .. +31 (two
+// A workgroup owns 128 queries of one head (64 in small launches, see tile_unified): wavefront w the 32 queries i0 + 32w .. +31 (two
 // blocks of 16).  The K and V tiles of a 32-key step are loaded once per workgroup into LDS
 // and read from there by all four wavefronts as MFMA A operands; Q^T stays in registers as the B
 // operand.  Every output row belongs to one wavefront: nothing is reduced across wavefronts, and
@@ -99,19 +99,28 @@ struct TileWave {
     int k_voff0, k_voff1;        // this thread's two chunks of a K tile, from the tile's start
     int v_voff0;                 // ... and its first of a V tile (the second is 4 KiB further)
     int k_rd[4], v_rd[4];        // this lane's operand reads, from the start of the LDS tile
+    bool masked;                 // its last step holds its own 32 keys (SPLIT: of the two wavefronts of a query group, of one)
     f16x8 qB[kQB][4];            // Q^T as the B operand: lane (n, g) holds d = 32 kb + 8g .. +7 of query w0 + 16 qb + n
 
-    __device__ __forceinline__ TileWave(const PrefillProblem &p, int b, int hq, int i0, int S)
+    // SPLIT: see tile_unified
+    __device__ __forceinline__ TileWave(const PrefillProblem &p, int b, int hq, int i0, int S, bool split = false)
     {
         const int tid = threadIdx.x;
         lane = tid & 63;
         wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         n = lane & 15;
         g = lane >> 4;
-        w0 = i0 + kWaveQ * wave;
-        nsteps = (min(i0 + kQTile, S) - 1) / kStep + 1;
+        w0 = i0 + kWaveQ * (split ? wave >> 1 : wave);
+        nsteps = (min(i0 + (split ? kQTile / 2 : kQTile), S) - 1) / kStep + 1;
         const int last_q = min(w0 + kWaveQ, S) - 1;                  // < w0 when the wavefront has no query (as in front of the prompt)
         mine = last_q >= w0 && w0 >= 0 ? last_q / kStep + 1 : 0;
+        masked = true;
+        const int part = split ? wave & 1 : 0;
+        if (split) {
+            nsteps = (nsteps + 1) / 2;
+            masked = ((mine - 1) & 1) == part;
+            mine = (mine - part + 1) / 2;                            // steps of this parity
+        }
         const size_t kv_head = (size_t)b * p.Hkv + hq / p.G;
         kbase = reinterpret_cast<const unsigned char *>(p.k + kv_head * p.Smax * kHeadDim);
         vbase = reinterpret_cast<const unsigned char *>(p.v + kv_head * p.Smax * kHeadDim);
@@ -120,10 +129,10 @@ struct TileWave {
         k_voff0 = r * 256 + c * 16;
         k_voff1 = (r + 16) * 256 + (c ^ 8) * 16;                     // k_key(r + 16) = k_key(r) ^ 8
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) k_rd[kb] = (8 * (n >> 2) + (n & 3)) * 256 + (((4 * kb + g) ^ n) << 4);
+        for (int kb = 0; kb < 4; ++kb) k_rd[kb] = part * kTileBytes + (8 * (n >> 2) + (n & 3)) * 256 + (((4 * kb + g) ^ n) << 4);
         v_voff0 = r * 256 + (((tid & 15) ^ ((r & 3) << 1)) << 4);    // 32-byte unit ^ key % 4, in 16-byte chunks
 #pragma unroll
-        for (int x = 0; x < 4; ++x) v_rd[x] = v_block(2 * g) + (n >> 2) * 256 + ((x ^ (n >> 2)) << 5) + (n & 3) * 8;
+        for (int x = 0; x < 4; ++x) v_rd[x] = part * kVTileBytes + v_block(2 * g) + (n >> 2) * 256 + ((x ^ (n >> 2)) << 5) + (n & 3) * 8;
         // rows past the prompt may hold anything: zeros in their place
         const uint16_t *qbase = p.q + (((size_t)b * p.Hq + hq) * p.Smax) * kHeadDim;
 #pragma unroll
@@ -203,7 +212,7 @@ struct TileWave {
         return __builtin_bit_cast(f16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
     }
     // scores of one step
-    __device__ __forceinline__ void scores(const PrefillLds &lds, int s, f32x4 (&sc)[kQB][2]) const
+    __device__ __forceinline__ void scores(const PrefillLds &lds, int slot, f32x4 (&sc)[kQB][2]) const
     {
 #pragma unroll
         for (int qb = 0; qb < kQB; ++qb)
@@ -213,7 +222,7 @@ struct TileWave {
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int kb = 0; kb < 4; ++kb) ka[t][kb] = read_k(lds, s & (kRing - 1), kb, t);
+            for (int kb = 0; kb < 4; ++kb) ka[t][kb] = read_k(lds, slot, kb, t);
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
@@ -230,11 +239,11 @@ struct Weights {
 };
 
 // O^T += V^T P^T with P = Ph + Pl, one step
-__device__ __forceinline__ void add_pv(const TileWave &tw, PrefillLds &lds, int s, const Weights &w, f32x4 (&acc)[8][kQB])
+__device__ __forceinline__ void add_pv(const TileWave &tw, PrefillLds &lds, int slot, const Weights &w, f32x4 (&acc)[8][kQB])
 {
     f16x8 av[8];
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) av[dt] = tw.read_v(lds, s & (kRing - 1), dt);
+    for (int dt = 0; dt < 8; ++dt) av[dt] = tw.read_v(lds, slot, dt);
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) {
 #pragma unroll
@@ -268,10 +277,10 @@ __device__ __forceinline__ float query_max(float a) { return columns_max(a); }
 
 // Output rows of a wavefront: acc / den, zeros for rows past the prompt.  The accumulators hold 8 bytes of each of 16 rows
 // per instruction; they go through 8 KiB of LDS of the wavefront's own (16-byte chunk c of row r in chunk c ^ (r % 16)), so that a
-// store instruction writes four whole rows; all of it is under way at once, without a branch.  What bounds a short prompt is
+// store instruction writes four whole rows (up to row `end`); all of it is under way at once, without a branch.  What bounds a short prompt is
 // what a workgroup does outside its loop: straight from the accumulators, 16 stores of 16 half lines each took a wavefront 3500
 // cycles, this 2000.  The rings have to be out of use.
-__device__ __forceinline__ void store_rows(const PrefillProblem &p, const TileWave &tw, PrefillLds &lds, int b, int hq, int S, const f32x4 (&acc)[8][kQB], const float (&den)[kQB])
+__device__ __forceinline__ void store_rows(const PrefillProblem &p, const TileWave &tw, PrefillLds &lds, int b, int hq, int S, const f32x4 (&acc)[8][kQB], const float (&den)[kQB], int end)
 {
     static_assert(4 * kWaveQ * kHeadDim * 2 <= sizeof(lds.k));
     unsigned char *rows = &lds.k[0][0] + tw.wave * (kWaveQ * kHeadDim * 2);
@@ -299,7 +308,7 @@ __device__ __forceinline__ void store_rows(const PrefillProblem &p, const TileWa
     // through a window that ends at the buffer's last row: what lies past it is not written
     const int row0 = max(tw.w0, 0);
     uint16_t *o = p.out + (((size_t)b * p.Hq + hq) * p.Smax + row0) * kHeadDim;
-    const int left = __builtin_amdgcn_readfirstlane(tw.w0 < 0 ? 0 : max(min(p.Smax - row0, kWaveQ), 0)) * (kHeadDim * 2);
+    const int left = __builtin_amdgcn_readfirstlane(tw.w0 < 0 ? 0 : max(min(end - row0, kWaveQ), 0)) * (kHeadDim * 2);
     const auto window = __builtin_amdgcn_make_buffer_rsrc(o, 0, left, 0x00027000);
 #pragma unroll
     for (int i = 0; i < kWaveQ / 4; ++i) {
@@ -353,9 +362,15 @@ template <class F, int... I> __device__ __forceinline__ void unrolled(std::integ
 {
     (f(std::integral_constant<int, I>{}), ...);
 }
+// SPLIT: a tile of 64 queries, two wavefronts to 32 of them: one takes the even key steps, the other the odd ones, each under scales of its own;
+// at the end the sums of the odd ones are brought to the common scale and added (Eq. 4).  A step is two tiles of K and of V for the workgroup, the rings hold
+// two, what iteration s fetches (K of s + 3, V of s + 1) it also waits for, and V is not read ahead.  Where a launch has few tiles its length is that of the
+// longest walk, and a step takes 0.65 us whether a SIMD holds one wavefront or two: here a walk is half the steps,
+// of two tiles each (1 x 32 heads x 1024 tokens, heaviest tile: 32 steps before, 16 now; whole call 24.9 / 21.2 us).
+template <bool SPLIT>
 __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds &lds, int b, int hq, int i0, int S)
 {
-    const TileWave tw(p, b, hq, i0, S);
+    const TileWave tw(p, b, hq, i0, S, SPLIT);
     const int tid = threadIdx.x, lane = tw.lane, wave = tw.wave, n = tw.n, g = tw.g, mine = tw.mine;
     const float c1 = p.scale * kLog2e, c0 = -p.phi * kLog2e;      // log2 of e^{s x - phi} = c1 x + c0
     const float lo2 = p.lo * kLog2e, hi2 = p.hi * kLog2e;
@@ -378,16 +393,39 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
     // s - 1 at the latest (those reads have returned: workgroup_barrier), and waits at its end for what iteration s - 1 fetched: a
     // load has two iterations to land.
     const u32x4 k0 = tw.k_window(0), v0 = tw.v_window(0);
-    tw.fetch_k<true>(lds, k0, 0, 0); tw.fetch_k<true>(lds, k0, 1, 1);
-    tw.fetch_v<true>(lds, v0, 0, 0); tw.fetch_k<true>(lds, k0, 2, 2);
-    tw.fetch_v<true>(lds, v0, 1, 1);
-    tw.fetch_k<true>(lds, k0, 3, 3); tw.fetch_v<true>(lds, v0, 2, 2);
-    auto fetch_ahead = [&](int s) { tw.fetch_k(lds, s + 4); tw.fetch_v(lds, s + 3); };
-    auto next_iteration = [&]() { wait_fetches<4>(); workgroup_barrier(); };
+    if constexpr (SPLIT) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) tw.fetch_k<true>(lds, k0, u, u);
+        tw.fetch_v<true>(lds, v0, 0, 0); tw.fetch_v<true>(lds, v0, 1, 1);
+    } else {
+        tw.fetch_k<true>(lds, k0, 0, 0); tw.fetch_k<true>(lds, k0, 1, 1);
+        tw.fetch_v<true>(lds, v0, 0, 0); tw.fetch_k<true>(lds, k0, 2, 2);
+        tw.fetch_v<true>(lds, v0, 1, 1);
+        tw.fetch_k<true>(lds, k0, 3, 3); tw.fetch_v<true>(lds, v0, 2, 2);
+    }
+    // one of the eight loads of a thread for step s (SPLIT), odd: s is odd
+    auto split_piece = [&](int piece, u32x4 rk, u32x4 rv, int odd) {
+        const int half = (piece >> 1) & 1, u = piece & 1;              // piece 0 .. 3: K tiles, 4 .. 7: V tiles
+        const int k_slot = odd ? u : 2 + u, v_slot = odd ? u : 2 + u;  // places of steps s + 3 and s + 1
+        if (piece < 4) tw.load<false>(rk, half ? tw.k_voff1 : tw.k_voff0, u * kTileBytes, lds.k[k_slot] + wave * 1024 + 4096 * half);
+        else tw.load<false>(rv, tw.v_voff0, u * kTileBytes + 4096 * half, lds.v[v_slot] + v_block(wave + 4 * half));
+    };
+    auto fetch_ahead = [&](int s) {
+        if constexpr (SPLIT) {
+            const u32x4 rk = tw.k_window(2 * (s + 3)), rv = tw.v_window(2 * (s + 1));
+#pragma unroll
+            for (int i = 0; i < 8; ++i) split_piece(i, rk, rv, s & 1);
+        } else {
+            tw.fetch_k(lds, s + 4);
+            tw.fetch_v(lds, s + 3);
+        }
+    };
+    const auto place = [](int s) { return SPLIT ? 2 * (s & 1) : s & (kRing - 1); };       // of step s in the rings
+    auto next_iteration = [&]() { wait_fetches<SPLIT ? 0 : 4>(); workgroup_barrier(); };
 
     // The last step of a wavefront holds its own 32 keys (causal mask): key 8g + j of the step, j = 4t + r, is visible to query
     // 16 qb + n of the wavefront where j - 16 qb <= own.
-    const int own = n - 8 * g;
+    const int own = tw.masked ? n - 8 * g : 64;
     // weights of a wavefront's first step from its scores, not woven into anything; last: it is its last one, too
     auto first_weights = [&](bool last, const f32x4 (&sc)[kQB][2], Weights &w) {
 #pragma unroll
@@ -444,6 +482,9 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
         if constexpr (kLast) {
 #pragma unroll
             for (int dt = 0; dt < 8; ++dt) av[dt] = tw.read_v(lds, slot, dt);
+        } else if constexpr (SPLIT) {
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt) av[dt] = tw.read_v(lds, slot, dt);
         }
         __builtin_amdgcn_sched_barrier(0);
         unrolled(std::make_integer_sequence<int, 48>{}, [&](auto slot_index) {
@@ -461,9 +502,10 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
             __builtin_amdgcn_sched_barrier(0);
             // operand reads and tile fetches
             if constexpr (!kLast && m < 8 && m % 2 == 1) av[4 + m / 2] = tw.read_v(lds, slot, 4 + m / 2);
-            if constexpr (!kLast && m >= 17 && m < 25) ka[m - 17] = tw.read_k(lds, (slot + 2) & (kRing - 1), (m - 17) >> 1, (m - 17) & 1);
-            if constexpr (!kLast && m >= 33 && m < 41 && m % 2 == 1) av[(m - 33) / 2] = tw.read_v(lds, (slot + 1) & (kRing - 1), (m - 33) / 2);
-            if constexpr (m >= 6 && (m - 6) % 11 == 0) tw.fetch_piece(lds, (m - 6) / 11, rk, rv, u, slot, (slot + 3) & (kRing - 1));
+            if constexpr (!kLast && m >= 17 && m < 25) ka[m - 17] = tw.read_k(lds, SPLIT ? slot : (slot + 2) & (kRing - 1), (m - 17) >> 1, (m - 17) & 1);
+            if constexpr (!SPLIT && !kLast && m >= 33 && m < 41 && m % 2 == 1) av[(m - 33) / 2] = tw.read_v(lds, (slot + 1) & (kRing - 1), (m - 33) / 2);
+            if constexpr (SPLIT && m >= 9 && m < 33 && (m - 9) % 3 == 0) split_piece((m - 9) / 3, rk, rv, u);
+            if constexpr (!SPLIT && m >= 6 && (m - 6) % 11 == 0) tw.fetch_piece(lds, (m - 6) / 11, rk, rv, u, slot, (slot + 3) & (kRing - 1));
             if constexpr (!kLast && m % 16 == 15 && m < 47) wait_reads();                // (the last 16 slots' reads: at the barrier)
             // weights: pair pr = (query block, keys 2j, 2j + 1)
             constexpr int pr = m / 6, qb = pr >> 2, j = pr & 3;
@@ -519,28 +561,41 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
     f32x4 scA[kQB][2], scB[kQB][2];
     Weights wA, wB;
     f16x8 av[8];
-    wait_fetches<10>();                                       // K tiles 0 and 1
+    wait_fetches<SPLIT ? 4 : 10>();                           // K tiles 0 and 1 (SPLIT: 0 to 3)
     workgroup_barrier();
     if (mine > 0) {
         // (step 1's scores also where there is no such step: they run under the weights of step 0)
         tw.scores(lds, 0, scB);
-        tw.scores(lds, 1, scA);
-        first_weights(mine == 1, scB, wA);
+        tw.scores(lds, place(1), scA);
     }
+    if constexpr (SPLIT) {                                    // step 2's K tiles where step 0's were
+        workgroup_barrier();
+        const u32x4 k2 = tw.k_window(4);
+        tw.fetch_k<true>(lds, k2, 0, 0); tw.fetch_k<true>(lds, k2, 1, 1);
+    }
+    if (mine > 0) first_weights(mine == 1, scB, wA);
     all_landed();                                             // V tiles 0 to 2, K tiles 2 and 3; Q^T on every path
     workgroup_barrier();
     int s = 0;
     if (mine > 2) {
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt) av[dt] = tw.read_v(lds, 0, dt);
-        wait_reads();
+        wait_reads();                                         // (SPLIT: every iteration reads them itself)
         // four at a time, left after any of them: places in the ring and registers are then fixed (nothing is computed, nothing is
         // moved; up to three iterations of a loop of their own took 1740 cycles each, these 1300.  Whole call, with those / this:
         // 2 x 28/4 heads x 700 tokens 21.6 / 21.1 us, 8 ragged prompts of up to 900 32.4 / 31.6, 1 x 32 x 512 15.2 / 14.9)
         constexpr std::false_type inner;
         const int end = mine - 2;
 #pragma unroll 1
-        for (;;) {
+        for (; SPLIT;) {
+            iteration(inner, 0, tw.k_window(2 * (s + 3)), tw.v_window(2 * (s + 1)), 0, scA, scB, wA, wB, av);
+            if (s + 1 == end) break;
+            iteration(inner, 2, tw.k_window(2 * (s + 4)), tw.v_window(2 * (s + 2)), 1, scB, scA, wB, wA, av);
+            s += 2;
+            if (s == end) break;
+        }
+#pragma unroll 1
+        for (; !SPLIT;) {
             const u32x4 rk = tw.k_window(s + 4), rv = tw.v_window(s + 3);
             iteration(inner, 0, rk, rv, 0, scA, scB, wA, wB, av);
             if (s + 1 == end) break;
@@ -569,14 +624,15 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
     // together before the first weights (2400 cycles, now 1660), whole call before / now: 4 ragged prompts of up to 1024 tokens 55.5 /
     // 52.0 us, 1 x 32 heads x 100 8.9 / 7.6, 1 x 32 x 1024 27.2 / 25.7, 2 x 64/8 x 4001 560 / 550, 1 x 32 x 8192 663 / 658.)
     if (mine > 1) {                                           // s == mine - 2
-        iteration(std::true_type{}, s & (kRing - 1), tw.k_window(s + 4), tw.v_window(s + 3), 0, scA, scB, wA, wB, av);
+        if constexpr (SPLIT) iteration(std::true_type{}, place(s), tw.k_window(2 * (s + 3)), tw.v_window(2 * (s + 1)), s & 1, scA, scB, wA, wB, av);
+        else iteration(std::true_type{}, s & (kRing - 1), tw.k_window(s + 4), tw.v_window(s + 3), 0, scA, scB, wA, wB, av);
 #pragma unroll
         for (int qb = 0; qb < kQB; ++qb) { wA.hi[qb] = wB.hi[qb]; wA.lo[qb] = wB.lo[qb]; }
         ++s;
     }
     if (mine > 0) {                                           // s == mine - 1
         fetch_ahead(s);
-        add_pv(tw, lds, s, wA, acc);
+        add_pv(tw, lds, place(s), wA, acc);
         next_iteration();
         ++s;
     }
@@ -603,9 +659,23 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
     }
     const unsigned long long any_bad = __ballot(bad), any_range = __ballot(range);
     if (lane == 0) { lds.bad[wave] = any_bad != 0ull; lds.redo[wave] = (any_bad | any_range) != 0ull; }
+    // SPLIT: the odd wavefront's sums, through 16 KiB of the rings (out of use since the last barrier, which all fetches were waited for at)
+    f32x4 *half_acc = reinterpret_cast<f32x4 *>(&lds.k[0][0] + (wave >> 1) * 16384) + lane;
+    float *half_den = reinterpret_cast<float *>(&lds.v[0][0]) + (wave >> 1) * 256 + lane;
+    if constexpr (SPLIT) {
+        static_assert(2 * 16384 <= sizeof(lds.k));
+        if (wave & 1) {
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+                for (int qb = 0; qb < kQB; ++qb) half_acc[64 * (kQB * dt + qb)] = acc[dt][qb];
+#pragma unroll
+            for (int qb = 0; qb < kQB; ++qb) { half_den[64 * qb] = den[qb]; half_den[64 * (kQB + qb)] = kq[qb]; }
+        }
+    }
     __syncthreads();
     // one flag byte per 64 queries
-    constexpr int kFlagTiles = kQTile / 64, kWavesPerFlag = 4 / kFlagTiles;
+    constexpr int kFlagTiles = SPLIT ? 1 : kQTile / 64, kWavesPerFlag = 4 / kFlagTiles;
     if (tid < kFlagTiles) {
         const int t64 = i0 / 64 + tid;
         int f = 0;
@@ -614,13 +684,31 @@ __device__ __forceinline__ bool tile_unified(const PrefillProblem &p, PrefillLds
         if ((unsigned)t64 < (unsigned)p.tiles) p.tile_flags[((size_t)b * p.Hq + hq) * p.tiles + t64] = f != 0;
     }
     if ((lds.redo[0] | lds.redo[1] | lds.redo[2] | lds.redo[3]) != 0) return true;   // uniform: the tile is redone, nothing stored
-    store_rows(p, tw, lds, b, hq, S, acc, den);
+    if constexpr (SPLIT) {
+        if (wave & 1) return false;
+#pragma unroll
+        for (int qb = 0; qb < kQB; ++qb) {
+            // both to the smaller of the two scales (that of the larger logit); an odd wavefront without a key the query sees has none
+            const float d1 = half_den[64 * qb], k1 = half_den[64 * (kQB + qb)];
+            const float k = d1 == 0.f ? kq[qb] : fminf(kq[qb], k1);
+            const float f0 = __builtin_amdgcn_exp2f(k - kq[qb]), f1 = d1 == 0.f ? 0.f : __builtin_amdgcn_exp2f(k - k1);
+            den[qb] = __builtin_fmaf(d1, f1, den[qb] * f0);
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt) {
+                const f32x4 o = half_acc[64 * (kQB * dt + qb)];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[dt][qb][e] = __builtin_fmaf(o[e], f1, acc[dt][qb][e] * f0);
+            }
+        }
+        wait_reads();
+    }
+    store_rows(p, tw, lds, b, hq, S, acc, den, p.Smax);
     return false;
 }
 
 // The same tile by the synchronized scheme (running maximum per query, Eq. 2); rare, so plain: one step after the
 // other, one barrier per step, the next step's tiles in flight meanwhile.
-__device__ __forceinline__ void tile_sync(const PrefillProblem &p, PrefillLds &lds, int b, int hq, int i0, int S)
+__device__ __forceinline__ void tile_sync(const PrefillProblem &p, PrefillLds &lds, int b, int hq, int i0, int S, int end)
 {
     const TileWave tw(p, b, hq, i0, S);
     const float c1 = p.scale * kLog2e, c0 = -p.phi * kLog2e;
@@ -644,7 +732,7 @@ __device__ __forceinline__ void tile_sync(const PrefillProblem &p, PrefillLds &l
         tw.fetch_v(lds, s + 1);
         if (s < tw.mine) {                                    // uniform over the wavefront
             f32x4 sc[kQB][2];
-            tw.scores(lds, s, sc);
+            tw.scores(lds, s & (kRing - 1), sc);
             Weights w;
 #pragma unroll
             for (int qb = 0; qb < kQB; ++qb) {
@@ -674,7 +762,7 @@ __device__ __forceinline__ void tile_sync(const PrefillProblem &p, PrefillLds &l
                     w.lo[qb][j >> 1] = l;
                 }
             }
-            add_pv(tw, lds, s, w, acc);
+            add_pv(tw, lds, s & (kRing - 1), w, acc);
         }
         wait_fetches<0>();
         __syncthreads();
@@ -683,7 +771,7 @@ __device__ __forceinline__ void tile_sync(const PrefillProblem &p, PrefillLds &l
     for (int qb = 0; qb < kQB; ++qb) {
         den[qb] = query_sum(den[qb]);
     }
-    store_rows(p, tw, lds, b, hq, S, acc, den);
+    store_rows(p, tw, lds, b, hq, S, acc, den, end);
 }
 
 // Which tile of the order below workgroup i of `grid` runs: a permutation that keeps i % 8.
@@ -693,8 +781,10 @@ __device__ __forceinline__ int tile_order(int i, int grid)
     return kComputeUnits + grid - 8 - (i & ~7) + (i & 7);
 }
 
+template <bool SPLIT>
 __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillProblem p)
 {
+    constexpr int kTile = SPLIT ? kQTile / 2 : kQTile;             // queries per workgroup
     __shared__ PrefillLds lds;
     // Order: heavy tiles (late queries see more keys) of all heads first, so that what runs last is short.
     // Workgroups are dealt to the 8 XCDs round-robin by index; each XCD has its own L2.  Where the KV heads divide by 8,
@@ -704,7 +794,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillProblem p)
     // that order / this: 4 ragged prompts of up to 1024 tokens 79.2 / 68.6 us, 2 x 64/8 heads x 4001 623.1 / 578.9, 1 x 32 x
     // 8192 753.5 / 695.7.)
     const int heads = p.B * p.Hq, kv_heads = p.B * p.Hkv;
-    const int qtiles = (p.Smax + kQTile - 1) / kQTile;
+    const int qtiles = (p.Smax + kTile - 1) / kTile;
     // A launch of one to two tiles per compute unit: a compute unit holds workgroups i and i + 256 from the start, so the second
     // half runs light tiles first and the heaviest shares its compute unit with the lightest (the XCD stays the same).  Whole call,
     // without / with: 1 x 32 heads x 2048 tokens 60.7 / 55.5 us, 1 x 16 x 4096 107.0 / 96.8, 2 x 32 x 1024 37.7 / 35.4,
@@ -726,23 +816,23 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const PrefillProblem p)
     }
     const int qt = qtiles - 1 - rank;
     const int b = head / p.Hq, hq = head - b * p.Hq;
-    const int i0 = qt * kQTile - p.shift;
+    const int i0 = qt * kTile - p.shift;
     int S = p.seq_lens[b];
     // (uniform, as the compiler has to see: else the loop's counters end up in vector registers, 0.4 % of 8192 tokens)
     S = __builtin_amdgcn_readfirstlane(S < 0 ? 0 : (S > p.Smax ? p.Smax : S));
     if (i0 >= S) {                                       // no prompt token in this tile: zeros, no flag
         const int at = max(i0, 0);
         uint16_t *o = p.out + (((size_t)b * p.Hq + hq) * p.Smax + at) * kHeadDim;
-        const int rows = min(i0 + kQTile, p.Smax) - at;
+        const int rows = min(i0 + kTile, p.Smax) - at;
         for (int i = threadIdx.x; i < rows * (kHeadDim / 8); i += 256)
             reinterpret_cast<u32x4 *>(o)[i] = u32x4{0u, 0u, 0u, 0u};
         const int t64 = i0 / 64 + (int)threadIdx.x;
-        if (threadIdx.x < kQTile / 64 && (unsigned)t64 < (unsigned)p.tiles) p.tile_flags[((size_t)b * p.Hq + hq) * p.tiles + t64] = 0;
+        if (threadIdx.x < kTile / 64 && (unsigned)t64 < (unsigned)p.tiles) p.tile_flags[((size_t)b * p.Hq + hq) * p.tiles + t64] = 0;
         return;
     }
-    if (tile_unified(p, lds, b, hq, i0, S)) {            // Section 3 "Recomputation", for this tile
+    if (tile_unified<SPLIT>(p, lds, b, hq, i0, S)) {            // Section 3 "Recomputation", for this tile
         __syncthreads();
-        tile_sync(p, lds, b, hq, i0, S);
+        tile_sync(p, lds, b, hq, i0, S, min(p.Smax, i0 + kTile));
     }
 }
 
@@ -773,18 +863,29 @@ hipError_t launch_prefill(const PrefillProblem &p0, hipStream_t s)
     if (p0.B == 0) return hipSuccess;
     PrefillProblem p = p0;
     const int qtiles = (p.Smax + kQTile - 1) / kQTile;
+    const long long tiles = (long long)p.B * p.Hq * qtiles;
+    // Launches that would leave compute units with one workgroup or none: tiles of 64 queries, walked by twice the wavefronts (see
+    // tile_unified).  Whole call, without / with: 1 x 32 heads x 256 tokens 10.1 / 8.8 us, 512 14.8 / 12.2, 1024 24.9 / 21.2, 1 x 16 x 2000 40.3 /
+    // 32.7, 1 x 32/8 x 512 14.5 / 11.5, 2 x 28/4 x 500 15.8 / 14.0; but 6 x 12/2 x 217 9.53 / 9.73.  A few tiles more: where a head has several, of unequal length
+    // (1 x 32 x 1152, 288 tiles, 27.6 / 24.0, 1 x 28/4 x 1260, 280, 29.2 / 25.1; 9 x 32 x 100, 288, 12.2 / 15.0).  With more the keys' second
+    // reading costs more than the shorter walk gives: 2 x 28/4 x 650, 336 tiles, 19.1 / 22.8, 1 x 32 x 1536, 384, 37.2 / 40.1, 2 x 32 x 1024, 512, 31.7 / 37.9.
+    if (tiles <= kComputeUnits || (tiles <= kComputeUnits + kComputeUnits / 8 && qtiles > 4)) {
+        p.group = p.B * p.Hq;
+        p.parts = 1;
+        p.shift = 0;
+        return launch(prefill_kernel<true>, dim3((unsigned)(p.group * ((p.Smax + kQTile / 2 - 1) / (kQTile / 2)))), dim3(256), s, p);
+    }
     head_group(p, qtiles);
     // Tiles end at a multiple of 128 queries, or of 64 where that leaves the last one of a prompt as long as the buffer at least half
     // full: it sees all keys, and with its queries as they come one or two wavefronts would walk them by themselves.  The first tile then starts 64 in
     // front of the prompt and its first two wavefronts have nothing to do; there are as many tiles as without.  Whole call, without / with: 8 x 40
     // heads x 1284 tokens 233.9 / 218.7 us, 4 x 32 x 1030 67.2 / 64.8, 8 x 64/8 x 400 57.0 / 55.5, 1 x 32 x 4100 175.2 / 173.2.  A launch of up to two
-    // tiles per compute unit ends with its longest tile, which is shorter with fewer of its wavefronts at work: there only for one of them (2 x
-    // 28/4 x 650, 336 tiles, 20.5 / 19.6; 1 x 32 x 1088, 288, two wavefronts, 24.5 / 25.5), and not in one of up to one tile (1 x 32 x 150 7.5 / 7.9, 300 10.2 / 11.2).
-    const long long tiles = (long long)p.B * p.Hq * qtiles;
+    // tiles per compute unit ends with its longest tile, and one of short prompts has little else: both take longer over a last tile with four wavefronts
+    // at work than with two, and shift for one only (2 x 28/4 x 650, 336 tiles, one wavefront, 20.5 / 19.6; 8 x 32 x 300, two, 25.1 / 27.2).
     const int over = p.Smax % kQTile;                                          // queries of the last tile as they come
-    const int most = tiles > 2 * kComputeUnits ? 2 * kWaveQ : tiles > kComputeUnits ? kWaveQ : 0;
+    const int most = tiles > 2 * kComputeUnits && qtiles > 4 ? 2 * kWaveQ : kWaveQ;
     p.shift = over > 0 && over <= most ? 64 : 0;
-    return launch(prefill_kernel, dim3((unsigned)((long long)p.B * p.Hq * qtiles)), dim3(256), s, p);
+    return launch(prefill_kernel<false>, dim3((unsigned)tiles), dim3(256), s, p);
 }
 
 }  // namespace fd

@@ -135,3 +135,14 @@ def test_tile_fetches_are_waited_for_by_the_source_alone(assembly):
     assert len(waits_over_tile_fetches(Code(text % "", "k"))) == 1
     assert not waits_over_tile_fetches(Code(text % ";#ASMSTART\n s_waitcnt vmcnt(0)\n;#ASMEND\n", "k"))
     assert not waits_over_tile_fetches(Code(assembly, "prefill_kernel"))
+
+
+@pytest.mark.parametrize("split", [0, 1])
+def test_both_forms_of_the_kernel(assembly, split):
+    """The three rules for the form with a query tile per wavefront and for the one whose wavefronts share the keys."""
+    code = Code(assembly, "prefill_kernelILb%dE" % split)
+    found = lds_reads_at_barriers(code)
+    assert len(found) >= 8 and not any(found.values()), found
+    assert not any(inline and re.match(r"[sv]_\w+ m0\b", ins) for block in code.blocks for ins, inline in block)
+    assert sum(inline and ins.startswith("buffer_load") and ins.endswith(" lds") for block in code.blocks for ins, inline in block) >= 16
+    assert not waits_over_tile_fetches(code)
