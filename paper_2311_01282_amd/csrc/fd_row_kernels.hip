@@ -4,12 +4,14 @@
 //
 //   decode_fused_kernel    : the whole method in one launch.  Every workgroup
 //       computes its chunk's Eq. 4 inner sums under the range guard; a chunk whose
-//       guard fired is recomputed on the spot with its own maximum (Eq. 2); the
+//       guard fires goes on with references of its own (Eq. 2); the
 //       workgroup that finishes a row last (elected by a small tree of arrival
 //       counters) runs the row epilogue.
 //   partial_unified_kernel : Eq. 4 inner sums + guard only (first launch of the chain).
 //   chain_combine_kernel   : row flags; Eq. 4 outer sums for clean rows, per-chunk
 //       synchronized recomputation for flagged rows (second launch of the chain).
+//   partial_sync_kernel    : every (row, chunk) by Eq. 2, in two passes, where that is
+//       better than the SYNC form of decode_fused_kernel (SyncLauncher).
 #include "fd_chunk.h"
 
 namespace fd {
