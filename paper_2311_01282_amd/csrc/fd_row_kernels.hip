@@ -145,7 +145,9 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void partial_unified_kernel(const
 template <int C> struct ChainTune {
     static constexpr int NW = 8;
     static constexpr int NG = C / (4 * NW);
-    static constexpr int UP = NG < 4 ? NG : 4;
+    // (chunks from 256 keys: with 4 the kernel takes up to 161 registers, a compute unit holds one workgroup instead of two, and the launch of 512 runs in
+    // two rounds: 4 x 32 heads x 32768 keys 30.9 us, with 2 21)
+    static constexpr int UP = C >= 256 ? 2 : NG < 4 ? NG : 4;
 };
 template <int C>
 __global__ __launch_bounds__(ChainTune<C>::NW * 64) void chain_combine_kernel(const Problem p)
