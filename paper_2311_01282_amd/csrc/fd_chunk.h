@@ -64,6 +64,14 @@ __device__ __forceinline__ float dot8(const u32x4 &a, const u32x4 &b)
     return acc;
 }
 
+// a * b as an fp32 number, whatever it is used in next: fused into an addition the product would not be rounded, and where logits are so large
+// that neighbouring fp32 numbers are whole units apart, equal ones have to come out equal.
+__device__ __forceinline__ float rounded_product(float a, float b)
+{
+#pragma clang fp contract(off)
+    return a * b;
+}
+
 // acc[0..7] += p * v[0..7]
 __device__ __forceinline__ void axpy8(float (&acc)[8], float p, const u32x4 &v)
 {

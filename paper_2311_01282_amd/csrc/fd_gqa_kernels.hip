@@ -52,7 +52,7 @@ struct GqaLds {
     // never live together.
     alignas(16) float tile[NW * 16 * kHeadDim];
     alignas(16) float den[16][NW];   // per head: the wavefronts' denominators ...
-    alignas(16) float inv[16][NW];   // ... and what takes their scales out of their tiles again (SYNC: the scale exponents ...
+    alignas(16) float inv[16][NW];   // ... and what takes their scales out of their tiles again (SYNC: the references ...
     alignas(16) float top[16][NW];   // ... and the wavefronts' largest logits)
     alignas(16) unsigned mask[NW];   // heads out of bounds, and << 16 heads with a weight beyond the fp16 operand
     float e_new[16];                 // weight of an appended key per head (written where there is one)
@@ -64,7 +64,7 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kFirstBlockLog2 = 4.f;    // a head's largest weight of the wavefront's first block lies in [2^3, 2^4] ...
 constexpr float kOverflowLog2 = 15.9f;    // ... and no later weight may reach 2^16 (fp16 ends at 65504)
-constexpr float kNoScale = 3e38f;         // SYNC: scale exponent of a head that has met no finite logit yet; any one sets it
+constexpr float kHeadroom = 8.f;           // SYNC: a logit this far above the reference raises it (2^(4 + 8 log2 e) is under 2^15.9)
 
 // Order by length (launches of more than one workgroup per compute unit, at most 64 sequences; see GqaLauncher): the chunks
 // that are full first, then the sequences' last, partial chunks from the longest to the shortest, then the chunks without keys; each for
@@ -148,9 +148,10 @@ __device__ __forceinline__ bool chunk_by_length(const Problem &p, int res, int &
 enum Start { kPlain, kEarly, kByLength };
 
 // SYNC: the chunk's part of the synchronized partial softmax (Eq. 2; fd_decode_attn_sync) by the same tile: m = max x, l = sum
-// e^{x-m}, f.V = sum e^{x-m} v, no guard, no flag.  The scale 2^k of a (wavefront, head) stands in for the running maximum: it is set by the first block
-// as above, and where a later weight would reach 2^15.9 it is set anew and the sums are brought to it, exactly (a power of two); m itself enters
-// at the workgroup reduction.  Bound by HBM reads like the rest; the check is a compare and a branch per 16 keys.  The per-row form
+// e^{x-m}, f.V = sum e^{x-m} v, no guard, no flag.  A (wavefront, head) has a reference in place of the running maximum: the largest logit of the
+// first block, and where a later one lies more than kHeadroom above it the reference becomes that and the sums are brought to it; m itself enters
+// at the workgroup reduction.  It is taken off the rounded logit before anything is multiplied: in a difference of products rounded one by
+// one, logits from 1e8 on would lose the scale.  Bound by HBM reads like the rest; the check is a compare and a branch per 16 keys.  The per-row form
 // read K and V once per query head, out of the caches where they held them: whole call, that / this, 5 x 28/4 heads x 14729 keys 107.0 / 28.8
 // us, 12 x 12/2 x 7924 79.4 / 20.0, 2 x 64/8 x 1000 10.5 / 8.35.
 template <int C, bool PAGED, Start START, bool SYNC = false, int NW = 4>
@@ -256,7 +257,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
     float den = 0.f;
     bool bad = false;
     const bool head_on = n < G;
-    float kq = SYNC ? kNoScale : 0.f;          // scale exponent of (this wavefront, head n), set by the first block
+    float kq = SYNC ? kFirstBlockLog2 : 0.f;   // scale exponent of (this wavefront, head n), set by the first block (SYNC: the same for all)
+    float ref = kNoRef;                        // SYNC: what the logits of (this wavefront, head n) are taken against
     float zmax = -INFINITY;                    // largest log2 of a scaled weight of head n so far
     float xmax = -INFINITY;                    // SYNC: largest logit of this lane's keys so far
     float neg1;                                // -1.0 the compiler cannot fold: keeps e - (float)hi one mixed-precision FMA
@@ -308,7 +310,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             valid[r] = k0 + 4 * r + g <= last;
-            dd[r] = SYNC ? sc[r] * scale : sc[r] * scale + nphi;
+            dd[r] = SYNC ? rounded_product(sc[r], scale) : sc[r] * scale + nphi;
             if constexpr (!SYNC) bad |= valid[r] & head_on & !((dd[r] > lo) & (dd[r] < hi));
         }
         if constexpr (SYNC) {
@@ -316,13 +318,13 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
 #pragma unroll
             for (int r = 0; r < 4; ++r) top = fmaxf(top, valid[r] ? dd[r] : -INFINITY);
             xmax = fmaxf(xmax, top);
-            if (__ballot(__builtin_fmaf(top, kLog2e, kq) >= kOverflowLog2) != 0ull) {       // the first block; rarely another
-                // the four lane groups of a head hold different keys: they agree on the new scale
+            if (__ballot(top - ref > kHeadroom) != 0ull) {       // the first block; rarely another
+                // the four lane groups of a head hold different keys: they agree on the new reference
                 float m = fmaxf(top, __shfl_xor(top, 16));
                 m = fmaxf(m, __shfl_xor(m, 32));
-                const float k = __builtin_fmaf(m, kLog2e, kq) >= kOverflowLog2 ? kFirstBlockLog2 - ceilf(m * kLog2e) : kq;
-                const float by = __builtin_amdgcn_exp2f(k - kq);       // 0 where there was none (the sums are zeros then), 1 where it stays
-                kq = k;
+                const bool moves = m - ref > kHeadroom;
+                const float by = moves ? __builtin_amdgcn_exp2f((ref - m) * kLog2e) : 1.f;     // 0 where there was none (the sums are zeros then)
+                ref = moves ? m : ref;
                 den *= by;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -331,6 +333,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
                     for (int e = 0; e < 8; ++e) acc[e][r] *= f;
                 }
             }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dd[r] -= ref;
         } else if (first) {
             // the head's scale: the four lane groups of a head hold different keys and agree on the maximum first
             float m = -INFINITY;
@@ -448,7 +452,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
     };
     const unsigned mask = heads_of(__ballot(bad)) | new_mask | heads_of(__ballot(head_on & (zmax >= kOverflowLog2))) << 16;
     // the scales are taken out where the tiles are added (exact: integer powers of two)
-    const float inv = SYNC ? kq : __builtin_amdgcn_exp2f(-kq);
+    const float inv = SYNC ? ref : __builtin_amdgcn_exp2f(-kq);
     den = halves_sum(den, den);
     den = rows_sum(den, den);
     if constexpr (SYNC) {
@@ -490,7 +494,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         for (int w = 0; w < NW; ++w) s += lds.den[h][w];
         return s;
     };
-    // SYNC: head h's maximum over the chunk, and what brings each wavefront's sums from its scale to that reference (0 for a
+    // SYNC: head h's maximum over the chunk, and what brings each wavefront's sums from its reference and the scale to it (0 for a
     // wavefront without a finite logit)
     auto sync_scales = [&](int h, float (&by)[NW]) {
         float m = lds.top[h][0];
@@ -498,7 +502,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         for (int w = 1; w < NW; ++w) m = fmaxf(m, lds.top[h][w]);
 #pragma unroll
         for (int w = 0; w < NW; ++w)
-            by[w] = lds.top[h][w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(-__builtin_fmaf(m, kLog2e, lds.inv[h][w]));
+            by[w] = lds.top[h][w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(__builtin_fmaf(lds.inv[h][w] - m, kLog2e, -kFirstBlockLog2));
         return m;
     };
     bool unsound = false;                      // SYNC: this thread met a sum that is not a finite number, or an impossible l
