@@ -315,6 +315,12 @@ fd_status fd_decode_attn_multikernel(const fd_shape *shape, const void *q, const
  * without steps 1-3.  This is the scheme the paper's method replaces; it is the
  * in-library baseline and the cross-check for the unified path.  No phi, no
  * bounds, no flags.
+ * Query heads that share a KV head (2 to 16 of them) take the tile of
+ * fd_decode_attn_gqa, which reads K and V once for all: the weights are formed in fp32 and
+ * enter the second product as the sum of two fp16 numbers, each rounded to nearest, within
+ * 2^-24 of the weight (half a unit in the last place of fp32); the error against exact
+ * arithmetic is that of the form with a KV head for each query head, which computes
+ * in fp32 throughout and shares nothing with the grouped kernel.
  */
 fd_status fd_decode_attn_sync(const fd_shape *shape, const void *q, const void *k_cache,
                               const void *v_cache, const int32_t *seq_lens,

@@ -61,10 +61,14 @@ struct GqaLds {
 
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kFirstBlockLog2 = 4.f;    // a head's largest weight of the wavefront's first block lies in [2^3, 2^4] ...
 constexpr float kOverflowLog2 = 15.9f;    // ... and no later weight may reach 2^16 (fp16 ends at 65504)
-constexpr float kHeadroom = 8.f;           // SYNC: a logit this far above the reference raises it (2^(4 + 8 log2 e) is under 2^15.9)
+// SYNC: the weight of a logit that equals the reference, and how far above it a logit raises the reference (2^10 e^4 is under 2^15.9).  High, so
+// that the smallest fp16 numbers lie 2^-34 below it: sums lose nothing there that fp32 would keep.  A factor of its own, not an
+// addition in the exponent, whose rounding error would grow with it.
+constexpr float kSyncScale = 1024.f, kHeadroom = 4.f;
 
 // Order by length (launches of more than one workgroup per compute unit, at most 64 sequences; see GqaLauncher): the chunks
 // that are full first, then the sequences' last, partial chunks from the longest to the shortest, then the chunks without keys; each for
@@ -160,7 +164,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
     static_assert(NW == 4 || NW == 8, "the appended key's lane assignment covers 16 heads with 4 wavefronts");
     static_assert(sizeof(ChunkLds<NW>) <= sizeof(GqaLds<NW>::tile), "recompute workspace must fit the tile");
     constexpr int kGqaThreads = NW * 64;
-    constexpr int UP = C / (4 * NW) < 4 ? C / (4 * NW) : 4;    // stage depth of the per-row recomputation
+    constexpr int UP = SYNC ? (C < 256 ? 1 : 2) : C / (4 * NW) < 4 ? C / (4 * NW) : 4;    // stage depth of the per-row recomputation (no register spilled)
     __shared__ GqaLds<NW> lds;
     constexpr int NBLK = C / 16;               // 16-key blocks in the chunk
     static_assert(!(PAGED && START == kEarly), "the page table has to arrive before the first load");
@@ -257,7 +261,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
     float den = 0.f;
     bool bad = false;
     const bool head_on = n < G;
-    float kq = SYNC ? kFirstBlockLog2 : 0.f;   // scale exponent of (this wavefront, head n), set by the first block (SYNC: the same for all)
+    float kq = 0.f;                            // scale exponent of (this wavefront, head n), set by the first block
     float ref = kNoRef;                        // SYNC: what the logits of (this wavefront, head n) are taken against
     float zmax = -INFINITY;                    // largest log2 of a scaled weight of head n so far
     float xmax = -INFINITY;                    // SYNC: largest logit of this lane's keys so far
@@ -299,10 +303,22 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         const int pk = 4 * (n & 3) + (n >> 2);
         const int pswz = n;                            // swz(pk) = (pk >> 2) | ((pk & 3) << 2) = n
         f32x4 sc = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (SYNC) {
+            // added as a tree: in a chain of four, large logits are less exact than by the per-row kernel's tree (error of logits beyond twice their
+            // spread against 64 bits, relative to the spread: per-row 1.17e-7, chain 1.53e-7, this 1.07e-7)
+            f32x4 part[4];
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-            const f16x8 ka = __builtin_bit_cast(f16x8, kst[pk * 16 + ((4 * kb + g) ^ pswz)]);
-            sc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka, qb[kb], sc, 0, 0, 0);
+            for (int kb = 0; kb < 4; ++kb) {
+                const f16x8 ka = __builtin_bit_cast(f16x8, kst[pk * 16 + ((4 * kb + g) ^ pswz)]);
+                part[kb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka, qb[kb], sc, 0, 0, 0);
+            }
+            sc = (part[0] + part[1]) + (part[2] + part[3]);
+        } else {
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) {
+                const f16x8 ka = __builtin_bit_cast(f16x8, kst[pk * 16 + ((4 * kb + g) ^ pswz)]);
+                sc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka, qb[kb], sc, 0, 0, 0);
+            }
         }
         // sc[r] = <q_head n, k_key>, key = k0 + 4r + g.  Guard on x - phi, then the scaled weight.
         float dd[4];
@@ -347,23 +363,27 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         float pw[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const float z = __builtin_fmaf(dd[r], kLog2e, kq);
+            const float z = SYNC ? dd[r] * kLog2e : __builtin_fmaf(dd[r], kLog2e, kq);
             if constexpr (!SYNC) zmax = fmaxf(zmax, valid[r] ? z : -INFINITY);
-            const float e = __builtin_amdgcn_exp2f(z);
+            const float e = SYNC ? __builtin_amdgcn_exp2f(z) * kSyncScale : __builtin_amdgcn_exp2f(z);
             pw[r] = valid[r] ? e : 0.f;
             den += pw[r];
         }
         // P as the A operand of the 16x16x16 product: lane (head n, g) holds contraction indices
         // 4g .. 4g+3, which stand for keys g, 4+g, 8+g, 12+g -- its own four weights.
-        // hi = the weight cut to fp16, lo = what that leaves (exact in fp32) cut to fp16: 22 bits.
-        const f16x2 h01 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(pw[0], pw[1]));
-        const f16x2 h23 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(pw[2], pw[3]));
+        // hi = the weight cut to fp16, lo = what that leaves (exact in fp32) cut to fp16: 22 bits.  SYNC: both rounded to nearest, which
+        // leaves an error of 2^-24 of the weight at most, as rounding to fp32 does (error of f.V against 64 bits with weights in fp32 / cut / rounded,
+        // chunks of 256 keys whose weights are alike 1.20e-7 / 1.88e-7 / 1.18e-7, the cut ones all too small; spread as usual 1.68e-7 / 2.42e-7 / 1.59e-7).
+        const auto halves = [](float a, float b) {
+            if constexpr (SYNC) return __builtin_convertvector(f32x2{a, b}, f16x2);
+            else return __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(a, b));
+        };
+        const f16x2 h01 = halves(pw[0], pw[1]), h23 = halves(pw[2], pw[3]);
         const _Float16 h0 = h01.x, h1 = h01.y, h2 = h23.x, h3 = h23.y;
         const float l0 = __builtin_fmaf((float)h0, neg1, pw[0]), l1 = __builtin_fmaf((float)h1, neg1, pw[1]);
         const float l2 = __builtin_fmaf((float)h2, neg1, pw[2]), l3 = __builtin_fmaf((float)h3, neg1, pw[3]);
         const f16x4 p_hi = __builtin_bit_cast(f16x4, make_uint2(__builtin_bit_cast(unsigned, h01), __builtin_bit_cast(unsigned, h23)));
-        const f16x4 p_lo = __builtin_bit_cast(f16x4, make_uint2(__builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(l0, l1)),
-                                                              __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(l2, l3))));
+        const f16x4 p_lo = __builtin_bit_cast(f16x4, make_uint2(__builtin_bit_cast(unsigned, halves(l0, l1)), __builtin_bit_cast(unsigned, halves(l2, l3))));
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
             // dword w of the four V rows holds elements d = 8n + 2w (low halves) and 8n + 2w + 1 (high
@@ -391,6 +411,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         // comes first fixes the scale of the fp16 weights.
         const int rot = (!EARLY && p.nc > 32 && nmine > 1) ? (int)((unsigned)(c * 3 + gi) % (unsigned)nmine) : 0;
         auto blk_of = [&](int i) { const int t = i + rot; return wave + NW * (t >= nmine ? t - nmine : t); };
+        constexpr bool kMoreBlocks = !SYNC || NBLK > NW;      // than one per wavefront (a matter of registers: five were spilled)
         u32x4 kB[4], vB[4];
         if constexpr (EARLY) {                 // (no launch of this kind has 32 chunks per row: rot = 0)
             if (16 * wave + 15 > last)         // what lies past the last key may be anything: no NaN into the products
@@ -402,7 +423,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         }
         int i = 0;
 #pragma unroll 1
-        for (; i + 2 < nmine; i += 2) {
+        for (; kMoreBlocks && i + 2 < nmine; i += 2) {
             issue(blk_of(i + 1), kB, vB);
             __builtin_amdgcn_sched_barrier(0);     // keep the prefetch ahead of the arithmetic
             reduce(blk_of(i), i == 0, kA, vA);
@@ -410,7 +431,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
             __builtin_amdgcn_sched_barrier(0);
             reduce(blk_of(i + 1), false, kB, vB);
         }
-        if (i + 2 == nmine) {
+        if (kMoreBlocks && i + 2 == nmine) {
             issue(blk_of(i + 1), kB, vB);
             __builtin_amdgcn_sched_barrier(0);
             reduce(blk_of(i), i == 0, kA, vA);
@@ -502,7 +523,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 3 : 1) void decode_fused_gqa_ker
         for (int w = 1; w < NW; ++w) m = fmaxf(m, lds.top[h][w]);
 #pragma unroll
         for (int w = 0; w < NW; ++w)
-            by[w] = lds.top[h][w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(__builtin_fmaf(lds.inv[h][w] - m, kLog2e, -kFirstBlockLog2));
+            by[w] = lds.top[h][w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((lds.inv[h][w] - m) * kLog2e) * (1.f / kSyncScale);
         return m;
     };
     bool unsound = false;                      // SYNC: this thread met a sum that is not a finite number, or an impossible l
