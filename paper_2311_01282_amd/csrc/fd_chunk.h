@@ -51,16 +51,14 @@ __device__ __forceinline__ float as_f32(uint32_t u) { return __builtin_bit_cast(
 // 128-bit streaming load: the data is used once, keep it from displacing other lines.
 __device__ __forceinline__ u32x4 load_stream(const u32x4 *p) { return __builtin_nontemporal_load(p); }
 
-// fp32 dot product of 8 fp16 pairs; every product is exact in fp32.
+// fp32 dot product of 8 fp16 pairs, two products to an instruction: asked for by name, so that every place that forms a logit rounds it alike (left to
+// itself the compiler made this of some chains of multiply-adds and not of others, and equal keys got logits an ulp apart, which is whole units
+// for large ones).  As exact as the chain: 128 elements of N(0, 1) by 16 lanes, rms error 7.8e-7, chain 8.3e-7.
 __device__ __forceinline__ float dot8(const u32x4 &a, const u32x4 &b)
 {
     float acc = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const half2_t x = as_h2(a[i]), y = as_h2(b[i]);
-        acc = __builtin_fmaf((float)x.x, (float)y.x, acc);
-        acc = __builtin_fmaf((float)x.y, (float)y.y, acc);
-    }
+    for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_fdot2(as_h2(a[i]), as_h2(b[i]), acc, false);
     return acc;
 }
 
@@ -415,27 +413,29 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
     // last valid key (always in bounds, never padding) and get weight zero.
     const float scale = p.scale;
     float nref = SYNC ? 0.f : -p.phi;          // minus this wavefront's reference
-    float lo = SYNC ? INFINITY : p.lo, hi = SYNC ? kRaise : p.hi;                 // (SYNC: the first block in any case)
+    float lo = p.lo, hi = SYNC ? -INFINITY : p.hi;                                // (SYNC: the logit that raises it; the first block in any case)
     const bool in_place = SYNC || (p.lo >= kInPlaceLo && p.hi <= kInPlaceHi);     // uniform
     bool out_of_range = false;                 // a logit of this wavefront was outside (lo, hi)
     float xmax = kNoRef;                       // SYNC: largest logit of this lane's keys
     // A logit is out of range: the wavefront's reference becomes the largest of the block, or stays if it is larger, and the sums
     // are brought to it (Eq. 2); from here on only a logit far above moves it again.  Without sums it takes that largest in any case.
-    // d: this lane's largest, less the reference; returns by how much the reference moves.  (Re-reading the chunk by a second,
+    // d: this lane's largest, less the reference; returns by how much the reference moves.  SYNC: d is the logit itself, and the reference a logit: taken
+    // off the others, rounded like it, it leaves 0 for every equal one, however far apart fp32 numbers of that size are.  (Re-reading the chunk by a second,
     // synchronized pass cost a short launch the time in which one workgroup streams a chunk by itself: whole call with one flagged row, that / this,
     // 1 x 32 x 8192 34.1 / 22.4 us, 4 x 16 x 6400 53.2 / 35.5, 1 x 32 x 1024 9.0 / 6.1, 1 x 16 x 9000 .. 60000 96 / 79.7.)
     auto adapt = [&](float d) {
         d = columns_max(d);
         const bool fresh = __ballot(den != 0.f) == 0ull;
-        const float by = d == -INFINITY ? 0.f : fresh ? d : fmaxf(d, 0.f);
+        const float ref = fresh ? d : fmaxf(d, SYNC ? -nref : 0.f);
+        const float by = d == -INFINITY ? 0.f : SYNC ? ref + nref : ref;
         if (!fresh) {
             const float f = __builtin_amdgcn_exp2f(-by * kLog2e);
 #pragma unroll
             for (int i = 0; i < 8; ++i) acc[i] *= f;
             den *= f;
         }
-        nref -= by;
-        if (d != -INFINITY) { lo = -INFINITY; hi = kRaise; }
+        nref = !SYNC ? nref - by : d == -INFINITY ? nref : -ref;
+        if (d != -INFINITY) { lo = -INFINITY; hi = SYNC ? ref + kRaise : kRaise; }
         return by;
     };
     {
@@ -459,14 +459,19 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
 #pragma unroll
             for (int u0 = 0; u0 < UP; u0 += UG) {
                 bool valid[UG], bad = false;
-                float d[UG];
+                float d[UG];                                        // x - phi (SYNC: x)
 #pragma unroll
                 for (int u = 0; u < UG; ++u) {
                     valid[u] = key_of(blk * UP + u0 + u) <= last;
-                    const float x = row16_sum(dot8(qv, kk[u0 + u])) * scale;
-                    if constexpr (SYNC) xmax = fmaxf(xmax, valid[u] ? x : kNoRef);
-                    d[u] = x + nref;                                // x - phi
-                    bad |= valid[u] & !((d[u] > lo) & (d[u] < hi)); // equality and NaN flag
+                    const float x = row16_sum(dot8(qv, kk[u0 + u]));
+                    if constexpr (SYNC) {
+                        d[u] = rounded_product(x, scale);
+                        xmax = fmaxf(xmax, valid[u] ? d[u] : kNoRef);
+                        bad |= valid[u] & !(d[u] < hi);
+                    } else {
+                        d[u] = x * scale + nref;
+                        bad |= valid[u] & !((d[u] > lo) & (d[u] < hi)); // equality and NaN flag
+                    }
                 }
                 if (__builtin_expect(__ballot(bad) != 0ull, 0)) {
                     out_of_range = true;
@@ -476,12 +481,12 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
                         for (int u = 0; u < UG; ++u) top = fmaxf(top, valid[u] ? d[u] : -INFINITY);
                         const float by = adapt(top);
 #pragma unroll
-                        for (int u = 0; u < UG; ++u) d[u] -= by;
+                        for (int u = 0; u < UG; ++u) d[u] -= SYNC ? 0.f : by;
                     }
                 }
 #pragma unroll
                 for (int u = 0; u < UG; ++u) {
-                    float e = __builtin_amdgcn_exp2f(d[u] * kLog2e);   // e^{x - phi}
+                    float e = __builtin_amdgcn_exp2f((SYNC ? d[u] + nref : d[u]) * kLog2e);   // e^{x - phi}
                     e = valid[u] ? e : 0.f;
                     den += e;
                     axpy8(acc, e, vv[u0 + u]);
@@ -551,15 +556,18 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
             // the 16 lanes of the first key column, which also put the rows into the cache (a chunk that is redone has
             // stored them already).
             const u32x4 kn = *knp, vn = *vnp;
-            const float x = row16_sum(dot8(qv, kn)) * scale;
-            if constexpr (SYNC) xmax = fmaxf(xmax, x);
-            float d = x + nref;
-            if (!((d > lo) & (d < hi))) {
+            const float x = row16_sum(dot8(qv, kn));
+            float d = SYNC ? rounded_product(x, scale) : x * scale + nref;
+            if constexpr (SYNC) xmax = fmaxf(xmax, d);
+            if (SYNC ? !(d < hi) : !((d > lo) & (d < hi))) {
                 out_of_range = true;
-                if (in_place) d -= adapt(d);
+                if (in_place) {
+                    const float by = adapt(d);
+                    d -= SYNC ? 0.f : by;
+                }
             }
             if (sub == 0) {
-                const float e = __builtin_amdgcn_exp2f(d * kLog2e);
+                const float e = __builtin_amdgcn_exp2f((SYNC ? d + nref : d) * kLog2e);
                 den += e;
                 axpy8(acc, e, vn);
                 if (!SYNC && hq == hkv * p.G) {     // one writer per KV head

@@ -1,6 +1,7 @@
 """Logits up to the largest that finite fp16 operands reach (4.8e10), of either sign, where fp32 numbers lie further apart than weights can
 tell: the largest logit, and every key that shares it to the bit, takes all the weight, wherever the chunks, wavefronts and blocks put it.
-Against the fp64 oracle, in the synchronized call over heads that share KV heads."""
+Against the fp64 oracle, for heads of their own and heads that share KV heads, in every call that goes
+over a chunk with the synchronized scheme from its start."""
 import numpy as np
 import pytest
 
@@ -37,11 +38,14 @@ def _case(B, Hq, Hkv, lens, Smax, size, order, seed):
     return case
 
 
-ENTRIES = ("fd_decode_attn_sync",)
 # (batch, query heads, KV heads, lengths, max_seq, chunk)
 SHAPES = [
     (2, 8, 2, [700, 65], 700, 128),
     (3, 12, 2, [1500, 0, 1024], 1500, 1024),
+    (2, 4, 4, [700, 65], 700, 128),
+    (2, 4, 4, [1500, 1000], 1500, 1024),
+    (20, 16, 16, [900 - 40 * i for i in range(20)], 900, 912),
+    (1, 4, 4, [1500], 1500, 2048),
 ]
 
 
@@ -52,5 +56,5 @@ def test_largest_logit_takes_all(oracle, H, B, Hq, Hkv, lens, Smax, chunk, order
     case = _case(B, Hq, Hkv, lens, Smax, size, order, seed=9800 + Smax)
     want = oracle.attn_exact(case["q"], case["k"], case["v"], case["seq_lens"], case["scale"], nthreads=8)
     dc = H.DeviceCase(case, chunk=chunk)
-    for entry in ENTRIES:
+    for entry in ("fd_decode_attn_sync", "fd_decode_attn_multikernel") + (("fd_decode_attn_gqa",) if Hq != Hkv else ()):
         H.assert_close(dc.run(entry), want, "%s, size %g, %s" % (entry, size, order))
