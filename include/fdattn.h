@@ -142,9 +142,10 @@ fd_status fd_workspace_init(const fd_shape *shape, fd_workspace ws, void *stream
  *      and no rescaling                               (Eq. 4, inner sums);
  *   2. where the guard fires, the keys from there on are summed by the synchronized
  *      scheme, with a reference of their own, and what was summed before is brought to
- *      it: (m, l, f.V)  (Eq. 2; "Recomputation").  Bounds below -64 or above 60 admit
- *      sums that cannot be brought to another reference in fp32: with those the chunk
- *      is recomputed at once instead;
+ *      it, all of it in the end to the chunk's largest logit: (m, l, f.V)  (Eq. 2;
+ *      "Recomputation").  Bounds below -64 or above 60 admit
+ *      sums that cannot be brought to another reference in fp32: with those, and for
+ *      logits beyond 65536, the chunk is recomputed at once instead;
  *   3. the workgroup that completes a row last -- elected by a small tree of
  *      integer arrival counters per row; the sums themselves use no atomics and
  *      run in fixed order -- forms the row: unflagged rows by the plain outer
@@ -372,8 +373,9 @@ fd_status fd_list_flagged_rows(const fd_shape *shape, const int32_t *seq_lens,
  *   num [batch*n_q_heads, ceil(max_seq/chunk), head_dim] fp32 = sum e^{x-phi} v
  *   den [batch*n_q_heads, ceil(max_seq/chunk)]           fp32 = sum e^{x-phi}
  * Chunks without a valid key hold zeros.  Chunks whose guard fired or that were
- * recomputed hold the synchronized scheme's (f.V, l) instead, by a reference of
- * their own; after fd_decode_attn_sync all do.
+ * recomputed hold the synchronized scheme's (f.V, l) instead, relative to the chunk's
+ * largest logit (to within fp32 rounding); after fd_decode_attn_sync all do.  (In a row that
+ * fd_decode_attn_multikernel flagged, every chunk was recomputed.)
  */
 fd_status fd_get_partials(const fd_shape *shape, fd_workspace ws,
                           const float **num, const float **den);

@@ -205,7 +205,7 @@ struct ChunkLds {
     alignas(16) float den[NW];
     alignas(16) int   flag[NW];
     alignas(16) float ref[NW];             // what the wavefronts' sums are scaled by ...
-    alignas(16) float top[NW];             // ... and, in the synchronized scheme, their largest logits
+    alignas(16) float top[NW];             // ... and their largest logits (unified scheme: largest weights)
 };
 
 // References that move (chunk_body).
@@ -214,6 +214,9 @@ constexpr float kRaise = 40.f;             // a logit this far above the wavefro
 // The bounds within which the weights of in-range logits leave sums that can be brought to another reference: e^-64 and 4096 e^60 max|v|
 // are ordinary fp32 numbers.
 constexpr float kInPlaceLo = -64.f, kInPlaceHi = 60.f;
+// And how far from 0 and from the old reference a new one may lie: the difference of two such numbers, rounded, is within 2^-7 of the exact one, so
+// the largest weight is 1 to within that.
+constexpr float kInPlaceReach = 65536.f;
 
 // A wavefront's four columns of sums added in registers, exchanging halves and rows of
 // two registers at a time, so that lane (sub, seg) ends up with elements 8 seg + 2 sub and the next: 12 instructions.
@@ -244,8 +247,9 @@ __device__ __forceinline__ const float2 *sums_read(const float *acc, int lane)
 //   SYNC == false : unified scaling factor phi -- Eq. 4 inner sums and the range
 //                   guard of Section 3 "Recomputation".  Writes num, den,
 //                   chunk_flags and mloc = phi (the reference the sums are scaled by).  Where the guard fires the wavefront goes on by the
-//                   synchronized scheme from that block of keys on (see `adapt` below), and the slot's reference is the largest of its
-//                   wavefronts'; with bounds beyond kInPlaceLo, kInPlaceHi the caller has to redo the chunk instead.
+//                   synchronized scheme from that block of keys on (see `adapt` below), and the slot's reference is the chunk's largest
+//                   logit, as after SYNC (formed from the largest weight: to within fp32 rounding); with bounds beyond kInPlaceLo, kInPlaceHi,
+//                   and for logits beyond kInPlaceReach, the caller has to redo the chunk instead.
 //   SYNC == true  : the chunk's part of the synchronized partial softmax, Eq. 2, in one pass: a wavefront keeps a reference that
 //                   a logit more than kRaise above it raises, and its sums are brought to m = max x at the end: l = sum e^{x-m}, f.V = sum
 //                   e^{x-m} v.  Writes num, den, mloc = m and leaves chunk_flags alone; `sync_flag` is what the
@@ -415,28 +419,34 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
     float nref = SYNC ? 0.f : -p.phi;          // minus this wavefront's reference
     float lo = p.lo, hi = SYNC ? -INFINITY : p.hi;                                // (SYNC: the logit that raises it; the first block in any case)
     const bool in_place = SYNC || (p.lo >= kInPlaceLo && p.hi <= kInPlaceHi);     // uniform
-    bool out_of_range = false;                 // a logit of this wavefront was outside (lo, hi)
-    float xmax = kNoRef;                       // SYNC: largest logit of this lane's keys
+    int out_of_range = 0;                      // 1: a logit of this wavefront was outside (lo, hi); | 2: and the chunk has to be redone for it
+    float top = SYNC ? kNoRef : 0.f;           // largest logit of this lane's keys (SYNC), their largest weight
     // A logit is out of range: the wavefront's reference becomes the largest of the block, or stays if it is larger, and the sums
     // are brought to it (Eq. 2); from here on only a logit far above moves it again.  Without sums it takes that largest in any case.
-    // d: this lane's largest, less the reference; returns by how much the reference moves.  SYNC: d is the logit itself, and the reference a logit: taken
+    // d: this lane's largest, less the reference.  SYNC: d is the logit itself, and the reference a logit: taken
     // off the others, rounded like it, it leaves 0 for every equal one, however far apart fp32 numbers of that size are.  (Re-reading the chunk by a second,
     // synchronized pass cost a short launch the time in which one workgroup streams a chunk by itself: whole call with one flagged row, that / this,
     // 1 x 32 x 8192 34.1 / 22.4 us, 4 x 16 x 6400 53.2 / 35.5, 1 x 32 x 1024 9.0 / 6.1, 1 x 16 x 9000 .. 60000 96 / 79.7.)
     auto adapt = [&](float d) {
         d = columns_max(d);
+        if constexpr (SYNC) {
+            if (d == -INFINITY) return;
+        } else if (!(fmaxf(fabsf(d), fabsf(nref - d)) < kInPlaceReach)) {        // (also where no logit of the block is a finite number)
+            out_of_range = 3;
+            return;
+        }
         const bool fresh = __ballot(den != 0.f) == 0ull;
         const float ref = fresh ? d : fmaxf(d, SYNC ? -nref : 0.f);
-        const float by = d == -INFINITY ? 0.f : SYNC ? ref + nref : ref;
         if (!fresh) {
-            const float f = __builtin_amdgcn_exp2f(-by * kLog2e);
+            const float f = __builtin_amdgcn_exp2f((SYNC ? -nref - ref : -ref) * kLog2e);
 #pragma unroll
             for (int i = 0; i < 8; ++i) acc[i] *= f;
             den *= f;
+            if constexpr (!SYNC) top *= f;
         }
-        nref = !SYNC ? nref - by : d == -INFINITY ? nref : -ref;
-        if (d != -INFINITY) { lo = -INFINITY; hi = SYNC ? ref + kRaise : kRaise; }
-        return by;
+        nref = SYNC ? -ref : nref - ref;
+        lo = -INFINITY;
+        hi = SYNC ? ref + kRaise : kRaise;
     };
     {
         // Rows of more than 32 chunks: every workgroup starts its chunk at a different block and wraps
@@ -466,29 +476,33 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
                     const float x = row16_sum(dot8(qv, kk[u0 + u]));
                     if constexpr (SYNC) {
                         d[u] = rounded_product(x, scale);
-                        xmax = fmaxf(xmax, valid[u] ? d[u] : kNoRef);
+                        top = fmaxf(top, valid[u] ? d[u] : kNoRef);
                         bad |= valid[u] & !(d[u] < hi);
                     } else {
-                        d[u] = x * scale + nref;
-                        bad |= valid[u] & !((d[u] > lo) & (d[u] < hi)); // equality and NaN flag
+                        d[u] = __builtin_fmaf(x, scale, nref);
+                        bad |= valid[u] & !((d[u] > lo) & (d[u] < hi));          // equality and NaN flag
                     }
                 }
                 if (__builtin_expect(__ballot(bad) != 0ull, 0)) {
-                    out_of_range = true;
+                    out_of_range |= 1;
                     if (in_place) {
-                        float top = -INFINITY;
+                        float most = -INFINITY;
 #pragma unroll
-                        for (int u = 0; u < UG; ++u) top = fmaxf(top, valid[u] ? d[u] : -INFINITY);
-                        const float by = adapt(top);
+                        for (int u = 0; u < UG; ++u) most = fmaxf(most, valid[u] ? d[u] : -INFINITY);
+                        adapt(most);
+                        // formed anew from the key, the difference is the same for equal keys of any block
+                        if constexpr (!SYNC) {
 #pragma unroll
-                        for (int u = 0; u < UG; ++u) d[u] -= SYNC ? 0.f : by;
+                            for (int u = 0; u < UG; ++u) d[u] = __builtin_fmaf(row16_sum(dot8(qv, kk[u0 + u])), scale, nref);
+                        }
                     }
                 }
 #pragma unroll
                 for (int u = 0; u < UG; ++u) {
-                    float e = __builtin_amdgcn_exp2f((SYNC ? d[u] + nref : d[u]) * kLog2e);   // e^{x - phi}
+                    float e = __builtin_amdgcn_exp2f((SYNC ? d[u] + nref : d[u]) * kLog2e);      // e^{x - phi}
                     e = valid[u] ? e : 0.f;
                     den += e;
+                    if constexpr (!SYNC) top = fmaxf(top, e);
                     axpy8(acc, e, vv[u0 + u]);
                 }
             }
@@ -556,18 +570,20 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
             // the 16 lanes of the first key column, which also put the rows into the cache (a chunk that is redone has
             // stored them already).
             const u32x4 kn = *knp, vn = *vnp;
-            const float x = row16_sum(dot8(qv, kn));
-            float d = SYNC ? rounded_product(x, scale) : x * scale + nref;
-            if constexpr (SYNC) xmax = fmaxf(xmax, d);
-            if (SYNC ? !(d < hi) : !((d > lo) & (d < hi))) {
-                out_of_range = true;
-                if (in_place) {
-                    const float by = adapt(d);
-                    d -= SYNC ? 0.f : by;
-                }
+            float x = row16_sum(dot8(qv, kn));
+            if constexpr (SYNC) {
+                x = rounded_product(x, scale);
+                top = fmaxf(top, x);
+            }
+            auto less_ref = [&] { return SYNC ? x + nref : __builtin_fmaf(x, scale, nref); };
+            const float d = less_ref();
+            if (SYNC ? !(x < hi) : !((d > lo) & (d < hi))) {
+                out_of_range |= 1;
+                if (in_place) adapt(SYNC ? x : d);
             }
             if (sub == 0) {
-                const float e = __builtin_amdgcn_exp2f((SYNC ? d + nref : d) * kLog2e);
+                const float e = __builtin_amdgcn_exp2f(less_ref() * kLog2e);
+                if constexpr (!SYNC) top = fmaxf(top, e);
                 den += e;
                 axpy8(acc, e, vn);
                 if (!SYNC && hq == hkv * p.G) {     // one writer per KV head
@@ -577,11 +593,12 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
             }
         }
     }
-    if constexpr (SYNC) {
-        xmax = columns_max(xmax);
-        if (lane == 0) lds.top[wave] = xmax;
-    }
-    if (lane == 0) { lds.flag[wave] = out_of_range; lds.ref[wave] = -nref; }
+    auto hand_over_reference = [&] {
+        top = columns_max(top);
+        if (lane == 0) { lds.ref[wave] = -nref; lds.top[wave] = top; }
+    };
+    if constexpr (SYNC) hand_over_reference();
+    else if (lane == 0) lds.flag[wave] = out_of_range;
 
     if constexpr (!SYNC) FD_PHASE(2);
     // Workgroup reduction.  Within a wavefront in registers; then wavefront 0 adds the others' sums and writes the slot by itself, and
@@ -592,19 +609,26 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
     *sums_place(lds.acc[wave], lane) = make_float2(u[0], u[1]);
     if (lane == 0) lds.den[wave] = den;
     __syncthreads();
-    bool flagged = false;
+    int flagged = 0;
     if constexpr (!SYNC) {
 #pragma unroll
-        for (int w = 0; w < NW; ++w) flagged |= lds.flag[w] != 0;
+        for (int w = 0; w < NW; ++w) flagged |= lds.flag[w];
+    }
+    const bool redo = flagged != 0 && (!in_place || flagged != 1);
+    const bool in_place_sums = !SYNC && __builtin_expect(flagged != 0 && !redo, 0);
+    if (in_place_sums) {                       // (uniform; only now are the references needed, so that other chunks do without them)
+        hand_over_reference();
+        __syncthreads();
     }
     if (wave == 0) {
         u[0] = u[1] = den = 0.f;
         float mc = p.phi;
-        if (SYNC || (flagged & in_place)) {
-            // from each wavefront's reference to the chunk's: the largest of those with sums (SYNC: the largest logit)
+        if (SYNC || in_place_sums) {
+            // from each wavefront's reference to the largest logit
             mc = kNoRef;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) mc = fmaxf(mc, SYNC ? lds.top[w] : lds.den[w] != 0.f ? lds.ref[w] : kNoRef);
+            for (int w = 0; w < NW; ++w)
+                mc = fmaxf(mc, SYNC ? lds.top[w] : lds.top[w] > 0.f ? __builtin_fmaf(__builtin_amdgcn_logf(lds.top[w]), 1.f / kLog2e, lds.ref[w]) : kNoRef);
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
                 const float2 o = *sums_read(lds.acc[w], lane);
@@ -629,16 +653,16 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
             store_coherent(&p.ws.mloc[slot], mc);
             // the flag the row epilogue ORs into the row flag: the guard's; a recomputed chunk carries what its caller
             // says (1 when the guard sent it here, 0 when it is redone for another reason)
-            store_meta(p, slot, den, mc, SYNC ? sync_flag : (int)flagged);
-            if (!SYNC) p.ws.chunk_flags[slot] = flagged ? 1 : 0;
+            store_meta(p, slot, den, mc, SYNC ? sync_flag : (int)(flagged != 0));
+            if (!SYNC) p.ws.chunk_flags[slot] = flagged != 0;
         }
     }
-    return flagged & !in_place;
+    return redo;
 }
 
 // Row epilogue of a workgroup of 256 threads, in a launch of its own: the synchronized update of Eq. 2 over the row's
 // partial results, each scaled by its own reference r_c -- phi for chunks summed
-// with the unified factor, the chunk maximum for recomputed ones:
+// with the unified factor, the chunk's largest logit for those whose guard fired or that were recomputed:
 //     m = max_c r_c,   out = sum_c e^{r_c-m} num_c / sum_c e^{r_c-m} den_c,
 // evaluated in one pass with a running maximum (partial sums are merged by the same
 // rule).  For a row without flags every r_c is phi, every factor is exactly 1 and

@@ -22,8 +22,8 @@ inline int chunk_capacity(int len)
 constexpr float kLog2e = 1.4426950408889634f;
 
 // One record per (row, chunk) slot, read by the row epilogue with a single 16-byte
-// load: the slot's denominator, the reference its sums are scaled by (phi, or the
-// chunk maximum after a recomputation) and whether the chunk's guard fired.
+// load: the slot's denominator, the reference its sums are scaled by (phi, or the chunk's largest
+// logit where the guard fired or the chunk was recomputed) and whether the chunk's guard fired.
 struct alignas(16) SlotMeta {
     float den, ref;
     int flagged, pad;
@@ -33,7 +33,7 @@ struct alignas(16) SlotMeta {
 struct WsView {
     float   *num;          // [rows, nc, 128]  sum e^{x-phi} v   (or f.V of the synchronized scheme)
     float   *den;          // [rows, nc]       sum e^{x-phi}     (or l)
-    float   *mloc;         // [rows, nc]       chunk maximum m (synchronized scheme only)
+    float   *mloc;         // [rows, nc]       the reference of num and den: phi, or the chunk's largest logit m
     uint8_t *chunk_flags;  // [rows, nc]
     SlotMeta *meta;        // [rows, nc]  (den, reference, flag) handed to the row epilogue
     uint8_t *row_flags;    // [rows]  (room for rows * nc)

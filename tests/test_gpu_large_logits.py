@@ -1,7 +1,6 @@
 """Logits up to the largest that finite fp16 operands reach (4.8e10), of either sign, where fp32 numbers lie further apart than weights can
 tell: the largest logit, and every key that shares it to the bit, takes all the weight, wherever the chunks, wavefronts and blocks put it.
-Against the fp64 oracle, for heads of their own and heads that share KV heads, in every call that goes
-over a chunk with the synchronized scheme from its start."""
+Against the fp64 oracle, for heads of their own and heads that share KV heads, in every decode call."""
 import numpy as np
 import pytest
 
@@ -56,5 +55,5 @@ def test_largest_logit_takes_all(oracle, H, B, Hq, Hkv, lens, Smax, chunk, order
     case = _case(B, Hq, Hkv, lens, Smax, size, order, seed=9800 + Smax)
     want = oracle.attn_exact(case["q"], case["k"], case["v"], case["seq_lens"], case["scale"], nthreads=8)
     dc = H.DeviceCase(case, chunk=chunk)
-    for entry in ("fd_decode_attn_sync", "fd_decode_attn_multikernel") + (("fd_decode_attn_gqa",) if Hq != Hkv else ()):
+    for entry in ("fd_decode_attn_sync", "fd_decode_attn", "fd_decode_attn_multikernel") + (("fd_decode_attn_gqa",) if Hq != Hkv else ()):
         H.assert_close(dc.run(entry), want, "%s, size %g, %s" % (entry, size, order))
