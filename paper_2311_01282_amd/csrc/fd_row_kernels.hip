@@ -33,7 +33,14 @@ template <int C> struct Tune {
 // 110.6 / 107.5, 12 x 40 x 187 .. 1500 in 6 41.6 / 41.0, 4 x 16 x 30000 in 30 156.7 / 155.8, 2 x 40 x 12564 .. 25128 in 25 a tie.  Where they do divide by 4, an XCD gets the
 // same few chunks of every row, which in a ragged batch are the full or the empty ones (16 x 32 x 512 .. 4096 in 8 110 / 136, 24 x 16 x 500 .. 4000
 // in 16 84.7 / 93.4, 23 x 16 x 379 .. 3037 in 12 59.0 / 61.8); rows of more than 32 chunks are turned (2 x 16 x 6740 .. 53923 in 53 130.2 / 133.6).
-__device__ __forceinline__ bool plain_order(const Problem &p) { return (p.rows & 7) != 0 || ((p.nc & 3) != 0 && p.nc <= 32); }
+// Two chunks, and six, leave an XCD one of the two, or every other of the six, which is no better in a ragged batch (110 x 16 x 465 .. 930 in 2 101.5 /
+// 110.7, 25 x 32 x 209 .. 1678 in 2 72.2 / 77.2, 25 x 16 x 759 .. 6073 in 6 109.5 / 113.4, 20 x 16 x 800 .. 2900 in 6 55.6 / 56.7; equal lengths would gain 2 %: 110 x
+// 16 x 1941 in 2 259 / 254); from ten on there are enough of them (2 x 40 x 3306 .. 13224 in 26 84.7 / 82.7).  The synchronized scheme keeps the
+// order there: 10 x 40 x 1339 .. 5356 in 6 127.8 / 122.9, 3 x 32 x 1525 .. 6103 in 6 44.4 / 36.2, 29 x 16 x 1700 in 2 66.6 / 65.0 (but 38 x 32 x 224 .. 1799 in 2 117.4 / 124.8).
+template <bool SYNC> __device__ __forceinline__ bool plain_order(const Problem &p)
+{
+    return (p.rows & 7) != 0 || ((p.nc & 3) != 0 && p.nc <= 32 && (SYNC || (p.nc & 1) != 0 || p.nc > 8));
+}
 
 // ELECT: rows are finished in the launch (elect_per_row in fd_api.hip says which launches do).
 // PAGED: K and V are page pools addressed through the sequence's block table.
@@ -72,7 +79,7 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void decode_fused_kernel(const Pr
     const int groups8 = (p.rows + 7) >> 3;
     const int j = blockIdx.x >> 3;
     constexpr bool CM = EARLY;                 // chunk-major in the one-round launches only (see below)
-    const bool plain = !ELECT && plain_order(p);
+    const bool plain = !ELECT && plain_order<SYNC>(p);
     const int c = plain ? (int)blockIdx.x % p.nc : CM ? j / groups8 : j % p.nc;
     const int row = plain ? (int)blockIdx.x / p.nc : row_slot(p, blockIdx.x & 7, c) + 8 * (CM ? j - c * groups8 : j / p.nc);
     if (row >= p.rows) return;
@@ -315,7 +322,7 @@ __global__ __launch_bounds__(256) void partial_sync_kernel(const Problem p)
     __shared__ ChunkLds<NW> lds;
     __shared__ float logit[C];
     fetch_arguments_now(p);
-    const bool plain = plain_order(p) || p.nc > 32;
+    const bool plain = plain_order<true>(p) || p.nc > 32;
     const int j = blockIdx.x >> 3;
     const int c = plain ? (int)blockIdx.x % p.nc : j % p.nc;
     const int row = plain ? (int)blockIdx.x / p.nc : row_slot(p, blockIdx.x & 7, c) + 8 * (j / p.nc);

@@ -19,6 +19,7 @@ def H():
     (1, 1, 64, 64), (1, 1, 33 * 64, 64), (1, 3, 40 * 64, 64), (2, 2, 129 * 64, 64), (7, 1, 70 * 96, 96),   # fewer than eight rows
     (1, 9, 5 * 64, 64), (3, 5, 130 * 64, 64),                                                              # rows that 8 does not divide
     (47, 4, 6 * 64, 64), (48, 22, 6 * 272, 272), (48, 22, 7 * 272, 272), (48, 22, 8 * 272, 272),           # 6, 7, 8 chunks
+    (24, 22, 2 * 272, 272), (8, 16, 10 * 272, 272),                                                        # 2 and 10, two launches
     (2, 8, 31 * 1024, 1024), (2, 16, 34 * 1024, 1024),
 ])
 def test_every_chunk_once(oracle, H, B, heads, Smax, chunk):
