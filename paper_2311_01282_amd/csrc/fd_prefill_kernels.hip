@@ -865,15 +865,27 @@ hipError_t launch_prefill(const PrefillProblem &p0, hipStream_t s)
     const int qtiles = (p.Smax + kQTile - 1) / kQTile;
     const long long tiles = (long long)p.B * p.Hq * qtiles;
     // Launches that would leave compute units with one workgroup or none: tiles of 64 queries, walked by twice the wavefronts (see
-    // tile_unified).  Whole call, without / with: 1 x 32 heads x 256 tokens 10.1 / 8.8 us, 512 14.8 / 12.2, 1024 24.9 / 21.2, 1 x 16 x 2000 40.3 /
-    // 32.7, 1 x 32/8 x 512 14.5 / 11.5, 2 x 28/4 x 500 15.8 / 14.0; but 6 x 12/2 x 217 9.53 / 9.73.  A few tiles more: where a head has several, of unequal length
-    // (1 x 32 x 1152, 288 tiles, 27.6 / 24.0, 1 x 28/4 x 1260, 280, 29.2 / 25.1; 9 x 32 x 100, 288, 12.2 / 15.0).  With more the keys' second
+    // tile_unified).  Whole call, without / with: 1 x 32 heads x 256 tokens 10.0 / 8.7 us, 512 14.6 / 11.7, 1024 24.0 / 20.4, 1 x 16 x 2000 38.9 /
+    // 31.8, 2 x 28/4 x 500 15.8 / 14.0.  What bounds short prompts is a tile's beginning and end, of which there are more then.  Up to 96 tokens a tile
+    // as it comes has at most three wavefronts at work and 64 queries gain nothing (1 x 32 x 64 5.8 / 6.6, 16 x 12/2 x 64 6.4 / 7.1, 1 x 32 x 88 6.74 /
+    // 6.74, 100 7.4 / 6.9); heads of one or two tiles of 128 need a compute unit for each of 64 (64 heads x 217 tokens, 256 of them, 9.3 / 8.5, 128 x 100, 256,
+    // 7.7 / 7.3; 160 x 100, 320, 7.9 / 9.1, 96 x 217, 384, 9.7 / 10.7), and heads of three 192 tiles or a last one with all four wavefronts
+    // at work (64 x 280, 192, 10.7 / 10.4, 80 x 384, 240, 13.5 / 12.6; 80 x 290, 240, 11.3 / 11.6).  A few tiles more than compute units where a head has
+    // more than four, of unequal length
+    // (1 x 32 x 1152, 288 tiles, 27.6 / 24.0, 1 x 28/4 x 1260, 280, 29.2 / 25.1).  With more the keys' second
     // reading costs more than the shorter walk gives: 2 x 28/4 x 650, 336 tiles, 19.1 / 22.8, 1 x 32 x 1536, 384, 37.2 / 40.1, 2 x 32 x 1024, 512, 31.7 / 37.9.
-    if (tiles <= kComputeUnits || (tiles <= kComputeUnits + kComputeUnits / 8 && qtiles > 4)) {
+    const int halves = (p.Smax + kQTile / 2 - 1) / (kQTile / 2);               // tiles of 64 queries of a head
+    const int over = p.Smax % kQTile;                                          // queries of the last tile as they come (0: all)
+    const bool last_busy = over == 0 || over > 3 * kWaveQ;
+    const bool split = qtiles > 4    ? tiles <= kComputeUnits + kComputeUnits / 8
+                       : qtiles == 4 ? tiles <= kComputeUnits
+                       : qtiles == 3 ? tiles <= (last_busy ? kComputeUnits : 3 * kComputeUnits / 4)
+                                     : p.Smax > 3 * kWaveQ && (long long)p.B * p.Hq * halves <= kComputeUnits;
+    if (split) {
         p.group = p.B * p.Hq;
         p.parts = 1;
         p.shift = 0;
-        return launch(prefill_kernel<true>, dim3((unsigned)(p.group * ((p.Smax + kQTile / 2 - 1) / (kQTile / 2)))), dim3(256), s, p);
+        return launch(prefill_kernel<true>, dim3((unsigned)(p.group * halves)), dim3(256), s, p);
     }
     head_group(p, qtiles);
     // Tiles end at a multiple of 128 queries, or of 64 where that leaves the last one of a prompt as long as the buffer at least half
@@ -882,7 +894,6 @@ hipError_t launch_prefill(const PrefillProblem &p0, hipStream_t s)
     // heads x 1284 tokens 233.9 / 218.7 us, 4 x 32 x 1030 67.2 / 64.8, 8 x 64/8 x 400 57.0 / 55.5, 1 x 32 x 4100 175.2 / 173.2.  A launch of up to two
     // tiles per compute unit ends with its longest tile, and one of short prompts has little else: both take longer over a last tile with four wavefronts
     // at work than with two, and shift for one only (2 x 28/4 x 650, 336 tiles, one wavefront, 20.5 / 19.6; 8 x 32 x 300, two, 25.1 / 27.2).
-    const int over = p.Smax % kQTile;                                          // queries of the last tile as they come
     const int most = tiles > 2 * kComputeUnits && qtiles > 4 ? 2 * kWaveQ : kWaveQ;
     p.shift = over > 0 && over <= most ? 64 : 0;
     return launch(prefill_kernel<false>, dim3((unsigned)tiles), dim3(256), s, p);

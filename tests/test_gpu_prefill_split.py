@@ -28,8 +28,11 @@ def test_edges_of_tiles_and_steps(H, Smax):
     _check(H, 6, 4, *draw(6, 4, 2, Smax, lens, seed=7700 + Smax), Smax, "prefill of %d" % Smax, flagged=False)
 
 
-# the rule: up to 256 tiles of 128 queries, up to 288 of which a head has more than four, and what is just beyond
-@pytest.mark.parametrize("B,Hq,Hkv,Smax", [(16, 16, 2, 100), (1, 257, 257, 40), (4, 12, 2, 700), (1, 49, 7, 650), (2, 24, 24, 641)])
+# the rule: up to 256 tiles of 128 queries, up to 288 of which a head has more than four, fewer where a head has one to three, none up to 96
+# queries, and what is just beyond
+@pytest.mark.parametrize("B,Hq,Hkv,Smax", [(16, 16, 2, 100), (1, 257, 257, 40), (4, 12, 2, 700), (1, 49, 7, 650), (2, 24, 24, 641), (1, 128, 16, 97),
+                                           (1, 128, 16, 96), (1, 129, 43, 97), (1, 64, 8, 217), (1, 65, 65, 217), (1, 64, 8, 290), (1, 65, 65, 290),
+                                           (1, 85, 85, 360), (1, 64, 8, 400)])
 def test_edges_of_the_rule(H, B, Hq, Hkv, Smax):
     q, k, v, sl = draw(B, Hq, Hkv, Smax, [Smax] + [max(0, Smax - 37 * b) for b in range(1, B)], seed=7800 + Smax)
     rng = np.random.default_rng(5)
