@@ -243,7 +243,9 @@ hipError_t dispatch_chunk(int C, Args... args)
 //   Smaller launches of up to 32 chunks per row lose (3 x 32 x 1500 in 5 15.0 / 15.35, 3 x 32 x 4096 33.15 / 33.8), and so do chunks of
 // 2048 keys (1 x 40 x 60000 in 30 198.0 / 202.1, 32 x 131072 314.7 / 316.4).  Shorter chunks than 256 keys have no third block.
 //   Paged caches in launches without a hand-over the same: 3 x 32 x 2470 .. 19765 (page 256) 95.7 / 93.6, 8 x 16 x 4000 .. 16000 (64) 108.75 / 108.3,
-// 11 x 16 x 1275 .. 10200 (16) 101.4 / 101.8.
+// 11 x 16 x 1275 .. 10200 (16) 101.4 / 101.8.  With a hand-over chunks of more than 512 keys do: 1 x 32 x 46680 (256) in 2048 122.8 / 119.1, 2 x 16 x 30000 (256) in
+// 2048 81.95 / 79.5, 1 x 16 x 18074 (256) in 1216 26.95 / 26.06, 1 x 32 x 8192 (64) in 1024 31.55 / 31.0; of 512 2 x 32 x 3000 (64) 19.8 / 19.9, 1 x 40 x 4000 (16)
+// 18.4 / 18.5.
 template <int C> struct LoadAhead {
     static constexpr bool kOneBuilt = C >= 256 && C <= 1024;
     static bool one(const Problem &p)
@@ -270,7 +272,7 @@ template <int C> struct FusedLauncher {
                 return launch(decode_fused_kernel<C, false, true, false, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p);
         }
         if (p.block_table)
-            return p.elect ? launch(decode_fused_kernel<C, true, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p)
+            return p.elect ? launch(decode_fused_kernel<C, true, true, false, (C >= 1024)>, dim3(grid), dim3(Tune<C>::NW * 64), s, p)
                            : launch(decode_fused_kernel<C, false, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p);
         if (p.elect && grid <= (unsigned)kComputeUnits)
             return launch(decode_fused_kernel<C, true, false, true>, dim3(grid), dim3(Tune<C>::NW * 64), s, p);
