@@ -37,9 +37,11 @@ template <int C> struct Tune {
 // 110.7, 25 x 32 x 209 .. 1678 in 2 72.2 / 77.2, 25 x 16 x 759 .. 6073 in 6 109.5 / 113.4, 20 x 16 x 800 .. 2900 in 6 55.6 / 56.7; equal lengths would gain 2 %: 110 x
 // 16 x 1941 in 2 259 / 254); from ten on there are enough of them (2 x 40 x 3306 .. 13224 in 26 84.7 / 82.7).  The synchronized scheme keeps the
 // order there: 10 x 40 x 1339 .. 5356 in 6 127.8 / 122.9, 3 x 32 x 1525 .. 6103 in 6 44.4 / 36.2, 29 x 16 x 1700 in 2 66.6 / 65.0 (but 38 x 32 x 224 .. 1799 in 2 117.4 / 124.8).
+// It takes it always where heads share KV heads: the heads of a group then read a chunk through the same XCD's L2 where the chunks divide by 8, through
+// two where they divide by 4 (1 x 32/4 x 1536 in 16 7.95 / 7.03, 1 x 28/4 x 1024 in 8 7.87 / 6.74, 1 x 32/4 x 4096 in 8 12.7 / 8.95).
 template <bool SYNC> __device__ __forceinline__ bool plain_order(const Problem &p)
 {
-    return (p.rows & 7) != 0 || ((p.nc & 3) != 0 && p.nc <= 32 && (SYNC || (p.nc & 1) != 0 || p.nc > 8));
+    return (p.rows & 7) != 0 || (SYNC && p.G > 1) || ((p.nc & 3) != 0 && p.nc <= 32 && (SYNC || (p.nc & 1) != 0 || p.nc > 8));
 }
 
 // ELECT: rows are finished in the launch (elect_per_row in fd_api.hip says which launches do).

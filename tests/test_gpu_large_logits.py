@@ -40,6 +40,7 @@ def _case(B, Hq, Hkv, lens, Smax, size, order, seed):
 # (batch, query heads, KV heads, lengths, max_seq, chunk)
 SHAPES = [
     (2, 8, 2, [700, 65], 700, 128),
+    (12, 8, 2, [700, 65, 0, 699] * 3, 700, 128),
     (3, 12, 2, [1500, 0, 1024], 1500, 1024),
     (2, 4, 4, [700, 65], 700, 128),
     (2, 4, 4, [1500, 1000], 1500, 1024),

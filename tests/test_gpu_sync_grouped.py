@@ -38,6 +38,22 @@ def _check(oracle, H, case, chunk, what, ramp):
     (2, 12, 2, [64 * 40, 64 * 33 + 1], 64 * 40, 64),
     (1, 2, 1, [900], 900, 64),
     (1, 2, 1, [900], 900, 96),
+    # as above, in launches that the tile takes: chunks beyond 512 keys, or more than 65536 keys in all of the per-row kernel's workgroups (one of 64 keys
+    # with early loads); and the edges of that rule
+    (36, 16, 2, [1, 15, 16, 17] * 9, 80, 64),
+    (3, 16, 1, [0, 700, 64], 700, 528),
+    (2, 4, 2, [600, 129], 600, 528),
+    (20, 15, 3, [1024 - 49 * i for i in range(20)], 1024, 80),
+    (3, 12, 2, [64 * 40, 64 * 33 + 1, 700], 64 * 40, 64),
+    (40, 2, 1, [900 - 23 * i for i in range(40)], 900, 64),
+    (40, 2, 1, [900 - 23 * i for i in range(40)], 900, 96),
+    (4, 64, 4, [500, 1, 64, 333], 500, 64),
+    (4, 16, 2, [2048, 1000, 3, 512], 2048, 512),
+    (4, 16, 2, [2112, 1000, 3, 512], 2112, 528),
+    (1, 32, 2, [2048], 2048, 128),
+    (1, 32, 2, [2049], 2049, 128),
+    (2, 32, 2, [1024, 900], 1024, 64),
+    (2, 32, 2, [1025, 900], 1025, 64),
 ])
 @pytest.mark.parametrize("ramp", [None, (-150.0, 150.0), (150.0, -150.0), (-900.0, -880.0), (700.0, 720.0)])
 def test_grouped_rows(oracle, H, B, Hq, Hkv, lens, Smax, chunk, ramp):
@@ -48,7 +64,8 @@ def test_grouped_rows(oracle, H, B, Hq, Hkv, lens, Smax, chunk, ramp):
 
 
 @pytest.mark.parametrize("what", ["v_inf", "v_nan", "k_nan", "k_inf", "k_minus_inf"])
-def test_not_finite_as_from_heads_of_their_own(H, what):
+@pytest.mark.parametrize("chunk", [128, 528])
+def test_not_finite_as_from_heads_of_their_own(H, what, chunk):
     G, Hkv, Smax = 4, 3, 500
     case = synth.make_case(B=1, Hq=G * Hkv, Hkv=Hkv, D=128, Smax=Smax, seed=9400, seq_lens=[Smax])
     if what[0] == "v":
@@ -56,9 +73,9 @@ def test_not_finite_as_from_heads_of_their_own(H, what):
     else:
         case["q"][..., 9] = np.abs(case["q"][..., 9]) + np.float16(0.25)          # no zero times infinity
         case["k"][0, 1, 77, 9] = {"k_nan": np.nan, "k_inf": np.inf, "k_minus_inf": -np.inf}[what]
-    got = H.DeviceCase(case, chunk=128).run("fd_decode_attn_sync")
+    got = H.DeviceCase(case, chunk=chunk).run("fd_decode_attn_sync")
     own = dict(case, Hkv=G * Hkv, k=np.repeat(case["k"], G, axis=1), v=np.repeat(case["v"], G, axis=1))
-    want = H.DeviceCase(own, chunk=128).run("fd_decode_attn_sync")
+    want = H.DeviceCase(own, chunk=chunk).run("fd_decode_attn_sync")
     fin = np.isfinite(want)
     assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~fin], want[~fin], equal_nan=True)
     assert np.abs(got[fin] - want[fin]).max() <= H.ABS_TOL
@@ -70,7 +87,8 @@ def test_not_finite_as_from_heads_of_their_own(H, what):
 def test_partial_sums_as_exact_as_from_heads_of_their_own(H, Hq, Hkv, Smax, chunk, spread):
     """f.V of the chunks against 64 bits: no further off than the per-row kernel's, whose weights are fp32 numbers.  (With weights cut to 22 bits it is,
     by 1.3 to 1.6 times.)  Both run in a fixed order, so the two errors are what they are on every run; 5 % stands for another seed."""
-    case = synth.make_case(B=2, Hq=Hq, Hkv=Hkv, D=128, Smax=Smax, seed=9450, seq_lens=[Smax, Smax])
+    B = 10                                     # enough workgroups for the tile
+    case = synth.make_case(B=B, Hq=Hq, Hkv=Hkv, D=128, Smax=Smax, seed=9450, seq_lens=[Smax] * B)
     case["q"] = (spread * case["q"].astype(np.float64)).astype(np.float16)
     k, v = (np.repeat(case[n], Hq // Hkv, axis=1) for n in "kv")
     x = np.matmul(k.astype(np.float64), case["q"].astype(np.float64)[..., None])[..., 0] * case["scale"]
