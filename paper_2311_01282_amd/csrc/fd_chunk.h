@@ -339,7 +339,8 @@ template <bool PAGED> struct KvRows {
 // large ragged launches leave it off.
 // ONE: a wavefront asks for a block of keys only when the one before has arrived, instead of
 // keeping two in flight (LoadAhead in fd_row_kernels.hip says where).
-template <int C, int NW, int UP, bool SYNC, bool EARLY = false, bool PAGED = false, bool ONE = false>
+// REDONE: another launch sums every chunk of a flagged row anew, so nothing is done about a guard that fires.
+template <int C, int NW, int UP, bool SYNC, bool EARLY = false, bool PAGED = false, bool ONE = false, bool REDONE = false>
 __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, ChunkLds<NW> &lds, int *len_out = nullptr,
                                            int sync_flag = 1)
 {
@@ -418,7 +419,7 @@ __device__ __forceinline__ bool chunk_body(const Problem &p, int row, int c, Chu
     const float scale = p.scale;
     float nref = SYNC ? 0.f : -p.phi;          // minus this wavefront's reference
     float lo = p.lo, hi = SYNC ? -INFINITY : p.hi;                                // (SYNC: the logit that raises it; the first block in any case)
-    const bool in_place = SYNC || (p.lo >= kInPlaceLo && p.hi <= kInPlaceHi);     // uniform
+    const bool in_place = SYNC || (!REDONE && p.lo >= kInPlaceLo && p.hi <= kInPlaceHi);      // uniform
     int out_of_range = 0;                      // 1: a logit of this wavefront was outside (lo, hi); | 2: and the chunk has to be redone for it
     float top = SYNC ? kNoRef : 0.f;           // largest logit of this lane's keys (SYNC), their largest weight
     // A logit is out of range: the wavefront's reference becomes the largest of the block, or stays if it is larger, and the sums

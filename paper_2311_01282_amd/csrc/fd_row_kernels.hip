@@ -4,10 +4,10 @@
 //
 //   decode_fused_kernel    : the whole method in one launch.  Every workgroup
 //       computes its chunk's Eq. 4 inner sums under the range guard; a chunk whose
-//       guard fires goes on with references of its own (Eq. 2); the
+//       guard fires goes on with references of its own, or is redone (Eq. 2); the
 //       workgroup that finishes a row last (elected by a small tree of arrival
 //       counters) runs the row epilogue.
-//   partial_unified_kernel : Eq. 4 inner sums + guard only (first launch of the chain).
+//   partial_unified_kernel : Eq. 4 inner sums + guard, which only flags (first launch of the chain).
 //   chain_combine_kernel   : row flags; Eq. 4 outer sums for clean rows, per-chunk
 //       synchronized recomputation for flagged rows (second launch of the chain).
 //   partial_sync_kernel    : every (row, chunk) by Eq. 2, in two passes, where that is
@@ -123,7 +123,9 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void decode_fused_kernel(const Pr
 }
 
 // First launch of the literal chain: Eq. 4 inner sums and the range guard, nothing else (no
-// recomputation, no hand-over).  Same workgroup shape, workgroup order and early loads as the
+// recomputation, no hand-over; a flagged chunk's sums are whatever they come to until the second launch replaces
+// them.  Going on in place as the fused kernel does took 1 x 32 heads x 1024 keys 10.95 us, now 10.75, 16 x 32 x 125 .. 1000 42.65, now
+// 42.3; 2 x 16 x 30000 79.0, now 79.9).  Same workgroup shape, workgroup order and early loads as the
 // fused kernel: SMALL = a launch of at most 1024 workgroups (kernel arguments fetched in one batch),
 // EARLY = of at most 256 (chunk-major order, first loads before the sequence length has arrived).  ONE: see
 // LoadAhead.
@@ -139,7 +141,7 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void partial_unified_kernel(const
     const int c = EARLY ? j / groups8 : j % p.nc;              // the fused kernel's orders
     const int row = row_slot(p, blockIdx.x & 7, c) + 8 * (EARLY ? j - c * groups8 : j / p.nc);
     if (row >= p.rows) return;
-    chunk_body<C, NW, UP, false, EARLY, false, ONE>(p, row, c, lds);
+    chunk_body<C, NW, UP, false, EARLY, false, ONE, true>(p, row, c, lds);
 }
 
 // Second launch of the literal chain, over (row, chunk) items: every item first forms its row's
