@@ -41,7 +41,7 @@ __device__ __forceinline__ int slot_of(float x, float x_min, float inv_width, in
 // 16x16x32 MFMAs; lane (n, g) ends up with the logits of head n, keys 4r + g).
 // Bound: HBM reads of K, and at the end the adds of all workgroups to the same n_bins + 2 addresses, which serialize
 // (with 1024 smaller workgroups for grouped heads, four dot products per key on the vector ALU and K fetched once per four
-// heads, the 203 MB of 32 ragged sequences x 64/8 heads x 4096 keys took 89.2 us, now 47.0 with the calls around it; with 512 for
+// heads, the 203 MB of 32 ragged sequences x 64/8 heads x 4096 keys took 89.2 us, now 43.3 with the calls around it; with 512 for
 // ungrouped heads, 1 x 32 heads x 8192 keys 22.9, now 17.3).
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
