@@ -37,12 +37,24 @@ template <int C> struct Tune {
 // 110.7, 25 x 32 x 209 .. 1678 in 2 72.2 / 77.2, 25 x 16 x 759 .. 6073 in 6 109.5 / 113.4, 20 x 16 x 800 .. 2900 in 6 55.6 / 56.7; equal lengths would gain 2 %: 110 x
 // 16 x 1941 in 2 259 / 254); from ten on there are enough of them (2 x 40 x 3306 .. 13224 in 26 84.7 / 82.7).  The synchronized scheme keeps the
 // order there: 10 x 40 x 1339 .. 5356 in 6 127.8 / 122.9, 3 x 32 x 1525 .. 6103 in 6 44.4 / 36.2, 29 x 16 x 1700 in 2 66.6 / 65.0 (but 38 x 32 x 224 .. 1799 in 2 117.4 / 124.8).
-// It takes it always where heads share KV heads: the heads of a group then read a chunk through the same XCD's L2 where the chunks divide by 8, through
-// two where they divide by 4 (1 x 32/4 x 1536 in 16 7.95 / 7.03, 1 x 28/4 x 1024 in 8 7.87 / 6.74, 1 x 32/4 x 4096 in 8 12.7 / 8.95).
 template <bool SYNC> __device__ __forceinline__ bool plain_order(const Problem &p)
 {
-    return (p.rows & 7) != 0 || (SYNC && p.G > 1) || ((p.nc & 3) != 0 && p.nc <= 32 && (SYNC || (p.nc & 1) != 0 || p.nc > 8));
+    return (p.rows & 7) != 0 || ((p.nc & 3) != 0 && p.nc <= 32 && (SYNC || (p.nc & 1) != 0 || p.nc > 8));
 }
+
+// The synchronized scheme's order where heads share KV heads: the heads of a group take a chunk one after the other on the same XCD, so that its L2
+// fetches the keys once, whatever the number of chunks.  Whole call, one chunk after the other / this: 2 x 32/4 x 1536 keys in 512 14.1 / 9.8 us, 1 x 28/4 x 1573 in 64 10.1 / 8.5, 1 x
+// 16/2 x 5580 in 512 14.3 / 10.1; of more heads than the tile takes 2 x 32/1 x 2000 .. 5000 in 512 21.2 / 15.9, 4 x 64/2 x 3000 .. 9000 in 1024 110.5 / 60.8 (bound by the L2s then).
+// False: a workgroup that only fills up the last eight.
+__device__ __forceinline__ bool shared_order(const Problem &p, int &row, int &c)
+{
+    const int j = (int)blockIdx.x >> 3, item = j / p.G * 8 + ((int)blockIdx.x & 7);      // (sequence, KV head, chunk)
+    const int group = item / p.nc;
+    c = item - group * p.nc;
+    row = group * p.G + j % p.G;
+    return group < p.B * p.Hkv;
+}
+inline unsigned shared_grid(const Problem &p) { return (unsigned)(((long long)p.B * p.Hkv * p.nc + 7) / 8 * 8 * p.G); }
 
 // ELECT: rows are finished in the launch (elect_per_row in fd_api.hip says which launches do).
 // PAGED: K and V are page pools addressed through the sequence's block table.
@@ -82,8 +94,9 @@ __global__ __launch_bounds__(Tune<C>::NW * 64) void decode_fused_kernel(const Pr
     const int j = blockIdx.x >> 3;
     constexpr bool CM = EARLY;                 // chunk-major in the one-round launches only (see below)
     const bool plain = !ELECT && plain_order<SYNC>(p);
-    const int c = plain ? (int)blockIdx.x % p.nc : CM ? j / groups8 : j % p.nc;
-    const int row = plain ? (int)blockIdx.x / p.nc : row_slot(p, blockIdx.x & 7, c) + 8 * (CM ? j - c * groups8 : j / p.nc);
+    int c = plain ? (int)blockIdx.x % p.nc : CM ? j / groups8 : j % p.nc;
+    int row = plain ? (int)blockIdx.x / p.nc : row_slot(p, blockIdx.x & 7, c) + 8 * (CM ? j - c * groups8 : j / p.nc);
+    if (SYNC && p.G > 1 && !shared_order(p, row, c)) return;
     if (row >= p.rows) return;
     FD_PHASE(0);
     if constexpr (SYNC) {
@@ -330,8 +343,9 @@ __global__ __launch_bounds__(256) void partial_sync_kernel(const Problem p)
     fetch_arguments_now(p);
     const bool plain = plain_order<true>(p) || p.nc > 32;
     const int j = blockIdx.x >> 3;
-    const int c = plain ? (int)blockIdx.x % p.nc : j % p.nc;
-    const int row = plain ? (int)blockIdx.x / p.nc : row_slot(p, blockIdx.x & 7, c) + 8 * (j / p.nc);
+    int c = plain ? (int)blockIdx.x % p.nc : j % p.nc;
+    int row = plain ? (int)blockIdx.x / p.nc : row_slot(p, blockIdx.x & 7, c) + 8 * (j / p.nc);
+    if (p.G > 1 && !shared_order(p, row, c)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, seg = lane & 15, sub = lane >> 4;
     const int b = row / p.Hq, hkv = (row - b * p.Hq) / p.G, start = c * p.C;
     const size_t slot = (size_t)row * p.nc + c;
@@ -421,16 +435,17 @@ template <int C> struct SyncLauncher {
         if (grid == 0) return hipSuccess;
         Problem p = p0;
         p.scatter = 1;
+        const dim3 blocks(p.G > 1 ? shared_grid(p) : grid);
         const dim3 block(Tune<C>::NW * 64);
         if constexpr (C <= 1024) {
-            if (grid <= (unsigned)kComputeUnits) return launch(decode_fused_kernel<C, false, false, true, false, true>, dim3(grid), block, s, p);
+            if (grid <= (unsigned)kComputeUnits) return launch(decode_fused_kernel<C, false, false, true, false, true>, blocks, block, s, p);
         }
-        if constexpr (C >= 1024) return launch(partial_sync_kernel<C>, dim3(grid), dim3(256), s, p);
+        if constexpr (C >= 1024) return launch(partial_sync_kernel<C>, blocks, dim3(256), s, p);
         else {
             if constexpr (LoadAhead<C>::kOneBuilt) {
-                if (LoadAhead<C>::one(p)) return launch(decode_fused_kernel<C, false, false, false, true, true>, dim3(grid), block, s, p);
+                if (LoadAhead<C>::one(p)) return launch(decode_fused_kernel<C, false, false, false, true, true>, blocks, block, s, p);
             }
-            return launch(decode_fused_kernel<C, false, false, false, false, true>, dim3(grid), block, s, p);
+            return launch(decode_fused_kernel<C, false, false, false, false, true>, blocks, block, s, p);
         }
     }
 };
