@@ -205,17 +205,17 @@ inline int elect_grouped(const fd::Problem &p)
 // 7.82; of two heads to one 16 x 32/16 x 1500 61.3 / 33.6, 1 x 32/16 x 700 10.2 / 9.8, 1 x 8/4 x 9000 in 144-key chunks 14.7 / 12.7.  Not two heads
 // on a few KV heads in chunks that leave a wavefront one block of 16 keys: 1 x 2/1 x 9000 in 64 12.7 / 13.2, 4 x 2/1 x 4096 in 64 10.1 / 11.1 (in 96
 // 8 x 3000 9.85 / 9.66).
-//   And not where a launch of the per-row kernel is about as long as one of its workgroups: the tile's way from scores over weights to sums is 1 us longer
-// than that kernel's, and K and V, of which a query head's chunk takes what the others of its group have just read, come out of the L2 (plain_order sees to it).
-// Twenty calls in a graph, per-row / grouped: 16/2 heads x 1000 keys in 64 (256 workgroups of the per-row kernel) 5.85 / 7.34 us, 32/2 x 1000 in 64 (512) 6.5 / 8.0,
-// 56/8 x 1024 in 64 (896) 7.43 / 7.68, 64/8 x 1024 in 64 (1024) 7.53 / 7.58, 32/4 x 1536 in 96 (512) 7.06 / 8.10, 28/4 x 1024 in 128 (448) 6.74 / 7.76, 32/8 x 2048 in 256
-// (256) 7.2 / 8.4, 32/4 x 4096 in 512 (256) 8.95 / 10.8; but 64/8 x 1280 in 64 (1280) 8.4 / 7.7, 32/8 x 1920 in 96 (640) 8.2 / 7.6, 28/4 x 1536 in 128 (672) 8.5 / 8.3, 28/4 x
-// 2048 in 256 (448) 9.1 / 8.9, 28/4 x 4096 in 512 (448) 13.0 / 11.1.  In between are shapes that lose up to 6 % on either side (64/8 x 480 in 96, 320: 8.0 / 7.5).
+//   And not where each workgroup of the per-row kernel has a compute unit to itself: the tile's way from scores over weights to sums is 1 us longer
+// than that kernel's, and K and V, of which a query head's chunk takes what the others of its group have just read, come out of the L2 (shared_order sees to
+// it).  Whole call, caches cold, per-row / tile: 1 x 28/4 x 1000 in 256 (112 workgroups of the per-row kernel) 7.4 / 8.8 us, 2 x 64/8 x 260 in 256 (256) 7.3 / 8.8, 2 x 32/8 x 1536 in
+// 512 (192) 9.6 / 10.9, 4 x 32/8 x 1185 in 1024 (256) 14.1 / 15.7; but 6 x 16/8 x 680 in 256 (288) 10.7 / 9.3, 2 x 28/4 x 2078 in 512 (280) 13.4 / 11.6, 3 x 32/16 x 1900 in 768 (288) 19.6 / 14.3.  Chunks
+// of up to 128 keys, several to a compute unit, half as many again: 1 x 64/8 x 370 in 64 (384) 7.7 / 8.0, 3 x 28/4 x 460 in 128 (336) 8.1 / 8.3; 2 x 16/8 x 782 in 64 (416) 8.55 / 8.15, 2 x 32/16 x 560 in 64
+// (576) 9.2 / 8.8, 1 x 32/8 x 2094 in 128 (544) 9.2 / 8.1.  Chunks beyond 1024 keys, which the per-row scheme takes in two passes, always by the tile: 2 x 32/4 x 5770 in 4096 (128) 56.6 / 41.9.
 inline bool sync_grouped(const fd::Problem &p)
 {
     if (p.G < 2 || p.G > 16 || (p.G == 2 && p.C < 96 && (long long)p.B * p.Hkv < 8)) return false;
     const long long workgroups = (long long)p.rows * p.nc;                     // of the per-row kernel
-    return workgroups * p.C > 65536 && (workgroups > fd::kComputeUnits || p.C > 512);
+    return p.C > 1024 || workgroups > (p.C <= 128 ? fd::kComputeUnits + fd::kComputeUnits / 2 : fd::kComputeUnits);
 }
 
 #define FD_TRY(expr) do { if ((expr) != hipSuccess) return FD_ERR_HIP; } while (0)

@@ -42,6 +42,7 @@ SHAPES = [
     (2, 8, 2, [700, 65], 700, 128),
     (12, 8, 2, [700, 65, 0, 699] * 3, 700, 128),
     (3, 12, 2, [1500, 0, 1024], 1500, 1024),
+    (3, 12, 2, [1500, 0, 1024], 1500, 1040),
     (2, 4, 4, [700, 65], 700, 128),
     (2, 4, 4, [1500, 1000], 1500, 1024),
     (20, 16, 16, [900 - 40 * i for i in range(20)], 900, 912),

@@ -38,8 +38,8 @@ def _check(oracle, H, case, chunk, what, ramp):
     (2, 12, 2, [64 * 40, 64 * 33 + 1], 64 * 40, 64),
     (1, 2, 1, [900], 900, 64),
     (1, 2, 1, [900], 900, 96),
-    # as above, in launches that the tile takes: chunks beyond 512 keys, or more than 65536 keys in all of the per-row kernel's workgroups (one of 64 keys
-    # with early loads); and the edges of that rule
+    # as above, in launches that the tile takes: chunks beyond 1024 keys, or more than 256 workgroups of the per-row kernel, 384 of up to 128 keys (two
+    # with early loads); and the edges of that rule, on both sides
     (36, 16, 2, [1, 15, 16, 17] * 9, 80, 64),
     (3, 16, 1, [0, 700, 64], 700, 528),
     (2, 4, 2, [600, 129], 600, 528),
@@ -54,6 +54,17 @@ def _check(oracle, H, case, chunk, what, ramp):
     (1, 32, 2, [2049], 2049, 128),
     (2, 32, 2, [1024, 900], 1024, 64),
     (2, 32, 2, [1025, 900], 1025, 64),
+    (3, 16, 1, [0, 700, 64], 700, 1040),
+    (2, 4, 2, [600, 129], 600, 1040),
+    (1, 8, 1, [1024], 1024, 1024),
+    (16, 16, 2, [512 - 16 * i for i in range(16)], 512, 512),
+    (17, 16, 2, [512 - 16 * i for i in range(17)], 512, 512),
+    (2, 32, 2, [576, 300], 576, 144),
+    (3, 30, 2, [432, 300, 1], 432, 144),
+    (1, 32, 2, [768], 768, 64),
+    (1, 32, 2, [769], 769, 64),
+    (1, 32, 2, [1536], 1536, 128),
+    (1, 32, 2, [1537], 1537, 128),
 ])
 @pytest.mark.parametrize("ramp", [None, (-150.0, 150.0), (150.0, -150.0), (-900.0, -880.0), (700.0, 720.0)])
 def test_grouped_rows(oracle, H, B, Hq, Hkv, lens, Smax, chunk, ramp):
@@ -64,10 +75,10 @@ def test_grouped_rows(oracle, H, B, Hq, Hkv, lens, Smax, chunk, ramp):
 
 
 @pytest.mark.parametrize("what", ["v_inf", "v_nan", "k_nan", "k_inf", "k_minus_inf"])
-@pytest.mark.parametrize("chunk", [128, 528])
-def test_not_finite_as_from_heads_of_their_own(H, what, chunk):
+@pytest.mark.parametrize("B,chunk", [(1, 128), (1, 528), (1, 1040), (10, 128)])
+def test_not_finite_as_from_heads_of_their_own(H, what, B, chunk):
     G, Hkv, Smax = 4, 3, 500
-    case = synth.make_case(B=1, Hq=G * Hkv, Hkv=Hkv, D=128, Smax=Smax, seed=9400, seq_lens=[Smax])
+    case = synth.make_case(B=B, Hq=G * Hkv, Hkv=Hkv, D=128, Smax=Smax, seed=9400, seq_lens=[Smax] * B)
     if what[0] == "v":
         case["v"][0, 1, 77, 5] = np.inf if what == "v_inf" else np.nan
     else:
